@@ -129,7 +129,8 @@ size_t cngp_workspace_bytes(const cngp_config *cfg, int64_t N);
 
 /* The part of it the forward calls use: room for a level-major copy of the encodings (N * L * F values of io_dtype)
  * when the level-resident variant would be taken for this configuration and N, else 0 (F != 2: the pair planes,
- * as above).  A forward call that is given less runs the tile variant instead, with the same result. */
+ * as above).  A forward call that is given less runs the tile variant instead, with the same result, and a batch of
+ * at most 2^20 corner lookups (N * L * 2^d) is encoded by a single launch that does not touch the workspace. */
 size_t cngp_fwd_workspace_bytes(const cngp_config *cfg, int64_t N);
 
 /* How a forward call with enough workspace would run: info[0] = 1 if the level-resident variant is taken, info[1] =

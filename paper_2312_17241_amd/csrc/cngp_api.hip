@@ -194,6 +194,15 @@ struct FwdLevelPlan {
     int64_t  parts = 0, per_part = 0;
     size_t   yT_bytes = 0;       // the level-major copy of the encodings: the workspace this variant needs
 };
+constexpr int64_t kCus = 256;
+// Corner lookups (N * L * 2^d) up to which encode_fwd_kernel, one launch with every lookup in flight at once, is the
+// fastest forward.  Measured, GPU and call together, us: nerf3d's tables, 8192 points (2^20 lookups): 11.5 against 12.9 for
+// the level-resident pair of launches and 57 for the tile kernel, 16384 points: 19 / 13 / 52; fp32 tables of 2^18 entries
+// (sdf3d) 18.8 / 29 / 120 at 8192, 33 / 28 / 119 at 16384; d = 2, 16384 points: 10.5 / 13.0 / 28; d = 4, 4096: 10.3 / 15.3 / 81.
+constexpr int64_t kSmallFwdRefs = 1 << 20;
+// The same against the tile kernel alone, for a caller without a workspace: nerf3d 34 / 46 us at 32768 points (2^22
+// lookups), the compressed model 23 / 31, d = 2 17 / 26 at 2^21; at 2^25 it is 217 / 99.
+constexpr int64_t kSmallFwdRefsNoRoom = 1 << 22;
 constexpr size_t  kLevelLdsBudget = 156 * 1024;
 constexpr int64_t kLevelPartPoints = 65536;              // points per workgroup when the batch is large
 
@@ -265,7 +274,8 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
         const FwdLevelPlan f = fwd_level_plan(c, p.L_loaded, N);
         const bool room = workspace && workspace_bytes >= f.yT_bytes && ((uintptr_t)workspace & 255u) == 0 &&
                           ((uintptr_t)D_f & 15u) == 0;
-        if (f.use && room) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
+        const bool small = ((N * c->L) << c->d) <= kSmallFwdRefs && !(c->flags & (CNGP_FWD_LEVEL | CNGP_FWD_TILE));
+        if (f.use && room && !small) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
         if ((c->flags & CNGP_FWD_LEVEL) != 0) return f.use ? CNGP_ERR_WORKSPACE : CNGP_ERR_UNSUPPORTED;
     }
     // tile variant: one level's index codebook and the tile's outputs fit in LDS
@@ -274,7 +284,8 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
     const size_t lds_probes = (((size_t)c->N_c + 1) / 2 + 15) & ~(size_t)15;
     const size_t lds = lds_probes + (size_t)kFwdTile * c->L * 2 * sizeof(IoT);
     const size_t lds_large = lds_probes + (size_t)kFwdTileLarge * c->L * 2 * sizeof(IoT);
-    if (lds <= 64 * 1024 && N >= kFwdTile && !(c->flags & CNGP_FWD_SIMPLE)) {
+    const bool small = ((N * c->L) << c->d) <= kSmallFwdRefsNoRoom && !(c->flags & CNGP_FWD_TILE);
+    if (lds <= 64 * 1024 && N >= kFwdTile && !small && !(c->flags & CNGP_FWD_SIMPLE)) {
         // Staging a level's codebook costs c_stride bytes per workgroup; a tile looks up TILE * 2^d entries.
         // When the staging outweighs the lookups of a small tile and there are points enough to keep every
         // CU busy with large ones, take the large tile.
@@ -304,13 +315,15 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
 #undef CNGP_FWD_TILE
         return launch_status("encode_fwd_tile_kernel");
     }
-    const int64_t pairs = N * c->L;
-    const int64_t blocks = (pairs + kBlock - 1) / kBlock;
+    // one wavefront per workgroup spreads a small batch over more CUs
+    const unsigned block = N * c->L <= 64 * 4 * kCus ? 64u : (unsigned)kBlock;
+    const uint32_t points = block / (uint32_t)c->L, level_magic = (65536u + (uint32_t)c->L - 1u) / (uint32_t)c->L;
+    const int64_t  blocks = (N + points - 1) / points;
     if (int rc = check_blocks(blocks)) return rc;
     LaunchTimer t(s, K_FWD);
 #define CNGP_FWD_SIMPLE_LAUNCH(FMT)                                                                     \
-    encode_fwd_kernel<D, FeatT, IoT, FMT><<<(unsigned)blocks, kBlock, 0, s>>>(                          \
-        p, x, (const FeatT *)D_f, (const uint8_t *)D_c, (IoT *)y, pairs, (uint32_t)c_stride, perm)
+    encode_fwd_kernel<D, FeatT, IoT, FMT><<<(unsigned)blocks, block, 0, s>>>(                           \
+        p, x, (const FeatT *)D_f, (const uint8_t *)D_c, (IoT *)y, N, points, level_magic, (uint32_t)c_stride, perm)
     if (fmt == CNGP_IDX_PACKED4) CNGP_FWD_SIMPLE_LAUNCH(kFmtPacked4);
     else if (fmt == CNGP_IDX_BITS) CNGP_FWD_SIMPLE_LAUNCH(kFmtBits);
     else CNGP_FWD_SIMPLE_LAUNCH(kFmtU8);
@@ -397,7 +410,6 @@ constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which 
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
-constexpr int64_t  kCus = 256;
 
 // Chunk count that minimises (rounds of workgroups over the CUs) x (items per chunk + fixed cost per
 // workgroup, in items: clearing and flushing its LDS slice).  `groups` workgroups exist per chunk.

@@ -6,20 +6,25 @@
 namespace cngp {
 
 // ------------------------------------------------------------------ forward (Eq. 6 + interpolation)
-// One thread per (point, level) pair, pairs numbered n * L + l, so that the F = 2 outputs
-// of consecutive threads are consecutive in y: every wavefront writes one contiguous run.
+// One lane per (point, level) pair, a workgroup takes blockDim / L whole points, pairs numbered n * L + l: the F = 2
+// outputs of consecutive lanes are consecutive in y, every wavefront writes one contiguous run.  Both lookups of a
+// corner go to memory, 2^(d+1) cache lines per pair, so for a large batch the line rate of the CUs bounds it and the
+// variants below that keep codebooks in LDS win.  For a small one nothing is bound but latency, and this kernel is the
+// shortest chain there is: point, probes, features, store, with every level of a point in flight at once (the tile
+// kernel takes the levels one after the other with two barriers each: 1001 points, 16 levels: 60 us a call against
+// 9.5, most of it now the call itself).  `level_magic` = ceil(2^16 / L): lane / L as one multiply (exact: lane * (L - 1) < 2^16).
 template <int D, typename FeatT, typename IoT, int FMT>
 __global__ __launch_bounds__(kBlock) void encode_fwd_kernel(
     const Params p, const float *__restrict__ x, const FeatT *__restrict__ D_f,
-    const uint8_t *__restrict__ D_c, IoT *__restrict__ y, const int64_t pairs, const uint32_t c_stride,
-    const int32_t *__restrict__ perm)
+    const uint8_t *__restrict__ D_c, IoT *__restrict__ y, const int64_t N, const uint32_t points, const uint32_t level_magic,
+    const uint32_t c_stride, const int32_t *__restrict__ perm)
 {
-    const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= pairs) return;
-    const int64_t n = i / p.L;
-    const int     l = (int)(i - n * p.L);
+    const uint32_t r = (threadIdx.x * level_magic) >> 16;                // point of the workgroup
+    const int      l = (int)(threadIdx.x - r * (uint32_t)p.L);
+    const int64_t  n = (int64_t)blockIdx.x * points + r;
+    if (r >= points || n >= N) return;
     // with a permutation the encoding of point n is row perm[n] of y
-    const size_t  o = perm ? (size_t)perm[n] * p.L + l : (size_t)i;
+    const size_t  o = (perm ? (size_t)perm[n] : (size_t)n) * p.L + l;
     if (l >= p.L_loaded) {                        // level not loaded
         store_pair(y, o, 0.0f, 0.0f);
         return;

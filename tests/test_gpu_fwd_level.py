@@ -130,3 +130,24 @@ def test_forced_where_it_cannot_run_is_an_error():
     with pytest.raises(cngp.CngpError) as e:
         cngp.encode_fwd(bad, dev(x), dev(D_f), dev(D_c))
     assert e.value.status == cngp.ERR_INVALID
+
+
+@pytest.mark.parametrize("d,L,N,fmt", [(3, 16, 1, cngp.IDX_U8), (3, 5, 1001, cngp.IDX_PACKED4), (3, 16, 2**13, cngp.IDX_BITS),
+                                       (3, 16, 2**13 + 1, cngp.IDX_U8), (2, 12, 5461, cngp.IDX_U8), (2, 12, 5462, cngp.IDX_PACKED4),
+                                       (4, 32, 2048, cngp.IDX_U8), (2, 32, 77, cngp.IDX_U8)])
+def test_small_batches_take_one_launch(d, L, N, fmt):
+    """Up to 2^20 corner lookups: one lane per (point, level), whole points per workgroup of 64 lanes (256 from 65537
+    pairs on); L that does not divide the workgroup; the first size beyond the line.  Same bits as the tile variant, also
+    with rows written through a permutation and with levels that are not loaded."""
+    w, x, D_f, D_c = case(d, 8, "f16", "f16", N=N, L=L, N_max=64)
+    cfg, tile = (cngp.Config.from_workload(w, index_format=fmt, flags=f) for f in (0, cngp.FWD_TILE))
+    args = (dev(x), dev(D_f), packed(fmt, D_c, 8))
+    ws = cngp.alloc_workspace(cfg, N)
+    y, y_tile = cngp.encode_fwd(cfg, *args, workspace=ws), cngp.encode_fwd(tile, *args)
+    part, part_tile = (cngp.encode_fwd_partial(c, L - 2, *args, workspace=ws) for c in (cfg, tile))
+    perm = torch.randperm(N, generator=torch.Generator().manual_seed(N)).to(torch.int32).to(DEV)
+    moved = cngp.encode_fwd_permuted(cfg, args[0][perm.long()].contiguous(), perm, *args[1:], workspace=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y_tile) and torch.equal(part, part_tile) and torch.equal(moved, y)
+    y_ref, ymag = oracle.encode_fwd(w, x, D_f, D_c)
+    check_close("y [small batch]", y.cpu().numpy(), y_ref, ymag, fp16_out=True)
