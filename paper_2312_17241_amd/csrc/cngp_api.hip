@@ -191,7 +191,7 @@ struct FwdLevelPlan {
     bool     use = false;
     uint32_t resident = 0;       // entries of a level's feature codebook that sit in LDS
     size_t   lds = 0;            // dynamic LDS of the kernel
-    int64_t  parts = 0, per_part = 0;
+    LevelSplit split = {};       // levels that interpolate from a resolved grid; points per workgroup of either kind
     size_t   yT_bytes = 0;       // the level-major copy of the encodings: the workspace this variant needs
 };
 constexpr int64_t kCus = 256;
@@ -205,8 +205,9 @@ constexpr int64_t kSmallFwdRefs = 1 << 20;
 constexpr int64_t kSmallFwdRefsNoRoom = 1 << 22;
 constexpr size_t  kLevelLdsBudget = 156 * 1024;
 constexpr int64_t kLevelPartPoints = 65536;              // points per workgroup when the batch is large
+constexpr uint64_t kFwdL2Bytes = 3u << 20;               // of an XCD's 4 MB, what tables can count on
 
-FwdLevelPlan fwd_level_plan(const cngp_config *c, int levels_loaded, int64_t N) {
+FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, int64_t N) {
     FwdLevelPlan f;
     if (c->F != 2 || levels_loaded < 1 || N <= 0 || (c->flags & (CNGP_FWD_SIMPLE | CNGP_FWD_TILE))) return f;
     const size_t entry = 2 * (c->feat_dtype == CNGP_F16 ? 2 : 4), io = c->io_dtype == CNGP_F16 ? 2 : 4;
@@ -223,22 +224,98 @@ FwdLevelPlan fwd_level_plan(const cngp_config *c, int levels_loaded, int64_t N) 
     f.use = true;
     f.resident = (uint32_t)resident;
     f.lds = probes + resident * entry + 16;
+    // Levels whose whole vertex grid fits the same LDS can interpolate from it (not where all of D_f is in LDS anyway:
+    // the compressed model got 9 % slower, filling the grids costs what the shorter lookups save).
+    uint32_t res[kMaxLevels];
+    level_table(c, res);
+    int      most_grids = 0;
+    uint64_t verts[kMaxGridLevels];
+    while (resident < c->N_f && most_grids < levels_loaded && most_grids < kMaxGridLevels && res[most_grids] < 4096) {
+        uint64_t v = 1;
+        for (int i = 0; i < c->d; ++i) v *= (uint64_t)res[most_grids] + 2;
+        if (v * entry > kLevelLdsBudget) break;
+        verts[most_grids++] = v;
+    }
+    // Clocks of a CU, fitted to measurements of single levels (nerf3d's and image2d's tables, 2^18 .. 2^24 points): a point
+    // that is looked up, by the share of lookups that leave the CU; a point on a grid; a vertex to fill in.
+    const double miss = 1.0 - (double)resident / c->N_f, lookup = (double)(1 << c->d) * (0.21 + 1.66 * miss);
+    const double on_grid = c->d == 2 ? 1.8 : c->d == 3 ? 2.4 : 4.0, fill = 3.3;
     const int64_t step = (int64_t)kLevelBlock * kLevelUnroll;
-    int64_t parts = 256 / levels_loaded;                                 // one workgroup per CU at least ...
-    if (parts < N / kLevelPartPoints) parts = N / kLevelPartPoints;       // ... and many short ones for a large batch: the levels differ in cost
-    if (parts > (N + step - 1) / step) parts = (N + step - 1) / step;
-    if (parts < 1) parts = 1;
-    f.per_part = ((N + parts - 1) / parts + step - 1) / step * step;
-    f.parts = (N + f.per_part - 1) / f.per_part;
+    auto parts_of = [&](double per) {                        // parts of at most `per` points, whole steps of a workgroup at least
+        const int64_t least = per < (double)step ? step : (int64_t)per;
+        return (N + least - 1) / least;
+    };
+    auto grid_points = [&](int l, double per) { return (per * lookup - (double)verts[l] * fill) / on_grid; };
+    // The launch in whole rounds of one workgroup per CU, all of about the same length: one round while the batch is small,
+    // more for a large one (the levels differ in cost).  The longest parts of looked-up levels that need no more workgroups
+    // than that, for every number of levels on grids; the shortest of these wins.
+    // (the looked-up levels in eight runs of equal length if they are kept apart by XCD)
+    auto by_xcd = [&](int64_t levels) { return (uint64_t)(c->N_f - resident) * entry * levels > kFwdL2Bytes; };
+    auto looked_up_units = [&](int64_t levels, int64_t parts) {
+        return by_xcd(levels) ? (levels * parts + kFwdXcds - 1) / kFwdXcds * kFwdXcds : levels * parts;
+    };
+    auto units_of = [&](int grids, double per) {
+        int64_t u = looked_up_units(levels_loaded - grids, parts_of(per));
+        for (int l = 0; l < grids; ++l) {
+            const double n = grid_points(l, per);
+            if (n < 64.0) return (int64_t)1 << 40;
+            u += parts_of(n);
+        }
+        return u;
+    };
+    int    grids = 0;
+    double best = 0.0, best_per = 0.0;
+    for (int g = 0; g <= most_grids; ++g) {
+        const double load = (double)N * ((levels_loaded - g) + g * on_grid / lookup) / kCus;      // in looked-up points per CU
+        int64_t rounds = (int64_t)(load / kLevelPartPoints + 0.5);
+        if (rounds < 1) rounds = 1;
+        double lo = 0.0, hi = 2.0 * (double)N * levels_loaded + 1e6;
+        for (int i = 0; i < 48 && hi - lo > 64.0; ++i) {
+            const double mid = 0.5 * (lo + hi);
+            if (units_of(g, mid) <= kCus * rounds) hi = mid;
+            else lo = mid;
+        }
+        const double cost = hi * (double)rounds;
+        if (g == 0 || cost < 0.97 * best) { best = cost; best_per = hi; grids = g; }
+    }
+    auto cut = [&](double per, int64_t &size) {
+        const int64_t parts = parts_of(per);
+        size = ((N + parts - 1) / parts + 63) / 64 * 64;
+        return (uint32_t)((N + size - 1) / size);
+    };
+    LevelSplit &ls = f.split;
+    const int64_t hashed = levels_loaded - grids;
+    ls.dense = (uint32_t)grids;
+    ls.by_xcd = by_xcd(hashed) ? 1u : 0u;
+    ls.hash_parts = cut(best_per, ls.hash_per);
+    ls.hash_units = (uint32_t)looked_up_units(hashed, ls.hash_parts);
+    for (int l = 0; l < grids; ++l) {
+        ls.grid_first[l + 1] = ls.grid_first[l] + cut(grid_points(l, best_per), ls.grid_per[l]);
+        if (verts[l] * entry > f.lds) f.lds = verts[l] * entry;
+    }
     f.yT_bytes = (size_t)N * c->L * 2 * io;
     return f;
+}
+
+// The plan depends on (configuration, levels, N) only; the last one is kept (host memory, per thread).
+FwdLevelPlan fwd_level_plan(const cngp_config *c, int levels_loaded, int64_t N) {
+    thread_local cngp_config  last_cfg;
+    thread_local int          last_levels = -1;
+    thread_local int64_t      last_N = -1;
+    thread_local FwdLevelPlan last_plan;
+    if (last_N == N && last_levels == levels_loaded && std::memcmp(&last_cfg, c, sizeof(*c)) == 0) return last_plan;
+    last_plan = fwd_level_plan_uncached(c, levels_loaded, N);
+    last_cfg = *c;
+    last_levels = levels_loaded;
+    last_N = N;
+    return last_plan;
 }
 
 template <int D, typename FeatT, typename IoT>
 int launch_fwd_level(const cngp_config *c, const FwdLevelPlan &f, const Params &p, const float *x, int64_t N, const void *D_f,
                      const void *D_c, void *y, void *yT, hipStream_t s, const int32_t *perm, bool rows = true) {
     const size_t  c_stride = index_level_bytes(c);
-    const int64_t blocks = f.parts * p.L_loaded;
+    const int64_t blocks = (int64_t)f.split.hash_units + f.split.grid_first[f.split.dense];
     if (int rc = check_blocks(blocks)) return rc;
     const int vec = (c_stride % 16 == 0 && ((uintptr_t)D_c & 15u) == 0) ? 1 : 0;
 #define CNGP_FWD_LEVEL_LAUNCH(FMT)                                                                          \
@@ -247,7 +324,7 @@ int launch_fwd_level(const cngp_config *c, const FwdLevelPlan &f, const Params &
         if (int rc = allow_big_lds(kernel, f.lds)) return rc;                                               \
         LaunchTimer t(s, K_FWD);                                                                            \
         kernel<<<(unsigned)blocks, kLevelBlock, f.lds, s>>>(p, x, (const FeatT *)D_f, (const uint8_t *)D_c, \
-                                                            (IoT *)yT, N, (uint32_t)c_stride, vec, f.resident, f.per_part); \
+                                                            (IoT *)yT, N, (uint32_t)c_stride, vec, f.resident, f.split); \
     } while (0)
     if (c->index_format == CNGP_IDX_PACKED4) CNGP_FWD_LEVEL_LAUNCH(kFmtPacked4);
     else if (c->index_format == CNGP_IDX_BITS) CNGP_FWD_LEVEL_LAUNCH(kFmtBits);
@@ -270,12 +347,11 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
                const void *D_c, void *y, hipStream_t s, const int32_t *perm = nullptr,
                void *workspace = nullptr, size_t workspace_bytes = 0) {
     // level-resident variant: large batches, when the caller lent the room for the level-major copy
-    {
+    if (((N * c->L) << c->d) > kSmallFwdRefs || (c->flags & (CNGP_FWD_LEVEL | CNGP_FWD_TILE))) {
         const FwdLevelPlan f = fwd_level_plan(c, p.L_loaded, N);
         const bool room = workspace && workspace_bytes >= f.yT_bytes && ((uintptr_t)workspace & 255u) == 0 &&
                           ((uintptr_t)D_f & 15u) == 0;
-        const bool small = ((N * c->L) << c->d) <= kSmallFwdRefs && !(c->flags & (CNGP_FWD_LEVEL | CNGP_FWD_TILE));
-        if (f.use && room && !small) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
+        if (f.use && room) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
         if ((c->flags & CNGP_FWD_LEVEL) != 0) return f.use ? CNGP_ERR_WORKSPACE : CNGP_ERR_UNSUPPORTED;
     }
     // tile variant: one level's index codebook and the tile's outputs fit in LDS
@@ -1087,7 +1163,7 @@ int cngp_fwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
     const FwdLevelPlan f = fwd_level_plan(&pairs, cfg->L, N);
     info[0] = f.use ? 1 : 0;
     info[1] = (int32_t)f.resident;
-    info[2] = (int32_t)(f.parts > 0x7fffffffLL ? 0x7fffffffLL : f.parts);
+    info[2] = (int32_t)f.split.hash_parts;
     info[3] = (int32_t)(f.lds);
     return CNGP_OK;
 }

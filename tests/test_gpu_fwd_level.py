@@ -151,3 +151,29 @@ def test_small_batches_take_one_launch(d, L, N, fmt):
     assert torch.equal(y, y_tile) and torch.equal(part, part_tile) and torch.equal(moved, y)
     y_ref, ymag = oracle.encode_fwd(w, x, D_f, D_c)
     check_close("y [small batch]", y.cpu().numpy(), y_ref, ymag, fp16_out=True)
+
+
+@pytest.mark.parametrize("d,L,N_min,N_max,feat,io,fmt", [
+    (3, 6, 4, 512, "f32", "f32", cngp.IDX_U8), (3, 16, 16, 2048, "f16", "f16", cngp.IDX_PACKED4), (2, 16, 3, 4096, "f16", "f32", cngp.IDX_BITS),
+    (4, 5, 2, 60, "f16", "f16", cngp.IDX_U8), (2, 4, 5, 90, "f32", "f16", cngp.IDX_PACKED4)])       # the last: every level on a grid
+def test_coarse_levels_interpolate_from_their_resolved_vertex_grid(d, L, N_min, N_max, feat, io, fmt):
+    """A batch large enough that the coarse levels fill their vertex grid once per workgroup: same bits as the tile variant,
+    at the corners of the cube, on every face, beyond 1 (x up to 3: looked up, not on the grid) and below 0."""
+    N = 2**17 + 77
+    w, x, D_f, D_c = case(d, 8, feat, io, N=N, L=L, N_min=N_min, N_max=N_max)
+    rng = np.random.default_rng(d * L)
+    x[3:2003] = rng.integers(0, 2, (2000, d))                      # the cube's corners
+    x[2003:4003, 0], x[4003:6003, d - 1] = 1.0, 0.0                # two faces
+    x[6003:7003] = rng.uniform(-0.5, 3.0, (1000, d))
+    x[-1] = 1.0 + 2**-20
+    y_level, y_tile = both_variants(w, x, D_f, D_c, fmt)
+    assert torch.equal(y_level, y_tile)
+    sample = np.concatenate([np.arange(6003), rng.choice(np.arange(7003, N - 1), 2000, replace=False)])
+    y_ref, ymag = oracle.encode_fwd(w, x[sample], D_f, D_c)
+    check_close("y [grids]", y_level[torch.from_numpy(sample).to(DEV)].cpu().numpy(), y_ref, ymag, fp16_out=(io == "f16"))
+    perm = torch.randperm(N, generator=torch.Generator().manual_seed(N)).to(torch.int32).to(DEV)
+    cfg = cngp.Config.from_workload(w, flags=cngp.FWD_LEVEL, index_format=fmt)
+    moved = cngp.encode_fwd_permuted(cfg, dev(x)[perm.long()].contiguous(), perm, dev(D_f), packed(fmt, D_c, w.N_p),
+                                     workspace=cngp.alloc_workspace(cfg, N))
+    torch.cuda.synchronize()
+    assert torch.equal(moved, y_level)
