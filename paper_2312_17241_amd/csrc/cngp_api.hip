@@ -482,6 +482,7 @@ constexpr uint32_t kMaxFusedNf = 4096;          // largest feature table per lev
 constexpr size_t   kFusedLdsBytes = 152 * 1024; // LDS of the workgroups that accumulate both gradients
 constexpr uint32_t kMinBinnedSlicesPerLevel = 24; // from here on binning the references beats the replicated scan
 constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated scan costs more than global atomics
+constexpr size_t   kSmallBwdLds = 128 * 1024;   // both gradient tables of a level (fp64) that a small batch accumulates in LDS
 constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
@@ -939,6 +940,31 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
     return CNGP_OK;
 }
 
+// LDS of encode_bwd_small_kernel, 0 where it is not taken.
+size_t small_bwd_lds(const cngp_config *c) {
+    const size_t lds = ((size_t)c->N_f * 2 + (c->N_p > 1 ? (size_t)c->N_c * c->N_p : 0)) * sizeof(double);
+    return lds <= kSmallBwdLds && !(c->flags & CNGP_BWD_DIRECT) ? lds : 0;
+}
+
+template <int D, int NP, typename FeatT, typename IoT>
+int launch_bwd_small(const cngp_config *c, const Params &p, const float *x, int64_t N, const void *D_f, const float *Dhat_c,
+                     const void *dy, float *gD_f, float *gDhat_c, hipStream_t s) {
+    constexpr int64_t PTS = kSmallBwdBlock / NP;
+    // one point per lane group while the chip has room for that many workgroups
+    int64_t chunks = (N + PTS - 1) / PTS;
+    if (chunks > kCus / c->L) chunks = kCus / c->L;
+    if (chunks < 1) chunks = 1;
+    const int64_t chunk = ((N + chunks - 1) / chunks + PTS - 1) / PTS * PTS;
+    chunks = (N + chunk - 1) / chunk;
+    auto kernel = encode_bwd_small_kernel<D, NP, FeatT, IoT>;
+    const size_t lds = small_bwd_lds(c);
+    if (int rc = allow_big_lds(kernel, lds)) return rc;
+    LaunchTimer t(s, K_BWD_DIRECT);
+    kernel<<<dim3((unsigned)chunks, (unsigned)c->L), kSmallBwdBlock, lds, s>>>(p, x, (const FeatT *)D_f, Dhat_c, (const IoT *)dy,
+                                                                              gD_f, gDhat_c, N, chunk);
+    return launch_status("encode_bwd_small_kernel");
+}
+
 template <int D, typename FeatT, typename IoT>
 int dispatch_bwd_np(const cngp_config *c, const Params &p, const BwdPlan &b, const float *x, int64_t N,
                     const void *D_f, const float *Dhat_c, const void *dy, float *gD_f, float *gDhat_c,
@@ -946,6 +972,7 @@ int dispatch_bwd_np(const cngp_config *c, const Params &p, const BwdPlan &b, con
 #define CNGP_BWD_CASE(NP)                                                                                        \
     if (b.sliced) return launch_bwd_sliced<D, NP, FeatT, IoT>(c, p, b, x, N, D_f, Dhat_c, dy, gD_f, gDhat_c, workspace, zero, s); \
     if (int rc = zero.launch(s)) return rc;                                                                         \
+    if (small_bwd_lds(c)) return launch_bwd_small<D, NP, FeatT, IoT>(c, p, x, N, D_f, Dhat_c, dy, gD_f, gDhat_c, s); \
     return launch_bwd_direct<D, NP, FeatT, IoT>(c, p, 0, c->L, x, N, D_f, Dhat_c, dy, gD_f, gDhat_c, s)
     switch (c->N_p) {
     case 1:  CNGP_BWD_CASE(1);

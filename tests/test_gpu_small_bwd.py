@@ -1,0 +1,39 @@
+"""Backward of small batches with small tables: a level's two gradient tables accumulated in LDS by workgroups of 1024
+lanes, against the oracle (Sec. 3, Fig. 3) and beside the variant that adds to memory directly."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2312_17241_amd as cngp
+import workloads as W
+from parity import check_close
+
+pytestmark = pytest.mark.gpu
+
+
+# one point, one less / more than a workgroup's lane groups, several chunks per level; N_p from 1 to 16; the largest
+# tables that are taken (2^13 feature entries at N_p = 1: exactly 128 KB) and the first that are not
+@pytest.mark.parametrize("d,L,N_f,N_c,N_p,N,feat,io,top_k", [
+    (2, 4, 2**10, 2**8, 4, 1, "f32", "f32", 0), (2, 4, 2**10, 2**8, 4, 255, "f32", "f32", 0), (2, 4, 2**10, 2**8, 4, 4097, "f16", "f32", 0),
+    (3, 5, 2**9, 2**6, 16, 65, "f16", "f16", 3), (3, 1, 2**13, 1, 1, 3001, "f32", "f16", 0), (3, 2, 2**13, 2, 2, 1500, "f32", "f32", 0),
+    (4, 3, 2**8, 2**7, 8, 1290, "f32", "f32", 0), (2, 32, 2**6, 2**5, 2, 700, "f16", "f32", 1)])
+def test_small_tables_accumulate_in_lds(d, L, N_f, N_c, N_p, N, feat, io, top_k):
+    w = W.custom(cfg=80 + d + N_p, d=d, L=L, F=2, N_f=N_f, N_c=N_c, N_p=N_p, N_min=4, N_max=64, N=N, feat_dtype=feat, io_dtype=io)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    x, D_f, Dhat, dy = W.make_points(w), W.make_feature_codebook(w), W.make_probe_logits(w), W.make_upstream_grad(w, N)
+    x[0] = 1.0
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, x, D_f, Dhat, dy, top_k=top_k) if top_k else oracle.encode_bwd(w, x, D_f, Dhat, dy)
+    for flags in (cngp.ZERO_GRADS, cngp.ZERO_GRADS | cngp.BWD_DIRECT):
+        cfg = cngp.Config.from_workload(w, flags=flags, top_k=top_k)
+        gF = torch.full((L, N_f, 2), 7.0, device="cuda")
+        gC = torch.full((L, N_c, N_p), 7.0, device="cuda")
+        cngp.encode_bwd(cfg, dev(x), dev(D_f), dev(Dhat), dev(dy), gF, gC)
+        torch.cuda.synchronize()
+        check_close("grad D_f", gF.cpu().numpy(), gF_ref, A_f, fp16_out=False)
+        check_close("grad Dhat_c", gC.cpu().numpy(), gC_ref, A_c, fp16_out=False)
+    # without clearing, a second call adds the same gradients once more
+    cfg = cngp.Config.from_workload(w, top_k=top_k)
+    cngp.encode_bwd(cfg, dev(x), dev(D_f), dev(Dhat), dev(dy), gF, gC)
+    torch.cuda.synchronize()
+    check_close("grad D_f, twice", gF.cpu().numpy(), 2 * gF_ref, 2 * A_f, fp16_out=False)
