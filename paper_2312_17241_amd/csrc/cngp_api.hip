@@ -407,6 +407,8 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
     return launch_status("encode_fwd_kernel");
 }
 
+constexpr size_t  kBwdInputLargeLds = 16 * 1024;
+constexpr int64_t kBwdInputLargePoints = 160 * 1024;
 template <int D, typename FeatT, typename IoT>
 int launch_bwd_input(const cngp_config *c, const Params &p, const float *x, int64_t N, const void *D_f,
                      const void *D_c, const void *dy, float *grad_x, hipStream_t s) {
@@ -414,19 +416,32 @@ int launch_bwd_input(const cngp_config *c, const Params &p, const float *x, int6
     const int    fmt = c->index_format;
     const size_t lds = (((size_t)c->N_c + 1) / 2 + 15) & ~(size_t)15;
     const bool   staged = lds <= 64 * 1024 && N >= kFwdTile;
-    const bool   large = staged && c_stride >= 8192 && N >= (int64_t)kFwdTileLarge * 1024;
-    const int    tile = large ? kFwdTileLarge : kFwdTile;
-    const int64_t blocks = (N + tile - 1) / tile;
+    // Workgroups of 1024 lanes where staging the codebook with every 256 points costs more than it should, all of the same
+    // size, in whole rounds: 4-byte entries (fp16) two workgroups per CU with a point per lane, 8-byte entries one with two
+    // points per lane.  Measured, us, 256-lane tiles / this, sdf3d's tables: fp32 300007 points 338 / 203, 2^20 725 (1024-lane
+    // tiles) / 578; fp16 300007 211 / 149, 100003 75 / 87.  Smaller codebooks (nerf3d's 8 KB) from 2^20 points, 455 / 413.
+    const bool big_codebook = lds >= kBwdInputLargeLds;
+    const bool large = staged && ((big_codebook && N >= kBwdInputLargePoints) ||
+                                  (c_stride >= 8192 && N >= (int64_t)kFwdTileLarge * 1024));
+    constexpr bool wide = sizeof(FeatT) == 4;
+    int64_t per = kFwdTile;
+    if (large) {
+        const int64_t slots = wide && big_codebook ? kCus : 2 * kCus, most = (wide && big_codebook ? 2 : 1) * kFwdTileLarge;
+        const int64_t wgs = (N + slots * most - 1) / (slots * most) * slots;
+        per = ((N + wgs - 1) / wgs + 63) / 64 * 64;
+    }
+    const int64_t blocks = (N + per - 1) / per;
     if (int rc = check_blocks(blocks)) return rc;
     const int vec = (c_stride % 16 == 0 && ((uintptr_t)D_c & 15u) == 0) ? 1 : 0;
     LaunchTimer t(s, K_BWD_INPUT);
-#define CNGP_BWD_INPUT(FMT, TILE, STAGED)                                                                   \
-    encode_bwd_input_kernel<D, FeatT, IoT, FMT, TILE, STAGED><<<(unsigned)blocks, TILE, STAGED ? lds : 0, s>>>( \
-        p, x, (const FeatT *)D_f, (const uint8_t *)D_c, (const IoT *)dy, grad_x, N, (uint32_t)c_stride, vec)
+#define CNGP_BWD_INPUT(FMT, TILE, STAGED, PTS)                                                              \
+    encode_bwd_input_kernel<D, FeatT, IoT, FMT, TILE, STAGED, PTS><<<(unsigned)blocks, TILE, STAGED ? lds : 0, s>>>( \
+        p, x, (const FeatT *)D_f, (const uint8_t *)D_c, (const IoT *)dy, grad_x, N, (uint32_t)c_stride, vec, (uint32_t)per)
 #define CNGP_BWD_INPUT_FMT(FMT)                                                                             \
-    if (!staged) CNGP_BWD_INPUT(FMT, kFwdTile, false);                                                      \
-    else if (large) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true);                                               \
-    else CNGP_BWD_INPUT(FMT, kFwdTile, true)
+    if (!staged) CNGP_BWD_INPUT(FMT, kFwdTile, false, 1);                                                   \
+    else if (large && wide && big_codebook) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, (wide ? 2 : 1));       \
+    else if (large) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, 1);                                            \
+    else CNGP_BWD_INPUT(FMT, kFwdTile, true, 1)
     if (fmt == CNGP_IDX_PACKED4) { CNGP_BWD_INPUT_FMT(kFmtPacked4); }
     else if (fmt == CNGP_IDX_BITS) { CNGP_BWD_INPUT_FMT(kFmtBits); }
     else { CNGP_BWD_INPUT_FMT(kFmtU8); }

@@ -241,21 +241,29 @@ __global__ __launch_bounds__(TILE) void encode_fwd_tile_kernel(
 // ------------------------------------------------------------------ gradient with respect to the points
 // dL/dx of the forward pass above (the index of Eq. 6 is constant inside a cell, so the derivative acts on
 // the d-linear weights):  dL/dx_j = sum_l N_l sum_c (+-1)_j prod_{i != j} w_i(c) <D_f[l][idx_c], dL/dy[n, l]>.
-// Same tile structure as the forward pass: the level's index codebook staged in LDS, one lane per point.
-template <int D, typename FeatT, typename IoT, int FMT, int TILE, bool STAGED>
+// Same tile structure as the forward pass: the level's index codebook staged in LDS, PTS points per lane, `per` <= PTS *
+// TILE points per workgroup (lanes without a point still help to stage; they look up the origin).  Bound by the cache lines
+// a CU can ask for, beside the staging of a large codebook (64 KB of bytes per level and workgroup at N_c = 2^16).
+template <int D, typename FeatT, typename IoT, int FMT, int TILE, bool STAGED, int PTS>
 __global__ __launch_bounds__(TILE) void encode_bwd_input_kernel(
     const Params p, const float *__restrict__ x, const FeatT *__restrict__ D_f, const uint8_t *__restrict__ D_c,
-    const IoT *__restrict__ dy, float *__restrict__ grad_x, const int64_t N, const uint32_t c_stride, const int vec)
+    const IoT *__restrict__ dy, float *__restrict__ grad_x, const int64_t N, const uint32_t c_stride, const int vec,
+    const uint32_t per)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     uint8_t *probes = smem;
     const uint32_t lds_c = (p.N_c + 1u) / 2u;
     const int     t = threadIdx.x;
-    const int64_t n = (int64_t)blockIdx.x * TILE + t;
-    const bool    valid = n < N;
-    float xp[D], gx[D];
+    const int64_t n0 = (int64_t)blockIdx.x * per;
+    float xp[PTS][D], gx[PTS][D];
+    bool  valid[PTS];
 #pragma unroll
-    for (int j = 0; j < D; ++j) { xp[j] = valid ? x[n * D + j] : 0.0f; gx[j] = 0.0f; }
+    for (int u = 0; u < PTS; ++u) {
+        const uint32_t i = (uint32_t)(u * TILE + t);
+        valid[u] = i < per && n0 + i < N;
+#pragma unroll
+        for (int j = 0; j < D; ++j) { xp[u][j] = valid[u] ? x[(n0 + i) * D + j] : 0.0f; gx[u][j] = 0.0f; }
+    }
 
     for (int l = 0; l < p.L; ++l) {
         const uint8_t *C_l = D_c + (size_t)l * c_stride;
@@ -264,40 +272,45 @@ __global__ __launch_bounds__(TILE) void encode_bwd_input_kernel(
             stage_probes<FMT, TILE>(probes, C_l, c_stride, lds_c, vec, t);
             __syncthreads();
         }
-        Cell<D> cell;
-        cell.locate(xp, p.N_l[l]);
         const FeatT *F_l = D_f + (size_t)l * p.N_f * 2;
-        uint32_t idx[1 << D];
 #pragma unroll
-        for (int c = 0; c < (1 << D); ++c) {
-            const uint32_t r = cell.hash2(c) & p.c_mask;
-            const uint32_t probe = !STAGED ? read_probe<FMT>(C_l, r, p.log2_Np)
-                                 : FMT == kFmtBits ? read_probe_bits_lds(probes, r, p.log2_Np)
-                                                   : read_probe<kFmtPacked4>(probes, r, p.log2_Np);
-            idx[c] = probe_base(cell.hash1(c), p) + probe;
-        }
-        float2 feat[1 << D];
+        for (int u = 0; u < PTS; ++u) {
+            Cell<D> cell;
+            cell.locate(xp[u], p.N_l[l]);
+            uint32_t idx[1 << D];
 #pragma unroll
-        for (int c = 0; c < (1 << D); ++c) feat[c] = load_pair(F_l, idx[c]);
-        const float2 g = valid ? load_pair(dy, (size_t)n * p.L + l) : make_float2(0.f, 0.f);
-        const float  res = (float)p.N_l[l];
+            for (int c = 0; c < (1 << D); ++c) {
+                const uint32_t r = cell.hash2(c) & p.c_mask;
+                const uint32_t probe = !STAGED ? read_probe<FMT>(C_l, r, p.log2_Np)
+                                     : FMT == kFmtBits ? read_probe_bits_lds(probes, r, p.log2_Np)
+                                                       : read_probe<kFmtPacked4>(probes, r, p.log2_Np);
+                idx[c] = probe_base(cell.hash1(c), p) + probe;
+            }
+            float2 feat[1 << D];
 #pragma unroll
-        for (int c = 0; c < (1 << D); ++c) {
-            const float tc = res * fmaf(feat[c].x, g.x, feat[c].y * g.y);
+            for (int c = 0; c < (1 << D); ++c) feat[c] = load_pair(F_l, idx[c]);
+            const float2 g = valid[u] ? load_pair(dy, (size_t)(n0 + u * TILE + t) * p.L + l) : make_float2(0.f, 0.f);
+            const float  res = (float)p.N_l[l];
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                float dw = ((c >> j) & 1) ? tc : -tc;
+            for (int c = 0; c < (1 << D); ++c) {
+                const float tc = res * fmaf(feat[c].x, g.x, feat[c].y * g.y);
 #pragma unroll
-                for (int i = 0; i < D; ++i)
-                    if (i != j) dw *= ((c >> i) & 1) ? cell.w[i] : 1.0f - cell.w[i];
-                gx[j] += dw;
+                for (int j = 0; j < D; ++j) {
+                    float dw = ((c >> j) & 1) ? tc : -tc;
+#pragma unroll
+                    for (int i = 0; i < D; ++i)
+                        if (i != j) dw *= ((c >> i) & 1) ? cell.w[i] : 1.0f - cell.w[i];
+                    gx[u][j] += dw;
+                }
             }
         }
     }
-    if (valid) {
 #pragma unroll
-        for (int j = 0; j < D; ++j) grad_x[n * D + j] = gx[j];
-    }
+    for (int u = 0; u < PTS; ++u)
+        if (valid[u]) {
+#pragma unroll
+            for (int j = 0; j < D; ++j) grad_x[(n0 + u * TILE + t) * D + j] = gx[u][j];
+        }
 }
 
 // ------------------------------------------------------------------ backward (Sec. 3 "Training")

@@ -63,3 +63,23 @@ def test_input_gradient_full_size_workloads():
     run(W.WORKLOADS["nerf3d"], cngp.IDX_U8)
     # more than 2^20 points with a 2^16-entry index codebook: the large-tile variant, ragged last tile
     run(W.WORKLOADS["compact3d"], cngp.IDX_BITS, n=2**20 + 1024 + 77)
+
+
+@pytest.mark.parametrize("feat,N", [("f16", 160 * 1024 - 1), ("f16", 160 * 1024), ("f32", 160 * 1024 + 63), ("f32", 2**19 + 1),
+                                    ("f16", 2**19 + 1)])
+def test_large_codebook_large_tiles(feat, N):
+    """N_c = 2^16: from 160 Ki points workgroups of 1024 lanes with equal shares, one or two points per lane; the last
+    size is one point more than a round holds.  Same bits as the same points in small batches (256-lane tiles)."""
+    w = W.custom(cfg=71, d=3, L=3, F=2, N_f=2**12, N_c=2**16, N_p=8, N_min=8, N_max=300, N=N, feat_dtype=feat, io_dtype=feat)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    x = dev(W.make_points(w))
+    D_f = dev(W.make_feature_codebook(w))
+    dy = dev(W.make_upstream_grad(w, N))
+    cfg = cngp.Config.from_workload(w)
+    D_c = cngp.bake_probes(cfg, dev(W.make_probe_logits(w)))
+    whole = cngp.encode_bwd_input(cfg, x, D_f, D_c, dy)
+    step = 100_000
+    parts = torch.cat([cngp.encode_bwd_input(cfg, x[i:i + step].contiguous(), D_f, D_c, dy[i:i + step].contiguous())
+                       for i in range(0, N, step)])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
