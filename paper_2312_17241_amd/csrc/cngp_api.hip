@@ -499,6 +499,11 @@ constexpr uint32_t kMinBinnedSlicesPerLevel = 24; // from here on binning the re
 constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated scan costs more than global atomics
 constexpr size_t   kSmallBwdLds = 128 * 1024;   // both gradient tables of a level (fp64) that a small batch accumulates in LDS
 constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
+// References per level (N * 2^d) from which the binned variant pre-reduces coarse levels: below, the extra launch and the two
+// vertex roles, which scan whole grids whatever the batch is, cost more than the references they save.  Backward, us, with /
+// without: nerf3d's tables 20011 points 152 / 119, 100003 290 / 235, 130000 354 / 323, 163840 384 / 403, 2^18 539 / 569;
+// sdf3d's 30011 198 / 157, 100000 439 / 372, 2^20 2786 / 3294; d = 2 200000 602 / 425, 600000 1001 / 1175; d = 4 50000 223 / 173.
+constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -656,6 +661,8 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N) {
             if (slices * 2 > per_level && slices > 1) break;
             if (b.fused) break;      // both gradients from one pass over the bins: cheaper than the grid sums and vertex scans (measured)
             if (b.binned && l == c->L - 1) break;                        // (at least one level stays hashed)
+            // (a caller who bounds the bins gets the smaller workspace: a pre-reduced level has records once instead of twice)
+            if (b.binned && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) && !c->bin_bytes_max) break;
             b.dense.side[l] = res[l] + 2;
             b.dense.verts[l] = (uint32_t)verts;
             b.dense.slices[l] = (uint32_t)slices;

@@ -37,3 +37,22 @@ def test_small_tables_accumulate_in_lds(d, L, N_f, N_c, N_p, N, feat, io, top_k)
     cngp.encode_bwd(cfg, dev(x), dev(D_f), dev(Dhat), dev(dy), gF, gC)
     torch.cuda.synchronize()
     check_close("grad D_f, twice", gF.cpu().numpy(), 2 * gF_ref, 2 * A_f, fp16_out=False)
+
+
+@pytest.mark.parametrize("d,N,dense", [(3, 2**17 - 1, False), (3, 2**17, True), (2, 2**18 - 1, False), (2, 2**18, True)])
+def test_binned_batches_pre_reduce_from_a_million_references_per_level(d, N, dense):
+    """The last batch that bins every level and the first that sums the coarse ones per vertex: the same gradients."""
+    w = W.custom(cfg=95 + d, d=d, L=8, F=2, N_f=2**18, N_c=2**14, N_p=16, N_min=8, N_max=256, N=N, feat_dtype="f32", io_dtype="f32")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+    args = [dev(a) for a in (W.make_points(w), W.make_feature_codebook(w), W.make_probe_logits(w), W.make_upstream_grad(w, N))]
+    cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS)
+    info = cngp.bwd_plan_info(cfg, N)
+    assert info["binned"] == 1 and (info["dense_levels"] > 0) == dense
+    got = cngp.encode_bwd(cfg, *args, workspace=cngp.alloc_workspace(cfg, N))
+    mag = cngp.encode_bwd(cfg, *args[:3], args[3].abs(), workspace=cngp.alloc_workspace(cfg, N))[0]
+    ref_cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS | cngp.BWD_DIRECT)
+    ref = cngp.encode_bwd(ref_cfg, *args)
+    torch.cuda.synchronize()
+    # the direct kernel sums in fp32: up to a few thousand terms to an entry, 2^-24 each, of the terms' magnitudes
+    assert bool(((got[0] - ref[0]).abs() <= 1e-4 * mag + 1e-12).all())
+    assert float((got[0] - ref[0]).norm() / ref[0].norm()) < 1e-5 and float((got[1] - ref[1]).norm() / ref[1].norm()) < 1e-5
