@@ -123,6 +123,8 @@ int cngp_storage_bytes(const cngp_config *cfg, size_t *D_f_bytes, size_t *D_c_le
  * (cngp_fwd_workspace_bytes below; without it they run a slower variant with the same result).  With F != 2 one pair
  * of features at a time is copied out of D_f, y, dL/dy and back, and those planes sit in the workspace too (the
  * forward calls then need it as well).
+ * cngp_encode_bwd also runs in less where a layout that pre-reduces more of the coarse levels fits: the workspace of
+ * a batch serves every shorter one.
  * The workspace must be 256-byte aligned; its contents are undefined before and after each call.
  * Returns 0 for an invalid configuration as well (the encode calls then report the error). */
 size_t cngp_workspace_bytes(const cngp_config *cfg, int64_t N);

@@ -593,7 +593,11 @@ void choose_geometry(const cngp_config *c, int64_t N, BwdPlan &b) {
 }
 
 
-BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N) {
+// Which levels a binned batch pre-reduces: those that pay, those that pay in a large batch, or every one that can be (its set
+// does not depend on N, so what the last layout needs only grows with N).
+enum Layout { LAYOUT_FAST = 0, LAYOUT_REDUCED, LAYOUT_LEAST, LAYOUT_COUNT };
+
+BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = LAYOUT_FAST) {
     BwdPlan b;
     std::memset(&b, 0, sizeof(b));
     const uint32_t groups = c->N_f / c->N_p;                               // hashed rows of D_f
@@ -657,12 +661,14 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N) {
             uint64_t verts = 1;
             for (int i = 0; i < c->d; ++i) verts *= (uint64_t)res[l] + 2;
             const uint64_t slices = (verts + kDenseSliceVerts - 1) / kDenseSliceVerts;
-            if (verts > kMaxDenseVerts || (N << c->d) < kMinRefsPerVertex * (int64_t)verts) break;
+            if (verts > kMaxDenseVerts) break;
+            if ((N << c->d) < kMinRefsPerVertex * (int64_t)verts && !(b.binned && layout == LAYOUT_LEAST)) break;
             if (slices * 2 > per_level && slices > 1) break;
             if (b.fused) break;      // both gradients from one pass over the bins: cheaper than the grid sums and vertex scans (measured)
             if (b.binned && l == c->L - 1) break;                        // (at least one level stays hashed)
             // (a caller who bounds the bins gets the smaller workspace: a pre-reduced level has records once instead of twice)
-            if (b.binned && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) && !c->bin_bytes_max) break;
+            if (b.binned && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) && !c->bin_bytes_max &&
+                layout == LAYOUT_FAST) break;
             b.dense.side[l] = res[l] + 2;
             b.dense.verts[l] = (uint32_t)verts;
             b.dense.slices[l] = (uint32_t)slices;
@@ -708,15 +714,17 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N) {
         b.ws_bytes = b.G_off + align256((size_t)b.dense_verts * 2 * sizeof(float));
         if (b.binned) {
             const size_t cap = (size_t)N << c->d;
+            // (room for as many chunks as any shorter batch has: 2^18 points are counted in 256, one more in 241)
+            const size_t rows = layout == LAYOUT_LEAST ? b.bin_chunks : (size_t)(N >= 256 * 1024 ? 256 : (N + 1023) / 1024);
             b.cntF_off = b.ws_bytes;
-            b.cntC_off = b.cntF_off + align256((size_t)Lh * b.bin_chunks * b.slices_f * 4);
-            b.baseF_off = b.cntC_off + align256((size_t)Lh * b.bin_chunks * b.slices_c * 4);
+            b.cntC_off = b.cntF_off + align256((size_t)Lh * rows * b.slices_f * 4);
+            b.baseF_off = b.cntC_off + align256((size_t)Lh * rows * b.slices_c * 4);
             b.baseC_off = b.baseF_off + align256((size_t)Lh * (b.slices_f + 1) * 4);
             b.recF_off = b.baseC_off + align256((size_t)Lh * (b.slices_c + 1) * 4);
             b.recC_off = b.recF_off + (b.fused ? 0 : align256((size_t)Lh * cap * kRecordBytes));
             b.cntG_off = b.recC_off + (b.slices_c ? align256((size_t)Lh * cap * kRecordBytes) : 0);
             const size_t Ld = (size_t)b.dense.count;
-            b.baseG_off = b.cntG_off + align256(Ld * b.bin_chunks * kGridBins * 4);
+            b.baseG_off = b.cntG_off + align256(Ld * rows * kGridBins * 4);
             b.recG_off = b.baseG_off + align256(Ld * (kGridBins + 1) * 4);
             b.ws_bytes = b.recG_off + align256(Ld * cap * kRecordBytes);
             // workgroups per slice of a level's grid: about 2^15 references each
@@ -735,16 +743,26 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N) {
     return b;
 }
 
-// The plan depends on (configuration, N) only; the last one is kept (host memory, per thread).
-BwdPlan make_bwd_plan(const cngp_config *c, int64_t N) {
-    thread_local cngp_config last_cfg;
-    thread_local int64_t     last_N = -1;
-    thread_local BwdPlan     last_plan;
-    if (last_N == N && std::memcmp(&last_cfg, c, sizeof(*c)) == 0) return last_plan;
-    last_plan = make_bwd_plan_uncached(c, N);
-    last_cfg = *c;
-    last_N = N;
-    return last_plan;
+// The plan depends on (configuration, N) only; the last one of each layout is kept (host memory, per thread).
+const BwdPlan &make_bwd_plan(const cngp_config *c, int64_t N, Layout layout = LAYOUT_FAST) {
+    struct Kept { cngp_config cfg; int64_t N = -1; BwdPlan plan; };
+    thread_local Kept kept[LAYOUT_COUNT];
+    Kept &k = kept[layout];
+    if (k.N == N && std::memcmp(&k.cfg, c, sizeof(*c)) == 0) return k.plan;
+    k.plan = make_bwd_plan_uncached(c, N, layout);
+    k.cfg = *c;
+    k.N = N;
+    return k.plan;
+}
+
+// The plan of a call that has `room` bytes: the first layout that fits.  What the fastest one needs does not only grow with N (a
+// level that is not pre-reduced has records in two tables instead of one: nerf3d's tables take 144 MB at 2^17 points, 160 at one
+// less), so that a workspace sized for the largest batch of a training run serves the shorter ones too.
+const BwdPlan &bwd_plan_for(const cngp_config *c, int64_t N, size_t room) {
+    const BwdPlan &b = make_bwd_plan(c, N);
+    if (!b.binned || b.ws_bytes <= room) return b;
+    const BwdPlan &reduced = make_bwd_plan(c, N, LAYOUT_REDUCED);
+    return reduced.ws_bytes <= room ? reduced : make_bwd_plan(c, N, LAYOUT_LEAST);
 }
 
 // Points per pass of cngp_encode_bwd.  A batch whose bins would pass the configured limit (or whose references
@@ -1065,16 +1083,23 @@ size_t workspace_bytes_pairs(const cngp_config *cfg, int64_t N) {
     const size_t  last = make_bwd_plan_uncached(cfg, N - (N - 1) / per * per).ws_bytes;
     return most > last ? most : last;
 }
+// The smallest workspace with which cngp_encode_bwd runs.
+size_t least_workspace_pairs(const cngp_config *cfg, int64_t N) {
+    const size_t bytes = workspace_bytes_pairs(cfg, N);
+    if (bwd_pass_points(cfg, N) < N) return bytes;
+    const size_t least = make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes;
+    return least < bytes ? least : bytes;
+}
 
 // ---------------------------------------------------------------- feature widths other than two
 // F = 1, 4, 8 run as ceil(F / 2) passes over pair planes (cngp_kernels.h, plane_take_kernel): behind the workspace
 // of the two-feature problem sit one plane of D_f, one plane of y or dL/dy, and one plane of grad D_f.
 struct PlaneSpace { size_t pairs, D_off, io_off, g_off, total; };
 cngp_config as_pairs(const cngp_config *c) { cngp_config p = *c; p.F = 2; return p; }
-PlaneSpace plane_space(const cngp_config *c, int64_t N) {
+PlaneSpace plane_space(const cngp_config *c, int64_t N, bool least = false) {
     const cngp_config c2 = as_pairs(c);
     PlaneSpace ps;
-    const size_t bwd = workspace_bytes_pairs(&c2, N), fwd = fwd_level_plan(&c2, c2.L, N).yT_bytes;
+    const size_t bwd = least ? least_workspace_pairs(&c2, N) : workspace_bytes_pairs(&c2, N), fwd = fwd_level_plan(&c2, c2.L, N).yT_bytes;
     ps.pairs = align256(bwd > fwd ? bwd : fwd);
     ps.D_off = ps.pairs;
     ps.io_off = ps.D_off + align256((size_t)c->L * c->N_f * 2 * (c->feat_dtype == CNGP_F16 ? 2 : 4));
@@ -1107,13 +1132,17 @@ int take_plane_dt(int dtype, const void *src, void *dst, int64_t rows, int F, in
 int put_plane_dt(int dtype, const void *src, void *dst, int64_t rows, int F, int plane, bool acc, hipStream_t s) {
     return dtype == CNGP_F16 ? put_plane<__half>(src, dst, rows, F, plane, acc, s) : put_plane<float>(src, dst, rows, F, plane, acc, s);
 }
+PlaneSpace plane_space_for(const cngp_config *c, int64_t N, size_t room) {
+    const PlaneSpace ps = plane_space(c, N);
+    return ps.total <= room ? ps : plane_space(c, N, true);
+}
 bool plane_workspace_ok(const void *ws, size_t bytes, const PlaneSpace &ps) {
     return ws && ((uintptr_t)ws & 255u) == 0 && bytes >= ps.total;
 }
 
 int fwd_planes(const cngp_config *cfg, int32_t levels_loaded, const float *x, int64_t N, const void *D_f, const void *D_c,
                void *y, void *workspace, size_t workspace_bytes, void *stream) {
-    const PlaneSpace ps = plane_space(cfg, N);
+    const PlaneSpace ps = plane_space_for(cfg, N, workspace_bytes);
     if (!plane_workspace_ok(workspace, workspace_bytes, ps)) return CNGP_ERR_WORKSPACE;
     const cngp_config c2 = as_pairs(cfg);
     hipStream_t s = (hipStream_t)stream;
@@ -1135,7 +1164,7 @@ int bwd_planes(const cngp_config *cfg, const float *x, int64_t N, const void *D_
         if (zero_first) { z.add(grad_D_f, (int64_t)cfg->L * cfg->N_f * cfg->F); z.add(grad_Dhat_c, (int64_t)cfg->L * cfg->N_c * cfg->N_p); }
         return z.launch(s);
     }
-    const PlaneSpace ps = plane_space(cfg, N);
+    const PlaneSpace ps = plane_space_for(cfg, N, workspace_bytes);
     if (!plane_workspace_ok(workspace, workspace_bytes, ps)) return CNGP_ERR_WORKSPACE;
     cngp_config c2 = as_pairs(cfg);
     c2.flags &= ~(uint32_t)CNGP_ZERO_GRADS;         // the plane of grad D_f is cleared here, grad D^_c once if asked
@@ -1340,7 +1369,7 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
         }
         return CNGP_OK;
     }
-    const BwdPlan b = make_bwd_plan(cfg, N);
+    const BwdPlan b = bwd_plan_for(cfg, N, workspace_bytes);
     if (N > 0 && b.sliced) {
         if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < b.ws_bytes) return CNGP_ERR_WORKSPACE;
     }
@@ -1378,6 +1407,11 @@ int cngp_encode_bwd_static(const cngp_config *cfg, const float *x, int64_t N, co
     // entry point never falls back to a slower variant behind the caller's back.
     cngp_config c = *cfg;
     size_t need = cngp_workspace_bytes(&c, N);
+    if (need > kStaticScratchBytes && N > 0) {      // in one pass all the same, if the smallest layout fits
+        const cngp_config pairs = as_pairs(cfg);
+        const size_t least = cfg->F != 2 ? plane_space(cfg, N, true).total : least_workspace_pairs(&pairs, N);
+        if (least <= kStaticScratchBytes) need = least;
+    }
     if (need > kStaticScratchBytes && N > 0) {
         const int64_t per0 = bwd_pass_points(cfg, N);
         const bool    binned = make_bwd_plan_uncached(cfg, per0 < N ? per0 : N).binned;

@@ -276,6 +276,23 @@ def test_backward_plan_layout_stays_inside_the_workspace():
     assert min(seen.values()) >= 5, seen          # the sweep reaches every variant
 
 
+def test_a_backward_workspace_holds_a_layout_of_every_shorter_batch():
+    """The need of a batch that bins every level may pass that of a larger one, which pre-reduces its coarse levels; the
+    pre-reduced layout, which cngp_encode_bwd falls back on, does not."""
+    dips = 0
+    for d, N_max, kw in ((3, 2048, {}), (2, 512, dict(L=12)), (4, 256, dict(L=12)), (3, 4096, dict(N_f=2**18, N_c=2**16, N_p=8))):
+        w = W.custom(**{**dict(cfg=9, d=d, L=16, N_f=2**16, N_c=2**14, N_p=16, N_min=16, N_max=N_max, N=1, feat_dtype="f16", io_dtype="f16"), **kw})
+        cfg, least = (cngp.Config.from_workload(w, flags=f) for f in (cngp.ZERO_GRADS, cngp.ZERO_GRADS | cngp.BWD_BINNED))
+        line = 2**20 >> d
+        for N in (line, line + 1, line + line // 8, 2 * line):
+            have = cngp.workspace_bytes(cfg, N)
+            for n in (line - 1, line * 7 // 8, line // 2 + 1, line // 4):
+                dips += cngp.workspace_bytes(cfg, n) > have
+                assert cngp.bwd_plan_info(cfg, n)["binned"] == 1
+                assert cngp.workspace_bytes(least, n) <= have, (d, N, n)
+    assert dips >= 4                              # (the first of these are real)
+
+
 def test_forward_plan_is_within_the_chip_and_the_workspace():
     """The level-resident forward variant for seeded random configurations: the resident part of a level's feature
     codebook is a whole number of 16-byte pieces, at most the codebook; index codebook and resident part fit 160 KB of
