@@ -499,14 +499,25 @@ constexpr uint32_t kMinBinnedSlicesPerLevel = 24; // from here on binning the re
 constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated scan costs more than global atomics
 constexpr size_t   kSmallBwdLds = 128 * 1024;   // both gradient tables of a level (fp64) that a small batch accumulates in LDS
 constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
-// References per level (N * 2^d) from which the binned variant pre-reduces coarse levels: below, the extra launch and the two
-// vertex roles, which scan whole grids whatever the batch is, cost more than the references they save.  Backward, us, with /
-// without: nerf3d's tables 20011 points 152 / 119, 100003 290 / 235, 130000 354 / 323, 163840 384 / 403, 2^18 539 / 569;
-// sdf3d's 30011 198 / 157, 100000 439 / 372, 2^20 2786 / 3294; d = 2 200000 602 / 425, 600000 1001 / 1175; d = 4 50000 223 / 173.
+// References per level (N * 2^d) from which the binned variant always pre-reduces coarse levels; below, binned_bwd_us decides.
+// Backward, us, with / without, beyond it: nerf3d's tables 163840 points 384 / 403, 2^18 539 / 569; sdf3d's 2^20 2786 / 3294;
+// d = 2 600000 1001 / 1175.
 constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
+
+// Drain workgroups per bin of a table with `slices` slices per level: about 2^16 records each, and enough workgroups to
+// fill the chip twice, but never less than 8192 records each.  `refs` references per level, `levels` hashed levels.
+uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level) {
+    if (!slices) return 1;
+    double want = refs / slices / 65536.0;
+    const double fill = 512.0 / ((double)levels * slices_per_level), by_size = refs / slices / 8192.0;
+    if (want < fill) want = fill;
+    if (want > by_size) want = by_size;
+    const uint32_t r = (uint32_t)(want + 0.5);
+    return r < 1 ? 1 : (r > 64 ? 64 : r);
+}
 
 // Chunk count that minimises (rounds of workgroups over the CUs) x (items per chunk + fixed cost per
 // workgroup, in items: clearing and flushing its LDS slice).  `groups` workgroups exist per chunk.
@@ -593,6 +604,45 @@ void choose_geometry(const cngp_config *c, int64_t N, BwdPlan &b) {
 }
 
 
+// Time of a binned backward with its first Ld levels pre-reduced, us.  The drain takes the longer of its work spread over the
+// CUs and its longest workgroup: a coarse level has few vertices, all of a vertex's references fall into one bin, and the
+// bins of such a level are far from equal (d = 2, N_min = 16: 324 vertices for all the references of the coarsest level).
+// Pre-reducing takes that away and makes its workgroups scan the whole vertex grid per slice, besides one launch more.
+// Fitted to 560 drawn configurations (d = 2 .. 4, 2 .. 24 levels, N_f 2^12 .. 2^19, N_c to 2^17, uniform points, rays and a
+// shell), each timed both ways: 12 % off on average, and 13 % on the ratio of the two ways.  Always pre-reducing was 1.19x slower than
+// the better of the two on average, never pre-reducing 1.08x (up to 4.6x); this choice 1.009x.  With / without, us: nerf3d's
+// tables 20011 points 152 / 119, 100003 290 / 235; d = 2, L = 12, the same tables to N_max = 512, 262143 points: 259 / 384.
+double binned_bwd_us(const cngp_config *c, int64_t N, const BwdPlan &b, int Ld) {
+    uint32_t res[kMaxLevels];
+    level_table(c, res);
+    const uint32_t tables[2] = {b.slices_f, b.slices_c}, slices = b.slices_f + b.slices_c;
+    const double   refs = (double)((uint64_t)N << c->d), flush = 5.8, record = 1.37e-3 + 4.3e-5 * c->N_p, vertex = 1.15e-3;
+    double work = 0.0, longest = 0.0, records = 0.0, most_verts = 0.0;
+    for (int l = 0; l < c->L; ++l) {
+        const double verts = std::pow((double)res[l] + 2.0, c->d);
+        if (l < Ld) {
+            work += slices * verts * vertex;
+            if (verts > most_verts) most_verts = verts;
+            continue;
+        }
+        const double seen = verts < refs ? verts : refs;
+        for (const uint32_t s : tables) {
+            if (!s) continue;
+            const uint32_t subs = drain_subs(refs, s, c->L - Ld, slices);
+            const double   mean = seen / s;
+            double fullest = mean + std::sqrt(2.0 * mean * std::log(s > 2 ? (double)s : 2.0)) + (mean < 3.0 ? 1.0 : 0.0);    // vertices of the fullest bin
+            if (fullest > seen) fullest = seen;
+            work += (double)s * subs * flush + refs * record;
+            records += refs;
+            const double t = refs / seen * fullest / subs * record + flush;
+            if (t > longest) longest = t;
+        }
+    }
+    work = (work + (double)Ld * slices * std::ceil(most_verts / 16384.0) * flush) / (double)kCus;
+    return 18.0 + 6.6e-6 * c->L * (double)c->N_c * c->N_p + std::sqrt(std::sqrt(work * work * work * work + longest * longest * longest * longest)) +
+           3.1e-6 * records + (Ld > 0 ? 23.0 + 6.4e-6 * Ld * refs : 0.0);
+}
+
 // Which levels a binned batch pre-reduces: those that pay, those that pay in a large batch, or every one that can be (its set
 // does not depend on N, so what the last layout needs only grows with N).
 enum Layout { LAYOUT_FAST = 0, LAYOUT_REDUCED, LAYOUT_LEAST, LAYOUT_COUNT };
@@ -666,9 +716,6 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             if (slices * 2 > per_level && slices > 1) break;
             if (b.fused) break;      // both gradients from one pass over the bins: cheaper than the grid sums and vertex scans (measured)
             if (b.binned && l == c->L - 1) break;                        // (at least one level stays hashed)
-            // (a caller who bounds the bins gets the smaller workspace: a pre-reduced level has records once instead of twice)
-            if (b.binned && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) && !c->bin_bytes_max &&
-                layout == LAYOUT_FAST) break;
             b.dense.side[l] = res[l] + 2;
             b.dense.verts[l] = (uint32_t)verts;
             b.dense.slices[l] = (uint32_t)slices;
@@ -677,6 +724,13 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             b.dense_slices += (uint32_t)slices;
             if (verts > b.dense_max_verts) b.dense_max_verts = (uint32_t)verts;
             b.dense.count = l + 1;
+        }
+        // (a caller who bounds the bins gets the smaller workspace: a pre-reduced level has records once instead of twice)
+        if (b.binned && b.dense.count > 0 && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) &&
+            !c->bin_bytes_max && layout == LAYOUT_FAST &&
+            binned_bwd_us(c, N, b, b.dense.count) > 0.96 * binned_bwd_us(c, N, b, 0)) {
+            std::memset(&b.dense, 0, sizeof(b.dense));
+            b.dense_verts = b.dense_slices = b.dense_max_verts = 0;
         }
     }
     const int Lh = c->L - b.dense.count;
@@ -687,20 +741,9 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         if (cp < 1024) cp = 1024;
         b.bin_chunk_pts = (uint32_t)cp;
         b.bin_chunks = (uint32_t)((N + cp - 1) / cp);
-        // drain workgroups per bin: about 2^16 records each, and enough workgroups to fill the chip twice
         const double refs = (double)((uint64_t)N << c->d);
-        auto subs = [&](uint32_t slices) -> uint32_t {
-            if (!slices) return 1;
-            double want = refs / slices / 65536.0;
-            const double fill = 512.0 / ((double)Lh * (b.slices_f + b.slices_c));
-            if (want < fill) want = fill;
-            const double by_size = refs / slices / 8192.0;              // but never less than 8192 records each
-            if (want > by_size) want = by_size;
-            uint32_t r = (uint32_t)(want + 0.5);
-            return r < 1 ? 1 : (r > 64 ? 64 : r);
-        };
-        b.subs_f = subs(b.slices_f);
-        b.subs_c = subs(b.slices_c);
+        b.subs_f = drain_subs(refs, b.slices_f, Lh, b.slices_f + b.slices_c);
+        b.subs_c = drain_subs(refs, b.slices_c, Lh, b.slices_f + b.slices_c);
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
     }
     const size_t queues = (size_t)kSlicedWaves * kRingBytes;

@@ -276,6 +276,17 @@ def test_backward_plan_layout_stays_inside_the_workspace():
     assert min(seen.values()) >= 5, seen          # the sweep reaches every variant
 
 
+def test_small_binned_batches_pre_reduce_where_the_coarse_bins_are_uneven():
+    """Below 2^20 references per level the plan weighs pre-reducing the coarse levels against binning them: many levels with
+    few vertices (d = 2) pre-reduce, three-dimensional batches of ray samples bin everything; a caller who bounds the bins,
+    asks for the binned variant or has more references per level always pre-reduces."""
+    dense = lambda N, flags=0, **kw: cngp.bwd_plan_info(base_cfg(flags=cngp.ZERO_GRADS | flags, **kw), N)["dense_levels"]
+    flat = dict(d=2, L=12, N_max=512)
+    assert dense(20011) == 0 and dense(100003) == 0 and dense(2**17) == 4
+    assert dense(2**18 - 1, **flat) == 10 and dense(150000, **flat) == 10 and dense(2**18, **flat) == 10
+    assert dense(20011, cngp.BWD_BINNED) == 3 and dense(20011, bin_bytes_max=1 << 30) == 3
+
+
 def test_a_backward_workspace_holds_a_layout_of_every_shorter_batch():
     """The need of a batch that bins every level may pass that of a larger one, which pre-reduces its coarse levels; the
     pre-reduced layout, which cngp_encode_bwd falls back on, does not."""
@@ -290,7 +301,7 @@ def test_a_backward_workspace_holds_a_layout_of_every_shorter_batch():
                 dips += cngp.workspace_bytes(cfg, n) > have
                 assert cngp.bwd_plan_info(cfg, n)["binned"] == 1
                 assert cngp.workspace_bytes(least, n) <= have, (d, N, n)
-    assert dips >= 4                              # (the first of these are real)
+    assert dips >= 3                              # (the first of these are real)
 
 
 def test_forward_plan_is_within_the_chip_and_the_workspace():

@@ -32,11 +32,9 @@ def same(got, ref):
         assert float((g - r).norm() / r.norm()) < 4e-6
 
 
-# (2^18 + 1 points are counted in fewer, longer chunks than 2^18 - 1)
-@pytest.mark.parametrize("d,L,F,N_max,most,N", [(3, 16, 2, 2048, 2**17, 2**17 - 1), (3, 16, 2, 2048, 2**17, 120001), (3, 16, 4, 2048, 2**17, 2**17 - 1),
-                                                (2, 12, 2, 512, 2**18 + 1, 2**18 - 1)])
-def test_a_workspace_of_a_larger_batch_serves_a_shorter_one(d, L, F, N_max, most, N):
-    w = W.custom(cfg=90 + d, d=d, L=L, F=F, N_f=2**16, N_c=2**14, N_p=16, N_min=16, N_max=N_max, N=N, feat_dtype="f16", io_dtype="f16")
+@pytest.mark.parametrize("F,most,N", [(2, 2**17, 2**17 - 1), (2, 2**17, 120001), (4, 2**17, 2**17 - 1)])
+def test_a_workspace_of_a_larger_batch_serves_a_shorter_one(F, most, N):
+    w = W.custom(cfg=93, d=3, L=16, F=F, N_f=2**16, N_c=2**14, N_p=16, N_min=16, N_max=2048, N=N, feat_dtype="f16", io_dtype="f16")
     cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS)
     ws = cngp.alloc_workspace(cfg, most)
     assert ws.numel() < cngp.workspace_bytes(cfg, N)               # the shorter batch would rather have more

@@ -39,10 +39,14 @@ def test_small_tables_accumulate_in_lds(d, L, N_f, N_c, N_p, N, feat, io, top_k)
     check_close("grad D_f, twice", gF.cpu().numpy(), 2 * gF_ref, 2 * A_f, fp16_out=False)
 
 
-@pytest.mark.parametrize("d,N,dense", [(3, 2**17 - 1, False), (3, 2**17, True), (2, 2**18 - 1, False), (2, 2**18, True)])
-def test_binned_batches_pre_reduce_from_a_million_references_per_level(d, N, dense):
-    """The last batch that bins every level and the first that sums the coarse ones per vertex: the same gradients."""
-    w = W.custom(cfg=95 + d, d=d, L=8, F=2, N_f=2**18, N_c=2**14, N_p=16, N_min=8, N_max=256, N=N, feat_dtype="f32", io_dtype="f32")
+# nerf3d's tables and one with few vertices on its coarse levels, on both sides of the choice and of the line above which it
+# is always taken; the dense grids of 2^20 references or more as before
+@pytest.mark.parametrize("d,L,N_min,N_max,N_f,N,dense", [(3, 16, 16, 2048, 2**16, 20011, False), (3, 16, 16, 2048, 2**16, 80000, True),
+                                                       (2, 12, 16, 512, 2**16, 60000, False), (2, 12, 16, 512, 2**16, 2**18 - 1, True),
+                                                       (3, 8, 8, 256, 2**18, 2**17 - 1, True), (3, 8, 8, 256, 2**18, 2**17, True), (2, 8, 8, 256, 2**18, 2**18, True)])
+def test_binned_batches_pre_reduce_where_it_pays(d, L, N_min, N_max, N_f, N, dense):
+    """A batch below a million references per level bins every level or sums the coarse ones per vertex: the same gradients."""
+    w = W.custom(cfg=95 + d, d=d, L=L, F=2, N_f=N_f, N_c=2**14, N_p=16, N_min=N_min, N_max=N_max, N=N, feat_dtype="f32", io_dtype="f32")
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
     args = [dev(a) for a in (W.make_points(w), W.make_feature_codebook(w), W.make_probe_logits(w), W.make_upstream_grad(w, N))]
     cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS)
