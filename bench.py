@@ -105,7 +105,7 @@ def distinct_vertices(np, x_h, res, sample=1 << 20):
     return out_v, out_r
 
 
-def level_rooflines(w, n, index_level_bytes, res, V, refs, rates, fwd_only, lds_share=0.0):
+def level_rooflines(w, n, index_level_bytes, res, V, refs, rates, fwd_only, lds_share=0.0, grids=0):
     """The applicable roofline, level by level: t_l = max(t_stream, t_rand, t_atomic), summed over the levels.
       t_stream  the level's share of the compulsory bytes (points and outputs split evenly over the levels, the
                 level's own tables) at the measured streaming rate of a cache-resident working set
@@ -114,7 +114,8 @@ def level_rooflines(w, n, index_level_bytes, res, V, refs, rates, fwd_only, lds_
                 (forward: one feature entry per vertex; backward: one softmax row and one feature row per vertex).
                 Forward with the level-resident kernel: the share `lds_share` of a level's feature codebook that a
                 CU's LDS holds is looked up there -- every reference, LDS has no reuse to offer -- at the measured
-                random LDS read rate, the rest as above
+                random LDS read rate, the rest as above; the `grids` coarsest levels interpolate from their vertex grid,
+                resolved in LDS: every reference is an LDS read there
       t_atomic  backward: every row of the two gradient tables that is touched must reach memory at least once,
                 at the measured rate of global atomic row updates
     Times in microseconds."""
@@ -129,9 +130,10 @@ def level_rooflines(w, n, index_level_bytes, res, V, refs, rates, fwd_only, lds_
         Dhat_l, gD_f_l = w.N_c * w.N_p * 4, w.N_f * w.F * 4
         pts = n * (4 * w.d / w.L + w.F * iob)
         f_stream = (pts + D_f_l + D_c_l) / rates["copy_GBps"] * 1e-3
-        f_rand = (1.0 - lds_share) * reused / (rates["gather4_Gps"] if D_f_l <= near else rates["gather4_far_Gps"]) * 1e-3
-        if lds_share > 0.0:
-            f_rand += lds_share * R / rates["lds_gather4_Gps"] * 1e-3
+        in_lds = 1.0 if l < grids else lds_share
+        f_rand = (1.0 - in_lds) * reused / (rates["gather4_Gps"] if D_f_l <= near else rates["gather4_far_Gps"]) * 1e-3
+        if in_lds > 0.0:
+            f_rand += in_lds * R / rates["lds_gather4_Gps"] * 1e-3
         row = {"level": l, "N_l": int(res[l]), "refs": R, "distinct_vertices": int(V[l]),
                "fwd": {"t_stream_us": round(f_stream, 3), "t_rand_us": round(f_rand, 3),
                        "t_roof_us": round(max(f_stream, f_rand), 3), "binds": "stream" if f_stream >= f_rand else "rand"}}
@@ -451,7 +453,7 @@ def main():
         "roofline": roofline,
         "beside_the_headline": extras or None,
         "bwd_plan": None if fwd_only else cngp.bwd_plan_info(cfg, N),
-        "fwd_plan": cngp.fwd_plan_info(cfg, N) if ws is not None else {"level_resident": 0},
+        "fwd_plan": {**cngp.fwd_plan_info(cfg, N), **cngp.fwd_route(cfg, N)} if ws is not None else {"level_resident": 0},
         "kernels_us_per_step": {k: round(v["ms"] * 1e3 / args.steps, 2) for k, v in per_kernel.items()},
         "kernel_parts": {k: v["parts"] for k, v in per_kernel.items() if len(v["parts"]) > 1},
     }
@@ -465,7 +467,8 @@ def main():
     V, refs = distinct_vertices(np, x_h, res)
     fplan = cngp.fwd_plan_info(cfg, N) if ws is not None else {"level_resident": 0}
     lds_share = fplan["resident_entries"] / w.N_f if fplan["level_resident"] else 0.0
-    levels = level_rooflines(w, N, cfg.index_cols, res, V, refs, rates, fwd_only, lds_share)
+    grids = cngp.fwd_route(cfg, N)["grids"] if ws is not None else 0
+    levels = level_rooflines(w, N, cfg.index_cols, res, V, refs, rates, fwd_only, lds_share, grids)
     # (with the decoder: the one call runs the level-resident forward and the decoder kernel, or the one fused kernel)
     fwd_kinds = ("encode_mlp_fwd", "encode_fwd", "mlp_fwd") if fused_dec else ("encode_fwd",)
     t_fwd = sum(per_kernel[k]["ms"] for k in fwd_kinds if k in per_kernel) / args.steps * 1e3                # us

@@ -75,9 +75,9 @@ enum {
     CNGP_FWD_LEVEL = 64u,   /* force the level-resident forward variant (a workgroup keeps one level's     */
                             /* codebooks in LDS and streams the points; needs cngp_fwd_workspace_bytes);   */
                             /* CNGP_ERR_UNSUPPORTED / CNGP_ERR_WORKSPACE where it cannot run                */
-    CNGP_FWD_TILE = 128u    /* never take the level-resident variant                                       */
-                            /* none of the three forward flags: the library picks by table size and N; the */
-                            /* three variants give bit-identical encodings                                 */
+    CNGP_FWD_TILE = 128u    /* never take the level-resident variant, nor the one-lane one while a tile fits */
+                            /* none of the three forward flags: the library picks by table size and N      */
+                            /* (cngp_fwd_route); the three variants give bit-identical encodings           */
 };
 
 /* Hyper-parameters of the encoding (Table 1 of the paper, same symbols). */
@@ -130,14 +130,26 @@ int cngp_storage_bytes(const cngp_config *cfg, size_t *D_f_bytes, size_t *D_c_le
 size_t cngp_workspace_bytes(const cngp_config *cfg, int64_t N);
 
 /* The part of it the forward calls use: room for a level-major copy of the encodings (N * L * F values of io_dtype)
- * when the level-resident variant would be taken for this configuration and N, else 0 (F != 2: the pair planes,
- * as above).  A forward call that is given less runs the tile variant instead, with the same result, and a batch of
- * at most 2^20 corner lookups (N * L * 2^d) is encoded by a single launch that does not touch the workspace. */
+ * when the level-resident variant can be taken for this configuration and N, else 0 (F != 2: the pair planes,
+ * as above).  A forward call that is given less runs another variant with the same result.  cngp_encode_mlp_fwd (with
+ * io_dtype fp16) takes the level-resident variant whenever it has this room; the other forward calls encode a batch of
+ * at most 2^20 corner lookups (N * L * 2^d) in a single launch that does not touch the workspace. */
 size_t cngp_fwd_workspace_bytes(const cngp_config *cfg, int64_t N);
 
-/* How a forward call with enough workspace would run: info[0] = 1 if the level-resident variant is taken, info[1] =
- * entries of a level's feature codebook it keeps in LDS (of N_f), info[2] = runs of points a level is cut into (the
- * grid has that many workgroups per level), info[3] = bytes of LDS per workgroup.  Host only. */
+/* Which kernel cngp_encode_fwd, _partial and _permuted run (levels_loaded = L for all but _partial), given workspace_bytes
+ * of aligned workspace: one of CNGP_FWD_ROUTE_*, or the error such a call returns.  grids (host, may be NULL): how many of
+ * the coarsest levels the level-resident variant interpolates from their vertex grid, resolved once in LDS.  Host only. */
+enum {
+    CNGP_FWD_ROUTE_LANES = 0,   /* one launch, one lane per (point, level), both tables read from memory */
+    CNGP_FWD_ROUTE_TILE = 1,    /* one launch, tiles of points, a level's index codebook staged in LDS    */
+    CNGP_FWD_ROUTE_LEVEL = 2    /* level-resident, then a kernel that turns level-major encodings into rows */
+};
+int cngp_fwd_route(const cngp_config *cfg, int32_t levels_loaded, int64_t N, size_t workspace_bytes, int32_t *grids);
+
+/* The level-resident variant for this configuration and N: info[0] = 1 if it can be taken (cngp_fwd_workspace_bytes is
+ * not 0; cngp_fwd_route says whether a call does take it), info[1] = entries of a level's feature codebook it keeps in LDS
+ * (of N_f), info[2] = runs of points a looked-up level is cut into (a level on a resolved grid is cut by its own
+ * cost), info[3] = bytes of LDS per workgroup.  Host only. */
 enum { CNGP_FWD_PLAN_INFO_COUNT = 4 };
 int cngp_fwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info);
 

@@ -101,6 +101,8 @@ def _load():
     lib.cngp_bwd_plan_info.argtypes = [cfgp, i64, vp]
     lib.cngp_fwd_plan_info.restype = ctypes.c_int
     lib.cngp_fwd_plan_info.argtypes = [cfgp, i64, vp]
+    lib.cngp_fwd_route.restype = ctypes.c_int
+    lib.cngp_fwd_route.argtypes = [cfgp, ctypes.c_int32, i64, sz, vp]
     lib.cngp_bwd_plan_layout.restype = ctypes.c_int
     lib.cngp_bwd_plan_layout.argtypes = [cfgp, i64, vp]
     lib.cngp_measure_rates.restype = ctypes.c_int
@@ -221,13 +223,26 @@ def workspace_bytes(cfg: Config, N: int) -> int:
 
 
 def fwd_workspace_bytes(cfg: Config, N: int) -> int:
-    """Bytes the forward calls use of a workspace (0: none; with less they run the tile variant, same result)."""
+    """Bytes the forward calls use of a workspace (0: none; with less they run another variant, same result)."""
     c = cfg.c()
     return int(_lib.cngp_fwd_workspace_bytes(ctypes.byref(c), N))
 
 
+def fwd_route(cfg: Config, N: int, workspace_bytes=None, levels_loaded=None) -> dict:
+    """The variant a forward call runs ("lanes", "tile" or "level") and how many levels it interpolates from resolved vertex
+    grids (see cngp_fwd_route); workspace_bytes: what the call is given (None: all it can use)."""
+    if workspace_bytes is None:
+        workspace_bytes = fwd_workspace_bytes(cfg, N)
+    grids = ctypes.c_int32(0)
+    c = cfg.c()
+    route = _lib.cngp_fwd_route(ctypes.byref(c), cfg.L if levels_loaded is None else levels_loaded, N, workspace_bytes, ctypes.byref(grids))
+    if route < 0:
+        _check(route)
+    return {"variant": ("lanes", "tile", "level")[route], "grids": grids.value}
+
+
 def fwd_plan_info(cfg: Config, N: int) -> dict:
-    """How encode_fwd would run for (cfg, N) when it is given its workspace (see cngp_fwd_plan_info)."""
+    """The level-resident forward variant for (cfg, N), where a call takes it (see cngp_fwd_plan_info, fwd_route)."""
     info = (ctypes.c_int32 * 4)()
     c = cfg.c()
     _check(_lib.cngp_fwd_plan_info(ctypes.byref(c), N, info))

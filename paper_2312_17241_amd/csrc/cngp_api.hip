@@ -124,14 +124,14 @@ int check_blocks(int64_t blocks) { return (blocks > 0x7fffffffLL) ? CNGP_ERR_INV
 // ---------------------------------------------------------------- per-kernel timing
 enum KernelId { K_FWD = 0, K_BWD_DIRECT, K_BWD_PREP, K_BWD_SLICED, K_BWD_SLICED_V, K_BWD_GRID_DRAIN,
                 K_BAKE, K_ZERO, K_DEBUG, K_ADAM, K_MLP_FWD, K_MLP_BWD,
-                K_BWD_BIN_OFFSETS, K_BWD_BIN_SCATTER, K_BWD_BIN_DRAIN, K_BWD_INPUT, K_FUSED_FWD, K_PLANES, K_FWD_ROWS, K_COUNT };
+                K_BWD_BIN_OFFSETS, K_BWD_BIN_SCATTER, K_BWD_BIN_DRAIN, K_BWD_INPUT, K_FUSED_FWD, K_PLANES, K_FWD_ROWS, K_BWD_SMALL, K_COUNT };
 const char *const kKernelNames[K_COUNT] = {"encode_fwd", "encode_bwd_direct", "encode_bwd_prepare",
                                            "encode_bwd_sliced_points_and_grid", "encode_bwd_sliced_vertices",
                                            "encode_bwd_bin_grid_sums", "bake_probes", "zero", "debug_indices",
                                            "adam_step_bake", "mlp_fwd", "mlp_bwd",
                                            "encode_bwd_bin_offsets", "encode_bwd_bin_scatter",
                                            "encode_bwd_bin_drain", "encode_bwd_input", "encode_mlp_fwd", "feature_planes",
-                                           "encode_fwd_rows"};
+                                           "encode_fwd_rows", "encode_bwd_small"};
 
 struct TimedLaunch { int id; hipEvent_t t0, t1; };
 bool g_profile = false;
@@ -217,9 +217,9 @@ FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, in
     if (resident > c->N_f) resident = c->N_f;
     resident &= ~(size_t)3;                                              // whole 16-byte pieces
     // Measured on nerf3d's, image2d's and the compressed model's tables from 2^12 to 2^24 points: never slower than the
-    // tile variant (1.2x - 3x faster), also when only a seventh of a level's feature codebook fits (sdf3d, 1.15x: the
-    // workgroups of a level run on one XCD, so a level's table is held by one L2 instead of all eight).  So it is taken
-    // whenever it can run -- except for a few thousand points, where its second launch costs more than it saves.
+    // tile variant (1.2x - 3x faster), also when only a seventh of a level's feature codebook fits (sdf3d, 1.15x).  So it
+    // can be taken whenever it can run -- except for a few thousand points, where its second launch costs more than it
+    // saves (that line is encode_mlp_fwd's; the encode_fwd calls have a shorter way up to kSmallFwdRefs).
     if (!(c->flags & CNGP_FWD_LEVEL) && N * levels_loaded < ((int64_t)1 << 15)) return f;
     f.use = true;
     f.resident = (uint32_t)resident;
@@ -342,26 +342,37 @@ int launch_fwd_level(const cngp_config *c, const FwdLevelPlan &f, const Params &
     return launch_status("level_major_to_rows_kernel");
 }
 
+// Which kernel encodes a batch, given `room` usable bytes of workspace: one of CNGP_FWD_ROUTE_*, or the error of a forced
+// variant that cannot run.  `plan` is filled in for the level-resident one.
+int fwd_route(const cngp_config *c, int levels_loaded, int64_t N, size_t room, FwdLevelPlan *plan) {
+    const int64_t refs = (N * c->L) << c->d;
+    if (refs > kSmallFwdRefs || (c->flags & (CNGP_FWD_LEVEL | CNGP_FWD_TILE))) {
+        *plan = fwd_level_plan(c, levels_loaded, N);
+        if (plan->use && room >= plan->yT_bytes) return CNGP_FWD_ROUTE_LEVEL;
+        if (c->flags & CNGP_FWD_LEVEL) return plan->use ? CNGP_ERR_WORKSPACE : CNGP_ERR_UNSUPPORTED;
+    }
+    // tile variant: one level's index codebook and the tile's outputs fit in LDS
+    const size_t lds = (((size_t)c->N_c + 1) / 2 + 15) / 16 * 16 + (size_t)kFwdTile * c->L * 2 * (c->io_dtype == CNGP_F16 ? 2 : 4);
+    const bool   small = refs <= kSmallFwdRefsNoRoom && !(c->flags & CNGP_FWD_TILE);
+    return lds <= 64 * 1024 && N >= kFwdTile && !small && !(c->flags & CNGP_FWD_SIMPLE) ? CNGP_FWD_ROUTE_TILE : CNGP_FWD_ROUTE_LANES;
+}
+
 template <int D, typename FeatT, typename IoT>
 int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N, const void *D_f,
                const void *D_c, void *y, hipStream_t s, const int32_t *perm = nullptr,
                void *workspace = nullptr, size_t workspace_bytes = 0) {
-    // level-resident variant: large batches, when the caller lent the room for the level-major copy
-    if (((N * c->L) << c->d) > kSmallFwdRefs || (c->flags & (CNGP_FWD_LEVEL | CNGP_FWD_TILE))) {
-        const FwdLevelPlan f = fwd_level_plan(c, p.L_loaded, N);
-        const bool room = workspace && workspace_bytes >= f.yT_bytes && ((uintptr_t)workspace & 255u) == 0 &&
-                          ((uintptr_t)D_f & 15u) == 0;
-        if (f.use && room) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
-        if ((c->flags & CNGP_FWD_LEVEL) != 0) return f.use ? CNGP_ERR_WORKSPACE : CNGP_ERR_UNSUPPORTED;
-    }
-    // tile variant: one level's index codebook and the tile's outputs fit in LDS
+    // (level-resident: when the caller lent the room for the level-major copy)
+    const bool   usable = workspace && ((uintptr_t)workspace & 255u) == 0 && ((uintptr_t)D_f & 15u) == 0;
+    FwdLevelPlan f;
+    const int    route = fwd_route(c, p.L_loaded, N, usable ? workspace_bytes : 0, &f);
+    if (route < 0) return route;
+    if (route == CNGP_FWD_ROUTE_LEVEL) return launch_fwd_level<D, FeatT, IoT>(c, f, p, x, N, D_f, D_c, y, workspace, s, perm);
     const size_t c_stride = index_level_bytes(c);
     const int    fmt = c->index_format;
     const size_t lds_probes = (((size_t)c->N_c + 1) / 2 + 15) & ~(size_t)15;
     const size_t lds = lds_probes + (size_t)kFwdTile * c->L * 2 * sizeof(IoT);
     const size_t lds_large = lds_probes + (size_t)kFwdTileLarge * c->L * 2 * sizeof(IoT);
-    const bool small = ((N * c->L) << c->d) <= kSmallFwdRefsNoRoom && !(c->flags & CNGP_FWD_TILE);
-    if (lds <= 64 * 1024 && N >= kFwdTile && !small && !(c->flags & CNGP_FWD_SIMPLE)) {
+    if (route == CNGP_FWD_ROUTE_TILE) {
         // Staging a level's codebook costs c_stride bytes per workgroup; a tile looks up TILE * 2^d entries.
         // When the staging outweighs the lookups of a small tile and there are points enough to keep every
         // CU busy with large ones, take the large tile.
@@ -1048,7 +1059,7 @@ int launch_bwd_small(const cngp_config *c, const Params &p, const float *x, int6
     auto kernel = encode_bwd_small_kernel<D, NP, FeatT, IoT>;
     const size_t lds = small_bwd_lds(c);
     if (int rc = allow_big_lds(kernel, lds)) return rc;
-    LaunchTimer t(s, K_BWD_DIRECT);
+    LaunchTimer t(s, K_BWD_SMALL);
     kernel<<<dim3((unsigned)chunks, (unsigned)c->L), kSmallBwdBlock, lds, s>>>(p, x, (const FeatT *)D_f, Dhat_c, (const IoT *)dy,
                                                                               gD_f, gDhat_c, N, chunk);
     return launch_status("encode_bwd_small_kernel");
@@ -1293,6 +1304,21 @@ int cngp_fwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
     info[2] = (int32_t)f.split.hash_parts;
     info[3] = (int32_t)(f.lds);
     return CNGP_OK;
+}
+
+int cngp_fwd_route(const cngp_config *cfg, int32_t levels_loaded, int64_t N, size_t workspace_bytes, int32_t *grids) {
+    if (int rc = validate(cfg)) return rc;
+    if (N < 0 || levels_loaded < 0 || levels_loaded > cfg->L) return CNGP_ERR_INVALID;
+    cngp_config pairs = as_pairs(cfg);
+    if (cfg->F != 2) {                                       // passes over pairs of features, in their part of the workspace
+        const PlaneSpace ps = plane_space_for(cfg, N, workspace_bytes);
+        if (workspace_bytes < ps.total) return CNGP_ERR_WORKSPACE;
+        workspace_bytes = ps.pairs;
+    }
+    FwdLevelPlan f;
+    const int route = fwd_route(&pairs, levels_loaded, N, workspace_bytes, &f);
+    if (grids) *grids = route == CNGP_FWD_ROUTE_LEVEL ? (int32_t)f.split.dense : 0;
+    return route;
 }
 
 size_t cngp_fwd_workspace_bytes(const cngp_config *cfg, int64_t N) {

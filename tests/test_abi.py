@@ -333,6 +333,29 @@ def test_forward_plan_is_within_the_chip_and_the_workspace():
     assert taken >= 100
 
 
+def test_forward_route_says_which_kernel_a_call_runs():
+    """One rule decides for the calls and for the query: a single launch up to 2^20 corner lookups (without room for the
+    level-major copy up to 2^22), the level-resident variant beyond it when the room is there, tiles otherwise; forced variants
+    and the error of one that cannot run; widths other than two inside their part of the workspace."""
+    cfg = base_cfg()
+    route = lambda N, c=cfg, **kw: cngp.fwd_route(c, N, **kw)["variant"]
+    for N in (1, 2048, 8192):
+        assert route(N) == route(N, workspace_bytes=0) == "lanes"
+    assert cngp.fwd_plan_info(cfg, 8192)["level_resident"] == 1 and cngp.fwd_workspace_bytes(cfg, 8192) > 0    # (encode_mlp_fwd's)
+    assert route(8193) == "level" and route(8193, workspace_bytes=cngp.fwd_workspace_bytes(cfg, 8193) - 1) == "lanes"
+    assert route(2**15, workspace_bytes=0) == "lanes" and route(2**15 + 1, workspace_bytes=0) == "tile"
+    assert route(2**18, levels_loaded=0) == "tile" and route(2**18, levels_loaded=3) == "level"
+    assert route(2000, base_cfg(flags=cngp.FWD_LEVEL)) == "level" and route(2**20, base_cfg(flags=cngp.FWD_SIMPLE)) == "lanes"
+    assert route(2000, base_cfg(flags=cngp.FWD_TILE)) == "tile" and route(200, base_cfg(flags=cngp.FWD_TILE)) == "lanes"
+    for c, room, status in ((base_cfg(flags=cngp.FWD_LEVEL), 0, cngp.ERR_WORKSPACE),
+                            (base_cfg(flags=cngp.FWD_LEVEL, N_c=2**18), 1 << 30, cngp.ERR_UNSUPPORTED), (base_cfg(F=4), 0, cngp.ERR_WORKSPACE)):
+        with pytest.raises(cngp.CngpError) as e:
+            cngp.fwd_route(c, 3000, workspace_bytes=room)
+        assert e.value.status == status
+    assert route(2**17, base_cfg(F=4), workspace_bytes=cngp.workspace_bytes(base_cfg(F=4), 2**17)) == "level"
+    assert cngp.fwd_route(base_cfg(N_f=2**18, N_max=256), 2**20)["grids"] >= 3 and cngp.fwd_route(base_cfg(N_f=2**8), 2**20)["grids"] == 0
+
+
 def test_morton_sort_workspace_is_host_arithmetic():
     """Two key columns, one index column, 128 counters per tile of 8192 points, 128 totals; no device is asked."""
     a = lambda v: (v + 255) // 256 * 256
