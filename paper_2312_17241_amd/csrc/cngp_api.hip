@@ -200,9 +200,12 @@ constexpr int64_t kCus = 256;
 // the level-resident pair of launches and 57 for the tile kernel, 16384 points: 19 / 13 / 52; fp32 tables of 2^18 entries
 // (sdf3d) 18.8 / 29 / 120 at 8192, 33 / 28 / 119 at 16384; d = 2, 16384 points: 10.5 / 13.0 / 28; d = 4, 4096: 10.3 / 15.3 / 81.
 constexpr int64_t kSmallFwdRefs = 1 << 20;
-// The same against the tile kernel alone, for a caller without a workspace: nerf3d 34 / 46 us at 32768 points (2^22
-// lookups), the compressed model 23 / 31, d = 2 17 / 26 at 2^21; at 2^25 it is 217 / 99.
-constexpr int64_t kSmallFwdRefsNoRoom = 1 << 22;
+// The same against the tile kernel alone, for a caller without a workspace.  That kernel takes the levels one after the other,
+// so with few of them it is the faster one sooner.  One launch / tiles, us, at 2^21.5 .. 2^22 lookups: L = 2 11.2 / 6.8 and
+// 11.8 / 10.0, L = 4 11.7 / 7.9, L = 6 23 / 16, L = 8 9.4 / 18, L = 16 (nerf3d) 34 / 46, the compressed model 23 / 31, L = 24
+// 24 / 49; at 2^21 lookups L = 4 9.8 / 20, L = 6 21.6 / 22; at 2^25 nerf3d 217 / 99.
+constexpr int64_t kSmallFwdRefsNoRoom = 1 << 22, kSmallFwdRefsNoRoomFewLevels = 1 << 21;
+constexpr int     kFewLevels = 8;
 constexpr size_t  kLevelLdsBudget = 156 * 1024;
 constexpr int64_t kLevelPartPoints = 65536;              // points per workgroup when the batch is large
 constexpr uint64_t kFwdL2Bytes = 3u << 20;               // of an XCD's 4 MB, what tables can count on
@@ -353,7 +356,7 @@ int fwd_route(const cngp_config *c, int levels_loaded, int64_t N, size_t room, F
     }
     // tile variant: one level's index codebook and the tile's outputs fit in LDS
     const size_t lds = (((size_t)c->N_c + 1) / 2 + 15) / 16 * 16 + (size_t)kFwdTile * c->L * 2 * (c->io_dtype == CNGP_F16 ? 2 : 4);
-    const bool   small = refs <= kSmallFwdRefsNoRoom && !(c->flags & CNGP_FWD_TILE);
+    const bool   small = refs <= (c->L < kFewLevels ? kSmallFwdRefsNoRoomFewLevels : kSmallFwdRefsNoRoom) && !(c->flags & CNGP_FWD_TILE);
     return lds <= 64 * 1024 && N >= kFwdTile && !small && !(c->flags & CNGP_FWD_SIMPLE) ? CNGP_FWD_ROUTE_TILE : CNGP_FWD_ROUTE_LANES;
 }
 

@@ -335,7 +335,7 @@ def test_forward_plan_is_within_the_chip_and_the_workspace():
 
 def test_forward_route_says_which_kernel_a_call_runs():
     """One rule decides for the calls and for the query: a single launch up to 2^20 corner lookups (without room for the
-    level-major copy up to 2^22), the level-resident variant beyond it when the room is there, tiles otherwise; forced variants
+    level-major copy up to 2^22, with fewer than eight levels 2^21), the level-resident variant beyond it when the room is there, tiles otherwise; forced variants
     and the error of one that cannot run; widths other than two inside their part of the workspace."""
     cfg = base_cfg()
     route = lambda N, c=cfg, **kw: cngp.fwd_route(c, N, **kw)["variant"]
@@ -344,6 +344,8 @@ def test_forward_route_says_which_kernel_a_call_runs():
     assert cngp.fwd_plan_info(cfg, 8192)["level_resident"] == 1 and cngp.fwd_workspace_bytes(cfg, 8192) > 0    # (encode_mlp_fwd's)
     assert route(8193) == "level" and route(8193, workspace_bytes=cngp.fwd_workspace_bytes(cfg, 8193) - 1) == "lanes"
     assert route(2**15, workspace_bytes=0) == "lanes" and route(2**15 + 1, workspace_bytes=0) == "tile"
+    few = base_cfg(L=4)                         # tiles, which take one level after the other, are the faster ones sooner with few levels
+    assert route(2**16, few, workspace_bytes=0) == "lanes" and route(2**16 + 1, few, workspace_bytes=0) == "tile"
     assert route(2**18, levels_loaded=0) == "tile" and route(2**18, levels_loaded=3) == "level"
     assert route(2000, base_cfg(flags=cngp.FWD_LEVEL)) == "level" and route(2**20, base_cfg(flags=cngp.FWD_SIMPLE)) == "lanes"
     assert route(2000, base_cfg(flags=cngp.FWD_TILE)) == "tile" and route(200, base_cfg(flags=cngp.FWD_TILE)) == "lanes"
