@@ -12,6 +12,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <numeric>
 #include <type_traits>
 #include <string>
 #include <vector>
@@ -266,6 +267,29 @@ FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, in
         }
         return u;
     };
+    // The tables (their parts outside LDS) that an XCD's L2 gets to see.  Every one of them is fetched into it once, at about
+    // 700 bytes a clock; and where the tables do not fit one L2 together, a run of units that begins and ends inside a level
+    // holds one more than it has to (14 levels in eight runs touch three each, 16 levels two), which costs 6 % per MB of a
+    // table (260 drawn configurations: 1.2x for 1.86 MB tables (fp32, 2^18 entries), 1.1x for 0.87 MB, 1.04x for 0.36 MB).
+    const double table = (double)((uint64_t)(c->N_f - resident) * entry);
+    auto tables_per_xcd = [&](int64_t levels, int64_t parts) {
+        if (levels < 1) return (int64_t)0;
+        if (!by_xcd(levels)) return levels / std::gcd(levels, (int64_t)kFwdXcds);
+        const int64_t run = looked_up_units(levels, parts) / kFwdXcds;
+        int64_t most = 0;
+        for (int64_t x = 0; x < (int64_t)kFwdXcds; ++x) {
+            const int64_t first = x * run / parts;
+            int64_t       last = ((x + 1) * run - 1) / parts;
+            if (last > levels - 1) last = levels - 1;
+            if (last - first + 1 > most) most = last - first + 1;
+        }
+        return most;
+    };
+    auto cost_of = [&](int64_t levels, double per, int64_t rounds) {
+        const int64_t tables = tables_per_xcd(levels, parts_of(per)), least = (levels + kFwdXcds - 1) / kFwdXcds;
+        const int64_t too_many = by_xcd(levels) && tables > least ? tables - least : 0;
+        return per * (double)rounds * (1.0 + 0.06 * table / (1 << 20) * (double)too_many) + (double)tables * table / (700.0 * lookup);
+    };
     int    grids = 0;
     double best = 0.0, best_per = 0.0;
     for (int g = 0; g <= most_grids; ++g) {
@@ -278,7 +302,7 @@ FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, in
             if (units_of(g, mid) <= kCus * rounds) hi = mid;
             else lo = mid;
         }
-        const double cost = hi * (double)rounds;
+        const double cost = cost_of(levels_loaded - g, hi, rounds);
         if (g == 0 || cost < 0.97 * best) { best = cost; best_per = hi; grids = g; }
     }
     auto cut = [&](double per, int64_t &size) {
