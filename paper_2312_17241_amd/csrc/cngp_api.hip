@@ -445,8 +445,47 @@ int launch_fwd(const cngp_config *c, const Params &p, const float *x, int64_t N,
     return launch_status("encode_fwd_kernel");
 }
 
-constexpr size_t  kBwdInputLargeLds = 16 * 1024;
-constexpr int64_t kBwdInputLargePoints = 160 * 1024;
+// Workgroups of the input gradient.  256 lanes, a point each, stage the level's codebook once per 256 points; 1024 lanes stage
+// it a quarter as often and keep the chip's lookups closer together, but fill fewer wavefronts while the batch is small, and
+// hold each other up at the barriers.  Where the large ones pay was measured on d = 2 .. 4, fp16 and fp32, all three formats,
+// N_f 2^8 .. 2^18, N_c 2^14 .. 2^17 and 60000 to 1600000 points (time with them by time without):
+//  * from 160 Ki points where only two 256-lane workgroups fit a CU (N_c = 2^17: 0.24 .. 0.9), and where what is staged is
+//    at least 32 KB in memory (with 8-byte entries of a table below 1 MB 64 KB: two points a lane leave it fewer wavefronts)
+//    and d <= 3 (bytes, N_c = 2^16: 0.65 .. 0.9; at d = 4 the lookups are what takes the time: 0.9 .. 1.2); 200 Ki with
+//    8-byte tables of 2 MB (0.72 .. 0.95);
+//  * from 2^18 points, which is all that 256-lane workgroups hold at once beside N_c = 2^16, with tables of 1 MB or more
+//    (0.5 .. 0.95), with bytes or d <= 3 there (0.45 .. 0.95) and with bytes and d <= 3 at N_c = 2^15 (0.7 .. 0.95); else it
+//    is 0.9 .. 1.2, at d = 4 up to 1.6;
+//  * from 2^20 points for any codebook of 8 KB or more.
+// 8-byte entries: one workgroup per CU with two points per lane (fp32, N_f = 2^18, 300007 points: 0.6, with one point 0.65);
+// from 2^20 points only where that still gains: a table of 2 MB (0.57 against 0.65), at d = 2 of 128 KB; smaller ones take
+// up to 1.15 times as long.  (The d = 4 instance with packed bytes spills 8 registers: 0.57 .. 0.7, as with one point.)
+// Below 2^20 points all are of the same size, in whole rounds (nothing but the last round's lanes is idle); above, full ones
+// with one point per lane (1300000 points: 5 .. 9 % faster, the rounds no longer run in step).
+struct BwdInputShape { bool large; int pts; int64_t per; };
+BwdInputShape bwd_input_shape(const cngp_config *c, int64_t N) {
+    const size_t stride = index_level_bytes(c), lds = (((size_t)c->N_c + 1) / 2 + 15) & ~(size_t)15;
+    const bool   wide = c->feat_dtype == CNGP_F32, huge = N >= (int64_t)kFwdTileLarge * 1024, bytes = c->index_format == CNGP_IDX_U8;
+    const size_t table = (size_t)c->N_f * (wide ? 8 : 4);
+    BwdInputShape b = {false, 1, kFwdTile};
+    if (lds > 64 * 1024 || N < kFwdTile) return b;
+    const bool codebook = lds >= 16 * 1024;
+    if (codebook && N >= 160 * 1024)
+        b.large = lds >= 64 * 1024 || (c->d <= 3 && stride >= (size_t)(wide && table < (1u << 20) ? 64 : 32) * 1024) ||
+                  (wide && table >= (2u << 20) && N >= 200 * 1024);
+    if (codebook && N > 256 * 1024)
+        b.large = b.large || table >= (1u << 20) || (c->d <= 3 && (lds >= 32 * 1024 || bytes)) || (lds >= 32 * 1024 && bytes);
+    if (huge && stride >= 8192) b.large = true;
+    if (!b.large) return b;
+    if (wide && codebook && (!huge || table >= (c->d == 2 ? 128u << 10 : 2u << 20))) b.pts = 2;
+    const int64_t most = (int64_t)b.pts * kFwdTileLarge, slots = b.pts == 2 ? kCus : 2 * kCus;
+    b.per = most;
+    if (!huge || b.pts == 2) {
+        const int64_t wgs = (N + slots * most - 1) / (slots * most) * slots;
+        b.per = ((N + wgs - 1) / wgs + 63) / 64 * 64;
+    }
+    return b;
+}
 template <int D, typename FeatT, typename IoT>
 int launch_bwd_input(const cngp_config *c, const Params &p, const float *x, int64_t N, const void *D_f,
                      const void *D_c, const void *dy, float *grad_x, hipStream_t s) {
@@ -454,20 +493,9 @@ int launch_bwd_input(const cngp_config *c, const Params &p, const float *x, int6
     const int    fmt = c->index_format;
     const size_t lds = (((size_t)c->N_c + 1) / 2 + 15) & ~(size_t)15;
     const bool   staged = lds <= 64 * 1024 && N >= kFwdTile;
-    // Workgroups of 1024 lanes where staging the codebook with every 256 points costs more than it should, all of the same
-    // size, in whole rounds: 4-byte entries (fp16) two workgroups per CU with a point per lane, 8-byte entries one with two
-    // points per lane.  Measured, us, 256-lane tiles / this, sdf3d's tables: fp32 300007 points 338 / 203, 2^20 725 (1024-lane
-    // tiles) / 578; fp16 300007 211 / 149, 100003 75 / 87.  Smaller codebooks (nerf3d's 8 KB) from 2^20 points, 455 / 413.
-    const bool big_codebook = lds >= kBwdInputLargeLds;
-    const bool large = staged && ((big_codebook && N >= kBwdInputLargePoints) ||
-                                  (c_stride >= 8192 && N >= (int64_t)kFwdTileLarge * 1024));
     constexpr bool wide = sizeof(FeatT) == 4;
-    int64_t per = kFwdTile;
-    if (large) {
-        const int64_t slots = wide && big_codebook ? kCus : 2 * kCus, most = (wide && big_codebook ? 2 : 1) * kFwdTileLarge;
-        const int64_t wgs = (N + slots * most - 1) / (slots * most) * slots;
-        per = ((N + wgs - 1) / wgs + 63) / 64 * 64;
-    }
+    const BwdInputShape shape = bwd_input_shape(c, N);
+    const int64_t per = shape.per;
     const int64_t blocks = (N + per - 1) / per;
     if (int rc = check_blocks(blocks)) return rc;
     const int vec = (c_stride % 16 == 0 && ((uintptr_t)D_c & 15u) == 0) ? 1 : 0;
@@ -477,8 +505,8 @@ int launch_bwd_input(const cngp_config *c, const Params &p, const float *x, int6
         p, x, (const FeatT *)D_f, (const uint8_t *)D_c, (const IoT *)dy, grad_x, N, (uint32_t)c_stride, vec, (uint32_t)per)
 #define CNGP_BWD_INPUT_FMT(FMT)                                                                             \
     if (!staged) CNGP_BWD_INPUT(FMT, kFwdTile, false, 1);                                                   \
-    else if (large && wide && big_codebook) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, (wide ? 2 : 1));       \
-    else if (large) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, 1);                                            \
+    else if (shape.large && shape.pts == 2) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, (wide ? 2 : 1));        \
+    else if (shape.large) CNGP_BWD_INPUT(FMT, kFwdTileLarge, true, 1);                                       \
     else CNGP_BWD_INPUT(FMT, kFwdTile, true, 1)
     if (fmt == CNGP_IDX_PACKED4) { CNGP_BWD_INPUT_FMT(kFmtPacked4); }
     else if (fmt == CNGP_IDX_BITS) { CNGP_BWD_INPUT_FMT(kFmtBits); }

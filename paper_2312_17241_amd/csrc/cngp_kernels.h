@@ -278,13 +278,28 @@ __global__ __launch_bounds__(TILE) void encode_bwd_input_kernel(
             Cell<D> cell;
             cell.locate(xp[u], p.N_l[l]);
             uint32_t idx[1 << D];
+            if constexpr (D == 4 && STAGED && FMT == kFmtPacked4 && TILE == kFwdTile) {
+                // every byte asked for before one is used: left to itself the compiler puts a wait after each of the sixteen
+                // here, to save registers (fp16, N_f = 2^16, N_c = 2^15, 100000 points on 8 levels 51 -> 44 us)
+                uint32_t r[1 << D], byte[1 << D];
 #pragma unroll
-            for (int c = 0; c < (1 << D); ++c) {
-                const uint32_t r = cell.hash2(c) & p.c_mask;
-                const uint32_t probe = !STAGED ? read_probe<FMT>(C_l, r, p.log2_Np)
-                                     : FMT == kFmtBits ? read_probe_bits_lds(probes, r, p.log2_Np)
-                                                       : read_probe<kFmtPacked4>(probes, r, p.log2_Np);
-                idx[c] = probe_base(cell.hash1(c), p) + probe;
+                for (int c = 0; c < (1 << D); ++c) {
+                    r[c] = cell.hash2(c) & p.c_mask;
+                    byte[c] = probes[r[c] >> 1];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int c = 0; c < (1 << D); ++c)
+                    idx[c] = probe_base(cell.hash1(c), p) + ((byte[c] >> ((r[c] & 1u) * 4u)) & ((1u << p.log2_Np) - 1u));
+            } else {
+#pragma unroll
+                for (int c = 0; c < (1 << D); ++c) {
+                    const uint32_t r = cell.hash2(c) & p.c_mask;
+                    const uint32_t probe = !STAGED ? read_probe<FMT>(C_l, r, p.log2_Np)
+                                         : FMT == kFmtBits ? read_probe_bits_lds(probes, r, p.log2_Np)
+                                                           : read_probe<kFmtPacked4>(probes, r, p.log2_Np);
+                    idx[c] = probe_base(cell.hash1(c), p) + probe;
+                }
             }
             float2 feat[1 << D];
 #pragma unroll

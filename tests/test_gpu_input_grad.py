@@ -83,3 +83,33 @@ def test_large_codebook_large_tiles(feat, N):
                        for i in range(0, N, step)])
     torch.cuda.synchronize()
     assert torch.equal(whole, parts)
+
+
+# the shapes that bwd_input_shape picks: 1024-lane workgroups with one or two points a lane, equal shares or full, every format
+@pytest.mark.parametrize("d,feat,fmt,N_f,N_c,N", [
+    (3, "f16", cngp.IDX_U8, 2**10, 2**16, 160 * 1024 + 1), (3, "f32", cngp.IDX_BITS, 2**18, 2**16, 2**18 + 1),
+    (4, "f32", cngp.IDX_PACKED4, 2**18, 2**15, 2**18 + 65), (2, "f16", cngp.IDX_BITS, 2**12, 2**17, 170_003),
+    (3, "f16", cngp.IDX_U8, 2**10, 2**13, 2**20 + 5), (2, "f32", cngp.IDX_U8, 2**15, 2**16, 2**20 + 7),
+    (3, "f32", cngp.IDX_PACKED4, 2**12, 2**16, 2**20 + 9), (4, "f16", cngp.IDX_PACKED4, 2**12, 2**15, 2**18 + 3)])
+def test_every_workgroup_shape_gives_the_bits_of_small_batches(d, feat, fmt, N_f, N_c, N):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    x = torch.rand((N, d), generator=g, device="cuda")
+    x[:2] = torch.tensor([[0.0] * d, [1.0] * d], device="cuda")
+    dt = torch.float16 if feat == "f16" else torch.float32
+    cfg = cngp.Config(d=d, L=2, F=2, N_f=N_f, N_c=N_c, N_p=8, N_min=16, N_max=200, feat_dtype=cngp.F16 if feat == "f16" else cngp.F32,
+                      io_dtype=cngp.F16 if feat == "f16" else cngp.F32, index_format=fmt)
+    D_f = (torch.randn((2, N_f, 2), generator=g, device="cuda") * 0.1).to(dt)
+    D_c = torch.randint(0, 8, (2, N_c), generator=g, device="cuda", dtype=torch.uint8)
+    D_c = cngp.pack4(D_c) if fmt == cngp.IDX_PACKED4 else cngp.pack_bits(D_c, 8) if fmt == cngp.IDX_BITS else D_c
+    dy = torch.randn((N, 4), generator=g, device="cuda").to(dt)
+    whole = cngp.encode_bwd_input(cfg, x, D_f, D_c, dy)
+    parts = torch.cat([cngp.encode_bwd_input(cfg, x[i:i + 100_000].contiguous(), D_f, D_c, dy[i:i + 100_000].contiguous())
+                       for i in range(0, N, 100_000)])
+    torch.cuda.synchronize()
+    assert torch.equal(whole, parts)
+
+
+def test_four_dimensions_with_packed_probes_against_the_oracle():
+    """The sixteen probe bytes of a point are all asked for before one is used."""
+    for N_p, feat in ((8, "f16"), (16, "f32"), (1, "f16")):
+        run(W.custom(cfg=79, d=4, L=3, N_f=2**12, N_c=2**15, N_p=N_p, N_min=4, N_max=60, N=1500 + 7, feat_dtype=feat, io_dtype=feat), cngp.IDX_PACKED4)
