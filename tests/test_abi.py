@@ -358,6 +358,18 @@ def test_forward_route_says_which_kernel_a_call_runs():
     assert cngp.fwd_route(base_cfg(N_f=2**18, N_max=256), 2**20)["grids"] >= 3 and cngp.fwd_route(base_cfg(N_f=2**8), 2**20)["grids"] == 0
 
 
+def test_stream_handle_without_torch_internals(monkeypatch):
+    """A torch without the two internal calls still gives the binding its stream, through the public one."""
+    class Stream:
+        cuda_stream = 77
+    monkeypatch.setattr("torch.cuda.current_stream", lambda: Stream)
+    assert cngp._stream_getter(object())() == 77
+    class Internals:
+        _cuda_getDevice = staticmethod(lambda: 3)
+        _cuda_getCurrentRawStream = staticmethod(lambda device: 100 + device)
+    assert cngp._stream_getter(Internals)() == 103
+
+
 def test_morton_sort_workspace_is_host_arithmetic():
     """Two key columns, one index column, 128 counters per tile of 8192 points, 128 totals; no device is asked."""
     a = lambda v: (v + 255) // 256 * 256
