@@ -57,7 +57,7 @@ def test_forward(N_p, feat, io):
     w, x, D_f, Dhat, _ = case(N_p, feat, io)
     D_c = oracle.bake_probes(Dhat)
     y_ref, ymag = oracle.encode_fwd(w, x, D_f, D_c)
-    for flags in (0, cngp.FWD_SIMPLE):
+    for flags in (0, cngp.FWD_TILE, cngp.FWD_SIMPLE):
         for fmt in (cngp.IDX_U8, cngp.IDX_BITS):
             cfg = cngp.Config.from_workload(w, flags=flags, index_format=fmt)
             y = cngp.encode_fwd(cfg, dev(x), dev(D_f), packed(fmt, D_c, N_p))

@@ -40,7 +40,7 @@ def test_forward(F, d, N_p, feat, io):
     w, x, D_f, Dhat, _ = case(F, d, N_p, feat, io)
     D_c = oracle.bake_probes(Dhat)
     y_ref, ymag = oracle.encode_fwd(w, x, D_f, D_c)
-    for flags in (0, cngp.FWD_SIMPLE):
+    for flags in (0, cngp.FWD_TILE, cngp.FWD_SIMPLE):
         cfg = cngp.Config.from_workload(w, flags=flags)
         ws = cngp.alloc_workspace(cfg, w.N)
         assert ws is not None                                  # the pair planes live there

@@ -153,14 +153,19 @@ def test_small_batches_take_one_launch(d, L, N, fmt):
     check_close("y [small batch]", y.cpu().numpy(), y_ref, ymag, fp16_out=True)
 
 
-@pytest.mark.parametrize("d,L,N_min,N_max,feat,io,fmt", [
-    (3, 6, 4, 512, "f32", "f32", cngp.IDX_U8), (3, 16, 16, 2048, "f16", "f16", cngp.IDX_PACKED4), (2, 16, 3, 4096, "f16", "f32", cngp.IDX_BITS),
-    (4, 5, 2, 60, "f16", "f16", cngp.IDX_U8), (2, 4, 5, 90, "f32", "f16", cngp.IDX_PACKED4)])       # the last: every level on a grid
-def test_coarse_levels_interpolate_from_their_resolved_vertex_grid(d, L, N_min, N_max, feat, io, fmt):
+# `grids`: how many levels interpolate from their grid (none in the second case, every one in the last two)
+@pytest.mark.parametrize("d,L,N_min,N_max,feat,io,fmt,N_f,N,grids", [
+    (3, 6, 4, 512, "f32", "f32", cngp.IDX_U8, 2**16, 2**17 + 77, 2), (3, 16, 16, 2048, "f16", "f16", cngp.IDX_PACKED4, 2**16, 2**17 + 77, 0),
+    (2, 16, 3, 4096, "f16", "f32", cngp.IDX_BITS, 2**16, 2**17 + 77, 6), (4, 5, 2, 60, "f16", "f16", cngp.IDX_U8, 2**16, 2**17 + 77, 2),
+    (2, 4, 5, 90, "f32", "f16", cngp.IDX_PACKED4, 2**16, 2**17 + 77, 2), (3, 8, 6, 300, "f16", "f16", cngp.IDX_PACKED4, 2**18, 2**17 + 77, 3),
+    (3, 12, 8, 256, "f16", "f16", cngp.IDX_U8, 2**17, 2**17 + 77, 4), (2, 3, 20, 90, "f32", "f32", cngp.IDX_BITS, 2**18, 2**20 + 1, 3),
+    (3, 2, 10, 20, "f16", "f16", cngp.IDX_U8, 2**18, 2**20 + 1, 2)])
+def test_coarse_levels_interpolate_from_their_resolved_vertex_grid(d, L, N_min, N_max, feat, io, fmt, N_f, N, grids):
     """A batch large enough that the coarse levels fill their vertex grid once per workgroup: same bits as the tile variant,
     at the corners of the cube, on every face, beyond 1 (x up to 3: looked up, not on the grid) and below 0."""
-    N = 2**17 + 77
-    w, x, D_f, D_c = case(d, 8, feat, io, N=N, L=L, N_min=N_min, N_max=N_max)
+    w, x, D_f, D_c = case(d, 8, feat, io, N=N, L=L, N_min=N_min, N_max=N_max, N_f=N_f)
+    route = cngp.fwd_route(cngp.Config.from_workload(w, flags=cngp.FWD_LEVEL, index_format=fmt), N)
+    assert route == {"variant": "level", "grids": grids}
     rng = np.random.default_rng(d * L)
     x[3:2003] = rng.integers(0, 2, (2000, d))                      # the cube's corners
     x[2003:4003, 0], x[4003:6003, d - 1] = 1.0, 0.0                # two faces

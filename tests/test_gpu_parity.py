@@ -516,10 +516,12 @@ def test_probe_entries_beyond_the_probe_range_are_masked():
         bad[:-1] += (w.N_p * rng.integers(0, top, bad[:-1].shape)).astype(np.uint8)
         assert bad.max() >= w.N_p
         pack = (lambda a: dev(a)) if fmt == cngp.IDX_U8 else (lambda a: cngp.pack4(dev(a)))
-        for flags in (0, cngp.FWD_SIMPLE):
+        for flags, variant in ((0, "lanes"), (cngp.FWD_SIMPLE, "lanes"), (cngp.FWD_TILE, "tile"), (cngp.FWD_LEVEL, "level")):
             cfg = cngp.Config.from_workload(w, index_format=fmt, flags=flags)
-            y_clean = cngp.encode_fwd(cfg, dev(x), dev(D_f), pack(D_c))
-            y_bad = cngp.encode_fwd(cfg, dev(x), dev(D_f), pack(bad))
+            ws = cngp.alloc_workspace(cfg, w.N) if variant == "level" else None
+            assert cngp.fwd_route(cfg, w.N, ws.numel() if ws is not None else 0)["variant"] == variant
+            y_clean = cngp.encode_fwd(cfg, dev(x), dev(D_f), pack(D_c), workspace=ws)
+            y_bad = cngp.encode_fwd(cfg, dev(x), dev(D_f), pack(bad), workspace=ws)
             torch.cuda.synchronize()
             assert torch.equal(y_clean, y_bad)
 

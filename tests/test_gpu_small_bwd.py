@@ -29,8 +29,15 @@ def test_small_tables_accumulate_in_lds(d, L, N_f, N_c, N_p, N, feat, io, top_k)
         cfg = cngp.Config.from_workload(w, flags=flags, top_k=top_k)
         gF = torch.full((L, N_f, 2), 7.0, device="cuda")
         gC = torch.full((L, N_c, N_p), 7.0, device="cuda")
+        cngp.profile_enable(True)
+        cngp.profile_read()
         cngp.encode_bwd(cfg, dev(x), dev(D_f), dev(Dhat), dev(dy), gF, gC)
         torch.cuda.synchronize()
+        ran = {k for k in cngp.profile_read() if k != "zero"}
+        cngp.profile_enable(False)
+        # fp64 copies of both tables in 128 KB of LDS
+        fits = 8 * (2 * N_f + (N_c * N_p if N_p > 1 else 0)) <= 128 * 1024
+        assert ran == {"encode_bwd_small" if fits and not flags & cngp.BWD_DIRECT else "encode_bwd_direct"}
         check_close("grad D_f", gF.cpu().numpy(), gF_ref, A_f, fp16_out=False)
         check_close("grad Dhat_c", gC.cpu().numpy(), gC_ref, A_c, fp16_out=False)
     # without clearing, a second call adds the same gradients once more

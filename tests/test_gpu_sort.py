@@ -87,17 +87,25 @@ def test_forward_through_the_permutation_equals_the_plain_forward(d, N_p, feat, 
     D_c = cngp.bake_probes(cfg, torch.from_numpy(W.make_probe_logits(w)).to(DEV))
     y = cngp.encode_fwd(cfg, x, D_f, D_c)
     perm, xs = cngp.morton_sort(x)
+    # (the plain forward of this batch is the one-lane kernel; through the permutation the tiles, unless that kernel is asked for)
+    tile = cfg if flags else cngp.Config.from_workload(w, index_format=fmt, flags=cngp.FWD_TILE)
+    assert cngp.fwd_route(cfg, w.N, 0)["variant"] == "lanes" and cngp.fwd_route(tile, w.N, 0)["variant"] == ("lanes" if flags else "tile")
     y2 = torch.full_like(y, float("nan"))
-    cngp.encode_fwd_permuted(cfg, xs, perm, D_f, D_c, y2)
+    cngp.encode_fwd_permuted(tile, xs, perm, D_f, D_c, y2)
     torch.cuda.synchronize()
     assert torch.equal(y.view(torch.int16 if io == "f16" else torch.int32), y2.view(torch.int16 if io == "f16" else torch.int32))
     if not flags:                                   # with room for the level-major copy: the level-resident variant, same bits
         y3 = torch.full_like(y, float("nan"))
         ws = cngp.alloc_workspace(cfg, w.N)
         assert cngp.fwd_plan_info(cfg, w.N)["level_resident"] == 1 and ws is not None
-        cngp.encode_fwd_permuted(cfg, xs, perm, D_f, D_c, y3, workspace=ws)
+        level = cngp.Config.from_workload(w, index_format=fmt, flags=cngp.FWD_LEVEL)
+        assert cngp.fwd_route(level, w.N, ws.numel())["variant"] == "level"
+        cngp.encode_fwd_permuted(level, xs, perm, D_f, D_c, y3, workspace=ws)
         torch.cuda.synchronize()
         assert torch.equal(y2, y3)
+        y4 = cngp.encode_fwd_permuted(cfg, xs, perm, D_f, D_c, workspace=ws)        # the library's own choice
+        torch.cuda.synchronize()
+        assert torch.equal(y2, y4)
     y_ref, ymag = oracle.encode_fwd(w, W.make_points(w), W.make_feature_codebook(w), oracle.bake_probes(W.make_probe_logits(w)))
     from parity import check_close
     check_close("y through the permutation", y2.cpu().numpy(), y_ref, ymag, fp16_out=(io == "f16"))

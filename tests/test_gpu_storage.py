@@ -55,7 +55,7 @@ def test_forward_and_indices_from_exact_width(case):
     D_c = oracle.bake_probes(W.make_probe_logits(w))
     packed = dev(oracle.pack_index_bits(D_c, w.N_p))
     y_ref, ymag = oracle.encode_fwd(w, x, D_f, D_c)
-    for flags in (0, cngp.FWD_SIMPLE):
+    for flags in (0, cngp.FWD_TILE, cngp.FWD_SIMPLE):
         cfg_b = cngp.Config.from_workload(w, index_format=cngp.IDX_BITS, flags=flags)
         cfg_u = cngp.Config.from_workload(w, index_format=cngp.IDX_U8, flags=flags)
         y_b = cngp.encode_fwd(cfg_b, dev(x), dev(D_f), packed)
@@ -105,7 +105,7 @@ def test_large_tile_forward(fmt):
 
 
 @pytest.mark.parametrize("levels", [0, 1, 5, 11, 12])
-@pytest.mark.parametrize("flags", [0, cngp.FWD_SIMPLE])
+@pytest.mark.parametrize("flags", [0, cngp.FWD_TILE, cngp.FWD_SIMPLE])
 def test_forward_from_a_partially_loaded_model(levels, flags):
     """Level-of-detail streaming: only the first levels are read (the rest of the arrays is poisoned with
     NaN features and out-of-range indices here), the other columns are zero."""
