@@ -1099,14 +1099,15 @@ template <int D, int NP, typename FeatT, typename IoT>
 int launch_bwd_small(const cngp_config *c, const Params &p, const float *x, int64_t N, const void *D_f, const float *Dhat_c,
                      const void *dy, float *gD_f, float *gDhat_c, hipStream_t s) {
     constexpr int64_t PTS = kSmallBwdBlock / NP, WAVE = 64 / NP;
-    // One point per lane group while the chip has room for that many workgroups.  From N_p = 4 on a batch that fills fewer
-    // than 16 of them is cut finer, into whole wavefronts: all the corners of a point follow each other in its lanes, so 16
-    // wavefronts on one CU take their time in turn (kernel alone, us, direct / uncut / cut: d = 4, 12 levels, N_p = 16, 100
-    // points 17 / 22 / 13; d = 3, L = 2, 315 points 10.8 / 13.2 / 10.0; N_p = 1, 4095 points, whose lanes hold a point each,
-    // were slower for it: a call 11.7 uncut, 14.4 cut).
-    constexpr int64_t kLeastChunks = 16;
+    // One point per lane group while the chip has room for that many workgroups.  A batch that fills only a few of them is cut
+    // finer, into whole wavefronts: all the corners of a point follow each other in its lanes, so 16 wavefronts on one CU
+    // take their time in turn (kernel alone, us, direct / uncut / cut: d = 4, 12 levels, N_p = 16, 100 points 17 / 22 / 13;
+    // d = 3, L = 2, N_p = 16, 315 points 10.8 / 13.2 / 10.0; d = 3, L = 1, N_p = 2, 513 points 10.9 / 13.3 / 8.5).  Fewer pieces
+    // where a lane group is short and holds more of the batch: every piece adds what it touched to memory (N_p = 1, 128 KB of
+    // tables, 4095 points on 16 levels: a call 11.7 in 4 pieces, 14.4 in 16; N_p = 2, 65 KB 14.8 in 8, 16.6 in 16).
+    constexpr int64_t kLeastChunks = NP >= 4 ? 16 : NP == 2 ? 8 : 4;
     int64_t chunks = (N + PTS - 1) / PTS, unit = PTS;
-    if (NP >= 4 && chunks < kLeastChunks) { chunks = kLeastChunks; unit = WAVE; }
+    if (chunks < kLeastChunks) { chunks = kLeastChunks; unit = WAVE; }
     if (chunks > kCus / c->L) chunks = kCus / c->L;
     if (chunks < 1) chunks = 1;
     const int64_t chunk = ((N + chunks - 1) / chunks + unit - 1) / unit * unit;

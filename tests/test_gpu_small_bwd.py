@@ -18,7 +18,8 @@ pytestmark = pytest.mark.gpu
     (2, 4, 2**10, 2**8, 4, 1, "f32", "f32", 0), (2, 4, 2**10, 2**8, 4, 255, "f32", "f32", 0), (2, 4, 2**10, 2**8, 4, 4097, "f16", "f32", 0),
     (3, 5, 2**9, 2**6, 16, 65, "f16", "f16", 3), (3, 1, 2**13, 1, 1, 3001, "f32", "f16", 0), (3, 2, 2**13, 2, 2, 1500, "f32", "f32", 0),
     (4, 3, 2**8, 2**7, 8, 1290, "f32", "f32", 0), (2, 32, 2**6, 2**5, 2, 700, "f16", "f32", 1),
-    (4, 12, 2**10, 2**9, 16, 100, "f32", "f32", 0), (3, 2, 2**11, 2**8, 16, 1023, "f16", "f16", 0)])   # cut into whole wavefronts
+    (4, 12, 2**10, 2**9, 16, 100, "f32", "f32", 0), (3, 2, 2**11, 2**8, 16, 1023, "f16", "f16", 0),   # cut into whole wavefronts
+    (3, 1, 2**12, 2**11, 2, 513, "f32", "f32", 0), (2, 3, 2**8, 1, 1, 1025, "f32", "f32", 0)])
 def test_small_tables_accumulate_in_lds(d, L, N_f, N_c, N_p, N, feat, io, top_k):
     w = W.custom(cfg=80 + d + N_p, d=d, L=L, F=2, N_f=N_f, N_c=N_c, N_p=N_p, N_min=4, N_max=64, N=N, feat_dtype=feat, io_dtype=io)
     dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
