@@ -9,8 +9,8 @@
 // A coarse level whose whole vertex grid fits in LDS is looked up once per VERTEX instead of 2^d times per point:
 // its workgroups fill a dense table of the grid's (N_l + 2)^d resolved features and interpolate from that, with no
 // hash, no index lookup and no memory access per point but the point itself.  Both kinds of workgroup measured, before
-// the grids and with them (level kernel alone, us): nerf3d's tables, 2^24 / 2^22 / 2^18 points 2711 / 686 / 55 -> 2036 /
-// 556 / 46, image2d's (2^20) 95 -> 68, sdf3d's (2^20) 461 -> 393.
+// the grids and with them (level kernel alone under rocprofv3, us, average): nerf3d's tables 2^24 uniform points 2734 ->
+// 2103, 2^18 ray samples 50 -> 40; image2d's (2^20) 93 -> 66, sdf3d's (2^20) 451 -> 337.
 // Per point and level the arithmetic is that of the tile kernel, in the same order: the results are bit-identical.
 #pragma once
 #include "cngp_kernels.h"
@@ -25,7 +25,8 @@ constexpr uint32_t kFwdXcds = 8;           // workgroups are handed to the XCDs 
 // Which workgroup does what.  The levels [0, dense) interpolate from a resolved vertex grid, the others look up; the dense
 // ones come last in the grid.  Looked-up units are numbered part by part, so that the levels read the same points at about
 // the same time; `by_xcd` (the parts of the tables that are not in LDS do not fit one XCD's L2 together): instead each
-// XCD (workgroup index mod 8) takes a run of them numbered level by level, so that a level's table is held by one or two L2s.
+// XCD (workgroup index mod 8) takes a run of them numbered level by level, so that a level's table is held by one or two L2s
+// (the plan prefers numbers of levels that eight runs cut evenly: one table too many per L2 costs more than a grid saves).
 struct LevelSplit {
     uint32_t dense, by_xcd;
     uint32_t hash_parts, hash_units;         // parts per looked-up level; workgroups for them (a multiple of 8 if by_xcd)
