@@ -246,7 +246,9 @@ int cngp_encode_bwd_input(const cngp_config *cfg, const float *x, int64_t N, con
 
 /* How cngp_encode_bwd would run for this configuration and N (host only; for tests, tuning and logs).
  * info (host, CNGP_PLAN_INFO_COUNT entries): [0] 1 = LDS-sliced variant, 0 = global atomics;
- * [1] number of coarse levels pre-reduced per grid vertex; [2], [3] slices per level of the feature and
+ * [1] number of coarse levels pre-reduced per grid vertex (a large binned batch merges the references of neighbouring
+ * points instead, on these levels -- those with at least four references per vertex of the grid -- and perhaps
+ * one more; its [6] .. [9] are those of the merged levels, without a grid); [2], [3] slices per level of the feature and
  * of the logit gradient table; [4], [5] point chunks of the feature / logit role on hashed levels;
  * [6], [7] vertex chunks of the two roles on pre-reduced levels; [8] point chunks and [9] total slices
  * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first, and then
@@ -260,8 +262,8 @@ int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info);
 
 /* Where cngp_encode_bwd keeps what in its workspace for this configuration and N (one pass of it, when the batch is
  * taken in passes).  Host only; for tests of the plan: region i covers bytes [regions[2i], regions[2i] + regions[2i+1])
- * -- the softmax table, the level-major dL/dy, the per-vertex sums, then for the binned variant the count matrices,
- * bin starts and records of the two tables and of the pre-reduced levels.  No two regions may overlap, every one
+ * -- the softmax table, the level-major dL/dy, the per-vertex sums (and what the merge needs to find them), then for the binned variant the count matrices,
+ * bin starts and records of the two tables and of the pre-reduced or merged levels.  No two regions may overlap, every one
  * starts on a 256-byte boundary and ends inside cngp_workspace_bytes(cfg, N).  Returns the number of regions
  * (at most CNGP_PLAN_REGIONS; 0 for the variant that needs no workspace) or a negative status. */
 enum { CNGP_PLAN_REGIONS = 12 };

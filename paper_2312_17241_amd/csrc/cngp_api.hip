@@ -5,6 +5,7 @@
 #include "cngp_fwd_level.h"
 #include "cngp_bwd_sliced.h"
 #include "cngp_bwd_binned.h"
+#include "cngp_bwd_merge.h"
 #include "cngp_rates.h"
 #include "cngp_optim.h"
 #include "cngp_mlp.h"
@@ -125,14 +126,14 @@ int check_blocks(int64_t blocks) { return (blocks > 0x7fffffffLL) ? CNGP_ERR_INV
 // ---------------------------------------------------------------- per-kernel timing
 enum KernelId { K_FWD = 0, K_BWD_DIRECT, K_BWD_PREP, K_BWD_SLICED, K_BWD_SLICED_V, K_BWD_GRID_DRAIN,
                 K_BAKE, K_ZERO, K_DEBUG, K_ADAM, K_MLP_FWD, K_MLP_BWD,
-                K_BWD_BIN_OFFSETS, K_BWD_BIN_SCATTER, K_BWD_BIN_DRAIN, K_BWD_INPUT, K_FUSED_FWD, K_PLANES, K_FWD_ROWS, K_BWD_SMALL, K_COUNT };
+                K_BWD_BIN_OFFSETS, K_BWD_BIN_SCATTER, K_BWD_BIN_DRAIN, K_BWD_INPUT, K_FUSED_FWD, K_PLANES, K_FWD_ROWS, K_BWD_SMALL, K_BWD_CELLS, K_BWD_MERGE, K_COUNT };
 const char *const kKernelNames[K_COUNT] = {"encode_fwd", "encode_bwd_direct", "encode_bwd_prepare",
                                            "encode_bwd_sliced_points_and_grid", "encode_bwd_sliced_vertices",
                                            "encode_bwd_bin_grid_sums", "bake_probes", "zero", "debug_indices",
                                            "adam_step_bake", "mlp_fwd", "mlp_bwd",
                                            "encode_bwd_bin_offsets", "encode_bwd_bin_scatter",
                                            "encode_bwd_bin_drain", "encode_bwd_input", "encode_mlp_fwd", "feature_planes",
-                                           "encode_fwd_rows", "encode_bwd_small"};
+                                           "encode_fwd_rows", "encode_bwd_small", "encode_bwd_cells", "encode_bwd_merge"};
 
 struct TimedLaunch { int id; hipEvent_t t0, t1; };
 bool g_profile = false;
@@ -553,9 +554,12 @@ struct BwdPlan {
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
     uint32_t subs_f, subs_c;            // drain workgroups per bin
     size_t   cntF_off, cntC_off, baseF_off, baseC_off, recF_off, recC_off;
-    size_t   cntG_off, baseG_off, recG_off;          // pre-reduced levels binned by slice of their vertex grid
+    size_t   cntG_off, baseG_off, recG_off;          // pre-reduced levels binned by slice of their vertex grid; merged ones by slice of the tables
+    bool     merged;                    // the first levels' references are merged per vertex and binned as entries (cngp_bwd_merge.h); dense.count of them
+    MergeParams merge;
+    uint64_t G_bytes, cntG_bytes, baseG_bytes, recG_bytes;
     GridDrainPlan grid_drain;
-    DenseLevels dense;                  // levels pre-reduced per grid vertex (a prefix of the levels)
+    DenseLevels dense;                  // levels pre-reduced per grid vertex (a prefix of the levels); merged: only their number
     uint32_t dense_slices, dense_verts, dense_max_verts;
 };
 
@@ -573,6 +577,15 @@ constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which 
 // Backward, us, with / without, beyond it: nerf3d's tables 163840 points 384 / 403, 2^18 539 / 569; sdf3d's 2^20 2786 / 3294;
 // d = 2 600000 1001 / 1175.
 constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
+// Merging (cngp_bwd_merge.h): references per level from which the three launches more are worth it, and references per vertex of
+// a level's grid, in hundredths, from which the level is merged (points are never spread more evenly than over the whole grid).
+// Sum of the kernels of a step, us, lines at 20 / 80 / 150 / 300 / 1500: nerf3d 728 / 611 / 594 / 587 / 601 (649 with grid sums),
+// sdf3d, whose points are anything but evenly spread, 2750 / 2704 / 2786 / 2815 / 2977 (3184), compact3d 504 / 465 / 448 / 453 / 478 (469).
+// Backward without / with merging over 110 drawn configurations from that batch size on: d = 3 1.19x faster on average (slowest 0.95x),
+// d = 2 1.28x; d = 4, where two or three levels have that many references per vertex, 0.99x (0.78 .. 1.21), and small feature
+// tables with d = 2 and N_p = 2, whose references cost the least, 0.90x: neither is merged.
+constexpr int64_t  kMinMergeRefs = 3 << 19;
+constexpr uint64_t kMinMergePerVertexPct = 150;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -713,11 +726,57 @@ double binned_bwd_us(const cngp_config *c, int64_t N, const BwdPlan &b, int Ld) 
            3.1e-6 * records + (Ld > 0 ? 23.0 + 6.4e-6 * Ld * refs : 0.0);
 }
 
-// Which levels a binned batch pre-reduces: those that pay, those that pay in a large batch, or every one that can be (its set
-// does not depend on N, so what the last layout needs only grows with N).
-enum Layout { LAYOUT_FAST = 0, LAYOUT_REDUCED, LAYOUT_LEAST, LAYOUT_COUNT };
+// Which levels a binned batch merges or pre-reduces: merged where that pays, else those whose grid sums pay, those that pay in a
+// large batch, or every one that can be (its set does not depend on N, so what the last layout needs only grows with N).
+enum Layout { LAYOUT_MERGED = 0, LAYOUT_FAST, LAYOUT_REDUCED, LAYOUT_LEAST, LAYOUT_COUNT };
 
-BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = LAYOUT_FAST) {
+// The arrays of the merged levels inside the workspace regions of the pre-reduced ones.
+struct MergedSpace { size_t entries, order, cells, total, G_bytes, cntF, cntC, made, cntG_bytes, baseF, baseC, baseG_bytes, recF, recC, recG_bytes; };
+MergedSpace merged_space(const BwdPlan &b, int64_t N, int d) {
+    const size_t M = (size_t)b.dense.count, cap = (size_t)N << d, sf = b.fused ? 0 : b.slices_f, sc = b.slices_c;
+    MergedSpace m;
+    m.entries = 0;
+    m.order = align256(M * cap * sizeof(uint4));
+    m.cells = m.order + align256((size_t)N * 4);
+    m.total = m.cells + (size_t)b.merge.tiles * kMergeCells * 4;
+    m.G_bytes = m.total + kMergeCells * 4;
+    m.cntF = 0;
+    m.cntC = align256(M * b.merge.chunks * sf * 4);
+    m.made = m.cntC + align256(M * b.merge.chunks * sc * 4);
+    m.cntG_bytes = m.made + M * b.merge.chunks * 4;
+    m.baseF = 0;
+    m.baseC = align256(M * (sf + 1) * 4);
+    m.baseG_bytes = m.baseC + M * (sc + 1) * 4;
+    m.recF = 0;
+    m.recC = sf ? align256(M * cap * sizeof(EntryRecord)) : 0;
+    m.recG_bytes = m.recC + (sc ? M * cap * sizeof(EntryRecord) : 0);
+    return m;
+}
+MergedBins merged_bins(const BwdPlan &b, int64_t N, int d, void *workspace) {
+    const MergedSpace m = merged_space(b, N, d);
+    char *ws = (char *)workspace;
+    return {(uint32_t *)(ws + b.cntG_off + m.cntF), (uint32_t *)(ws + b.cntG_off + m.cntC), (uint32_t *)(ws + b.cntG_off + m.made),
+            (uint32_t *)(ws + b.baseG_off + m.baseF), (uint32_t *)(ws + b.baseG_off + m.baseC),
+            (EntryRecord *)(ws + b.recG_off + m.recF), (EntryRecord *)(ws + b.recG_off + m.recC),
+            b.merge.levels, b.merge.chunks, b.merge.chunk_pts, (uint4 *)(ws + b.G_off + m.entries)};
+}
+
+// Levels (a prefix) whose references a batch of N points merges.
+int merge_levels(const cngp_config *c, int64_t N) {
+    uint32_t res[kMaxLevels];
+    level_table(c, res);
+    const uint64_t limit = (c->d == 2 ? 1u << 16 : 1u << 10) - 2u;                              // coordinates a table key holds
+    int M = 0;
+    while (M < c->L - 1 && M < kMaxDense && (uint64_t)res[M] + 1 < limit) {
+        uint64_t verts = 1;
+        for (int i = 0; i < c->d; ++i) verts *= (uint64_t)res[M] + 2;
+        if (((uint64_t)N << c->d) * 100 < verts * kMinMergePerVertexPct) break;
+        ++M;
+    }
+    return M;
+}
+
+BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = LAYOUT_MERGED) {
     BwdPlan b;
     std::memset(&b, 0, sizeof(b));
     const uint32_t groups = c->N_f / c->N_p;                               // hashed rows of D_f
@@ -771,10 +830,16 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     if (c->flags & CNGP_BWD_DIRECT) b.sliced = false;
     if ((c->flags & CNGP_BWD_SLICED) && (uint64_t)per_level * 32u * 64u < 0x7fffffffull) b.sliced = true;
     if (!keys_fit) b.sliced = false;
+    b.merged = b.binned && layout == LAYOUT_MERGED && !(c->flags & CNGP_BWD_NO_PREREDUCE) && !c->bin_bytes_max &&
+               c->d <= 3 && !(b.fused && c->d == 2 && c->N_p == 2) && (N << c->d) >= kMinMergeRefs && (b.fused ? 0 : b.slices_f) + b.slices_c <= kMergeMaxBins;
+    if (b.merged) {
+        b.dense.count = merge_levels(c, N);
+        b.merged = b.dense.count > 0;
+    }
     // coarse levels whose dense vertex grid is small, much smaller than the number of references, and
     // takes clearly fewer slice scans than the level's hashed tables.  With binning a hashed level costs
     // no replicated scan, and pre-reduction only pays for grids of a few slices.
-    if (b.sliced && !(c->flags & CNGP_BWD_NO_PREREDUCE)) {
+    if (b.sliced && !b.merged && !(c->flags & CNGP_BWD_NO_PREREDUCE)) {
         uint32_t res[kMaxLevels];
         level_table(c, res);
         for (int l = 0; l < c->L && l < kMaxDense; ++l) {
@@ -797,7 +862,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         }
         // (a caller who bounds the bins gets the smaller workspace: a pre-reduced level has records once instead of twice)
         if (b.binned && b.dense.count > 0 && (N << c->d) < kMinBinnedPrereduceRefs && !(c->flags & CNGP_BWD_BINNED) &&
-            !c->bin_bytes_max && layout == LAYOUT_FAST &&
+            !c->bin_bytes_max && layout <= LAYOUT_FAST &&
             binned_bwd_us(c, N, b, b.dense.count) > 0.96 * binned_bwd_us(c, N, b, 0)) {
             std::memset(&b.dense, 0, sizeof(b.dense));
             b.dense_verts = b.dense_slices = b.dense_max_verts = 0;
@@ -815,6 +880,24 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.subs_f = drain_subs(refs, b.slices_f, Lh, b.slices_f + b.slices_c);
         b.subs_c = drain_subs(refs, b.slices_c, Lh, b.slices_f + b.slices_c);
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
+        if (b.merged) {
+            // half as many drain workgroups per bin: at most about half of a merged level's references are left
+            b.feat_vtx = Geom{b.fused ? 2u : (b.subs_f + 1) / 2, 0};
+            b.logit_vtx = Geom{(b.subs_c + 1) / 2, 0};
+            b.merge.levels = (uint32_t)b.dense.count;
+            // chunks of at least two rounds, at most 512 of them: sparse parts of space leave several times the entries of
+            // dense ones, and the many short workgroups even that out
+            const int64_t round = kMergeRefs >> c->d;
+            int64_t mp = ((N + 511) / 512 + round - 1) / round * round;
+            if (mp < 2 * round) mp = 2 * round;
+            b.merge.chunk_pts = (uint32_t)mp;
+            b.merge.chunks = (uint32_t)((N + mp - 1) / mp);
+            // tiles of at least 4096 points, at most 256 of them
+            int64_t tp = ((N + 255) / 256 + 1023) / 1024 * 1024;
+            if (tp < 4096) tp = 4096;
+            b.merge.tile_pts = (uint32_t)tp;
+            b.merge.tiles = (uint32_t)((N + tp - 1) / tp);
+        }
     }
     const size_t queues = (size_t)kSlicedWaves * kRingBytes;
     b.lds_f = ((size_t)1 << b.rows_f_log2) * c->N_p * 2 * 8 + queues;
@@ -824,7 +907,10 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.sigma_off = 0;
         b.dyT_off = align256((size_t)c->L * c->N_c * c->N_p * sizeof(float));
         b.G_off = b.dyT_off + align256((size_t)N * c->L * c->F * io);
-        b.ws_bytes = b.G_off + align256((size_t)b.dense_verts * 2 * sizeof(float));
+        b.G_bytes = (size_t)b.dense_verts * 2 * sizeof(float);
+        MergedSpace m;
+        if (b.merged) { m = merged_space(b, N, c->d); b.G_bytes = m.G_bytes; }
+        b.ws_bytes = b.G_off + align256(b.G_bytes);
         if (b.binned) {
             const size_t cap = (size_t)N << c->d;
             // (room for as many chunks as any shorter batch has: 2^18 points are counted in 256, one more in 241)
@@ -837,12 +923,17 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             b.recC_off = b.recF_off + (b.fused ? 0 : align256((size_t)Lh * cap * kRecordBytes));
             b.cntG_off = b.recC_off + (b.slices_c ? align256((size_t)Lh * cap * kRecordBytes) : 0);
             const size_t Ld = (size_t)b.dense.count;
-            b.baseG_off = b.cntG_off + align256(Ld * rows * kGridBins * 4);
-            b.recG_off = b.baseG_off + align256(Ld * (kGridBins + 1) * 4);
-            b.ws_bytes = b.recG_off + align256(Ld * cap * kRecordBytes);
+            b.baseG_off = b.cntG_off + align256(b.merged ? m.cntG_bytes : Ld * rows * kGridBins * 4);
+            b.recG_off = b.baseG_off + align256(b.merged ? m.baseG_bytes : Ld * (kGridBins + 1) * 4);
+            b.ws_bytes = b.recG_off + align256(b.merged ? m.recG_bytes : Ld * cap * kRecordBytes);
+            b.cntG_bytes = b.merged ? m.cntG_bytes : Ld * b.bin_chunks * kGridBins * 4;
+            b.baseG_bytes = b.merged ? m.baseG_bytes : Ld * (kGridBins + 1) * 4;
+            b.recG_bytes = b.merged ? m.recG_bytes : Ld * cap * kRecordBytes;
+            // (an entry takes 16 bytes and there may be as many as references: not asked for beyond what the bins may take)
+            if (b.merged && b.ws_bytes > kMaxAutoBinBytes) return make_bwd_plan_uncached(c, N, LAYOUT_FAST);
             // workgroups per slice of a level's grid: about 2^15 references each
             uint32_t next = 0;
-            for (int l = 0; l < b.dense.count; ++l) {
+            for (int l = 0; l < b.dense.count && !b.merged; ++l) {
                 uint64_t subs = (cap / b.dense.slices[l] + 32767) / 32768;
                 if (subs < 1) subs = 1;
                 if (subs > 256) subs = 256;
@@ -857,7 +948,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
 }
 
 // The plan depends on (configuration, N) only; the last one of each layout is kept (host memory, per thread).
-const BwdPlan &make_bwd_plan(const cngp_config *c, int64_t N, Layout layout = LAYOUT_FAST) {
+const BwdPlan &make_bwd_plan(const cngp_config *c, int64_t N, Layout layout = LAYOUT_MERGED) {
     struct Kept { cngp_config cfg; int64_t N = -1; BwdPlan plan; };
     thread_local Kept kept[LAYOUT_COUNT];
     Kept &k = kept[layout];
@@ -874,6 +965,8 @@ const BwdPlan &make_bwd_plan(const cngp_config *c, int64_t N, Layout layout = LA
 const BwdPlan &bwd_plan_for(const cngp_config *c, int64_t N, size_t room) {
     const BwdPlan &b = make_bwd_plan(c, N);
     if (!b.binned || b.ws_bytes <= room) return b;
+    const BwdPlan &fast = make_bwd_plan(c, N, LAYOUT_FAST);
+    if (fast.ws_bytes <= room) return fast;
     const BwdPlan &reduced = make_bwd_plan(c, N, LAYOUT_REDUCED);
     return reduced.ws_bytes <= room ? reduced : make_bwd_plan(c, N, LAYOUT_LEAST);
 }
@@ -906,18 +999,18 @@ BinParams make_bin_params(const cngp_config *c, const BwdPlan &b, int64_t N) {
     bp.rows_c_log2 = b.rows_c_log2; bp.slices_c = NP > 1 ? b.slices_c : 0;
     bp.chunks = b.bin_chunks; bp.chunk_pts = b.bin_chunk_pts;
     bp.cap = (uint32_t)((uint64_t)N << c->d);
-    bp.dense_bins = b.dense.count > 0 ? 1 : 0;
+    bp.merged = b.merged ? 1 : 0;
     return bp;
 }
 // Bins of the level with the most of them, and the copies of the histogram the count keeps in LDS.
 uint32_t most_bins_of(const BinParams &bp) { return bp.slices_f + bp.slices_c > kGridBins ? bp.slices_f + bp.slices_c : kGridBins; }
 uint32_t hist_replicas_of(uint32_t most_bins) { return most_bins <= 64 ? 16u : most_bins <= 512 ? 4u : 1u; }
 
-// Binned variant: (the count has run with the preparation launch) offsets, scatter (+ vertex-grid accumulation of the dense levels), drain
+// Binned variant: (the count has run with the preparation launch) merge of the merged levels, offsets, scatter (+ vertex-grid accumulation of the dense levels), drain
 // (+ the two roles of the dense levels, which scan the finished vertex grids).
 template <int D, int NP, typename FeatT, typename IoT>
 int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, const float *x, int64_t N,
-                      const void *D_f, const float *sigma, const IoT *dyT, float *G, float *gD_f, float *gDhat_c,
+                      const void *D_f, const float *sigma, const IoT *dy, const IoT *dyT, float *G, float *gD_f, float *gDhat_c,
                       void *workspace, hipStream_t s) {
     const int Ld = b.dense.count, Lh = c->L - Ld;
     char *ws = (char *)workspace;
@@ -925,33 +1018,53 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     uint32_t *baseF = (uint32_t *)(ws + b.baseF_off), *baseC = (uint32_t *)(ws + b.baseC_off);
     BinRecord *recF = (BinRecord *)(ws + b.recF_off), *recC = (BinRecord *)(ws + b.recC_off);
     uint32_t *cntG = (uint32_t *)(ws + b.cntG_off), *baseG = (uint32_t *)(ws + b.baseG_off);
+    MergedBins mb;
+    std::memset(&mb, 0, sizeof(mb));
+    if (b.merged) mb = merged_bins(b, N, D, workspace);
     BinRecord *recG = (BinRecord *)(ws + b.recG_off);
     const bool zero_first = (c->flags & CNGP_ZERO_GRADS) != 0;
     const BinParams bp = make_bin_params<NP>(c, b, N);
-    const int64_t blocks = (int64_t)(Lh + Ld) * bp.chunks;
+    const int64_t blocks = (int64_t)(b.merged ? Lh : Lh + Ld) * bp.chunks + (int64_t)mb.levels * mb.chunks;
     if (int rc = check_blocks(blocks)) return rc;
     const size_t lds_bins = (size_t)most_bins_of(bp) * sizeof(uint32_t);
     // One wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
     // like (measured: drain 7 % faster); with many bins a lone wavefront fills its cache lines too slowly
     // for the memory system to merge the 4-byte writes, and four wavefronts sharing the cursors write
     // 1.7 times faster (measured at 64 bins per level).
+    if constexpr (D <= 3) if (b.merged) {      // the points in the order of their cells (the histogram ran with the preparation), then the entries
+        const MergedSpace m = merged_space(b, N, D);
+        uint32_t *order = (uint32_t *)(ws + b.G_off + m.order), *cells = (uint32_t *)(ws + b.G_off + m.cells), *total = (uint32_t *)(ws + b.G_off + m.total);
+        {
+            LaunchTimer t(s, K_BWD_CELLS);
+            merge_scan_kernel<<<kMergeCells / 64, kMergeScanBlock, 0, s>>>(b.merge, cells, total);
+            if (int rc = launch_status("merge_scan_kernel")) return rc;
+            merge_order_kernel<D><<<b.merge.tiles, 1024, 0, s>>>(b.merge, x, N, cells, total, order);
+            if (int rc = launch_status("merge_order_kernel")) return rc;
+        }
+        auto kernel = bwd_merge_kernel<D, IoT>;
+        if (int rc = allow_big_lds(kernel, kMergeLdsBytes)) return rc;
+        LaunchTimer t(s, K_BWD_MERGE);
+        kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, order, mb);
+        if (int rc = launch_status("bwd_merge_kernel")) return rc;
+    }
     const unsigned bin_block = bp.slices_f + bp.slices_c >= 48 ? 256u : (unsigned)kBinBlock;
     {
         LaunchTimer t(s, K_BWD_BIN_OFFSETS);
         uint32_t big = bp.slices_f > bp.slices_c ? bp.slices_f : bp.slices_c;
-        if (Ld > 0 && big < kGridBins) big = kGridBins;
-        const uint32_t words = (uint64_t)bp.chunks * big <= 36864 ? bp.chunks * big : 0u;    // up to 144 KB of LDS
+        if (Ld > 0 && !b.merged && big < kGridBins) big = kGridBins;
+        const uint32_t most = mb.chunks > bp.chunks ? mb.chunks : bp.chunks;
+        const uint32_t words = (uint64_t)most * big <= 36864 ? most * big : 0u;    // up to 144 KB of LDS
         if (int rc = allow_big_lds(bin_offsets_kernel, (size_t)words * 4)) return rc;
-        bin_offsets_kernel<<<(unsigned)(2 * Lh + Ld), kOffsetsBlock, (size_t)words * 4, s>>>(bp, cntF, cntC, cntG, baseF, baseC,
-                                                                                            baseG, words);
+        bin_offsets_kernel<<<(unsigned)(2 * Lh + (b.merged ? 2 * Ld : Ld)), kOffsetsBlock, (size_t)words * 4, s>>>(
+            bp, cntF, cntC, cntG, baseF, baseC, baseG, mb, words);
         if (int rc = launch_status("bin_offsets_kernel")) return rc;
     }
     {
         LaunchTimer t(s, K_BWD_BIN_SCATTER);
-        bin_scatter_kernel<D><<<(unsigned)blocks, bin_block, lds_bins, s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG);
+        bin_scatter_kernel<D><<<(unsigned)blocks, bin_block, lds_bins, s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG, mb);
         if (int rc = launch_status("bin_scatter_kernel")) return rc;
     }
-    if (Ld > 0) {   // vertex-grid sums of the pre-reduced levels from their bins
+    if (Ld > 0 && !b.merged) {   // vertex-grid sums of the pre-reduced levels from their bins
         auto kernel = bin_grid_drain_kernel<D, IoT>;
         const size_t lds_grid = (size_t)kDenseSliceVerts * 2 * sizeof(double);
         if (int rc = allow_big_lds(kernel, lds_grid)) return rc;
@@ -979,7 +1092,8 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     BwdRoles vtx;
     std::memset(&vtx, 0, sizeof(vtx));
     vtx.sp[ROLE_LOGIT_VTX] = role(b.rows_c_log2, slices_c, b.logit_vtx, 0, Ld, wgs_cv);
-    vtx.sp[ROLE_FEAT_VTX] = role(b.rows_f_log2, b.slices_f, b.feat_vtx, 0, Ld, wgs_fv);
+    vtx.sp[ROLE_FEAT_VTX] = role(b.rows_f_log2, b.merged && b.fused ? 0u : b.slices_f, b.feat_vtx, 0, Ld, wgs_fv);
+    vtx.sp[ROLE_LOGIT_VTX].spread = vtx.sp[ROLE_FEAT_VTX].spread = b.merged ? 1 : 0;
     vtx.first[ROLE_LOGIT_VTX] = 0;
     vtx.first[ROLE_FEAT_VTX] = wgs_cv;
     auto kernel = bin_drain_kernel<D, NP, FeatT, IoT>;
@@ -993,7 +1107,7 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     if (total == 0) return CNGP_OK;
     LaunchTimer t(s, K_BWD_BIN_DRAIN);
     kernel<<<total, kSlicedBlock, lds, s>>>(p, sp_c, sp_f, wgs_c, wgs_c + wgs_f, x, dyT, N, (const FeatT *)D_f, sigma, recF, recC,
-                                            baseF, baseC, bp.cap, vtx, b.dense, G, gD_f, gDhat_c);
+                                            baseF, baseC, bp.cap, vtx, b.dense, G, b.merged ? 1 : 0, mb, gD_f, gDhat_c);
     return launch_status("bin_drain_kernel");
 }
 
@@ -1011,7 +1125,7 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
         grid_direct = true;
         for (int l = 0; l < Ld; ++l) grid_direct = grid_direct && b.grid_drain.subs[l] == 1;
     }
-    if (Ld > 0 && !grid_direct) zero.add(G, (int64_t)b.dense_verts * 2);
+    if (Ld > 0 && !b.merged && !grid_direct) zero.add(G, (int64_t)b.dense_verts * 2);
     {   // one launch: clear what is accumulated with atomics, softmax table, level-major dL/dy
         using PairT = typename std::conditional<sizeof(IoT) == 2, uint32_t, float2>::type;
         const int64_t elems = NP > 1 ? (int64_t)c->L * c->N_c * NP : 0;
@@ -1025,17 +1139,20 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
         PrepArgs a;
         a.seg = zero.seg; a.seg_count = (uint32_t)zero.n; a.zero_blocks = (uint32_t)zero_blocks;
         a.Dhat_c = Dhat_c; a.sigma = sigma; a.elems = elems; a.softmax_blocks = (uint32_t)softmax_blocks;
-        a.dy = dy; a.dyT = dyT; a.N = N; a.L = c->L; a.top_k = p.top_k;
+        a.dy = dy; a.dyT = dyT; a.N = N; a.L = c->L; a.level0 = b.merged ? Ld : 0; a.top_k = p.top_k;
         LaunchTimer t(s, K_BWD_PREP);
         if (b.binned) {          // the count of the binned variant rides along: it needs nothing this launch writes
             const BinParams bp = make_bin_params<NP>(c, b, N);
-            const int64_t   count_blocks = (int64_t)c->L * bp.chunks;
-            if (int rc = check_blocks(blocks + count_blocks)) return rc;
+            const int64_t   count_blocks = (int64_t)(b.merged ? Lh : c->L) * bp.chunks;
+            if (int rc = check_blocks(blocks + count_blocks + b.merge.tiles)) return rc;
             const uint32_t most = most_bins_of(bp), reps = hist_replicas_of(most);
             char *ws = (char *)workspace;
-            bwd_prep_count_kernel<D, NP, PairT><<<(unsigned)(blocks + count_blocks), kBlock, (size_t)most * reps * sizeof(uint32_t), s>>>(
+            size_t lds = (size_t)most * reps * sizeof(uint32_t);
+            if (b.merged && lds < kMergeCells * sizeof(uint32_t)) lds = kMergeCells * sizeof(uint32_t);
+            uint32_t *cells = b.merged ? (uint32_t *)(ws + b.G_off + merged_space(b, N, D).cells) : nullptr;
+            bwd_prep_count_kernel<D, NP, PairT><<<(unsigned)(blocks + count_blocks + b.merge.tiles), kBlock, lds, s>>>(
                 a, p, bp, b.dense, x, (uint32_t *)(ws + b.cntF_off), (uint32_t *)(ws + b.cntC_off), (uint32_t *)(ws + b.cntG_off),
-                reps, (uint32_t)count_blocks);
+                reps, (uint32_t)count_blocks, b.merge, cells);
         } else {
             bwd_prep_kernel<NP, PairT><<<(unsigned)blocks, kBlock, 0, s>>>(a);
         }
@@ -1045,7 +1162,7 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
     }
 
     if (b.binned)
-        return launch_bwd_binned<D, NP, FeatT, IoT>(c, p, b, x, N, D_f, sigma, dyT, G, gD_f, gDhat_c, workspace, s);
+        return launch_bwd_binned<D, NP, FeatT, IoT>(c, p, b, x, N, D_f, sigma, (const IoT *)dy, dyT, G, gD_f, gDhat_c, workspace, s);
 
     // Launch 1: feature and logit gradients of the hashed levels (scan the points) together with the
     // vertex-grid accumulation of the dense levels.  Launch 2: the two gradients of the dense levels
@@ -1395,8 +1512,16 @@ int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
     cfg = &pairs;
     const int64_t per = bwd_pass_points(cfg, N);
     const BwdPlan b = make_bwd_plan(cfg, per < N ? per : N);
+    int32_t prereduced = b.dense.count;
+    if (b.merged) {         // reported: the levels with at least kMinRefsPerVertex references per vertex
+        uint32_t res[kMaxLevels];
+        level_table(cfg, res);
+        prereduced = 0;
+        while (prereduced < b.dense.count && !b.fused &&
+               std::pow((double)res[prereduced] + 2.0, cfg->d) * kMinRefsPerVertex <= (double)(uint64_t)(per < N ? per : N) * (1 << cfg->d)) ++prereduced;
+    }
     const int32_t v[CNGP_PLAN_INFO_COUNT] = {
-        b.sliced ? 1 : 0, b.dense.count, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
+        b.sliced ? 1 : 0, prereduced, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
         (int32_t)b.feat_pts.chunks, (int32_t)b.logit_pts.chunks, (int32_t)b.feat_vtx.chunks,
         (int32_t)b.logit_vtx.chunks, (int32_t)b.grid.chunks, (int32_t)b.dense_slices,
         b.binned ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
@@ -1422,7 +1547,7 @@ int cngp_bwd_plan_layout(const cngp_config *cfg, int64_t N, uint64_t *regions) {
     auto add = [&](size_t off, uint64_t bytes) { regions[2 * k] = off; regions[2 * k + 1] = bytes; ++k; };
     add(b.sigma_off, (uint64_t)cfg->L * cfg->N_c * cfg->N_p * 4);
     add(b.dyT_off, (uint64_t)n * cfg->L * cfg->F * io);
-    add(b.G_off, (uint64_t)b.dense_verts * 2 * 4);
+    add(b.G_off, b.G_bytes);
     if (b.binned) {
         const uint64_t sf = b.fused ? 0 : b.slices_f, sc = cfg->N_p > 1 ? b.slices_c : 0;
         add(b.cntF_off, Lh * b.bin_chunks * sf * 4);
@@ -1431,9 +1556,9 @@ int cngp_bwd_plan_layout(const cngp_config *cfg, int64_t N, uint64_t *regions) {
         add(b.baseC_off, sc ? Lh * (sc + 1) * 4 : 0);
         add(b.recF_off, sf ? Lh * cap * kRecordBytes : 0);
         add(b.recC_off, sc ? Lh * cap * kRecordBytes : 0);
-        add(b.cntG_off, Ld * b.bin_chunks * kGridBins * 4);
-        add(b.baseG_off, Ld ? Ld * (kGridBins + 1) * 4 : 0);
-        add(b.recG_off, Ld * cap * kRecordBytes);
+        add(b.cntG_off, b.cntG_bytes);
+        add(b.baseG_off, b.baseG_bytes);
+        add(b.recG_off, b.recG_bytes);
     }
     return k;
 }

@@ -38,11 +38,32 @@ struct BinParams {
     uint32_t rows_c_log2, slices_c;       // logit-gradient slices per level; slices_c = 0 when N_p = 1
     uint32_t chunks, chunk_pts;           // point chunks of count / scatter
     uint32_t cap;                         // records per level and role: N * 2^d
-    int32_t  dense_bins;                  // 1: the pre-reduced coarse levels are binned too, by slice of their vertex grid
+    int32_t  merged;                      // 1: levels 0 .. level0 - 1 are merged (cngp_bwd_merge.h), 0: pre-reduced per vertex of their grid
 };
 // slices_f = 0: no bins by feature-table slice.  That is the case of a small feature table (the paper's
 // N_f = 2^6 .. 2^11), whose whole level sits in LDS beside a slice of the confidence table: the workgroups
 // that drain the confidence-table bins then accumulate both gradients in one pass (drain_both).
+
+// Levels whose references are merged per vertex before they are binned (cngp_bwd_merge.h): levels 0 .. levels - 1.
+constexpr uint32_t kMergeCells = 4096;
+struct MergeParams {
+    uint32_t levels;
+    uint32_t chunks, chunk_pts;           // chunks of the ordered points that are merged and counted together
+    uint32_t tiles, tile_pts;             // of the histogram and the order
+};
+// An entry in a bin: row inside the slice | row of the other table << log2(rows per slice), and g.  Whole, unlike a
+// reference's record: there are few of them, and naming their place would cost a 128-byte line each.
+struct EntryRecord { uint32_t key; float gx, gy; };
+struct MergedBins {                       // as the references' own arrays, by level
+    uint32_t  *cntF, *cntC, *made;        // made[level][chunk]: entries
+    uint32_t  *baseF, *baseC;
+    EntryRecord *recF, *recC;
+    uint32_t   levels, chunks, chunk_pts;
+    uint4     *entries;                   // {hashed row, row of the confidence table, g (two floats)}
+};
+template <int D>
+__device__ __forceinline__ void merge_hist_block(const MergeParams &mp, const float *__restrict__ x, const int64_t N,
+                                                 uint32_t *__restrict__ cells, const uint32_t tile);
 
 // Bins of a pre-reduced level: slices of kDenseSliceVerts vertices of its dense grid; every level is given
 // kGridBins of them (the largest grid that is pre-reduced has that many).
@@ -100,8 +121,8 @@ __device__ __forceinline__ void corner_rows(const Cell<D> &cell, const Params &p
     h2 = cell.hash2(c) & p.c_mask;
 }
 
-// Workgroups [0, nlevels * chunks) count the hashed levels; with dense_bins the next level0 * chunks ones
-// count the pre-reduced levels 0 .. level0 - 1 by slice of their vertex grid.
+// Workgroups [0, nlevels * chunks) count the hashed levels; the next level0 * chunks ones count the pre-reduced levels
+// 0 .. level0 - 1 by slice of their vertex grid, unless those are merged (which counts them itself).
 template <int D>
 __device__ __forceinline__ void bin_count_block(
     const Params &p, const BinParams &bp, const DenseLevels &dl, const float *__restrict__ x, const int64_t N,
@@ -172,15 +193,17 @@ __device__ __forceinline__ void bin_count_block(
 
 // The count shares its launch with the preparation of cngp_bwd_sliced.h (clearing, softmax table, level-major
 // dL/dy): neither needs the other's results, one is bound by hashing and LDS atomics, the other by memory.
-// Workgroups [0, count_blocks) count, the rest prepare (alternating the two kinds over the grid was slower).
+// The first mp.tiles workgroups count points by cell for the merged levels, the next count_blocks ones references by
+// slice, the rest prepare (alternating the two kinds over the grid was slower).
 template <int D, int NP, typename PairT>
 __global__ __launch_bounds__(kBlock) void bwd_prep_count_kernel(
     const PrepArgs a, const Params p, const BinParams bp, const DenseLevels dl, const float *__restrict__ x,
     uint32_t *__restrict__ cntF, uint32_t *__restrict__ cntC, uint32_t *__restrict__ cntG, const uint32_t hist_replicas,
-    const uint32_t count_blocks)
+    const uint32_t count_blocks, const MergeParams mp, uint32_t *__restrict__ cells)
 {
-    if (blockIdx.x < count_blocks) bin_count_block<D>(p, bp, dl, x, a.N, cntF, cntC, cntG, hist_replicas, blockIdx.x);
-    else bwd_prep_block<NP, PairT>(a, blockIdx.x - count_blocks);
+    if (blockIdx.x < mp.tiles) merge_hist_block<D>(mp, x, a.N, cells, blockIdx.x);
+    else if (blockIdx.x - mp.tiles < count_blocks) bin_count_block<D>(p, bp, dl, x, a.N, cntF, cntC, cntG, hist_replicas, blockIdx.x - mp.tiles);
+    else bwd_prep_block<NP, PairT>(a, blockIdx.x - mp.tiles - count_blocks);
 }
 
 constexpr int kOffsetsBlock = 256;
@@ -192,19 +215,21 @@ constexpr int kOffsetsBlock = 256;
 // Threads form a [segment][slice] array: a thread owns one slice's counts of a run of chunks.
 __global__ __launch_bounds__(kOffsetsBlock) void bin_offsets_kernel(
     const BinParams bp, uint32_t *__restrict__ cntF, uint32_t *__restrict__ cntC, uint32_t *__restrict__ cntG,
-    uint32_t *__restrict__ baseF, uint32_t *__restrict__ baseC, uint32_t *__restrict__ baseG, const uint32_t lds_words)
+    uint32_t *__restrict__ baseF, uint32_t *__restrict__ baseC, uint32_t *__restrict__ baseG, const MergedBins mb, const uint32_t lds_words)
 {
     extern __shared__ __align__(16) uint32_t mat[];
     __shared__ uint32_t part[kOffsetsBlock];                // [segment][slice lane]: sum of the thread's run
     __shared__ uint32_t carry;                              // records of the slices handled in earlier rounds
-    // workgroups 0 .. 2 nlevels - 1: (hashed level, table); then one per pre-reduced level
-    const bool     dense = blockIdx.x >= 2u * (uint32_t)bp.nlevels;
-    const uint32_t li = dense ? blockIdx.x - 2u * (uint32_t)bp.nlevels : blockIdx.x >> 1, role = blockIdx.x & 1u;
+    // workgroups 0 .. 2 nlevels - 1: (hashed level, table); then one per pre-reduced level, or two per merged one
+    const bool     first = blockIdx.x >= 2u * (uint32_t)bp.nlevels, dense = first && !bp.merged;
+    const uint32_t block = first ? blockIdx.x - 2u * (uint32_t)bp.nlevels : blockIdx.x;
+    const uint32_t li = dense ? block : block >> 1, role = block & 1u;
     const uint32_t slices = dense ? kGridBins : role ? bp.slices_c : bp.slices_f;
     if (slices == 0) return;
-    uint32_t *gcnt = (dense ? cntG : role ? cntC : cntF) + (size_t)li * bp.chunks * slices;
-    uint32_t *base = (dense ? baseG : role ? baseC : baseF) + (size_t)li * (slices + 1);
-    const uint32_t elems = bp.chunks * slices;
+    const uint32_t chunks = first && !dense ? mb.chunks : bp.chunks;
+    uint32_t *gcnt = (dense ? cntG : role ? (first ? mb.cntC : cntC) : (first ? mb.cntF : cntF)) + (size_t)li * chunks * slices;
+    uint32_t *base = (dense ? baseG : role ? (first ? mb.baseC : baseC) : (first ? mb.baseF : baseF)) + (size_t)li * (slices + 1);
+    const uint32_t elems = chunks * slices;
     const bool     in_lds = elems <= lds_words;
     uint32_t      *cnt = in_lds ? mat : gcnt;
     // (the copies in and out move 16 bytes per lane and step: word by word they were a chain of memory latencies that
@@ -220,8 +245,8 @@ __global__ __launch_bounds__(kOffsetsBlock) void bin_offsets_kernel(
     const uint32_t width = slices < (uint32_t)kOffsetsBlock ? slices : (uint32_t)kOffsetsBlock;   // slices per round
     const uint32_t segs = kOffsetsBlock / width;                                                // width is a power of two
     const uint32_t lane_s = threadIdx.x % width, seg = threadIdx.x / width;
-    const uint32_t per = (bp.chunks + segs - 1) / segs;
-    const uint32_t c0 = seg * per, c1 = (c0 + per < bp.chunks) ? c0 + per : bp.chunks;
+    const uint32_t per = (chunks + segs - 1) / segs;
+    const uint32_t c0 = seg * per, c1 = (c0 + per < chunks) ? c0 + per : chunks;
     for (uint32_t s_round = 0; s_round < slices; s_round += width) {
         const uint32_t s = s_round + lane_s;                // < slices: both are powers of two
         uint32_t sum = 0;
@@ -265,15 +290,45 @@ __global__ __launch_bounds__(kOffsetsBlock) void bin_offsets_kernel(
     }
 }
 
-// Scatter, one workgroup per (level, chunk).
+// Scatter, one workgroup per (level, chunk): first the merged levels, the one with the most entries first.
 template <int D>
 __global__ __launch_bounds__(256) void bin_scatter_kernel(
     const Params p, const BinParams bp, const DenseLevels dl, const float *__restrict__ x, const int64_t N,
     const uint32_t *__restrict__ cntF, const uint32_t *__restrict__ cntC, const uint32_t *__restrict__ cntG,
-    BinRecord *__restrict__ recF, BinRecord *__restrict__ recC, BinRecord *__restrict__ recG)
+    BinRecord *__restrict__ recF, BinRecord *__restrict__ recC, BinRecord *__restrict__ recG, const MergedBins mb)
 {
     extern __shared__ uint32_t cursor[];                    // [max(slices_f + slices_c, kGridBins)]
-    const uint32_t li = blockIdx.x / bp.chunks, chunk = blockIdx.x % bp.chunks;
+    if (blockIdx.x < mb.levels * mb.chunks) {               // a merged level: the chunk's entries by their rows
+        const uint32_t lm = mb.levels - 1u - blockIdx.x / mb.chunks, chunk = blockIdx.x % mb.chunks;
+        const size_t   row = (size_t)lm * mb.chunks + chunk;
+        for (uint32_t s = threadIdx.x; s < bp.slices_f; s += blockDim.x) cursor[s] = mb.cntF[row * bp.slices_f + s];
+        for (uint32_t s = threadIdx.x; s < bp.slices_c; s += blockDim.x) cursor[bp.slices_f + s] = mb.cntC[row * bp.slices_c + s];
+        __syncthreads();
+        const uint32_t made = mb.made[row], rows_f = (1u << bp.rows_f_log2) - 1u, rows_c = (1u << bp.rows_c_log2) - 1u;
+        const uint4   *in = mb.entries + (size_t)lm * bp.cap + ((size_t)(chunk * mb.chunk_pts) << D);
+        EntryRecord *toF = mb.recF + (size_t)lm * bp.cap, *toC = mb.recC + (size_t)lm * bp.cap;
+        constexpr uint32_t kAhead = 8;                      // loads in flight per lane
+        for (uint32_t i0 = threadIdx.x; i0 < made; i0 += kAhead * blockDim.x) {
+            uint4 e[kAhead];
+#pragma unroll
+            for (uint32_t t = 0; t < kAhead; ++t) {
+                const uint32_t i = i0 + t * blockDim.x;
+                e[t] = in[i < made ? i : made - 1u];
+            }
+#pragma unroll
+            for (uint32_t t = 0; t < kAhead; ++t) {
+                const uint32_t i = i0 + t * blockDim.x;
+                if (i >= made) break;
+                const float gx = __uint_as_float(e[t].z), gy = __uint_as_float(e[t].w);
+                if (bp.slices_f)
+                    toF[atomicAdd(&cursor[e[t].x >> bp.rows_f_log2], 1u)] = {(e[t].x & rows_f) | (e[t].y << bp.rows_f_log2), gx, gy};
+                if (bp.slices_c)
+                    toC[atomicAdd(&cursor[bp.slices_f + (e[t].y >> bp.rows_c_log2)], 1u)] = {(e[t].y & rows_c) | (e[t].x << bp.rows_c_log2), gx, gy};
+            }
+        }
+        return;
+    }
+    const uint32_t block = blockIdx.x - mb.levels * mb.chunks, li = block / bp.chunks, chunk = block % bp.chunks;
     if (li >= (uint32_t)bp.nlevels) {                       // a pre-reduced level, binned by slice of its vertex grid
         const uint32_t ld = li - (uint32_t)bp.nlevels;
         const uint32_t *rowG = cntG + ((size_t)ld * bp.chunks + chunk) * kGridBins;
@@ -395,8 +450,9 @@ __device__ __forceinline__ void accum_steps(const uint4 &r, const T (&g)[NP], Ac
 // slice (the softmax row of the record's own confidence row), the accumulator row is the other table's.
 // ACC: doubles per candidate of an accumulator row (2 where both features of a row sit side by side).
 // BY_FEAT: the bin belongs to a slice of the feature table (rows by hash), else of the confidence table (hash2).
-template <int D, int NP, typename T, bool BOTH, int ACC, bool BY_FEAT, typename IoT, typename Load, typename Accum>
-__device__ __forceinline__ void drain_records(const Params &p, const BinRecord *__restrict__ rec, const uint32_t beg, const uint32_t end,
+// MERGED: the records are entries, which hold their rows and g.
+template <int D, int NP, typename T, bool BOTH, int ACC, bool BY_FEAT, bool MERGED, typename Record, typename IoT, typename Load, typename Accum>
+__device__ __forceinline__ void drain_records(const Params &p, const Record *__restrict__ rec, const uint32_t beg, const uint32_t end,
                                               const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
                                               const uint32_t rows_log2, Load load, Accum accum)
 {
@@ -414,46 +470,58 @@ __device__ __forceinline__ void drain_records(const Params &p, const BinRecord *
     //   D  accumulate
     // Each stage consumes what the stage before it loaded one step earlier; within a step the loads are
     // issued A, B, C, so that a wait for an older stage's data leaves the younger loads in flight.
-    BinRecord Q[4];
-    float X[4][D];
-    Pair  Y[4];
+    Record Q[4];
+    struct Point { float xp[D]; Pair y; };
+    Point S[4];                                              // what the record names
     uint4 R[4];                                              // gather offset, weight * dL/dy (two floats), LDS offset
     T     G[4][NP];
-    auto stage_a = [&](const uint32_t base, BinRecord &q) {
+    auto stage_a = [&](const uint32_t base, Record &q) {
         const uint32_t i = base + lane;
         // streamed once: a non-temporal load keeps it out of the way of the rows that are gathered again and again
-        q = __builtin_nontemporal_load(rec + (i < last ? i : last));
+        if constexpr (MERGED) q = rec[i < last ? i : last];
+        else q = __builtin_nontemporal_load(rec + (i < last ? i : last));
     };
-    auto stage_b = [&](const BinRecord &q, float (&xp)[D], Pair &y) {
-        const uint32_t n = q >> D;
+    auto stage_b = [&](const Record &q, Point &src) {
+        if constexpr (!MERGED) {
+            const uint32_t n = q >> D;
 #pragma unroll
-        for (int j = 0; j < D; ++j) xp[j] = x[(size_t)n * D + j];
-        y = reinterpret_cast<const Pair *>(dy_l)[n];
+            for (int j = 0; j < D; ++j) src.xp[j] = x[(size_t)n * D + j];
+            src.y = reinterpret_cast<const Pair *>(dy_l)[n];
+        }
     };
-    auto stage_c = [&](const uint32_t base, const BinRecord &q, const float (&xp)[D], const Pair &y, uint4 &r, T (&g)[NP]) {
-        const uint32_t c = q & ((1u << D) - 1u);
+    auto stage_c = [&](const uint32_t base, const Record &q, const Point &src, uint4 &r, T (&g)[NP]) {
         float    wt = (base + lane < end) ? 1.0f : 0.0f;     // beyond the bin: contributes nothing
-        uint32_t h1 = 0, h2 = 0;                             // Eq. 3 for this corner, as in Cell<D>
-        {
+        uint32_t inside, other;                              // rows: of this slice's table, of the other one
+        float2   gy;
+        if constexpr (MERGED) {
+            inside = q.key & row_lo_mask;
+            other = q.key >> rows_log2;
+            gy = make_float2(q.gx, q.gy);
+        } else {                                             // Eq. 3 for this corner, as in Cell<D>
+            const uint32_t c = q & ((1u << D) - 1u);
+            uint32_t h1 = 0, h2 = 0;
+            {
 #pragma clang fp contract(off)
 #pragma unroll
-            for (int j = 0; j < D; ++j) {
-                const float    pos = xp[j] * res;            // one rounded fp32 multiply
-                const float    fl = floorf(pos);
-                const float    w = pos - fl;
-                const uint32_t up = (c >> j) & 1u;
-                wt *= up ? w : 1.0f - w;
-                const uint32_t v = (uint32_t)fl + up;
-                h1 ^= v * kPi[j];
-                h2 ^= v * kPi2[j];
+                for (int j = 0; j < D; ++j) {
+                    const float    pos = src.xp[j] * res;        // one rounded fp32 multiply
+                    const float    fl = floorf(pos);
+                    const float    w = pos - fl;
+                    const uint32_t up = (c >> j) & 1u;
+                    wt *= up ? w : 1.0f - w;
+                    const uint32_t v = (uint32_t)fl + up;
+                    h1 ^= v * kPi[j];
+                    h2 ^= v * kPi2[j];
+                }
             }
+            h1 &= p.row_mask;
+            h2 &= p.c_mask;
+            gy = pair_to_float2(src.y);
+            inside = (BY_FEAT ? h1 : h2) & row_lo_mask;
+            other = BY_FEAT ? h2 : h1;
         }
-        h1 &= p.row_mask;
-        h2 &= p.c_mask;
-        const float2 gy = pair_to_float2(y);
         // once per record: byte offset of the row the gather reads (candidate 0), and byte offset of the
         // accumulator row in LDS; the lanes of the group add their candidate's share
-        const uint32_t inside = (BY_FEAT ? h1 : h2) & row_lo_mask, other = BY_FEAT ? h2 : h1;
         r = make_uint4((BOTH ? inside : other) * (uint32_t)(NP * sizeof(T)), __float_as_uint(wt * gy.x),
                        __float_as_uint(wt * gy.y), (BOTH ? other : inside) * (uint32_t)(ACC * NP * sizeof(double)));
         gather_steps<NP, 0>(r, g, load);
@@ -462,13 +530,13 @@ __device__ __forceinline__ void drain_records(const Params &p, const BinRecord *
     stage_a(b, Q[0]);
     stage_a(b + stride, Q[1]);
     stage_a(b + 2 * stride, Q[2]);
-    stage_b(Q[0], X[0], Y[0]);
-    stage_b(Q[1], X[1], Y[1]);
-    stage_c(b, Q[0], X[0], Y[0], R[0], G[0]);
+    stage_b(Q[0], S[0]);
+    stage_b(Q[1], S[1]);
+    stage_c(b, Q[0], S[0], R[0], G[0]);
 #define CNGP_DRAIN_STEP(P0, P1, P2, P3)                                                  \
         stage_a(b + 3 * stride, Q[P3]);                                                  \
-        stage_b(Q[P2], X[P2], Y[P2]);                                                    \
-        stage_c(b + stride, Q[P1], X[P1], Y[P1], R[P1], G[P1]);                          \
+        stage_b(Q[P2], S[P2]);                                                           \
+        stage_c(b + stride, Q[P1], S[P1], R[P1], G[P1]);                                 \
         accum_steps<NP, 0, BOTH>(R[P0], G[P0], accum);                                         \
         b += stride;                                                                     \
         if (b >= end) break;
@@ -577,10 +645,10 @@ __global__ __launch_bounds__(kSlicedBlock) void bin_grid_drain_kernel(
 }
 
 // sp: rows_log2, slices, chunks (= drain workgroups per bin), store_direct, level0, nlevels as in the sliced variant.
-template <int D, int NP, typename IoT>
+template <int D, int NP, bool MERGED, typename IoT, typename Record>
 __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
                                            const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
-                                           const float *__restrict__ sigma, const BinRecord *__restrict__ recF,
+                                           const float *__restrict__ sigma, const Record *__restrict__ recF,
                                            const uint32_t *__restrict__ baseF, const uint32_t cap, float *__restrict__ gD_f)
 {
     const uint32_t rows = 1u << sp.rows_log2, plane = rows * NP;
@@ -604,7 +672,7 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
     };
     uint32_t beg, end;
     bin_range(baseF, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, float, false, 2, true>(p, recF + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+    drain_records<D, NP, float, false, 2, true, MERGED>(p, recF + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                                           (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
     float *out = gD_f + (size_t)co.level * p.N_f * 2 + (size_t)co.slice * plane * 2;
@@ -616,11 +684,11 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
     }
 }
 
-template <int D, int NP, typename FeatT, typename IoT>
+template <int D, int NP, bool MERGED, typename FeatT, typename IoT, typename Record>
 __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
                                             const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
                                             const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
-                                            const BinRecord *__restrict__ recC, const uint32_t *__restrict__ baseC,
+                                            const Record *__restrict__ recC, const uint32_t *__restrict__ baseC,
                                             const uint32_t cap, float *__restrict__ gDhat_c)
 {
     const uint32_t rows = 1u << sp.rows_log2;
@@ -642,7 +710,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
     };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, Raw, false, 1, false>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+    drain_records<D, NP, Raw, false, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                               (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
@@ -666,11 +734,11 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
 // level's feature codebook, so the only gather left per record is its softmax row -- from the 64 KB or so of
 // rows of this slice instead of the whole table.  The feature gradient goes out with atomics (every
 // workgroup of the level holds a share of it): the caller has cleared it.
-template <int D, int NP, typename FeatT, typename IoT>
+template <int D, int NP, bool MERGED, typename FeatT, typename IoT, typename Record>
 __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
                                            const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
                                            const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
-                                           const BinRecord *__restrict__ recC, const uint32_t *__restrict__ baseC,
+                                           const Record *__restrict__ recC, const uint32_t *__restrict__ baseC,
                                            const uint32_t cap, float *__restrict__ gD_f, float *__restrict__ gDhat_c)
 {
     using Raw = typename RawPair<FeatT>::type;
@@ -701,7 +769,7 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, float, true, 1, false>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+    drain_records<D, NP, float, true, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                                       (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
     float *outF = gD_f + (size_t)co.level * p.N_f * 2;
@@ -724,8 +792,9 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
 }
 
 // Workgroups [0, first_feat) drain the confidence-table bins, [first_feat, first_vtx) the feature-table
-// bins; the rest are the two roles of the pre-reduced coarse levels (cngp_bwd_sliced.h: they scan the
-// vertex grids that the launch before this one has completed), sharing the launch so that the CUs stay busy.
+// bins; the rest are the two roles of the first levels: of the merged ones the same drains of their entries, of the
+// pre-reduced ones those of cngp_bwd_sliced.h (they scan the vertex grids that the launch before this one has
+// completed), sharing the launch so that the CUs stay busy.
 template <int D, int NP, typename FeatT, typename IoT>
 __global__ __launch_bounds__(kSlicedBlock) void bin_drain_kernel(
     const Params p, const SliceParams sp_c, const SliceParams sp_f, const uint32_t first_feat, const uint32_t first_vtx,
@@ -733,26 +802,34 @@ __global__ __launch_bounds__(kSlicedBlock) void bin_drain_kernel(
     const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
     const BinRecord *__restrict__ recF, const BinRecord *__restrict__ recC,
     const uint32_t *__restrict__ baseF, const uint32_t *__restrict__ baseC, const uint32_t cap,
-    const BwdRoles vtx, const DenseLevels dl, const float *__restrict__ G,
+    const BwdRoles vtx, const DenseLevels dl, const float *__restrict__ G, const int merged, const MergedBins mb,
     float *__restrict__ gD_f, float *__restrict__ gDhat_c)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     if (blockIdx.x < first_feat) {
         if constexpr (NP > 1) {
-            if (sp_f.nlevels == 0) drain_both<D, NP, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gD_f, gDhat_c);
-            else drain_logit<D, NP, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gDhat_c);
+            if (sp_f.nlevels == 0) drain_both<D, NP, false, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gD_f, gDhat_c);
+            else drain_logit<D, NP, false, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gDhat_c);
         }
     } else if (blockIdx.x < first_vtx) {
-        drain_feat<D, NP, IoT>(p, sp_f, blockIdx.x - first_feat, smem, x, dyT, N, sigma, recF, baseF, cap, gD_f);
+        drain_feat<D, NP, false, IoT>(p, sp_f, blockIdx.x - first_feat, smem, x, dyT, N, sigma, recF, baseF, cap, gD_f);
     } else {
         const uint32_t wg = blockIdx.x - first_vtx;
-        if (wg < vtx.first[ROLE_FEAT_VTX]) {
+        const SliceParams &vc = vtx.sp[ROLE_LOGIT_VTX], &vf = vtx.sp[ROLE_FEAT_VTX];
+        if (merged) {
+            if (wg < vtx.first[ROLE_FEAT_VTX]) {
+                if constexpr (NP > 1) {
+                    if (vf.nlevels == 0) drain_both<D, NP, true, FeatT, IoT>(p, vc, wg, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gD_f, gDhat_c);
+                    else drain_logit<D, NP, true, FeatT, IoT>(p, vc, wg, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gDhat_c);
+                }
+            } else {
+                drain_feat<D, NP, true, IoT>(p, vf, wg - vtx.first[ROLE_FEAT_VTX], smem, x, dyT, N, sigma, mb.recF, mb.baseF, cap, gD_f);
+            }
+        } else if (wg < vtx.first[ROLE_FEAT_VTX]) {
             if (NP > 1)
-                bwd_logit_sliced<D, NP, true, FeatT, float>(p, vtx.sp[ROLE_LOGIT_VTX], dl, wg - vtx.first[ROLE_LOGIT_VTX], smem,
-                                                            x, D_f, sigma, G, gDhat_c, N);
+                bwd_logit_sliced<D, NP, true, FeatT, float>(p, vc, dl, wg - vtx.first[ROLE_LOGIT_VTX], smem, x, D_f, sigma, G, gDhat_c, N);
         } else {
-            bwd_feat_sliced<D, NP, true, float>(p, vtx.sp[ROLE_FEAT_VTX], dl, wg - vtx.first[ROLE_FEAT_VTX], smem, x, sigma,
-                                                G, gD_f, N);
+            bwd_feat_sliced<D, NP, true, float>(p, vf, dl, wg - vtx.first[ROLE_FEAT_VTX], smem, x, sigma, G, gD_f, N);
         }
     }
 }

@@ -44,6 +44,7 @@ struct SliceParams {
     int32_t  store_direct;  // 1: every slice is written by exactly one workgroup -> plain stores
     int32_t  level0;        // levels [level0, level0 + nlevels) are covered by this launch
     int32_t  nlevels;
+    int32_t  spread;        // 1: levels of unequal work (merged ones): every level over all XCDs, the last level first
 };
 
 // Levels whose dense vertex grid is small enough to pre-reduce the upstream gradient per vertex.
@@ -73,10 +74,11 @@ __device__ __forceinline__ SliceCoord slice_coord(const SliceParams &sp, const u
     const uint32_t per_level = sp.slices * sp.chunks;
     const uint32_t total = per_level * (uint32_t)sp.nlevels;
     const uint32_t per_xcd = (total + kXcds - 1) / kXcds;
-    const uint32_t unit = xcd * per_xcd + j;
+    uint32_t unit = xcd * per_xcd + j;
+    if (sp.spread) unit = i < total ? total - 1u - i : total;
     SliceCoord c;
     const uint32_t rem = unit % per_level;
-    c.index = (j < per_xcd && unit < total) ? (int)(unit / per_level) : -1;
+    c.index = ((sp.spread || j < per_xcd) && unit < total) ? (int)(unit / per_level) : -1;
     c.level = sp.level0 + c.index;
     // chunk-major inside a level: the workgroups that run side by side on an XCD take the SAME run of points through
     // neighbouring slices, so the points and their gradients are read from memory once per level, not once per slice
@@ -120,14 +122,14 @@ __device__ __forceinline__ void softmax_rows(const float *__restrict__ Dhat_c, f
     sigma[i] = e / group_sum<NP>(e);
 }
 
-// dyT[l][n] = dy[n][l] for the F = 2 pair of each level (PairT: 4 bytes for fp16, 8 for fp32).
+// dyT[l][n] = dy[n][l] for the F = 2 pair of each level from level0 on (PairT: 4 bytes for fp16, 8 for fp32).
 template <typename PairT>
 __device__ __forceinline__ void transpose_rows(const PairT *__restrict__ dy, PairT *__restrict__ dyT,
-                                               const int64_t N, const int L, const uint32_t block)
+                                               const int64_t N, const int L, const int level0, const uint32_t block)
 {
     const int64_t n = (int64_t)block * kBlock + threadIdx.x;
     if (n >= N) return;
-    for (int l = 0; l < L; ++l) dyT[(size_t)l * N + n] = dy[(size_t)n * L + l];
+    for (int l = level0; l < L; ++l) dyT[(size_t)l * N + n] = dy[(size_t)n * L + l];
 }
 
 // Everything the accumulation kernels need first, in one launch: the gradient (and vertex-grid) ranges
@@ -143,7 +145,7 @@ struct PrepArgs {
     const void  *dy;
     void        *dyT;
     int64_t      N;
-    int32_t      L;
+    int32_t      L, level0;
     uint32_t     top_k;
 };
 
@@ -159,7 +161,7 @@ __device__ __forceinline__ void bwd_prep_block(const PrepArgs &a, uint32_t b)
         softmax_rows<NP>(a.Dhat_c, a.sigma, a.elems, b, a.top_k);
         return;
     }
-    transpose_rows<PairT>(reinterpret_cast<const PairT *>(a.dy), reinterpret_cast<PairT *>(a.dyT), a.N, a.L, b - a.softmax_blocks);
+    transpose_rows<PairT>(reinterpret_cast<const PairT *>(a.dy), reinterpret_cast<PairT *>(a.dyT), a.N, a.L, a.level0, b - a.softmax_blocks);
 }
 
 template <int NP, typename PairT>
