@@ -581,11 +581,13 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // a level's grid, in hundredths, from which the level is merged (points are never spread more evenly than over the whole grid).
 // Sum of the kernels of a step, us, lines at 20 / 80 / 150 / 300 / 1500: nerf3d 728 / 611 / 594 / 587 / 601 (649 with grid sums),
 // sdf3d, whose points are anything but evenly spread, 2750 / 2704 / 2786 / 2815 / 2977 (3184), compact3d 504 / 465 / 448 / 453 / 478 (469).
+// Backward without / with merging, mean (slowest) of 40 drawn batches of 2^18 .. 2^20 points, lines at 60 / 90 / 150 / 250: 1.25 (0.91), 1.25 (0.91), 1.26
+// (0.94), 1.27 (0.97).
 // Backward without / with merging over 110 drawn configurations from that batch size on: d = 3 1.19x faster on average (slowest 0.95x),
 // d = 2 1.28x; d = 4, where two or three levels have that many references per vertex, 0.99x (0.78 .. 1.21), and small feature
 // tables with d = 2 and N_p = 2, whose references cost the least, 0.90x: neither is merged.
 constexpr int64_t  kMinMergeRefs = 3 << 19;
-constexpr uint64_t kMinMergePerVertexPct = 150;
+constexpr uint64_t kMinMergePerVertexPct = 240;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -834,7 +836,14 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
                c->d <= 3 && !(b.fused && c->d == 2 && c->N_p == 2) && (N << c->d) >= kMinMergeRefs && (b.fused ? 0 : b.slices_f) + b.slices_c <= kMergeMaxBins;
     if (b.merged) {
         b.dense.count = merge_levels(c, N);
-        b.merged = b.dense.count > 0;
+        const uint32_t per_level_now = b.slices_f + b.slices_c;
+        // (a small feature table's gradient is added up by every drain workgroup of its level, in fp32: merging must not make
+        // them more for the levels that are left, and with as few as before their last round is mostly empty -- N_f = 2^8,
+        // N_c = 2^16, N_p = 8, 250007 points: 456 us, merged with two workgroups per bin 436 and an error of 1.5e-7 instead of
+        // 1.3e-7, with one 468)
+        b.merged = b.dense.count > 0 && !(b.fused && drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L - b.dense.count, per_level_now) !=
+                                                         drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L, per_level_now));
+        if (!b.merged) b.dense.count = 0;
     }
     // coarse levels whose dense vertex grid is small, much smaller than the number of references, and
     // takes clearly fewer slice scans than the level's hashed tables.  With binning a hashed level costs
@@ -877,8 +886,8 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.bin_chunk_pts = (uint32_t)cp;
         b.bin_chunks = (uint32_t)((N + cp - 1) / cp);
         const double refs = (double)((uint64_t)N << c->d);
-        b.subs_f = drain_subs(refs, b.slices_f, Lh, b.slices_f + b.slices_c);
-        b.subs_c = drain_subs(refs, b.slices_c, Lh, b.slices_f + b.slices_c);
+        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c);
+        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c);
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
@@ -1093,7 +1102,6 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     std::memset(&vtx, 0, sizeof(vtx));
     vtx.sp[ROLE_LOGIT_VTX] = role(b.rows_c_log2, slices_c, b.logit_vtx, 0, Ld, wgs_cv);
     vtx.sp[ROLE_FEAT_VTX] = role(b.rows_f_log2, b.merged && b.fused ? 0u : b.slices_f, b.feat_vtx, 0, Ld, wgs_fv);
-    vtx.sp[ROLE_LOGIT_VTX].spread = vtx.sp[ROLE_FEAT_VTX].spread = b.merged ? 1 : 0;
     vtx.first[ROLE_LOGIT_VTX] = 0;
     vtx.first[ROLE_FEAT_VTX] = wgs_cv;
     auto kernel = bin_drain_kernel<D, NP, FeatT, IoT>;

@@ -644,6 +644,19 @@ __global__ __launch_bounds__(kSlicedBlock) void bin_grid_drain_kernel(
     }
 }
 
+// Merged levels are of unequal work: every level over all XCDs, the last one, which has the most entries, first (a level to an
+// XCD, as the others: 470 us for nerf3d's drain where this took 415).
+__device__ __forceinline__ SliceCoord merged_coord(const SliceParams &sp, const uint32_t i) {
+    const uint32_t per_level = sp.slices * sp.chunks, total = per_level * (uint32_t)sp.nlevels;
+    const uint32_t unit = total - 1u - i, rem = unit % per_level;
+    SliceCoord c;
+    c.index = i < total ? (int)(unit / per_level) : -1;
+    c.level = sp.level0 + c.index;
+    c.chunk = rem / sp.slices;
+    c.slice = rem % sp.slices;
+    return c;
+}
+
 // sp: rows_log2, slices, chunks (= drain workgroups per bin), store_direct, level0, nlevels as in the sliced variant.
 template <int D, int NP, bool MERGED, typename IoT, typename Record>
 __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
@@ -653,7 +666,7 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
 {
     const uint32_t rows = 1u << sp.rows_log2, plane = rows * NP;
     double *acc = reinterpret_cast<double *>(smem);
-    const SliceCoord co = slice_coord(sp, wg);
+    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) acc[i] = 0.0;
     __syncthreads();
@@ -693,7 +706,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
 {
     const uint32_t rows = 1u << sp.rows_log2;
     double *acc = reinterpret_cast<double *>(smem);
-    const SliceCoord co = slice_coord(sp, wg);
+    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
     for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) acc[i] = 0.0;
     __syncthreads();
@@ -746,7 +759,7 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     double *accQ = reinterpret_cast<double *>(smem);                    // [rows][NP]
     double *accF = accQ + (size_t)rows * NP;                            // [2][N_f]: feature 0 of every entry, then feature 1
     Raw    *feat = reinterpret_cast<Raw *>(accF + 2 * (size_t)plane);   // [N_f]
-    const SliceCoord co = slice_coord(sp, wg);
+    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
     const Raw *F_l = reinterpret_cast<const Raw *>(D_f + (size_t)co.level * p.N_f * 2);
     for (uint32_t i = threadIdx.x; i < rows * NP + 2 * plane; i += kSlicedBlock) accQ[i] = 0.0;

@@ -44,7 +44,6 @@ struct SliceParams {
     int32_t  store_direct;  // 1: every slice is written by exactly one workgroup -> plain stores
     int32_t  level0;        // levels [level0, level0 + nlevels) are covered by this launch
     int32_t  nlevels;
-    int32_t  spread;        // 1: levels of unequal work (merged ones): every level over all XCDs, the last level first
 };
 
 // Levels whose dense vertex grid is small enough to pre-reduce the upstream gradient per vertex.
@@ -74,11 +73,10 @@ __device__ __forceinline__ SliceCoord slice_coord(const SliceParams &sp, const u
     const uint32_t per_level = sp.slices * sp.chunks;
     const uint32_t total = per_level * (uint32_t)sp.nlevels;
     const uint32_t per_xcd = (total + kXcds - 1) / kXcds;
-    uint32_t unit = xcd * per_xcd + j;
-    if (sp.spread) unit = i < total ? total - 1u - i : total;
+    const uint32_t unit = xcd * per_xcd + j;
     SliceCoord c;
     const uint32_t rem = unit % per_level;
-    c.index = ((sp.spread || j < per_xcd) && unit < total) ? (int)(unit / per_level) : -1;
+    c.index = (j < per_xcd && unit < total) ? (int)(unit / per_level) : -1;
     c.level = sp.level0 + c.index;
     // chunk-major inside a level: the workgroups that run side by side on an XCD take the SAME run of points through
     // neighbouring slices, so the points and their gradients are read from memory once per level, not once per slice

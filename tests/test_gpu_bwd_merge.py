@@ -52,18 +52,18 @@ def check(w, args, **kw):
     (3, 250007, 3, 2**13, 2**10, 8, 60, "f16", "f32"),         # a ragged last round and chunk
     (2, 500009, 4, 2**13, 2**11, 2, 900, "f32", "f16"),
     (2, 2**19 + 1, 3, 2**13, 1, 1, 300, "f32", "f32"),         # plain hashing: no confidence bins
-    (3, 2**18, 5, 2**12, 2**10, 4, 40, "f32", "f32"),          # every level but the last
-    (3, 200003, 4, 2**8, 2**14, 8, 90, "f16", "f16"),          # small feature table: both gradients in one pass
+    (3, 2**18, 5, 2**13, 2**10, 4, 40, "f32", "f32"),          # every level but the last
+    (3, 200003, 16, 2**8, 2**16, 8, 2048, "f16", "f16"),          # small feature table: both gradients in one pass
 ])
 def test_merged_levels_against_the_oracle(d, N, L, N_f, N_c, N_p, N_max, feat, io):
-    w = W.custom(cfg=110, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=8, N_max=N_max, N=N, feat_dtype=feat, io_dtype=io)
+    w = W.custom(cfg=110, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=8 if L < 16 else 40, N_max=N_max, N=N, feat_dtype=feat, io_dtype=io)
     check(w, inputs(w))
 
 
 def test_more_vertices_than_slots():
     """85 % of the points in one cell, the others spread: where they are, almost every reference is a vertex of its own
     (1024 points, 3700 vertices, 3520 slots), on a level that is merged because of the average."""
-    w = W.custom(cfg=111, d=2, L=3, N_f=2**12, N_c=2**10, N_p=4, N_min=600, N_max=1000, N=450001, feat_dtype="f16", io_dtype="f16")
+    w = W.custom(cfg=111, d=2, L=3, N_f=2**13, N_c=2**10, N_p=4, N_min=600, N_max=1000, N=450001, feat_dtype="f16", io_dtype="f16")
     rng = np.random.default_rng(5)
     x = rng.random((w.N, 2), dtype=np.float32)
     x[rng.random(w.N) < 0.85] = (0.3, 0.7)
@@ -73,7 +73,7 @@ def test_more_vertices_than_slots():
 
 
 def test_points_outside_the_cube_agree_with_the_direct_variant():
-    w = W.custom(cfg=112, d=3, L=2, N_f=2**12, N_c=2**10, N_p=4, N_min=8, N_max=100, N=200001, feat_dtype="f32", io_dtype="f32")
+    w = W.custom(cfg=112, d=3, L=2, N_f=2**13, N_c=2**10, N_p=4, N_min=8, N_max=100, N=200001, feat_dtype="f32", io_dtype="f32")
     rng = np.random.default_rng(6)
     x = rng.random((w.N, 3), dtype=np.float32)
     far = rng.random(w.N) < 0.1
@@ -104,7 +104,7 @@ def test_a_smaller_workspace_and_no_pre_reduction_are_not_merged():
 
 
 def test_capture_replays_the_merge():
-    w = W.custom(cfg=114, d=3, L=3, N_f=2**12, N_c=2**10, N_p=8, N_min=16, N_max=90, N=200003, feat_dtype="f16", io_dtype="f16")
+    w = W.custom(cfg=114, d=3, L=3, N_f=2**13, N_c=2**10, N_p=8, N_min=16, N_max=90, N=200003, feat_dtype="f16", io_dtype="f16")
     args = inputs(w)
     gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args)
     cfg = cngp.Config.from_workload(w, flags=FLAGS)
