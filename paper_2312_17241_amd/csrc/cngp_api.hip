@@ -843,6 +843,9 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         // 1.3e-7, with one 468)
         b.merged = b.dense.count > 0 && !(b.fused && drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L - b.dense.count, per_level_now) !=
                                                          drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L, per_level_now));
+        // (plain hashing has one table and the cheapest references: three merged levels do not pay for the order of the points;
+        // d = 3, L = 8, N_max = 8192, 499487 points: 246 us, merged 266; L = 16 and more of them 288 / 265)
+        if (c->N_p == 1 && b.dense.count < 4) b.merged = false;
         if (!b.merged) b.dense.count = 0;
     }
     // coarse levels whose dense vertex grid is small, much smaller than the number of references, and

@@ -51,7 +51,7 @@ def check(w, args, **kw):
     (3, 196608, 4, 2**13, 2**11, 16, 80, "f16", "f16"),        # the smallest batch that is merged
     (3, 250007, 3, 2**13, 2**10, 8, 60, "f16", "f32"),         # a ragged last round and chunk
     (2, 500009, 4, 2**13, 2**11, 2, 900, "f32", "f16"),
-    (2, 2**19 + 1, 3, 2**13, 1, 1, 300, "f32", "f32"),         # plain hashing: no confidence bins
+    (2, 2**19 + 1, 6, 2**13, 1, 1, 300, "f32", "f32"),         # plain hashing: no confidence bins
     (3, 2**18, 5, 2**13, 2**10, 4, 40, "f32", "f32"),          # every level but the last
     (3, 200003, 16, 2**8, 2**16, 8, 2048, "f16", "f16"),          # small feature table: both gradients in one pass
 ])
