@@ -229,21 +229,18 @@ __global__ __launch_bounds__(kMergeBlock, 8) void bwd_merge_kernel(
                         vb[j] = v0 + 1u - up;
                         fits = fits && v0 < kLimit - 1u;            // the upper vertex too, and never the empty key
                     }
-                    if (!live) wa[0] = wb[0] = 0.0f;
                 }
                 const float2 g = pair_to_float2(cur.y);
                 uint32_t slot[kCorners], key[kCorners], found[kCorners];
                 float    wt[kCorners];
 #pragma unroll
                 for (uint32_t k = 0; k < kCorners; ++k) {
-                    float    t = 1.0f;
                     uint32_t q = 0;
 #pragma unroll
-                    for (int j = 0; j < D; ++j) {
-                        t *= (k >> j) & 1u ? wb[j] : wa[j];
-                        q |= ((k >> j) & 1u ? vb[j] : va[j]) << (kBits * j);
-                    }
-                    wt[k] = t;                                      // a corner of weight zero adds nothing and is left out
+                    for (int j = 0; j < D; ++j) q |= ((k >> j) & 1u ? vb[j] : va[j]) << (kBits * j);
+                    // a corner of weight zero adds nothing and is left out; all of a lane's beyond the chunk are, whatever the point
+                    // it repeats, so that a chunk makes at most 2^d entries per point of its own (the room it has)
+                    wt[k] = corner_weight_if<D>(live, wa, wb, k);
                     key[k] = q;
                     slot[k] = __umulhi(q * 2654435769u, kMergeSlots);
                 }

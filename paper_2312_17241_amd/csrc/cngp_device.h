@@ -75,6 +75,17 @@ struct Cell {
     }
 };
 
+// Weight of a corner from its factors along every dimension (wb where bit j of k is set, else wa); exactly 0 for a lane without a
+// point of its own.  It is the product that is replaced, not a factor: a lane beyond its batch repeats another lane's point, and
+// a coordinate that is infinite or NaN has a NaN fraction, of which 0 * NaN would be left.
+template <int D>
+__host__ __device__ __forceinline__ float corner_weight_if(const bool live, const float (&wa)[D], const float (&wb)[D], const uint32_t k) {
+    float t = 1.0f;
+#pragma unroll
+    for (int j = 0; j < D; ++j) t *= (k >> j) & 1u ? wb[j] : wa[j];
+    return live ? t : 0.0f;
+}
+
 // Eq. 6: (N_p * hash(v)) mod N_f, i.e. the low log2(N_f / N_p) bits of the hash moved above
 // the log2(N_p) learned bits.
 __device__ __forceinline__ uint32_t probe_base(uint32_t h1, const Params &p) {

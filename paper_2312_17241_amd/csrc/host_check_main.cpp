@@ -1,10 +1,12 @@
 // Exerciser of the library's HOST code under AddressSanitizer and UndefinedBehaviorSanitizer: argument
 // validation, level table, storage sizes, the backward plan (slices, chunks, bins, passes) and its workspace
-// layout, for seeded random configurations.  It is linked with cngp_api.hip and cngp_sort.hip compiled with the
+// layout, for seeded random configurations, and the rule that decides which corners of a point become entries.  It is linked with cngp_api.hip and cngp_sort.hip compiled with the
 // sanitizers on the host side only (`python paper_2312_17241_amd/build.py --host-sanitizers`) and launches
 // nothing: every call below returns before a kernel would be enqueued, so it runs without a GPU.
 // Exit code 0 = clean.
 #include "../../include/cngp.h"
+#include "cngp_device.h"
+#include <cmath>
 #include <cstdint>
 #include <cstdio>
 #include <cstring>
@@ -19,8 +21,39 @@ static uint64_t next_u64() {                       // splitmix64
 }
 static uint32_t below(uint32_t n) { return (uint32_t)(next_u64() % n); }
 
+// Corner references a lane makes of a point on a grid of `res` cells (as bwd_merge_kernel: weight different from zero).
+template <int D>
+static uint32_t references(const bool live, const float (&x)[D], const float res, const uint32_t flip) {
+    float wa[D], wb[D];
+    for (int j = 0; j < D; ++j) {
+        const float    pos = x[j] * res, w = pos - std::floor(pos);
+        const uint32_t up = (flip >> j) & 1u;
+        wa[j] = up ? w : 1.0f - w;
+        wb[j] = up ? 1.0f - w : w;
+    }
+    uint32_t n = 0;
+    for (uint32_t k = 0; k < 1u << D; ++k) n += cngp::corner_weight_if<D>(live, wa, wb, k) != 0.0f;
+    return n;
+}
+// A lane beyond its chunk makes none, whatever the coordinates of the point it repeats; one with a point at most 2^D.
+template <int D>
+static bool idle_lanes_make_no_references() {
+    const float v[] = {0.3f, 0.0f, 1.0f, -2.5f, 3e38f, INFINITY, -INFINITY, NAN};
+    uint32_t    combos = 1, seen = 0;
+    for (int j = 0; j < D; ++j) combos *= 8;
+    for (uint32_t c = 0; c < combos; ++c)
+        for (uint32_t flip = 0; flip < 1u << D; ++flip) {
+            float x[D];
+            for (int j = 0; j < D; ++j) x[j] = v[(c >> (3 * j)) & 7u];
+            if (references<D>(false, x, 48.0f, flip) != 0) return false;
+            seen += references<D>(true, x, 48.0f, flip);
+        }
+    return seen > 0 && seen <= (combos << D) << D;
+}
+
 int main() {
     int bad = 0;
+    if (!idle_lanes_make_no_references<2>() || !idle_lanes_make_no_references<3>()) bad |= 16384;
     const int64_t sizes[] = {0, 1, 63, 4097, 70001, 1 << 18, (1 << 20) + 5, 1 << 22, (int64_t)1 << 26};
     const uint32_t flag_sets[] = {0, CNGP_BWD_DIRECT, CNGP_BWD_SLICED, CNGP_BWD_BINNED, CNGP_BWD_BINNED | CNGP_BWD_NO_PREREDUCE,
                                   CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE};

@@ -89,6 +89,26 @@ def test_points_outside_the_cube_agree_with_the_direct_variant():
         assert np.abs(g - h).max() <= 4e-6 * np.abs(A).max()
 
 
+@pytest.mark.parametrize("d,N,last", [
+    (3, 200001, (np.inf, np.inf, np.inf)), (3, 200001, (0.95, np.inf, 0.95)), (3, 200001, (np.inf, 3e38, 0.99)), (3, 199681, (0.99, 0.99, np.inf)),
+    (2, 400003, (np.inf, np.inf)), (2, 400003, (0.99, np.inf))])
+def test_lanes_beyond_a_ragged_chunk_ignore_a_point_at_infinity(d, N, last):
+    """The point the idle lanes of the last round repeat is not finite (the last of the order: nobody else is in its cell).  The rows it
+    touches are meaningless in every variant, and the same ones; all others are as if it were not there."""
+    w = W.custom(cfg=115, d=d, L=3, N_f=2**13, N_c=2**10, N_p=4, N_min=8, N_max=60, N=N, feat_dtype="f16", io_dtype="f16")
+    x = np.random.default_rng(7).random((N, d), dtype=np.float32) * np.float32(0.9)
+    x[N // 3] = last
+    args = inputs(w, x)
+    gF, gC, names = backward(w, args)
+    assert "encode_bwd_merge" in names
+    hF, hC, _ = backward(w, args, flags=cngp.ZERO_GRADS | cngp.BWD_DIRECT)
+    _, _, A_f, A_c = oracle.encode_bwd(w, np.where(np.isfinite(x) & (x <= 1.0), x, np.float32(0.5)), *args[1:])
+    for g, h, A in ((gF, hF, A_f), (gC, hC, A_c)):
+        touched = ~np.isfinite(h)
+        assert 0 < touched.sum() < 0.02 * h.size and (touched == ~np.isfinite(g)).all()
+        assert np.abs(g - h)[~touched].max() <= 4e-6 * np.abs(A).max()      # the direct variant's fp32 sums, as above
+
+
 def test_a_smaller_workspace_and_no_pre_reduction_are_not_merged():
     w = W.custom(cfg=113, d=3, L=4, N_f=2**13, N_c=2**11, N_p=8, N_min=16, N_max=200, N=200003, feat_dtype="f16", io_dtype="f16")
     args = inputs(w)
