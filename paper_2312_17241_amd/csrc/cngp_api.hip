@@ -1324,18 +1324,21 @@ int launch_fused_fwd(const cngp_config *c, const Params &p, const MlpDims &d, co
 
 namespace {
 // Workspace of the entry points for entries of two features (every kernel's native width).
-size_t workspace_bytes_pairs(const cngp_config *cfg, int64_t N) {
-    const int64_t per = bwd_pass_points(cfg, N);
-    if (per >= N) return make_bwd_plan(cfg, N).ws_bytes;
-    const size_t  most = make_bwd_plan_uncached(cfg, per).ws_bytes;          // the last pass is the shorter one
-    const size_t  last = make_bwd_plan_uncached(cfg, N - (N - 1) / per * per).ws_bytes;
+size_t workspace_bytes_passes(const cngp_config *cfg, int64_t N, int64_t per, Layout layout) {
+    const size_t most = make_bwd_plan_uncached(cfg, per, layout).ws_bytes;   // the last pass is the shorter one
+    const size_t last = make_bwd_plan_uncached(cfg, N - (N - 1) / per * per, layout).ws_bytes;
     return most > last ? most : last;
 }
-// The smallest workspace with which cngp_encode_bwd runs.
+size_t workspace_bytes_pairs(const cngp_config *cfg, int64_t N) {
+    const int64_t per = bwd_pass_points(cfg, N);
+    return per >= N ? make_bwd_plan(cfg, N).ws_bytes : workspace_bytes_passes(cfg, N, per, LAYOUT_MERGED);
+}
+// The smallest workspace with which cngp_encode_bwd runs (in passes: without merging, which may take three times as much and is
+// left out by bwd_plan_for where it does not fit).
 size_t least_workspace_pairs(const cngp_config *cfg, int64_t N) {
-    const size_t bytes = workspace_bytes_pairs(cfg, N);
-    if (bwd_pass_points(cfg, N) < N) return bytes;
-    const size_t least = make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes;
+    const size_t  bytes = workspace_bytes_pairs(cfg, N);
+    const int64_t per = bwd_pass_points(cfg, N);
+    const size_t  least = per < N ? workspace_bytes_passes(cfg, N, per, LAYOUT_FAST) : make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes;
     return least < bytes ? least : bytes;
 }
 
@@ -1626,7 +1629,7 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
     hipStream_t s = (hipStream_t)stream;
     const int64_t per = bwd_pass_points(cfg, N);
     if (per < N) {      // several passes over runs of points; the first one clears if asked, the rest accumulate
-        if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < cngp_workspace_bytes(cfg, N))
+        if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < least_workspace_pairs(cfg, N))
             return CNGP_ERR_WORKSPACE;
         cngp_config   pass = *cfg;
         const size_t  io = cfg->io_dtype == CNGP_F16 ? 2 : 4;

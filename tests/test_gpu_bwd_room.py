@@ -1,6 +1,8 @@
 """A backward workspace that was sized for a larger batch: the need does not only grow with N (a batch that bins every
 level has records in two tables where a larger one has one record of a pre-reduced level), and a training run that
 allocates for its largest batch then passes what an occupancy grid leaves of it."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -45,6 +47,27 @@ def test_a_workspace_of_a_larger_batch_serves_a_shorter_one(F, most, N):
     same(got, ref)
     with pytest.raises(cngp.CngpError) as e:                        # below the smallest layout it is still refused
         cngp.encode_bwd(cfg, *args, workspace=ws[:cngp.workspace_bytes(cfg, N) // 2 // 256 * 256])
+    assert e.value.status == cngp.ERR_WORKSPACE
+
+
+@pytest.mark.parametrize("F", [2, 4])
+def test_a_batch_in_passes_runs_in_the_room_of_its_unmerged_layout(F):
+    """Two passes whose plan merges the coarser levels when it has the room (7 GiB); the room without that (2.3) is enough."""
+    N = 27218550
+    cfg = cngp.Config(d=3, L=5, F=F, N_f=2**6, N_c=2**14, N_p=4, N_min=15, N_max=15360, feat_dtype=cngp.F16, io_dtype=cngp.F16, flags=cngp.ZERO_GRADS)
+    need, room = cngp.workspace_bytes(cfg, N), cngp.workspace_bytes(dataclasses.replace(cfg, bin_bytes_max=(8 << 30) - 1), N)
+    assert cngp.bwd_plan_info(cfg, N)["passes"] == 2 and need > 2 * room
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.rand((N, 3), generator=g, device="cuda")
+    D_f, dy = (torch.randn(s, generator=g, device="cuda", dtype=torch.float16) for s in ((5, 2**6, F), (N, 5 * F)))
+    args = (x, D_f, torch.randn((5, 2**14, 4), generator=g, device="cuda"), dy)
+    run = lambda size: launches(lambda: cngp.encode_bwd(cfg, *args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")))
+    got, narrow = run(room)
+    ref, wide = run(need)
+    assert narrow.get("encode_bwd_merge", 0) == 0 and wide["encode_bwd_merge"] == F
+    same(got, ref)
+    with pytest.raises(cngp.CngpError) as e:
+        run(room // 2 // 256 * 256)
     assert e.value.status == cngp.ERR_WORKSPACE
 
 
