@@ -246,9 +246,8 @@ int cngp_encode_bwd_input(const cngp_config *cfg, const float *x, int64_t N, con
 
 /* How cngp_encode_bwd would run for this configuration and N (host only; for tests, tuning and logs).
  * info (host, CNGP_PLAN_INFO_COUNT entries): [0] 1 = LDS-sliced variant, 0 = global atomics;
- * [1] number of coarse levels pre-reduced per grid vertex (a large binned batch merges the references of neighbouring
- * points instead, on these levels -- those with at least four references per vertex of the grid -- and perhaps
- * one more; its [6] .. [9] are those of the merged levels, without a grid); [2], [3] slices per level of the feature and
+ * [1] number of coarse levels pre-reduced per vertex of their grid (0 where levels are merged instead, see
+ * cngp_bwd_merge_info; [6] .. [9] then describe no level); [2], [3] slices per level of the feature and
  * of the logit gradient table; [4], [5] point chunks of the feature / logit role on hashed levels;
  * [6], [7] vertex chunks of the two roles on pre-reduced levels; [8] point chunks and [9] total slices
  * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first, and then
@@ -259,6 +258,14 @@ int cngp_encode_bwd_input(const cngp_config *cfg, const float *x, int64_t N, con
  * describe the first pass). */
 enum { CNGP_PLAN_INFO_COUNT = 15 };
 int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info);
+
+/* The merged levels of that call: a large binned batch in a workspace of cngp_workspace_bytes sums the references of
+ * neighbouring points per vertex on its coarser levels, in place of the sums per vertex of a grid.  A smaller workspace that is
+ * still accepted runs without.  Host only.  info (host, CNGP_MERGE_INFO_COUNT entries; all 0 where nothing is merged):
+ * [0] levels merged, from the coarsest on; [1] chunks of the ordered points and [2] points per chunk; [3] tiles of the
+ * order; [4], [5] workgroups that drain one bin of a merged level's entries, feature / logit table. */
+enum { CNGP_MERGE_INFO_COUNT = 6 };
+int cngp_bwd_merge_info(const cngp_config *cfg, int64_t N, int32_t *info);
 
 /* Where cngp_encode_bwd keeps what in its workspace for this configuration and N (one pass of it, when the batch is
  * taken in passes).  Host only; for tests of the plan: region i covers bytes [regions[2i], regions[2i] + regions[2i+1])

@@ -99,6 +99,8 @@ def _load():
     lib.cngp_debug_indices.argtypes = [cfgp, vp, i64, vp, vp, vp, vp, vp, vp]
     lib.cngp_bwd_plan_info.restype = ctypes.c_int
     lib.cngp_bwd_plan_info.argtypes = [cfgp, i64, vp]
+    lib.cngp_bwd_merge_info.restype = ctypes.c_int
+    lib.cngp_bwd_merge_info.argtypes = [cfgp, i64, vp]
     lib.cngp_fwd_plan_info.restype = ctypes.c_int
     lib.cngp_fwd_plan_info.argtypes = [cfgp, i64, vp]
     lib.cngp_fwd_route.restype = ctypes.c_int
@@ -257,14 +259,17 @@ def fwd_plan_info(cfg: Config, N: int) -> dict:
 
 
 def bwd_plan_info(cfg: Config, N: int) -> dict:
-    """How encode_bwd would run for (cfg, N): variant, pre-reduced levels, slices and chunk counts."""
-    info = (ctypes.c_int32 * 15)()
+    """How encode_bwd would run for (cfg, N): variant, pre-reduced or merged levels, slices and chunk counts
+    (see cngp_bwd_plan_info, cngp_bwd_merge_info)."""
+    info, merge = (ctypes.c_int32 * 15)(), (ctypes.c_int32 * 6)()
     c = cfg.c()
     _check(_lib.cngp_bwd_plan_info(ctypes.byref(c), N, info))
+    _check(_lib.cngp_bwd_merge_info(ctypes.byref(c), N, merge))
     names = ("sliced", "dense_levels", "slices_f", "slices_c", "chunks_feat_pts", "chunks_logit_pts",
              "chunks_feat_vtx", "chunks_logit_vtx", "chunks_grid", "grid_slices",
-             "binned", "drain_wgs_feat", "drain_wgs_logit", "bin_chunks", "passes")
-    return dict(zip(names, list(info)))
+             "binned", "drain_wgs_feat", "drain_wgs_logit", "bin_chunks", "passes",
+             "merged_levels", "merge_chunks", "merge_chunk_points", "merge_tiles", "merged_drain_wgs_feat", "merged_drain_wgs_logit")
+    return dict(zip(names, list(info) + list(merge)))
 
 
 def bwd_plan_layout(cfg: Config, N: int):

@@ -1526,21 +1526,27 @@ int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
     cfg = &pairs;
     const int64_t per = bwd_pass_points(cfg, N);
     const BwdPlan b = make_bwd_plan(cfg, per < N ? per : N);
-    int32_t prereduced = b.dense.count;
-    if (b.merged) {         // reported: the levels with at least kMinRefsPerVertex references per vertex
-        uint32_t res[kMaxLevels];
-        level_table(cfg, res);
-        prereduced = 0;
-        while (prereduced < b.dense.count && !b.fused &&
-               std::pow((double)res[prereduced] + 2.0, cfg->d) * kMinRefsPerVertex <= (double)(uint64_t)(per < N ? per : N) * (1 << cfg->d)) ++prereduced;
-    }
     const int32_t v[CNGP_PLAN_INFO_COUNT] = {
-        b.sliced ? 1 : 0, prereduced, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
-        (int32_t)b.feat_pts.chunks, (int32_t)b.logit_pts.chunks, (int32_t)b.feat_vtx.chunks,
-        (int32_t)b.logit_vtx.chunks, (int32_t)b.grid.chunks, (int32_t)b.dense_slices,
+        b.sliced ? 1 : 0, b.merged ? 0 : b.dense.count, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
+        (int32_t)b.feat_pts.chunks, (int32_t)b.logit_pts.chunks, b.merged ? 1 : (int32_t)b.feat_vtx.chunks,
+        b.merged ? 1 : (int32_t)b.logit_vtx.chunks, b.merged ? 0 : (int32_t)b.grid.chunks, (int32_t)b.dense_slices,
         b.binned ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
         (int32_t)(N > 0 ? (N + per - 1) / per : 1)};
     for (int i = 0; i < CNGP_PLAN_INFO_COUNT; ++i) info[i] = v[i];
+    return CNGP_OK;
+}
+
+int cngp_bwd_merge_info(const cngp_config *cfg, int64_t N, int32_t *info) {
+    if (!info) return CNGP_ERR_NULL;
+    if (int rc = validate(cfg)) return rc;
+    if (N < 0) return CNGP_ERR_INVALID;
+    const cngp_config pairs = as_pairs(cfg);
+    cfg = &pairs;
+    const int64_t per = bwd_pass_points(cfg, N);
+    const BwdPlan b = make_bwd_plan(cfg, per < N ? per : N);
+    const int32_t v[CNGP_MERGE_INFO_COUNT] = {b.dense.count, (int32_t)b.merge.chunks, (int32_t)b.merge.chunk_pts, (int32_t)b.merge.tiles,
+                                              (int32_t)b.feat_vtx.chunks, (int32_t)b.logit_vtx.chunks};
+    for (int i = 0; i < CNGP_MERGE_INFO_COUNT; ++i) info[i] = b.merged ? v[i] : 0;
     return CNGP_OK;
 }
 

@@ -175,11 +175,13 @@ def test_storage_bytes_match_the_oracle_arithmetic():
 
 
 def test_backward_plan_is_reported_on_the_host():
-    """The plan needs no GPU: benchmark shapes take the LDS-sliced variant with pre-reduced coarse levels,
-    a tiny batch takes global atomics, and the flags override the choice."""
+    """The plan needs no GPU: benchmark shapes take the LDS-sliced variant with merged coarse levels, pre-reduced ones in a
+    bounded workspace, a tiny batch takes global atomics, and the flags override the choice."""
     w = W.WORKLOADS["nerf3d"]
     p = cngp.bwd_plan_info(cngp.Config.from_workload(w), w.N)
-    assert p["sliced"] == 1 and p["slices_f"] == 8 and p["slices_c"] == 16 and 1 <= p["dense_levels"] <= 6
+    assert p["sliced"] == 1 and p["slices_f"] == 8 and p["slices_c"] == 16 and p["dense_levels"] == 0 and p["merged_levels"] == 6
+    pg = cngp.bwd_plan_info(cngp.Config.from_workload(w, bin_bytes_max=4 << 30), w.N)
+    assert pg["sliced"] == 1 and 1 <= pg["dense_levels"] <= 6 and pg["merged_levels"] == 0
     assert cngp.workspace_bytes(cngp.Config.from_workload(w), w.N) >= 4 * w.L * w.N_c * w.N_p + 2 * w.N * w.L * w.F
     t = W.WORKLOADS["tiny2d"]
     assert cngp.bwd_plan_info(cngp.Config.from_workload(t), t.N)["sliced"] == 0
@@ -214,6 +216,23 @@ def test_backward_plan_is_reported_on_the_host():
     assert cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(d=3, L=16, N_f=2**13, N_c=2**10, N_p=4, N_min=16, N_max=2048, N=2**18)), 2**18)["slices_f"] > 0
     big = W.custom(d=3, L=16, N_f=2**24, N_c=2**24, N_p=2, N_min=16, N_max=2048, N=2**18)
     assert cngp.bwd_plan_info(cngp.Config.from_workload(big), big.N)["sliced"] == 0     # too many slices
+
+
+def test_merged_levels_are_reported_as_what_they_are():
+    """Levels are either merged or pre-reduced on their grids: never both, and each under its own name."""
+    plan = lambda flags=0, **kw: cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(**kw), flags=cngp.ZERO_GRADS | flags), kw["N"])
+    head = dict(d=3, L=16, N_f=2**16, N_c=2**14, N_p=16, N=2**18)
+    p = plan(N_min=64, N_max=180, **head)                       # levels of 64 .. 90 cells: from 2.4 references per vertex on
+    assert p["merged_levels"] == 6 and p["dense_levels"] == 0 and p["chunks_grid"] == p["grid_slices"] == 0
+    assert p["merge_chunks"] * p["merge_chunk_points"] >= 2**18 > (p["merge_chunks"] - 1) * p["merge_chunk_points"]
+    assert p["merge_tiles"] == 64 and p["merged_drain_wgs_feat"] >= 1 and p["merged_drain_wgs_logit"] >= 1
+    fused = plan(cngp.BWD_BINNED, d=3, L=16, N_f=2**8, N_c=2**16, N_p=8, N_min=40, N_max=2048, N=200003)
+    assert fused["merged_levels"] == 3 and fused["slices_f"] == 0 and fused["dense_levels"] == 0
+    for other in (plan(cngp.BWD_NO_PREREDUCE, N_min=16, N_max=2048, **head), plan(cngp.BWD_BINNED, N_min=16, N_max=2048, **{**head, "N": 2**17}),
+                  plan(cngp.BWD_SLICED, N_min=16, N_max=2048, **head), plan(N_min=16, N_max=2048, **{**head, "N": 2**22})):
+        assert [other[k] for k in other if k.startswith("merge")] == [0] * 6
+    with pytest.raises(cngp.CngpError):
+        cngp.bwd_plan_info(base_cfg(), -1)
 
 
 def test_binding_rejects_host_tensors_and_wrong_shapes():
