@@ -269,12 +269,20 @@ int cngp_bwd_merge_info(const cngp_config *cfg, int64_t N, int32_t *info);
 
 /* Where cngp_encode_bwd keeps what in its workspace for this configuration and N (one pass of it, when the batch is
  * taken in passes).  Host only; for tests of the plan: region i covers bytes [regions[2i], regions[2i] + regions[2i+1])
- * -- the softmax table, the level-major dL/dy, the per-vertex sums (and what the merge needs to find them), then for the binned variant the count matrices,
- * bin starts and records of the two tables and of the pre-reduced or merged levels.  No two regions may overlap, every one
+ * -- the softmax table, the level-major dL/dy, the per-vertex sums, then for the binned variant the count matrices, bin
+ * starts and records of the two tables and of the pre-reduced levels.  Where levels are merged, the third region and the last
+ * three hold the merge's arrays (cngp_bwd_merge_layout).  No two regions may overlap, every one
  * starts on a 256-byte boundary and ends inside cngp_workspace_bytes(cfg, N).  Returns the number of regions
  * (at most CNGP_PLAN_REGIONS; 0 for the variant that needs no workspace) or a negative status. */
 enum { CNGP_PLAN_REGIONS = 12 };
 int cngp_bwd_plan_layout(const cngp_config *cfg, int64_t N, uint64_t *regions);
+
+/* The same of the merged levels' arrays, from the pointers a launch is given and what the kernels index from them: entries, order
+ * of the points, points per cell and tile, per cell; then the count matrices of the two tables, entries per chunk, bin starts of
+ * the two tables and the bins.  Each lies inside one of the regions of cngp_bwd_plan_layout, and no two overlap.
+ * Returns the number of regions (CNGP_MERGE_REGIONS; 0 where nothing is merged) or a negative status. */
+enum { CNGP_MERGE_REGIONS = 11 };
+int cngp_bwd_merge_layout(const cngp_config *cfg, int64_t N, uint64_t *regions);
 
 /* Bake (Fig. 3; Sec. 3): D_c[l][r] = index of the largest confidence value in row r of D^_c.
  * Ties: lowest index; NaN never wins; an all-NaN row gives 0.  Result always < N_p.

@@ -107,6 +107,8 @@ def _load():
     lib.cngp_fwd_route.argtypes = [cfgp, ctypes.c_int32, i64, sz, vp]
     lib.cngp_bwd_plan_layout.restype = ctypes.c_int
     lib.cngp_bwd_plan_layout.argtypes = [cfgp, i64, vp]
+    lib.cngp_bwd_merge_layout.restype = ctypes.c_int
+    lib.cngp_bwd_merge_layout.argtypes = [cfgp, i64, vp]
     lib.cngp_measure_rates.restype = ctypes.c_int
     lib.cngp_measure_rates.argtypes = [vp, vp, sz, vp]
     lib.cngp_profile_enable.restype = ctypes.c_int
@@ -274,9 +276,18 @@ def bwd_plan_info(cfg: Config, N: int) -> dict:
 
 def bwd_plan_layout(cfg: Config, N: int):
     """[(offset, bytes)] of the workspace regions encode_bwd would use (see cngp_bwd_plan_layout)."""
-    reg = (ctypes.c_uint64 * 24)()
+    return _regions(_lib.cngp_bwd_plan_layout, 12, cfg, N)
+
+
+def bwd_merge_layout(cfg: Config, N: int):
+    """[(offset, bytes)] of the arrays of the merged levels (see cngp_bwd_merge_layout)."""
+    return _regions(_lib.cngp_bwd_merge_layout, 11, cfg, N)
+
+
+def _regions(query, most, cfg, N):
+    reg = (ctypes.c_uint64 * (2 * most))()
     c = cfg.c()
-    k = _lib.cngp_bwd_plan_layout(ctypes.byref(c), N, reg)
+    k = query(ctypes.byref(c), N, reg)
     if k < 0:
         _check(k)
     return [(int(reg[2 * i]), int(reg[2 * i + 1])) for i in range(k)]

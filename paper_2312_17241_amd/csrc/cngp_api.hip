@@ -754,13 +754,18 @@ MergedSpace merged_space(const BwdPlan &b, int64_t N, int d) {
     m.recG_bytes = m.recC + (sc ? M * cap * sizeof(EntryRecord) : 0);
     return m;
 }
-MergedBins merged_bins(const BwdPlan &b, int64_t N, int d, void *workspace) {
+struct MergeArrays { MergedBins bins; uint32_t *order, *cells, *total; };
+MergeArrays merge_arrays(const BwdPlan &b, int64_t N, int d, void *workspace) {
     const MergedSpace m = merged_space(b, N, d);
-    char *ws = (char *)workspace;
-    return {(uint32_t *)(ws + b.cntG_off + m.cntF), (uint32_t *)(ws + b.cntG_off + m.cntC), (uint32_t *)(ws + b.cntG_off + m.made),
-            (uint32_t *)(ws + b.baseG_off + m.baseF), (uint32_t *)(ws + b.baseG_off + m.baseC),
-            (EntryRecord *)(ws + b.recG_off + m.recF), (EntryRecord *)(ws + b.recG_off + m.recC),
-            b.merge.levels, b.merge.chunks, b.merge.chunk_pts, (uint4 *)(ws + b.G_off + m.entries)};
+    char *G = (char *)workspace + b.G_off, *cnt = (char *)workspace + b.cntG_off, *base = (char *)workspace + b.baseG_off, *rec = (char *)workspace + b.recG_off;
+    MergeArrays a;
+    a.bins = {(uint32_t *)(cnt + m.cntF), (uint32_t *)(cnt + m.cntC), (uint32_t *)(cnt + m.made),
+              (uint32_t *)(base + m.baseF), (uint32_t *)(base + m.baseC), (EntryRecord *)(rec + m.recF), (EntryRecord *)(rec + m.recC),
+              b.merge.levels, b.merge.chunks, b.merge.chunk_pts, (uint4 *)(G + m.entries)};
+    a.order = (uint32_t *)(G + m.order);
+    a.cells = (uint32_t *)(G + m.cells);
+    a.total = (uint32_t *)(G + m.total);
+    return a;
 }
 
 // Levels (a prefix) whose references a batch of N points merges.
@@ -1030,9 +1035,10 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     uint32_t *baseF = (uint32_t *)(ws + b.baseF_off), *baseC = (uint32_t *)(ws + b.baseC_off);
     BinRecord *recF = (BinRecord *)(ws + b.recF_off), *recC = (BinRecord *)(ws + b.recC_off);
     uint32_t *cntG = (uint32_t *)(ws + b.cntG_off), *baseG = (uint32_t *)(ws + b.baseG_off);
-    MergedBins mb;
-    std::memset(&mb, 0, sizeof(mb));
-    if (b.merged) mb = merged_bins(b, N, D, workspace);
+    MergeArrays ma;
+    std::memset(&ma, 0, sizeof(ma));
+    if (b.merged) ma = merge_arrays(b, N, D, workspace);
+    const MergedBins &mb = ma.bins;
     BinRecord *recG = (BinRecord *)(ws + b.recG_off);
     const bool zero_first = (c->flags & CNGP_ZERO_GRADS) != 0;
     const BinParams bp = make_bin_params<NP>(c, b, N);
@@ -1044,19 +1050,17 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     // for the memory system to merge the 4-byte writes, and four wavefronts sharing the cursors write
     // 1.7 times faster (measured at 64 bins per level).
     if constexpr (D <= 3) if (b.merged) {      // the points in the order of their cells (the histogram ran with the preparation), then the entries
-        const MergedSpace m = merged_space(b, N, D);
-        uint32_t *order = (uint32_t *)(ws + b.G_off + m.order), *cells = (uint32_t *)(ws + b.G_off + m.cells), *total = (uint32_t *)(ws + b.G_off + m.total);
         {
             LaunchTimer t(s, K_BWD_CELLS);
-            merge_scan_kernel<<<kMergeCells / 64, kMergeScanBlock, 0, s>>>(b.merge, cells, total);
+            merge_scan_kernel<<<kMergeCells / 64, kMergeScanBlock, 0, s>>>(b.merge, ma.cells, ma.total);
             if (int rc = launch_status("merge_scan_kernel")) return rc;
-            merge_order_kernel<D><<<b.merge.tiles, 1024, 0, s>>>(b.merge, x, N, cells, total, order);
+            merge_order_kernel<D><<<b.merge.tiles, 1024, 0, s>>>(b.merge, x, N, ma.cells, ma.total, ma.order);
             if (int rc = launch_status("merge_order_kernel")) return rc;
         }
         auto kernel = bwd_merge_kernel<D, IoT>;
         if (int rc = allow_big_lds(kernel, kMergeLdsBytes)) return rc;
         LaunchTimer t(s, K_BWD_MERGE);
-        kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, order, mb);
+        kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, ma.order, mb);
         if (int rc = launch_status("bwd_merge_kernel")) return rc;
     }
     const unsigned bin_block = bp.slices_f + bp.slices_c >= 48 ? 256u : (unsigned)kBinBlock;
@@ -1160,7 +1164,7 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
             char *ws = (char *)workspace;
             size_t lds = (size_t)most * reps * sizeof(uint32_t);
             if (b.merged && lds < kMergeCells * sizeof(uint32_t)) lds = kMergeCells * sizeof(uint32_t);
-            uint32_t *cells = b.merged ? (uint32_t *)(ws + b.G_off + merged_space(b, N, D).cells) : nullptr;
+            uint32_t *cells = b.merged ? merge_arrays(b, N, D, workspace).cells : nullptr;
             bwd_prep_count_kernel<D, NP, PairT><<<(unsigned)(blocks + count_blocks + b.merge.tiles), kBlock, lds, s>>>(
                 a, p, bp, b.dense, x, (uint32_t *)(ws + b.cntF_off), (uint32_t *)(ws + b.cntC_off), (uint32_t *)(ws + b.cntG_off),
                 reps, (uint32_t)count_blocks, b.merge, cells);
@@ -1580,6 +1584,36 @@ int cngp_bwd_plan_layout(const cngp_config *cfg, int64_t N, uint64_t *regions) {
         add(b.baseG_off, b.baseG_bytes);
         add(b.recG_off, b.recG_bytes);
     }
+    return k;
+}
+
+int cngp_bwd_merge_layout(const cngp_config *cfg, int64_t N, uint64_t *regions) {
+    if (!regions) return CNGP_ERR_NULL;
+    if (int rc = validate(cfg)) return rc;
+    if (N < 0) return CNGP_ERR_INVALID;
+    const cngp_config pairs = as_pairs(cfg);
+    cfg = &pairs;
+    const int64_t per = bwd_pass_points(cfg, N);
+    const int64_t n = per < N ? per : N;
+    const BwdPlan b = make_bwd_plan(cfg, n);
+    if (!b.merged) return 0;
+    // the pointers a launch is given, as if the workspace began at an address of that alignment, and what the kernels index from them
+    char *const       ws = (char *)(uintptr_t)(1u << 20);
+    const MergeArrays a = merge_arrays(b, n, cfg->d, ws);
+    const uint64_t    M = a.bins.levels, chunks = a.bins.chunks, cap = (uint64_t)n << cfg->d, sf = b.fused ? 0 : b.slices_f, sc = cfg->N_p > 1 ? b.slices_c : 0;
+    int k = 0;
+    auto add = [&](const void *p, uint64_t bytes) { regions[2 * k] = (uint64_t)((const char *)p - ws); regions[2 * k + 1] = bytes; ++k; };
+    add(a.bins.entries, M * cap * sizeof(uint4));
+    add(a.order, (uint64_t)n * 4);
+    add(a.cells, (uint64_t)b.merge.tiles * kMergeCells * 4);
+    add(a.total, kMergeCells * 4);
+    add(a.bins.cntF, M * chunks * sf * 4);
+    add(a.bins.cntC, M * chunks * sc * 4);
+    add(a.bins.made, M * chunks * 4);
+    add(a.bins.baseF, sf ? M * (sf + 1) * 4 : 0);
+    add(a.bins.baseC, sc ? M * (sc + 1) * 4 : 0);
+    add(a.bins.recF, sf ? M * cap * sizeof(EntryRecord) : 0);
+    add(a.bins.recC, sc ? M * cap * sizeof(EntryRecord) : 0);
     return k;
 }
 

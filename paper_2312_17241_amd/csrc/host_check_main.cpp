@@ -100,6 +100,12 @@ int main() {
             for (int i = 0; i < rr; ++i)
                 if (regions[2 * i + 1] && (regions[2 * i] % 256 || regions[2 * i] + regions[2 * i + 1] > ws)) bad |= 2;
             if (info[14] < 1) bad |= 4;
+            int32_t   minfo[CNGP_MERGE_INFO_COUNT];
+            uint64_t  arrays[2 * CNGP_MERGE_REGIONS];
+            const int rm = cngp_bwd_merge_layout(&c, N, arrays);
+            if (cngp_bwd_merge_info(&c, N, minfo) != CNGP_OK || (rm != 0) != (minfo[0] > 0) || (rm != 0 && rm != CNGP_MERGE_REGIONS)) bad |= 32768;
+            for (int i = 0; i < rm; ++i)
+                if (arrays[2 * i + 1] && (arrays[2 * i] % 16 || arrays[2 * i] + arrays[2 * i + 1] > ws)) bad |= 32768;
         } else if (ws != 0 && N > 0) {
             bad |= 8;                                                       // an invalid configuration needs no workspace
         }

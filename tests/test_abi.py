@@ -258,10 +258,11 @@ def test_product_does_not_import_the_oracle():
 
 def test_backward_plan_layout_stays_inside_the_workspace():
     """For seeded random configurations and batch sizes, on every backward variant: the regions of the workspace the
-    kernels index (cngp_bwd_plan_layout computes them from the kernels' own extents) are 256-byte aligned, do not
+    kernels index (cngp_bwd_plan_layout computes them from the kernels' own extents, but for those that hold the merged levels'
+    arrays, whose extents the next test checks) are 256-byte aligned, do not
     overlap, and end inside cngp_workspace_bytes; the plan's counts are consistent with each other."""
     rng = np.random.default_rng(2024)
-    seen = {"direct": 0, "sliced": 0, "binned": 0, "passes": 0, "fused": 0}
+    seen = {"direct": 0, "sliced": 0, "binned": 0, "passes": 0, "fused": 0, "merged": 0}
     for it in range(400):
         d = int(rng.choice([2, 3]))
         N_p = int(2 ** rng.integers(0, 5))
@@ -292,7 +293,46 @@ def test_backward_plan_layout_stays_inside_the_workspace():
         seen["binned" if plan["binned"] else "sliced" if plan["sliced"] else "direct"] += 1
         seen["passes"] += plan["passes"] > 1
         seen["fused"] += plan["binned"] == 1 and plan["slices_f"] == 0
+        seen["merged"] += plan["merged_levels"] > 0
     assert min(seen.values()) >= 5, seen          # the sweep reaches every variant
+
+
+def test_arrays_of_the_merged_levels_do_not_overlap():
+    """Every array of the merge, with the extent its kernels index (computed here from levels, chunks, slices and N), lies inside
+    one of the four regions the plan has for them, apart from all others and from every other region."""
+    rng = np.random.default_rng(31)
+    merged, seen = 0, {"passes": 0, "fused": 0, "plain": 0, "flat": 0, "planes": 0}
+    for it in range(400):
+        d, N_p = int(rng.choice([2, 3])), int(2 ** rng.integers(0, 5))
+        N_f = int(2 ** rng.integers(max(4, int(np.log2(N_p))), 21))
+        N = int(2 ** rng.uniform(21 - d, 26))
+        L, N_min, N_c = int(rng.integers(2, 17)), int(rng.integers(8, 200)), int(2 ** rng.integers(1, 19))
+        N_max = int(N_min * 2 ** rng.integers(1, 9))
+        if it % 20 == 0:                                        # (the largest that are merged: few of the levels, in passes)
+            d, N_p, N_f, N, L, N_min, N_c, N_max = 3, 4, 2**6, int(rng.integers(27_000_000, 28_000_000)), 5, 15, 2**14, 15360
+        cfg = cngp.Config.from_workload(W.custom(cfg=7, d=d, L=L, F=int(rng.choice([2, 2, 4])), N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min,
+                                                 N_max=N_max, N=N, feat_dtype="f16", io_dtype=str(rng.choice(["f16", "f32"]))),
+                                        flags=cngp.ZERO_GRADS | int(rng.choice([0, cngp.BWD_BINNED])))
+        plan, arrays = cngp.bwd_plan_info(cfg, N), cngp.bwd_merge_layout(cfg, N)
+        assert (len(arrays) > 0) == (plan["merged_levels"] > 0)
+        if not arrays:
+            continue
+        merged += 1
+        n = N if plan["passes"] == 1 else (-(-N // plan["passes"]) + 63) // 64 * 64
+        M, chunks, cap, sf, sc = plan["merged_levels"], plan["merge_chunks"], n << d, plan["slices_f"], plan["slices_c"]
+        assert chunks * plan["merge_chunk_points"] >= n and 0 < M < L
+        assert [b for _, b in arrays] == [M * cap * 16, n * 4, plan["merge_tiles"] * 4096 * 4, 4096 * 4, M * chunks * sf * 4, M * chunks * sc * 4, M * chunks * 4,
+                                          M * (sf + 1) * 4 if sf else 0, M * (sc + 1) * 4 if sc else 0, M * cap * 12 if sf else 0, M * cap * 12 if sc else 0]
+        regions = cngp.bwd_plan_layout(cfg, N)
+        homes, others = [regions[i] for i in (2, 9, 10, 11)], [regions[i] for i in range(12) if i not in (2, 9, 10, 11)]
+        for home, own in zip(homes, (arrays[:4], arrays[4:7], arrays[7:9], arrays[9:])):
+            assert all(home[0] <= o and o + b <= home[0] + home[1] for o, b in own if b), (cfg, N, home, own)
+        spans = sorted((o, o + b) for o, b in arrays + others if b)
+        assert all(e0 <= o1 for (_, e0), (o1, _) in zip(spans, spans[1:])) and spans[-1][1] <= cngp.workspace_bytes(cfg, N), (cfg, N, spans)
+        assert all(o % 256 == 0 for o, _ in spans)
+        for k, v in (("passes", plan["passes"] > 1), ("fused", sf == 0), ("plain", sc == 0), ("flat", d == 2), ("planes", cfg.F == 4)):
+            seen[k] += v
+    assert merged >= 100 and min(seen.values()) >= 3, (merged, seen)
 
 
 def test_small_binned_batches_pre_reduce_where_the_coarse_bins_are_uneven():
