@@ -903,9 +903,11 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             b.logit_vtx = Geom{(b.subs_c + 1) / 2, 0};
             b.merge.levels = (uint32_t)b.dense.count;
             // chunks of at least two rounds, at most 512 of them: sparse parts of space leave several times the entries of
-            // dense ones, and the many short workgroups even that out
-            const int64_t round = kMergeRefs >> c->d;
-            int64_t mp = ((N + 511) / 512 + round - 1) / round * round;
+            // dense ones, and the many short workgroups even that out.  With 128 slices of a table or more at most as many as the
+            // references' own: beyond, the counts leave the LDS of bin_offsets_kernel, or make its scans through memory longer
+            // (N_f = 2^20, N_c = 2^18, N_p = 4, 2^19 points: offsets 100 us with 512 chunks, 31 with 256; merge 112 and 109)
+            const int64_t round = kMergeRefs >> c->d, most = (b.fused || b.slices_c > b.slices_f ? b.slices_c : b.slices_f) >= 128 ? 256 : 512;
+            int64_t mp = ((N + most - 1) / most + round - 1) / round * round;
             if (mp < 2 * round) mp = 2 * round;
             b.merge.chunk_pts = (uint32_t)mp;
             b.merge.chunks = (uint32_t)((N + mp - 1) / mp);

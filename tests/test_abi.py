@@ -235,6 +235,16 @@ def test_merged_levels_are_reported_as_what_they_are():
         cngp.bwd_plan_info(base_cfg(), -1)
 
 
+@pytest.mark.parametrize("N_f,N_c,N_p", [(2**20, 2**14, 2), (2**20, 1, 1), (2**16, 2**18, 8), (2**11, 2**18, 4), (2**20, 2**20, 2), (2**21, 1, 1), (2**16, 2**14, 16)])
+def test_counts_of_merged_levels_stay_in_lds_with_the_others(N_f, N_c, N_p):
+    """One workgroup scans a level's counts, [chunk][slice], in up to 36864 words of LDS, and through memory, one dependent load
+    after the other, where some level's do not fit: the merged levels' fit where the references' own 256 rows do, or are no more rows."""
+    for N in (2**18 + 2**16, 2**19, 2**19 + 1, 2**20, 3 * 2**19 + 77):
+        p = cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(d=3, L=16, N_f=N_f, N_c=N_c, N_p=N_p, N_min=16, N_max=2048, N=N), flags=cngp.ZERO_GRADS | cngp.BWD_BINNED), N)
+        big = max(p["slices_f"], p["slices_c"])
+        assert p["merged_levels"] > 0 and p["merge_chunks"] <= max(36864 // big, 256), (N, p)
+
+
 def test_binding_rejects_host_tensors_and_wrong_shapes():
     import torch
     cfg = base_cfg()
