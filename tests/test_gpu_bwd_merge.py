@@ -1,6 +1,7 @@
 """Backward pass whose coarser levels merge the references of neighbouring points per vertex before they are binned
 (csrc/cngp_bwd_merge.h), against the oracle and the direct variant: ragged batches, both dimensions, one-pass small tables, chunks
-with more vertices than the table has slots, points a table key cannot hold, the fall-back to a smaller workspace, and capture."""
+with more vertices than the table has slots, points a table key cannot hold, gradients that are added to, the sparse softmax, wider
+features, the fall-back to a smaller workspace, and capture."""
 import numpy as np
 import pytest
 import torch
@@ -24,12 +25,12 @@ def inputs(w, x=None):
     return W.make_points(w) if x is None else x, D_f, W.make_probe_logits(w), W.make_upstream_grad(w)
 
 
-def backward(w, args, flags=FLAGS, ws=None, **kw):
+def backward(w, args, flags=FLAGS, ws=None, init=float("nan"), **kw):
     cfg = cngp.Config.from_workload(w, flags=flags, **kw)
     ws = cngp.alloc_workspace(cfg, w.N) if ws is None else ws
     if ws is not None:
         ws.fill_(0xAB)                                          # nothing in it is assumed to be zero
-    gF, gC = (torch.full(s, float("nan"), device="cuda") for s in ((w.L, w.N_f, 2), (w.L, w.N_c, w.N_p)))
+    gF, gC = (torch.full(s, init, device="cuda") for s in ((w.L, w.N_f, w.F), (w.L, w.N_c, w.N_p)))
     cngp.profile_enable(True)
     cngp.profile_read()
     cngp.encode_bwd(cfg, *(dev(a) for a in args), gF, gC, workspace=ws)
@@ -39,12 +40,12 @@ def backward(w, args, flags=FLAGS, ws=None, **kw):
     return gF.cpu().numpy(), gC.cpu().numpy(), names
 
 
-def check(w, args, **kw):
+def check(w, args, start=0.0, **kw):
     gF, gC, names = backward(w, args, **kw)
     assert "encode_bwd_merge" in names, names
-    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args)
-    check_close("grad D_f", gF, gF_ref, A_f, fp16_out=False)
-    check_close("grad Dhat_c", gC, gC_ref, A_c, fp16_out=False)
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args, top_k=kw.get("top_k", 0))
+    check_close("grad D_f", gF, gF_ref + start, A_f + abs(start), fp16_out=False)
+    check_close("grad Dhat_c", gC, gC_ref + start, A_c + abs(start), fp16_out=False)
 
 
 @pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_max,feat,io", [
@@ -53,11 +54,38 @@ def check(w, args, **kw):
     (2, 500009, 4, 2**13, 2**11, 2, 900, "f32", "f16"),
     (2, 2**19 + 1, 6, 2**13, 1, 1, 300, "f32", "f32"),         # plain hashing: no confidence bins
     (3, 2**18, 5, 2**13, 2**10, 4, 40, "f32", "f32"),          # every level but the last
+    (3, 200003, 4, 2**18, 2**16, 8, 70, "f16", "f16"),         # one drain workgroup per bin of a merged level: nothing is cleared first
     (3, 200003, 16, 2**8, 2**16, 8, 2048, "f16", "f16"),          # small feature table: both gradients in one pass
 ])
 def test_merged_levels_against_the_oracle(d, N, L, N_f, N_c, N_p, N_max, feat, io):
     w = W.custom(cfg=110, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=8 if L < 16 else 40, N_max=N_max, N=N, feat_dtype=feat, io_dtype=io)
     check(w, inputs(w))
+
+
+@pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_max", [
+    (3, 200003, 4, 2**18, 2**16, 8, 70),                       # one drain workgroup per bin of a merged level: stores where the array is cleared, adds here
+    (3, 2**19 + 3, 4, 2**13, 2**10, 4, 70),                    # several
+    (2, 400003, 6, 2**13, 1, 1, 300),                          # plain hashing
+    (3, 200003, 16, 2**8, 2**16, 8, 2048)])                    # both gradients in one pass
+def test_merged_levels_add_onto_the_gradients_that_are_there(d, N, L, N_f, N_c, N_p, N_max):
+    w = W.custom(cfg=116, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=8 if L < 16 else 40, N_max=N_max, N=N, feat_dtype="f16", io_dtype="f16")
+    check(w, inputs(w), flags=cngp.BWD_BINNED, init=-0.5, start=-0.5)
+
+
+@pytest.mark.parametrize("L,N_f,N_c,N_p,top_k", [(4, 2**13, 2**11, 16, 3), (4, 2**13, 2**10, 4, 1), (16, 2**8, 2**16, 8, 2)])
+def test_merged_levels_with_the_sparse_softmax(L, N_f, N_c, N_p, top_k):
+    w = W.custom(cfg=117, d=3, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=8 if L < 16 else 40, N_max=80 if L < 16 else 2048, N=200003,
+                 feat_dtype="f16", io_dtype="f16")
+    check(w, inputs(w), top_k=top_k)
+
+
+@pytest.mark.parametrize("F,d,N,N_p,feat,io", [(4, 3, 200003, 8, "f16", "f16"), (4, 2, 400003, 1, "f32", "f32"), (1, 3, 200003, 4, "f32", "f16")])
+def test_merged_levels_with_other_feature_widths(F, d, N, N_p, feat, io):
+    """A pair of features at a time: dL/dy is then the pair's plane, and the second pass adds to the confidence gradient."""
+    w = W.custom(cfg=118, d=d, L=5, F=F, N_f=2**13, N_c=2**11 if N_p > 1 else 1, N_p=N_p, N_min=8, N_max=80, N=N, feat_dtype=feat, io_dtype=io)
+    args = inputs(w)
+    check(w, args)
+    check(w, args, flags=cngp.BWD_BINNED, init=0.25, start=0.25)
 
 
 def test_more_vertices_than_slots():
