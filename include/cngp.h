@@ -98,8 +98,11 @@ typedef struct {
     int32_t  index_format; /* cngp_index_format of D_c                                         */
     uint32_t flags;        /* bitwise OR of the CNGP_* flags above                             */
     uint64_t bin_bytes_max; /* most workspace cngp_encode_bwd spends on binned references (4 bytes per
-                              corner reference, level and gradient table); 0 = 8 GiB.  A larger batch
-                              is taken in several passes inside the one call                      */
+                              corner reference, level and gradient table).  A larger batch is taken in
+                              several passes inside the one call.  0: at most 8 GiB, and within that the
+                              fastest layout, which may take more than the bins (merged levels, see
+                              cngp_bwd_merge_info); any other value, 8 GiB too, asks for the smaller
+                              layout, without merging                                             */
     uint32_t top_k;        /* cngp_encode_bwd only.  0 or N_p: the paper's backward (softmax over all N_p
                               candidates of a row).  1 .. N_p - 1: sparse variant (Sec. 5 names sparse
                               alternatives to the dense softmax as future work; top-k is this library's
@@ -123,8 +126,9 @@ int cngp_storage_bytes(const cngp_config *cfg, size_t *D_f_bytes, size_t *D_c_le
  * (cngp_fwd_workspace_bytes below; without it they run a slower variant with the same result).  With F != 2 one pair
  * of features at a time is copied out of D_f, y, dL/dy and back, and those planes sit in the workspace too (the
  * forward calls then need it as well).
- * cngp_encode_bwd also runs in less where a layout that pre-reduces more of the coarse levels fits: the workspace of
- * a batch serves every shorter one.
+ * For a large batch this includes the room to merge references (cngp_bwd_merge_info): 40 bytes for each one of a merged
+ * level, while the whole stays within 8 GiB.  cngp_encode_bwd also runs in less where a layout without merging, or one that
+ * pre-reduces more of the coarse levels, fits: the workspace of a batch serves every shorter one.
  * The workspace must be 256-byte aligned; its contents are undefined before and after each call.
  * Returns 0 for an invalid configuration as well (the encode calls then report the error). */
 size_t cngp_workspace_bytes(const cngp_config *cfg, int64_t N);

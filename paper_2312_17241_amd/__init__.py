@@ -141,7 +141,7 @@ class Config:
     io_dtype: int = F32
     index_format: int = IDX_U8
     flags: int = 0
-    bin_bytes_max: int = 0      # 0 = the library's 8 GiB
+    bin_bytes_max: int = 0      # 0 = at most 8 GiB, the fastest layout within them; a bound asks for the smaller layout
     top_k: int = 0              # backward: 0 = softmax over all N_p candidates; else over the top_k largest only
 
     @staticmethod
