@@ -573,12 +573,19 @@ constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated sca
 // where a coarse level's few vertices collide; the slowest 0.95x (12.2 us against 11.5).
 constexpr size_t   kSmallBwdLds = 128 * 1024;
 constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
-// References per level (N * 2^d) from which the binned variant always pre-reduces coarse levels; below, binned_bwd_us decides.
+// References per level (N * 2^d) from which the binned variant, where it does not merge, always pre-reduces coarse levels; below,
+// binned_bwd_us decides.
 // Backward, us, with / without, beyond it: nerf3d's tables 163840 points 384 / 403, 2^18 539 / 569; sdf3d's 2^20 2786 / 3294;
 // d = 2 600000 1001 / 1175.
 constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // Merging (cngp_bwd_merge.h): references per level from which the three launches more are worth it, and references per vertex of
 // a level's grid, in hundredths, from which the level is merged (points are never spread more evenly than over the whole grid).
+// Backward, us, without / with merging, at 2^19, 2^20, 3 * 2^19 and 2^21 references per level: nerf3d's tables 244 / 238, 334 / 306,
+// 434 / 403, 541 / 489; sdf3d's 351 / 236, 507 / 407, 669 / 576, 831 / 739; d = 2 (2^18 and 2^16 rows, N_p = 8) 343 / 208, 661 / 325,
+// 800 / 463, 926 / 596; plain hashing (2^19 rows) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  The line is on the safe side: batches
+// from it on are the ones that the figures below were drawn from; that it pays from 2^20 on was seen on these tables only.
+// Points anything but evenly spread, without / with: all equal 1719 / 1279 (nerf3d's tables, 2^18 points), in a cube of side 0.02
+// 1233 / 812, on a line 1145 / 951, on a plane 544 / 519; sdf3d's 2^20 points 6127 / 3684, 3693 / 2137, 3548 / 2329, 2780 / 2139.
 // Sum of the kernels of a step, us, lines at 20 / 80 / 150 / 300 / 1500: nerf3d 728 / 611 / 594 / 587 / 601 (649 with grid sums),
 // sdf3d, whose points are anything but evenly spread, 2750 / 2704 / 2786 / 2815 / 2977 (3184), compact3d 504 / 465 / 448 / 453 / 478 (469).
 // Backward without / with merging, mean (slowest) of 40 drawn batches of 2^18 .. 2^20 points, lines at 60 / 90 / 150 / 250: 1.25 (0.91), 1.25 (0.91), 1.26
@@ -848,8 +855,9 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         // 1.3e-7, with one 468)
         b.merged = b.dense.count > 0 && !(b.fused && drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L - b.dense.count, per_level_now) !=
                                                          drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L, per_level_now));
-        // (plain hashing has one table and the cheapest references: three merged levels do not pay for the order of the points;
-        // d = 3, L = 8, N_max = 8192, 499487 points: 246 us, merged 266; L = 16 and more of them 288 / 265)
+        // (plain hashing has one table and the cheapest references: three merged levels do not pay for the order of the points.
+        // 32 drawn batches, d = 2 and 3, L = 8 .. 16, N_f = 2^18 .. 2^20, without / with merging: three levels 0.965 .. 0.984 (three
+        // batches; d = 3, L = 8, N_max = 8192, 385625 points: 227 us, merged 235), four and more 1.07 .. 2.5)
         if (c->N_p == 1 && b.dense.count < 4) b.merged = false;
         if (!b.merged) b.dense.count = 0;
     }

@@ -13,13 +13,15 @@
 //               per entry and table (nerf3d: drain 411 us so, 365 with whole entries; sdf3d 1676 and 1480)
 // Nothing has to be complete: a vertex that two workgroups saw, or that found no room in a table, simply has two entries.
 //
-// Share of the references that is left (2^18 ray samples, the level's N_l: 42 0.11, 80 0.33, 111 0.54; 2^20 points near a surface:
-// 48 0.04, 101 0.17, 147 0.27, 212 0.41; 2^20 uniform points, d = 2: 445 0.08, 1024 0.29).
+// Share of the references that is left (2^18 ray samples, the level's N_l: 42 0.11, 58 0.20, 80 0.33; 2^20 points near a surface:
+// 48 0.04, 101 0.17, 147 0.27; 2^20 uniform points, d = 2: 445 0.08, 1024 0.29).
 //
-// What bounds the merge kernel: LDS (one compare-and-swap and two fp64 additions at random addresses per reference, 1.3 clocks
-// of the CU: busy 55 % of the time) and, for a batch in no order, the lines of x and dL/dy (2^20 points, 8 levels: 383 us with
-// the levels one after the other, 276 with a chunk's levels side by side).  Features in planes instead of pairs, one lane per
-// four corners instead of eight and a wavefront's points spread over the round took 78 us to 61 (2^18 ray samples, 7 levels).
+// What bounds the merge kernel: LDS (one compare-and-swap and two fp64 additions at random addresses per reference, 1.3 .. 1.5
+// clocks of the CU, half of them bank and address conflicts: at work 67 % of the time a CU has waves with 2^18 ray samples, 74 %
+// with 2^20 points near a surface) and, for a batch in no order, the lines of x and dL/dy (2^20 points, with a finer eighth level
+// merged as well: 383 us with the levels one after the other, 276 with a chunk's levels side by side).  Features in planes instead
+// of pairs, one lane per four corners instead of eight and a wavefront's points spread over the round took 78 us to 61 (2^18 ray
+// samples, with a finer seventh level; the six levels now merged take 49, the seven of the surface's points 230).
 #pragma once
 #include "cngp_bwd_binned.h"
 
@@ -28,7 +30,8 @@ namespace cngp {
 constexpr int      kMergeBlock = 1024;
 constexpr uint32_t kMergeRefs  = 4096;              // references per round of a workgroup
 // Slots of the table: with 20 bytes each, the lists and the counters, two workgroups fit the 160 KB of a CU, one inserting while
-// the other loads or writes; a level that merges at all leaves well under 3520 of 4096 references.
+// the other loads or writes.  On average a merged level leaves a third of a round's 4096 references or less (list above); where
+// the points are so sparse that more than 3520 are left, those that find no slot become entries of their own.
 constexpr uint32_t kMergeSlots = 3520;
 constexpr uint32_t kMergeProbes = 16;               // slots tried; a reference that finds none becomes an entry of its own
 constexpr uint32_t kMergeEmpty = 0xFFFFFFFFu;
