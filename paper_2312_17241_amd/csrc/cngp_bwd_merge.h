@@ -17,8 +17,8 @@
 // 48 0.04, 101 0.17, 147 0.27; 2^20 uniform points, d = 2: 445 0.08, 1024 0.29).
 //
 // What bounds the merge kernel: LDS (one compare-and-swap and two fp64 additions at random addresses per reference, 1.3 .. 1.5
-// clocks of the CU, half of them bank and address conflicts: at work 67 % of the time a CU has waves with 2^18 ray samples, 74 %
-// with 2^20 points near a surface) and, for a batch in no order, the lines of x and dL/dy (2^20 points, with a finer eighth level
+// clocks of the CU, 38 .. 42 % of them bank conflicts: at work 67 % of the time a CU has waves with 2^18 ray samples, 74 % with
+// 2^20 points near a surface) and, for a batch in no order, the lines of x and dL/dy (2^20 points, with a finer eighth level
 // merged as well: 383 us with the levels one after the other, 276 with a chunk's levels side by side).  Features in planes instead
 // of pairs, one lane per four corners instead of eight and a wavefront's points spread over the round took 78 us to 61 (2^18 ray
 // samples, with a finer seventh level; the six levels now merged take 49, the seven of the surface's points 230).
