@@ -581,8 +581,9 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // Merging (cngp_bwd_merge.h): references per level from which the three launches more are worth it, and references per vertex of
 // a level's grid, in hundredths, from which the level is merged (points are never spread more evenly than over the whole grid).
 // Backward, us, without / with merging, at 2^19, 2^20, 3 * 2^19 and 2^21 references per level: nerf3d's tables 244 / 238, 334 / 306,
-// 434 / 403, 541 / 489; sdf3d's 351 / 236, 507 / 407, 669 / 576, 831 / 739; d = 2 (2^18 and 2^16 rows, N_p = 8) 343 / 208, 661 / 325,
-// 800 / 463, 926 / 596; plain hashing (2^19 rows) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  The line is on the safe side: batches
+// 434 / 403, 541 / 489; sdf3d's 351 / 236, 507 / 407, 669 / 576, 831 / 739; d = 2 (N_f = 2^18, N_c = 2^16, N_p = 8) 343 / 208,
+// 661 / 325, 800 / 463, 926 / 596; N_f = 2^18, N_c = 2^14, N_p = 4 197 / 175, 270 / 231, 343 / 314, 429 / 371; plain hashing
+// (N_f = 2^19) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  The line is on the safe side: batches
 // from it on are the ones that the figures below were drawn from; that it pays from 2^20 on was seen on these tables only.
 // Points anything but evenly spread, without / with: all equal 1719 / 1279 (nerf3d's tables, 2^18 points), in a cube of side 0.02
 // 1233 / 812, on a line 1145 / 951, on a plane 544 / 519; sdf3d's 2^20 points 6127 / 3684, 3693 / 2137, 3548 / 2329, 2780 / 2139.
