@@ -5,7 +5,7 @@
 #include "cngp_fwd_level.h"
 #include "cngp_bwd_sliced.h"
 #include "cngp_bwd_binned.h"
-#include "cngp_bwd_merge.h"
+#include "cngp_bwd_runs.h"
 #include "cngp_rates.h"
 #include "cngp_optim.h"
 #include "cngp_mlp.h"
@@ -596,6 +596,11 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // tables with d = 2 and N_p = 2, whose references cost the least, 0.90x: neither is merged.
 constexpr int64_t  kMinMergeRefs = 3 << 19;
 constexpr uint64_t kMinMergePerVertexPct = 240;
+// Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us: sdf3d's tables (32 + 32
+// bins) 30000 points 150 / 140, 100000 345 / 309, 2^18 uniform 723 / 656, 2^20 near a surface 2407 / 2170; 32 + 16 bins 681 / 632,
+// 8 + 64 797 / 746, 64 + 128 1078 / 997, d = 2, 32 + 32 999 / 922.  Below the line the scatter gains as well, but the drain loses as
+// much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.
+constexpr uint32_t kMinRunBins = 48;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -1056,10 +1061,9 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     const int64_t blocks = (int64_t)(b.merged ? Lh : Lh + Ld) * bp.chunks + (int64_t)mb.levels * mb.chunks;
     if (int rc = check_blocks(blocks)) return rc;
     const size_t lds_bins = (size_t)most_bins_of(bp) * sizeof(uint32_t);
-    // One wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
-    // like (measured: drain 7 % faster); with many bins a lone wavefront fills its cache lines too slowly
-    // for the memory system to merge the 4-byte writes, and four wavefronts sharing the cursors write
-    // 1.7 times faster (measured at 64 bins per level).
+    // Direct scatter: one wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
+    // like (measured: drain 7 % faster); with more bins than the scatter in runs takes, four wavefronts share the cursors
+    // (a lone one fills its cache lines too slowly for the memory system to merge the 4-byte writes).
     if constexpr (D <= 3) if (b.merged) {      // the points in the order of their cells (the histogram ran with the preparation), then the entries
         {
             LaunchTimer t(s, K_BWD_CELLS);
@@ -1074,7 +1078,7 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
         kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, ma.order, mb);
         if (int rc = launch_status("bwd_merge_kernel")) return rc;
     }
-    const unsigned bin_block = bp.slices_f + bp.slices_c >= 48 ? 256u : (unsigned)kBinBlock;
+    const unsigned bin_block = bp.slices_f + bp.slices_c >= kMinRunBins ? 256u : (unsigned)kBinBlock;
     {
         LaunchTimer t(s, K_BWD_BIN_OFFSETS);
         uint32_t big = bp.slices_f > bp.slices_c ? bp.slices_f : bp.slices_c;
@@ -1088,7 +1092,14 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     }
     {
         LaunchTimer t(s, K_BWD_BIN_SCATTER);
-        bin_scatter_kernel<D><<<(unsigned)blocks, bin_block, lds_bins, s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG, mb);
+        const uint32_t bins = scatter_bins(bp.slices_f, bp.slices_c);
+        if (bp.slices_f + bp.slices_c >= kMinRunBins && bins <= kScatMaxBins) {
+            const int64_t runs = (int64_t)(b.merged ? Lh : Lh + Ld) * bp.chunks + (int64_t)mb.levels * ((mb.chunks + kScatSpan - 1) / kScatSpan);
+            if (int rc = allow_big_lds(bin_scatter_runs_kernel<D>, scatter_lds(bins))) return rc;
+            bin_scatter_runs_kernel<D><<<(unsigned)runs, kScatBlock, scatter_lds(bins), s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG, mb);
+        } else {
+            bin_scatter_kernel<D><<<(unsigned)blocks, bin_block, lds_bins, s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG, mb);
+        }
         if (int rc = launch_status("bin_scatter_kernel")) return rc;
     }
     if (Ld > 0 && !b.merged) {   // vertex-grid sums of the pre-reduced levels from their bins

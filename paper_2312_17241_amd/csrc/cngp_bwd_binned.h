@@ -25,7 +25,7 @@ namespace cngp {
 // Count and scatter run one workgroup per chunk of points.  With a single wavefront (the default block size)
 // the records a chunk adds to a bin follow the order of the points, so the drain's gathers of a batch of
 // records (the points and their upstream gradients) fall into a few cache lines instead of one line per
-// record; the host launches 256 lanes instead when there are many bins.
+// record; the host launches 256 lanes instead when there are more bins than the scatter in runs takes (cngp_bwd_runs.h).
 constexpr int kBinBlock = 64;
 
 // A binned corner reference: point index * 2^d + corner (the host keeps N * 2^d below 2^31 per pass).
@@ -290,6 +290,33 @@ __global__ __launch_bounds__(kOffsetsBlock) void bin_offsets_kernel(
     }
 }
 
+// A chunk of a pre-reduced level, binned by slice of its vertex grid.
+template <int D>
+__device__ __forceinline__ void scatter_grid_refs(
+    const Params &p, const BinParams &bp, const DenseLevels &dl, const float *__restrict__ x, const int64_t N, const uint32_t ld, const uint32_t chunk,
+    const uint32_t *__restrict__ cntG, BinRecord *__restrict__ recG, uint32_t *cursor)
+{
+    const uint32_t *rowG = cntG + ((size_t)ld * bp.chunks + chunk) * kGridBins;
+    for (uint32_t s = threadIdx.x; s < kGridBins; s += blockDim.x) cursor[s] = rowG[s];
+    __syncthreads();
+    BinRecord *outG = recG + (size_t)ld * bp.cap;
+    const int64_t m0 = (int64_t)chunk * bp.chunk_pts;
+    const int64_t m1 = (m0 + bp.chunk_pts < N) ? m0 + bp.chunk_pts : N;
+    for (int64_t n = m0 + threadIdx.x; n < m1; n += blockDim.x) {
+        float xp[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) xp[j] = x[n * D + j];
+        uint32_t v[1 << D];
+        corner_vertices<D>(xp, (float)p.N_l[ld], dl.side[ld], v);
+#pragma unroll
+        for (int c = 0; c < (1 << D); ++c) {
+            if (corner_weight<D>(xp, (float)p.N_l[ld], c) == 0.0f) continue;
+            const uint32_t pos = atomicAdd(&cursor[grid_bin(v[c])], 1u);
+            outG[pos] = ((uint32_t)n << D) | (uint32_t)c;
+        }
+    }
+}
+
 // Scatter, one workgroup per (level, chunk): first the merged levels, the one with the most entries first.
 template <int D>
 __global__ __launch_bounds__(256) void bin_scatter_kernel(
@@ -329,27 +356,8 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(
         return;
     }
     const uint32_t block = blockIdx.x - mb.levels * mb.chunks, li = block / bp.chunks, chunk = block % bp.chunks;
-    if (li >= (uint32_t)bp.nlevels) {                       // a pre-reduced level, binned by slice of its vertex grid
-        const uint32_t ld = li - (uint32_t)bp.nlevels;
-        const uint32_t *rowG = cntG + ((size_t)ld * bp.chunks + chunk) * kGridBins;
-        for (uint32_t s = threadIdx.x; s < kGridBins; s += blockDim.x) cursor[s] = rowG[s];
-        __syncthreads();
-        BinRecord *outG = recG + (size_t)ld * bp.cap;
-        const int64_t m0 = (int64_t)chunk * bp.chunk_pts;
-        const int64_t m1 = (m0 + bp.chunk_pts < N) ? m0 + bp.chunk_pts : N;
-        for (int64_t n = m0 + threadIdx.x; n < m1; n += blockDim.x) {
-            float xp[D];
-#pragma unroll
-            for (int j = 0; j < D; ++j) xp[j] = x[n * D + j];
-            uint32_t v[1 << D];
-            corner_vertices<D>(xp, (float)p.N_l[ld], dl.side[ld], v);
-#pragma unroll
-            for (int c = 0; c < (1 << D); ++c) {
-                if (corner_weight<D>(xp, (float)p.N_l[ld], c) == 0.0f) continue;
-                const uint32_t pos = atomicAdd(&cursor[grid_bin(v[c])], 1u);
-                outG[pos] = ((uint32_t)n << D) | (uint32_t)c;
-            }
-        }
+    if (li >= (uint32_t)bp.nlevels) {
+        scatter_grid_refs<D>(p, bp, dl, x, N, li - (uint32_t)bp.nlevels, chunk, cntG, recG, cursor);
         return;
     }
     const int      l = bp.level0 + (int)li;
