@@ -44,6 +44,7 @@ struct SliceParams {
     int32_t  store_direct;  // 1: every slice is written by exactly one workgroup -> plain stores
     int32_t  level0;        // levels [level0, level0 + nlevels) are covered by this launch
     int32_t  nlevels;
+    double  *partial;       // not NULL: every workgroup leaves its accumulators as they are, [level][chunk][slice], for bwd_partial_sums_kernel
 };
 
 // Levels whose dense vertex grid is small enough to pre-reduce the upstream gradient per vertex.
@@ -83,6 +84,12 @@ __device__ __forceinline__ SliceCoord slice_coord(const SliceParams &sp, const u
     c.chunk = rem / sp.slices;
     c.slice = rem % sp.slices;
     return c;
+}
+
+// A workgroup's accumulators, `n` doubles, where bwd_partial_sums_kernel looks for them.
+__device__ __forceinline__ void store_partial(const SliceParams &sp, const SliceCoord &co, const double *acc, const uint32_t n) {
+    double *out = sp.partial + (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * n;
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[i] = acc[i];
 }
 
 // A two-feature codebook entry as it sits in memory.
@@ -408,6 +415,7 @@ __device__ __forceinline__ void bwd_feat_sliced(
         scan_chunk<D, NP, true, false, float>(p, sp, co, x, grad + (size_t)l * N * 2, N, 0u, ring_mem, load, accum);
     __syncthreads();
 
+    if (sp.partial) return store_partial(sp, co, acc, plane * 2);
     float *out = gD_f + (size_t)l * p.N_f * 2 + (size_t)co.slice * plane * 2;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {     // i = (row * NP + k) * 2 + f
         const float v = (float)acc[(i & 1u) * plane + (i >> 1)];
@@ -451,6 +459,7 @@ __device__ __forceinline__ void bwd_logit_sliced(
         scan_chunk<D, NP, false, false, Raw>(p, sp, co, x, grad + (size_t)l * N * 2, N, 0u, ring_mem, load, accum);
     __syncthreads();
 
+    if (sp.partial) return store_partial(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)l * p.N_c + (size_t)co.slice * rows;
     const float *sig = sigma + row0 * NP;
@@ -573,6 +582,42 @@ __global__ __launch_bounds__(kSlicedBlock) void bwd_sliced_kernel(
         const SliceParams &sp = roles.sp[ROLE_GRID];
         bwd_vertex_grid<D, IoT>(p, dl, sp.chunks, sp.chunk_pts, sp.store_direct, wg - roles.first[ROLE_GRID], smem, x,
                                 dyT, G, N);
+    }
+}
+
+// Sums of what the chunks of a slice left, in fp64 and rounded once, for batches that are cut into many chunks to fill the chip: added to
+// the gradients with fp32 atomics, 16 chunks were off from 64 bits by 1.06e-7 (2-norm) where one is by 8.0e-8, and cost as much.  The
+// partial sums (at most 768 slices of 128 KB) are written and read once.  Blocks: 256 entries of a slice of the feature table (two sums
+// each), then 256 logits of a slice of the confidence table; a role whose slices have one chunk each has stored them itself.
+template <int NP>
+__global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
+    const Params p, const SliceParams sp_f, const SliceParams sp_c, const uint32_t blocks_f, const float *__restrict__ sigma,
+    const int zero_first, float *__restrict__ gD_f, float *__restrict__ gDhat_c)
+{
+    const bool         logit = blockIdx.x >= blocks_f;
+    const SliceParams &sp = logit ? sp_c : sp_f;
+    const uint32_t plane = NP << sp.rows_log2, per_slice = (plane + kBlock - 1) / kBlock;
+    const uint32_t unit = (blockIdx.x - (logit ? blocks_f : 0u)) / per_slice, i = (blockIdx.x - (logit ? blocks_f : 0u)) % per_slice * kBlock + threadIdx.x;
+    const uint32_t level = unit / sp.slices, slice = unit % sp.slices;
+    const size_t   n = logit ? plane : 2 * (size_t)plane, step = sp.slices * n;
+    const double  *in = sp.partial + ((size_t)level * sp.chunks * sp.slices + slice) * n + i;
+    if (i >= plane) return;                                   // (plane is a multiple of NP: whole rows)
+    if (logit) {
+        double Q = 0.0;
+        for (uint32_t c = 0; c < sp.chunks; ++c) Q += in[c * step];
+        const size_t at = ((size_t)(sp.level0 + (int)level) * p.N_c) * NP + (size_t)slice * plane + i;
+        const double s = (double)sigma[at];
+        double dot = s * Q;
+#pragma unroll
+        for (int o = NP / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, NP);
+        const float v = (float)(s * (Q - dot));
+        gDhat_c[at] = zero_first ? v : gDhat_c[at] + v;
+    } else {
+        double a = 0.0, b = 0.0;
+        for (uint32_t c = 0; c < sp.chunks; ++c) { a += in[c * step]; b += in[c * step + plane]; }
+        float *out = gD_f + 2 * ((size_t)(sp.level0 + (int)level) * p.N_f + (size_t)slice * plane + i);
+        out[0] = zero_first ? (float)a : out[0] + (float)a;
+        out[1] = zero_first ? (float)b : out[1] + (float)b;
     }
 }
 
