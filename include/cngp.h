@@ -255,7 +255,8 @@ int cngp_encode_bwd_input(const cngp_config *cfg, const float *x, int64_t N, con
  * cngp_bwd_merge_info; [6] .. [9] then describe no level); [2], [3] slices per level of the feature and
  * of the logit gradient table; [4], [5] point chunks of the feature / logit role on hashed levels;
  * [6], [7] vertex chunks of the two roles on pre-reduced levels; [8] point chunks and [9] total slices
- * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first, and then
+ * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first because of the number of
+ * slices (they are as well, whatever stands here, where levels are merged: cngp_bwd_merge_info), and then
  * [11], [12] workgroups that drain one bin of the feature / logit table and [13] point chunks of the binning;
  * with [2] = 0 when a level's feature table is small enough (N_f <= 4096) to be accumulated whole in LDS by the
  * workgroups that drain the confidence-table bins (one pass for both gradients, no pre-reduced levels);
@@ -274,8 +275,8 @@ int cngp_bwd_merge_info(const cngp_config *cfg, int64_t N, int32_t *info);
 
 /* Where cngp_encode_bwd keeps what in its workspace for this configuration and N (one pass of it, when the batch is
  * taken in passes).  Host only; for tests of the plan: region i covers bytes [regions[2i], regions[2i] + regions[2i+1])
- * -- the softmax table, the level-major dL/dy, the per-vertex sums, then for the binned variant the count matrices, bin
- * starts and records of the two tables and of the pre-reduced levels.  Where levels are merged, the third region and the last
+ * -- the softmax table, the level-major dL/dy, the per-vertex sums, then for a replicated scan in many chunks their partial sums of
+ * the two tables, for the binned variant the count matrices, bin starts and records of the two tables and of the pre-reduced levels.  Where levels are merged, the third region and the last
  * three hold the merge's arrays (cngp_bwd_merge_layout).  No two regions may overlap, every one
  * starts on a 256-byte boundary and ends inside cngp_workspace_bytes(cfg, N).  Returns the number of regions
  * (at most CNGP_PLAN_REGIONS; 0 for the variant that needs no workspace) or a negative status. */

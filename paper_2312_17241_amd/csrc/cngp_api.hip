@@ -552,6 +552,7 @@ struct BwdPlan {
     bool     split;                     // replicated scan in many chunks whose sums meet in the workspace (bwd_partial_sums_kernel)
     size_t   sigma_off, dyT_off, G_off, partF_off, partC_off, ws_bytes;
     bool     binned;                    // hashed levels: references binned by slice first (cngp_bwd_binned.h)
+    bool     few, scarce;               // ... because levels are merged, of tables whose slices alone would be scanned; either these or plain hashing of few slices
     bool     fused;                     // ... by slice of the confidence table only: a level's whole feature gradient sits in LDS beside it
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
     uint32_t subs_f, subs_c;            // drain workgroups per bin
@@ -569,6 +570,12 @@ constexpr uint64_t kMaxAutoBinBytes = 8ull << 30;   // workspace the library ask
 constexpr uint32_t kMaxFusedNf = 4096;          // largest feature table per level whose gradient is kept whole in LDS
 constexpr size_t   kFusedLdsBytes = 152 * 1024; // LDS of the workgroups that accumulate both gradients
 constexpr uint32_t kMinBinnedSlicesPerLevel = 24; // from here on binning the references beats the replicated scan
+// Plain hashing (N_p = 1), whose scans cost as much as any and whose references cost the least, is binned from fewer slices on: slices, and
+// slices times references per level.  Backward, scanned / binned, us: N_f = 2^17 (16 slices) d = 3, L = 8, 2^20 points 1030 / 379,
+// 2^18 278 / 149, L = 16 100000 217 / 131, 30000 97 / 107; d = 2 300000 244 / 142; d = 4 100000 300 / 144; N_f = 2^16 (8) d = 3, 2^18
+// 195 / 135, 100000 138 / 139, d = 4 2^18 473 / 308; d = 2, N_max = 512, 439631 points, four levels to scan (kMinMergedScans) 174 / 191.
+constexpr uint32_t kMinBinnedPlainSlices = 8;
+constexpr int64_t  kMinBinnedPlainScans = 12 << 20;
 constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated scan costs more than global atomics
 // Both gradient tables of a level (fp64) that a small batch accumulates in LDS.  420 drawn tables up to that size, 30 points to
 // 2^19 references, kernel alone against the direct one: 2.4x faster on average (up to 48 KB 2.6x, 96 .. 128 KB 1.6x), up to 145x
@@ -603,16 +610,26 @@ constexpr uint64_t kMinMergePerVertexPct = 240;
 // 8 + 64 797 / 746, 64 + 128 1078 / 997, d = 2, 32 + 32 999 / 922.  Below the line the scatter gains as well, but the drain loses as
 // much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.
 constexpr uint32_t kMinRunBins = 48;
+// Tables of fewer slices than kMinBinnedSlicesPerLevel are binned all the same where levels are merged (kMinMergeRefs and what stands
+// there): slices per level from which, and for N_p <= 2, whose references cost the least, slices times levels that a scan would not
+// pre-reduce.  Backward, scanned / binned with merged levels, us: image2d's tables (8 + 2 slices) 1021 / 778; 62 drawn batches of
+// 3 * 2^19 .. 2^23 references a level from the lines on 1.00 .. 2.5x, 1.33x on average.  Below: 1 + 1 slices 0.91, 2 + 1 0.93 .. 1.34,
+// 4 + 1 0.83 .. 1.37; 8 + 1 with N_p = 2 and five levels to scan 0.91.
+constexpr uint32_t kMinMergedSlices = 6;
+constexpr int64_t  kMinMergedScans = 48;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
 
 // Drain workgroups per bin of a table with `slices` slices per level: about 2^16 records each, and enough workgroups to
 // fill the chip twice, but never less than 8192 records each.  `refs` references per level, `levels` hashed levels.
-uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level) {
+// `longer`: of the long bins of a few slices, 1.5 times the records each, so that no more fp32 sums are added to an entry than the chunks
+// of a scan would add (error against 64 bits, 2-norm, scanned / 65536 records / 98304: image2d's tables 1.03e-7 / 1.05e-7 / 0.97e-7), and
+// the chip filled once where there is one table (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
+uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool longer = false, bool alone = false) {
     if (!slices) return 1;
-    double want = refs / slices / 65536.0;
-    const double fill = 512.0 / ((double)levels * slices_per_level), by_size = refs / slices / 8192.0;
+    double want = refs / slices / (longer ? 98304.0 : 65536.0);
+    const double fill = (alone ? 256.0 : 512.0) / ((double)levels * slices_per_level), by_size = refs / slices / 8192.0;
     if (want < fill) want = fill;
     if (want > by_size) want = by_size;
     const uint32_t r = (uint32_t)(want + 0.5);
@@ -849,6 +866,21 @@ int merge_levels(const cngp_config *c, int64_t N) {
     return M;
 }
 
+// Levels that a replicated scan over `per_level` slices pre-reduces: those whose dense vertex grid is small, much smaller than the number
+// of references, and takes clearly fewer slice scans than the level's hashed tables.
+int scan_dense_levels(const cngp_config *c, int64_t N, uint32_t per_level) {
+    uint32_t res[kMaxLevels];
+    level_table(c, res);
+    int l = 0;
+    for (; l < c->L && l < kMaxDense; ++l) {
+        uint64_t verts = 1;
+        for (int i = 0; i < c->d; ++i) verts *= (uint64_t)res[l] + 2;
+        const uint64_t slices = (verts + kDenseSliceVerts - 1) / kDenseSliceVerts;
+        if (verts > kMaxDenseVerts || (N << c->d) < kMinRefsPerVertex * (int64_t)verts || (slices * 2 > per_level && slices > 1)) break;
+    }
+    return l;
+}
+
 // Sums that the chunks of a role leave in the workspace.
 size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit) {
     const Geom &g = logit ? b.logit_pts : b.feat_pts;
@@ -898,9 +930,17 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     const uint64_t bin_bytes_max = c->bin_bytes_max ? c->bin_bytes_max : kMaxAutoBinBytes;
     // (with both gradients in one pass binning pays from four slices per level: below that the replicated scan is as fast)
     const bool plenty = (N << c->d) * c->L >= kMinBinnedRefs;           // below, the three extra launches cost more than they save
-    b.binned = bin_ok && plenty && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4)) && bin_bytes <= bin_bytes_max;
+    const bool plain = c->N_p == 1 && per_level >= kMinBinnedPlainSlices && (N << c->d) * (int64_t)per_level >= kMinBinnedPlainScans &&
+                       (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >= kMinMergedScans;
+    b.binned = bin_ok && plenty && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
+    // tables of a few slices, where enough of the levels are merged
+    b.few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && per_level >= kMinMergedSlices &&
+            !(c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE)) && !c->bin_bytes_max && (N << c->d) >= kMinMergeRefs &&
+            merge_levels(c, N) >= (c->N_p > 1 ? 1 : 4) && (c->N_p > 2 || (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >= kMinMergedScans);
+    b.binned = b.binned || b.few;
+    b.scarce = b.binned && per_level < kMinBinnedSlicesPerLevel && !fused_ok;
     b.fused = b.binned && fused_ok;
     if (b.fused) {
         b.rows_c_log2 = fused_rows_c_log2;
@@ -968,8 +1008,8 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.bin_chunk_pts = (uint32_t)cp;
         b.bin_chunks = (uint32_t)((N + cp - 1) / cp);
         const double refs = (double)((uint64_t)N << c->d);
-        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c);
-        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c);
+        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
+        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
@@ -1635,7 +1675,7 @@ int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
         b.sliced ? 1 : 0, b.merged ? 0 : b.dense.count, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
         (int32_t)b.feat_pts.chunks, (int32_t)b.logit_pts.chunks, b.merged ? 1 : (int32_t)b.feat_vtx.chunks,
         b.merged ? 1 : (int32_t)b.logit_vtx.chunks, b.merged ? 0 : (int32_t)b.grid.chunks, (int32_t)b.dense_slices,
-        b.binned ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
+        b.binned && !b.few ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
         (int32_t)(N > 0 ? (N + per - 1) / per : 1)};
     for (int i = 0; i < CNGP_PLAN_INFO_COUNT; ++i) info[i] = v[i];
     return CNGP_OK;

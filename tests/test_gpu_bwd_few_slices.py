@@ -1,0 +1,65 @@
+"""Backward of large batches with tables of a few slices, which is binned where levels are merged or there is no probing, and scanned in a
+smaller workspace (csrc/cngp_api.hip, kMinMergedSlices and kMinBinnedPlainScans), against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2312_17241_amd as cngp
+import workloads as W
+from parity import check_close
+
+pytestmark = pytest.mark.gpu
+SCAN, DRAIN, MERGE = "encode_bwd_sliced_points_and_grid", "encode_bwd_bin_drain", "encode_bwd_merge"
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def run(w, args, room=None, start=None, **kw):
+    cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS if start is None else 0, **kw)
+    ws = torch.full((cngp.workspace_bytes(cfg, w.N) if room is None else room,), 0xAB, dtype=torch.uint8, device="cuda")
+    gF, gC = (torch.full(s, float("nan") if start is None else start, device="cuda") for s in ((w.L, w.N_f, 2), (w.L, w.N_c, w.N_p)))
+    cngp.profile_enable(True)
+    cngp.profile_read()
+    try:
+        cngp.encode_bwd(cfg, *(dev(a) for a in args), gF, gC, workspace=ws)
+        torch.cuda.synchronize()
+        names = {k for k, (_, n) in cngp.profile_read().items() if n}
+    finally:
+        cngp.profile_enable(False)
+    return gF.cpu().numpy(), gC.cpu().numpy(), names
+
+
+@pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_min,N_max,feat,io,merged", [
+    (2, 400003, 16, 2**16, 2**12, 8, 16, 8192, "f16", "f16", True),    # 8 + 2 slices
+    (3, 196609, 8, 2**15, 2**12, 8, 16, 600, "f16", "f32", True),      # 4 + 2: the fewest; little more than the fewest points
+    (3, 200003, 8, 2**13, 2**15, 4, 30, 600, "f32", "f16", True),      # 1 + 8
+    (2, 500009, 8, 2**16, 2**10, 2, 200, 4000, "f16", "f16", True),    # N_p = 2: 8 + 1, six levels a scan would not pre-reduce
+    (3, 196613, 8, 2**16, 1, 1, 60, 8192, "f32", "f32", False),        # plain hashing, three levels that could be merged: binned without
+    (3, 110003, 8, 2**17, 1, 1, 60, 2048, "f16", "f16", False),        # 16 slices, fewer points
+])
+def test_tables_of_few_slices_are_binned(d, N, L, N_f, N_c, N_p, N_min, N_max, feat, io, merged):
+    w = W.custom(cfg=140, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N, feat_dtype=feat, io_dtype=io)
+    D_f = W.make_feature_codebook(w)
+    args = W.make_points(w), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w), W.make_upstream_grad(w)
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args)
+
+    def check(gF, gC, start=0.0):
+        check_close("grad D_f", gF, gF_ref + start, A_f + abs(start), fp16_out=False)
+        check_close("grad Dhat_c", gC, gC_ref + start, A_c + abs(start), fp16_out=False)
+
+    gF, gC, names = run(w, args)
+    assert DRAIN in names and SCAN not in names and (MERGE in names) == merged
+    check(gF, gC)
+    gF, gC, names = run(w, args, start=0.5)
+    assert DRAIN in names
+    check(gF, gC, 0.5)
+    if merged:
+        cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, bin_bytes_max=8 << 30)     # (a bound: nothing is merged for it)
+        room = cngp.workspace_bytes(cfg, N)
+        assert room < cngp.workspace_bytes(cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS), N)
+        gF, gC, names = run(w, args, room=room)
+        assert SCAN in names and DRAIN not in names
+        check(gF, gC)
