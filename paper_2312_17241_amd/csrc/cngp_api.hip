@@ -728,8 +728,7 @@ void choose_geometry(const cngp_config *c, int64_t N, BwdPlan &b, const bool spl
             const double t = simulate_makespan(batches, n);
             if (best < 0.0 || t < best) { best = t; b.logit_pts = gc; b.feat_pts = gf; }
         }
-    // (plain hashing, whose references cost the least: only where it fills less than half of the chip)
-    if (!split || workgroups(b.logit_pts, b.feat_pts) >= (c->N_p > 1 ? kFilledWorkgroups : kFilledWorkgroups / 2)) return;
+    if (!split || workgroups(b.logit_pts, b.feat_pts) >= kFilledWorkgroups) return;
     // A batch that leaves CUs without a workgroup is cut finer, to chunks of 512 points: costs that follow N_p, the grid sums that share
     // the launch, and the partial sums of slices with several chunks (per 64 bytes of gradient, as much as an atomic would take); of the choices within 5 % of
     // the shortest the one with the fewest workgroups.  Of 70 drawn configurations (d = 2 .. 4, 1 .. 23 slices, every N_p, 2^16 .. 2^22
@@ -754,7 +753,9 @@ void choose_geometry(const cngp_config *c, int64_t N, BwdPlan &b, const bool spl
     };
     struct Tried { double t; int64_t groups; Geom gc, gf; };
     std::vector<Tried> tried;
-    best = cost(b.logit_pts, b.feat_pts) * 0.89;         // (a gain that the costs cannot tell from none is left)
+    // a gain that the costs cannot tell from none is left; of plain hashing, whose scans they overrate, a gain of less than three times
+    // (d = 3, N_f = 2^8, L = 16, 31452 ray samples, 45 workgroups made 120: 83 us, 90)
+    best = cost(b.logit_pts, b.feat_pts) * (c->N_p > 1 ? 0.89 : 0.35);
     for (const int64_t cc : kTry)
         for (const int64_t cf : kTry) {
             if ((cc > 1 && (cc * 512 > N || !b.slices_c)) || (cf > 1 && cf * 512 > N)) continue;
