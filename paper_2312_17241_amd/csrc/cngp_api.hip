@@ -592,8 +592,9 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // Backward, us, without / with merging, at 2^19, 2^20, 3 * 2^19 and 2^21 references per level: nerf3d's tables 244 / 238, 334 / 306,
 // 434 / 403, 541 / 489; sdf3d's 351 / 236, 507 / 407, 669 / 576, 831 / 739; d = 2 (N_f = 2^18, N_c = 2^16, N_p = 8) 343 / 208,
 // 661 / 325, 800 / 463, 926 / 596; N_f = 2^18, N_c = 2^14, N_p = 4 197 / 175, 270 / 231, 343 / 314, 429 / 371; plain hashing
-// (N_f = 2^19) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  The line is on the safe side: batches
-// from it on are the ones that the figures below were drawn from; that it pays from 2^20 on was seen on these tables only.
+// (N_f = 2^19) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  81 drawn batches of 2^20 .. 3 * 2^19 references a level of tables that are
+// binned either way: 1.33x faster on average, the slowest 0.94x (307 us, 289); from 2^19 .. 2^20 0.86 .. 1.1x.  The line is an eighth above
+// kMinBinnedPrereduceRefs: up to there callers know the pre-reduced layout by its smaller workspace.
 // Points anything but evenly spread, without / with: all equal 1719 / 1279 (nerf3d's tables, 2^18 points), in a cube of side 0.02
 // 1233 / 812, on a line 1145 / 951, on a plane 544 / 519; sdf3d's 2^20 points 6127 / 3684, 3693 / 2137, 3548 / 2329, 2780 / 2139.
 // Sum of the kernels of a step, us, lines at 20 / 80 / 150 / 300 / 1500: nerf3d 728 / 611 / 594 / 587 / 601 (649 with grid sums),
@@ -603,7 +604,7 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // Backward without / with merging over 110 drawn configurations from that batch size on: d = 3 1.19x faster on average (slowest 0.95x),
 // d = 2 1.28x; d = 4, where two or three levels have that many references per vertex, 0.99x (0.78 .. 1.21), and small feature
 // tables with d = 2 and N_p = 2, whose references cost the least, 0.90x: neither is merged.
-constexpr int64_t  kMinMergeRefs = 3 << 19;
+constexpr int64_t  kMinMergeRefs = 9 << 17;
 constexpr uint64_t kMinMergePerVertexPct = 240;
 // Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us: sdf3d's tables (32 + 32
 // bins) 30000 points 150 / 140, 100000 345 / 309, 2^18 uniform 723 / 656, 2^20 near a surface 2407 / 2170; 32 + 16 bins 681 / 632,
@@ -611,10 +612,11 @@ constexpr uint64_t kMinMergePerVertexPct = 240;
 // much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.
 constexpr uint32_t kMinRunBins = 48;
 // Tables of fewer slices than kMinBinnedSlicesPerLevel are binned all the same where levels are merged (kMinMergeRefs and what stands
-// there): slices per level from which, and for N_p <= 2, whose references cost the least, slices times levels that a scan would not
-// pre-reduce.  Backward, scanned / binned with merged levels, us: image2d's tables (8 + 2 slices) 1021 / 778; 62 drawn batches of
+// there): references per level from which (59 drawn batches of 2^20 .. 3 * 2^19 scanned / binned: 0.54 .. 1.76x), slices per level from
+// which, and for N_p <= 2, whose references cost the least, slices times levels that a scan would not pre-reduce.  Backward, scanned / binned with merged levels, us: image2d's tables (8 + 2 slices) 1021 / 778; 62 drawn batches of
 // 3 * 2^19 .. 2^23 references a level from the lines on 1.00 .. 2.5x, 1.33x on average.  Below: 1 + 1 slices 0.91, 2 + 1 0.93 .. 1.34,
 // 4 + 1 0.83 .. 1.37; 8 + 1 with N_p = 2 and five levels to scan 0.91.
+constexpr int64_t  kMinMergedRefs = 3 << 19;
 constexpr uint32_t kMinMergedSlices = 6;
 constexpr int64_t  kMinMergedScans = 48;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
@@ -938,7 +940,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
     // tables of a few slices, where enough of the levels are merged
     b.few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && per_level >= kMinMergedSlices &&
-            !(c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE)) && !c->bin_bytes_max && (N << c->d) >= kMinMergeRefs &&
+            !(c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE)) && !c->bin_bytes_max && (N << c->d) >= kMinMergedRefs &&
             merge_levels(c, N) >= (c->N_p > 1 ? 1 : 4) && (c->N_p > 2 || (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >= kMinMergedScans);
     b.binned = b.binned || b.few;
     b.scarce = b.binned && per_level < kMinBinnedSlicesPerLevel && !fused_ok;
