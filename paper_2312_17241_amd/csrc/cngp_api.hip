@@ -576,6 +576,11 @@ constexpr uint32_t kMinBinnedSlicesPerLevel = 24; // from here on binning the re
 // 195 / 135, 100000 138 / 139, d = 4 2^18 473 / 308; d = 2, N_max = 512, 439631 points, four levels to scan (kMinMergedScans) 174 / 191.
 constexpr uint32_t kMinBinnedPlainSlices = 8;
 constexpr int64_t  kMinBinnedPlainScans = 12 << 20;
+// One drain workgroup per bin then, where no levels are merged (fp64 sums, rounded once), and stretches of kPlainGridRecords of the grid sums'
+// records each: with 32768, and two to five workgroups per bin, more fp32 sums met in an entry than the scan's chunks add (error against 64
+// bits, 2-norm, scanned / so / now: N_f = 2^17, L = 8, 2^18 points 6.7e-8 / 7.6e-8 / 5.7e-8, 700009 points 9.0e-8 / 10.5e-8 / 6.6e-8).
+// Fewer bins than kMinBinnedPlainGroups would leave CUs idle (L = 8, 8 slices, 520823 points: 335 us, so 401).
+constexpr int64_t  kMinBinnedPlainGroups = 96, kPlainGridRecords = 131072;
 constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated scan costs more than global atomics
 // Both gradient tables of a level (fp64) that a small batch accumulates in LDS.  420 drawn tables up to that size, 30 points to
 // 2^19 references, kernel alone against the direct one: 2.4x faster on average (up to 48 KB 2.6x, 96 .. 128 KB 1.6x), up to 145x
@@ -934,7 +939,8 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     // (with both gradients in one pass binning pays from four slices per level: below that the replicated scan is as fast)
     const bool plenty = (N << c->d) * c->L >= kMinBinnedRefs;           // below, the three extra launches cost more than they save
     const bool plain = c->N_p == 1 && per_level >= kMinBinnedPlainSlices && (N << c->d) * (int64_t)per_level >= kMinBinnedPlainScans &&
-                       (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >= kMinMergedScans;
+                       (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >=
+                           (c->d <= 3 && layout == LAYOUT_MERGED && !c->bin_bytes_max && (N << c->d) >= kMinMergeRefs && merge_levels(c, N) >= 4 ? kMinMergedScans : kMinBinnedPlainGroups);
     b.binned = bin_ok && plenty && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
@@ -1002,6 +1008,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             b.dense_verts = b.dense_slices = b.dense_max_verts = 0;
         }
     }
+    const bool plain_bins = b.scarce && c->N_p == 1 && !b.merged && !(c->flags & CNGP_BWD_BINNED);     // (kMinBinnedPlainGroups)
     const int Lh = c->L - b.dense.count;
     if (b.sliced) choose_geometry(c, N, b, layout == LAYOUT_MERGED && !c->bin_bytes_max);
     if (b.binned) {
@@ -1013,6 +1020,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         const double refs = (double)((uint64_t)N << c->d);
         b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
         b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
+        if (plain_bins) b.subs_f = 1;
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
@@ -1075,7 +1083,8 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             // workgroups per slice of a level's grid: about 2^15 references each
             uint32_t next = 0;
             for (int l = 0; l < b.dense.count && !b.merged; ++l) {
-                uint64_t subs = (cap / b.dense.slices[l] + 32767) / 32768;
+                const uint64_t each = plain_bins ? kPlainGridRecords : 32768;
+                uint64_t subs = (cap / b.dense.slices[l] + each - 1) / each;
                 if (subs < 1) subs = 1;
                 if (subs > 256) subs = 256;
                 b.grid_drain.first[l] = next;
