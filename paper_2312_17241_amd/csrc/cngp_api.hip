@@ -938,9 +938,11 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     const uint64_t bin_bytes_max = c->bin_bytes_max ? c->bin_bytes_max : kMaxAutoBinBytes;
     // (with both gradients in one pass binning pays from four slices per level: below that the replicated scan is as fast)
     const bool plenty = (N << c->d) * c->L >= kMinBinnedRefs;           // below, the three extra launches cost more than they save
-    const bool plain = c->N_p == 1 && per_level >= kMinBinnedPlainSlices && (N << c->d) * (int64_t)per_level >= kMinBinnedPlainScans &&
+    // (these and the tables of a few slices below are scanned in a workspace that holds no bins, and under a bound on them)
+    const bool plain = c->N_p == 1 && layout != LAYOUT_LEAST && !c->bin_bytes_max &&
+                       per_level >= kMinBinnedPlainSlices && (N << c->d) * (int64_t)per_level >= kMinBinnedPlainScans &&
                        (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >=
-                           (c->d <= 3 && layout == LAYOUT_MERGED && !c->bin_bytes_max && (N << c->d) >= kMinMergeRefs && merge_levels(c, N) >= 4 ? kMinMergedScans : kMinBinnedPlainGroups);
+                           (c->d <= 3 && layout == LAYOUT_MERGED && (N << c->d) >= kMinMergeRefs && merge_levels(c, N) >= 4 ? kMinMergedScans : kMinBinnedPlainGroups);
     b.binned = bin_ok && plenty && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
@@ -1139,6 +1141,8 @@ int64_t bwd_pass_points(const cngp_config *c, int64_t N) {
     const int64_t per = ((N + passes - 1) / passes + 63) / 64 * 64;
     return make_bwd_plan_uncached(c, per).binned ? per : N;
 }
+// Whether passes of `per` points are scanned where the room for their bins is missing.
+bool scanned_in_least_room(const cngp_config *c, int64_t per) { return !make_bwd_plan_uncached(c, per, LAYOUT_LEAST).binned; }
 
 template <int NP>
 BinParams make_bin_params(const cngp_config *c, const BwdPlan &b, int64_t N) {
@@ -1491,11 +1495,12 @@ size_t workspace_bytes_pairs(const cngp_config *cfg, int64_t N) {
     return per >= N ? make_bwd_plan(cfg, N).ws_bytes : workspace_bytes_passes(cfg, N, per, LAYOUT_MERGED);
 }
 // The smallest workspace with which cngp_encode_bwd runs (in passes: without merging, which may take three times as much and is
-// left out by bwd_plan_for where it does not fit).
+// left out by bwd_plan_for where it does not fit; tables that are scanned without room for the bins: without those).
 size_t least_workspace_pairs(const cngp_config *cfg, int64_t N) {
     const size_t  bytes = workspace_bytes_pairs(cfg, N);
     const int64_t per = bwd_pass_points(cfg, N);
-    const size_t  least = per < N ? workspace_bytes_passes(cfg, N, per, LAYOUT_FAST) : make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes;
+    const size_t  least = per < N ? workspace_bytes_passes(cfg, N, per, scanned_in_least_room(cfg, per) ? LAYOUT_LEAST : LAYOUT_FAST)
+                                  : make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes;
     return least < bytes ? least : bytes;
 }
 
@@ -1824,7 +1829,9 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
     if (N > 0 && (!x || !D_f || !Dhat_c || !dy)) return CNGP_ERR_NULL;
     if (cfg->F != 2) return bwd_planes(cfg, x, N, D_f, Dhat_c, dy, grad_D_f, grad_Dhat_c, workspace, workspace_bytes, stream);
     hipStream_t s = (hipStream_t)stream;
-    const int64_t per = bwd_pass_points(cfg, N);
+    int64_t per = bwd_pass_points(cfg, N);
+    // (passes whose bins do not fit, of tables that are scanned then: one scan where that fits, which adds fewer fp32 sums to an entry than scans in passes)
+    if (per < N && !bwd_plan_for(cfg, per, workspace_bytes).binned && make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes <= workspace_bytes) per = N;
     if (per < N) {      // several passes over runs of points; the first one clears if asked, the rest accumulate
         if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < least_workspace_pairs(cfg, N))
             return CNGP_ERR_WORKSPACE;

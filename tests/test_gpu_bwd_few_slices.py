@@ -56,10 +56,9 @@ def test_tables_of_few_slices_are_binned(d, N, L, N_f, N_c, N_p, N_min, N_max, f
     gF, gC, names = run(w, args, start=0.5)
     assert DRAIN in names
     check(gF, gC, 0.5)
-    if merged:
-        cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, bin_bytes_max=8 << 30)     # (a bound: nothing is merged for it)
-        room = cngp.workspace_bytes(cfg, N)
-        assert room < cngp.workspace_bytes(cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS), N)
-        gF, gC, names = run(w, args, room=room)
-        assert SCAN in names and DRAIN not in names
-        check(gF, gC)
+    cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, bin_bytes_max=8 << 30)     # (a bound: the scan)
+    room = cngp.workspace_bytes(cfg, N)
+    assert room < cngp.workspace_bytes(cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS), N)
+    gF, gC, names = run(w, args, room=room)
+    assert SCAN in names and DRAIN not in names
+    check(gF, gC)

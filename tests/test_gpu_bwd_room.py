@@ -71,6 +71,21 @@ def test_a_batch_in_passes_runs_in_the_room_of_its_unmerged_layout(F):
     assert e.value.status == cngp.ERR_WORKSPACE
 
 
+def test_plain_hashing_in_passes_is_scanned_in_one_without_room_for_its_bins():
+    N = 8_500_003
+    cfg = cngp.Config(d=4, L=16, F=2, N_f=2**17, N_c=1, N_p=1, N_min=16, N_max=256, feat_dtype=cngp.F16, io_dtype=cngp.F16, flags=cngp.ZERO_GRADS)
+    need, room = cngp.workspace_bytes(cfg, N), cngp.workspace_bytes(dataclasses.replace(cfg, bin_bytes_max=1 << 20), N)
+    assert cngp.bwd_plan_info(cfg, N)["passes"] == 2 and need > 2 * room
+    g = torch.Generator(device="cuda").manual_seed(4)
+    D_f, dy = (torch.randn(s, generator=g, device="cuda", dtype=torch.float16) for s in ((16, 2**17, 2), (N, 32)))
+    args = (torch.rand((N, 4), generator=g, device="cuda"), D_f, torch.zeros((16, 1, 1), device="cuda"), dy)
+    run = lambda size: launches(lambda: cngp.encode_bwd(cfg, *args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")))
+    got, narrow = run(room)
+    ref, wide = run(need)
+    assert narrow["encode_bwd_sliced_points_and_grid"] == 1 and narrow.get("encode_bwd_bin_drain", 0) == 0 and wide["encode_bwd_bin_drain"] == 2
+    same(got[:1], ref[:1])                                          # (without probing the logits' gradient is zero)
+
+
 def test_static_scratch_takes_in_one_pass_what_fits_pre_reduced():
     """48000 points of the headline shape: 62 MB with the coarse levels pre-reduced, more without; the array holds 64."""
     w = W.custom(cfg=97, d=3, L=16, F=2, N_f=2**16, N_c=2**14, N_p=16, N_min=16, N_max=2048, N=48000, feat_dtype="f16", io_dtype="f16")
