@@ -587,7 +587,8 @@ __global__ __launch_bounds__(kSlicedBlock) void bwd_sliced_kernel(
 
 // Sums of what the chunks of a slice left, in fp64 and rounded once, for batches that are cut into many chunks to fill the chip: added to
 // the gradients with fp32 atomics, 16 chunks were off from 64 bits by 1.06e-7 (2-norm) where one is by 8.0e-8, and cost as much.  The
-// partial sums (at most 768 slices of 128 KB) are written and read once.  Blocks: 256 entries of a slice of the feature table (two sums
+// partial sums (at most 768 slices of 128 KB) are written and read once.  Gradients that are added to are added to with atomics all the
+// same: another call may add to them at the same time, from another stream and workspace.  Blocks: 256 entries of a slice of the feature table (two sums
 // each), then 256 logits of a slice of the confidence table; a role whose slices have one chunk each has stored them itself.
 template <int NP>
 __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
@@ -611,13 +612,18 @@ __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
 #pragma unroll
         for (int o = NP / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, NP);
         const float v = (float)(s * (Q - dot));
-        gDhat_c[at] = zero_first ? v : gDhat_c[at] + v;
+        if (zero_first) gDhat_c[at] = v;
+        else if (v != 0.0f) atomic_add(gDhat_c + at, v);
     } else {
         double a = 0.0, b = 0.0;
         for (uint32_t c = 0; c < sp.chunks; ++c) { a += in[c * step]; b += in[c * step + plane]; }
         float *out = gD_f + 2 * ((size_t)(sp.level0 + (int)level) * p.N_f + (size_t)slice * plane + i);
-        out[0] = zero_first ? (float)a : out[0] + (float)a;
-        out[1] = zero_first ? (float)b : out[1] + (float)b;
+        const float v0 = (float)a, v1 = (float)b;
+        if (zero_first) { out[0] = v0; out[1] = v1; }
+        else {
+            if (v0 != 0.0f) atomic_add(out, v0);
+            if (v1 != 0.0f) atomic_add(out + 1, v1);
+        }
     }
 }
 

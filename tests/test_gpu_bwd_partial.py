@@ -89,6 +89,25 @@ def test_a_workspace_without_the_room_for_partial_sums_is_enough():
     assert e.value.status == cngp.ERR_WORKSPACE
 
 
+def test_calls_on_two_streams_add_to_the_same_gradients():
+    """Each with a workspace of its own: no sum of either is lost, as where the chunks' sums are added with atomics."""
+    w, times = workload(3, 25752, 8, 2**13, 2**11, 16, 16, 512), 8
+    args = inputs(w)
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args)
+    cfg = cngp.Config.from_workload(w, flags=0)
+    t = [dev(a) for a in args]
+    gF, gC = torch.zeros((w.L, w.N_f, 2), device="cuda"), torch.zeros((w.L, w.N_c, w.N_p), device="cuda")
+    sides = [(torch.cuda.Stream(), cngp.alloc_workspace(cfg, w.N)) for _ in range(2)]
+    torch.cuda.synchronize()
+    for _ in range(times):
+        for stream, ws in sides:
+            with torch.cuda.stream(stream):
+                cngp.encode_bwd(cfg, *t, gF, gC, workspace=ws)
+    torch.cuda.synchronize()
+    check_close("grad D_f", gF.cpu().numpy(), 2 * times * gF_ref, 2 * times * A_f, fp16_out=False)
+    check_close("grad Dhat_c", gC.cpu().numpy(), 2 * times * gC_ref, 2 * times * A_c, fp16_out=False)
+
+
 def test_capture_replays_partial_sums():
     w = workload(3, 25752, 8, 2**13, 2**11, 16, 16, 512)
     args = inputs(w)
