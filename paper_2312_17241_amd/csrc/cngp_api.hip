@@ -552,6 +552,7 @@ struct BwdPlan {
     bool     split;                     // replicated scan in many chunks whose sums meet in the workspace (bwd_partial_sums_kernel)
     size_t   sigma_off, dyT_off, G_off, partF_off, partC_off, ws_bytes;
     bool     binned;                    // hashed levels: references binned by slice first (cngp_bwd_binned.h)
+    bool     summed;                    // ... and the sums of a bin's drain workgroups meet in the workspace, where the merged entries were
     bool     few, scarce;               // ... because levels are merged, of tables whose slices alone would be scanned; either these or plain hashing of few slices
     bool     fused;                     // ... by slice of the confidence table only: a level's whole feature gradient sits in LDS beside it
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
@@ -630,12 +631,10 @@ constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pa
 
 // Drain workgroups per bin of a table with `slices` slices per level: about 2^16 records each, and enough workgroups to
 // fill the chip twice, but never less than 8192 records each.  `refs` references per level, `levels` hashed levels.
-// `longer`: of the long bins of a few slices, 1.5 times the records each, so that no more fp32 sums are added to an entry than the chunks
-// of a scan would add (error against 64 bits, 2-norm, scanned / 65536 records / 98304: image2d's tables 1.03e-7 / 1.05e-7 / 0.97e-7), and
-// the chip filled once where there is one table (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
-uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool longer = false, bool alone = false) {
+// `alone`: of plain hashing with few slices, whose one table has few bins, enough to fill it once (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
+uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool alone = false) {
     if (!slices) return 1;
-    double want = refs / slices / (longer ? 98304.0 : 65536.0);
+    double want = refs / slices / 65536.0;
     const double fill = (alone ? 256.0 : 512.0) / ((double)levels * slices_per_level), by_size = refs / slices / 8192.0;
     if (want < fill) want = fill;
     if (want > by_size) want = by_size;
@@ -889,11 +888,26 @@ int scan_dense_levels(const cngp_config *c, int64_t N, uint32_t per_level) {
     return l;
 }
 
-// Sums that the chunks of a role leave in the workspace.
-size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit) {
-    const Geom &g = logit ? b.logit_pts : b.feat_pts;
+// Sums that `writers` workgroups per slice of a table leave in the workspace on `levels` levels.
+size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit, uint32_t writers, int levels) {
     const size_t slice = ((size_t)c->N_p << (logit ? b.rows_c_log2 : b.rows_f_log2)) * (logit ? 1 : 2) * sizeof(double);
-    return b.split && g.chunks > 1 ? (size_t)(c->L - b.dense.count) * g.chunks * (logit ? b.slices_c : b.slices_f) * slice : 0;
+    return writers > 1 ? (size_t)levels * writers * (logit ? b.slices_c : b.slices_f) * slice : 0;
+}
+size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit) {
+    return b.split ? partial_bytes(c, b, logit, (logit ? b.logit_pts : b.feat_pts).chunks, c->L - b.dense.count) : 0;
+}
+// Where a binned batch's drain leaves them, from the start of the merged entries on, which nothing reads any more: roles as in PartialRoles.
+struct DrainPartials { uint32_t writers[4]; size_t off[4], bytes; };
+DrainPartials drain_partials(const cngp_config *c, const BwdPlan &b) {
+    const uint32_t writers[4] = {b.subs_f, b.subs_c, b.feat_vtx.chunks, b.logit_vtx.chunks};
+    DrainPartials d;
+    d.bytes = 0;
+    for (int r = 0; r < 4; ++r) {
+        d.writers[r] = b.summed ? writers[r] : 0;
+        d.off[r] = d.bytes;
+        d.bytes += align256(partial_bytes(c, b, r & 1, d.writers[r], r < 2 ? c->L - b.dense.count : b.dense.count));
+    }
+    return d;
 }
 
 BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = LAYOUT_MERGED) {
@@ -1020,14 +1034,20 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.bin_chunk_pts = (uint32_t)cp;
         b.bin_chunks = (uint32_t)((N + cp - 1) / cp);
         const double refs = (double)((uint64_t)N << c->d);
-        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
-        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
+        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce && c->N_p == 1);
+        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce && c->N_p == 1);
         if (plain_bins) b.subs_f = 1;
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
             b.feat_vtx = Geom{b.fused ? 2u : (b.subs_f + 1) / 2, 0};
             b.logit_vtx = Geom{(b.subs_c + 1) / 2, 0};
+            // Of tables of few slices, which a scan gives up to a dozen chunks per slice, a bin has up to 64 workgroups: their sums meet in
+            // fp64.  Error against 64 bits, 2-norm, logit gradient, scanned / added with fp32 atomics / so: d = 3, L = 12, 8 + 1 slices,
+            // 745393 points, 61 workgroups 1.15e-7 / 1.46e-7 / 0.80e-7; image2d's tables 1.03e-7 / 0.98e-7 / 0.75e-7; none of twelve
+            // tables above 0.83e-7.  568 drawn batches are as fast as with the atomics and 98304 records a workgroup (0.99x on average; image2d's
+            // step 850 us, so 883).
+            b.summed = b.scarce;
             b.merge.levels = (uint32_t)b.dense.count;
             // chunks of at least two rounds, at most 512 of them: sparse parts of space leave several times the entries of
             // dense ones, and the many short workgroups even that out.  With 128 slices of a table or more at most as many as the
@@ -1055,7 +1075,11 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.G_off = b.dyT_off + align256((size_t)N * c->L * c->F * io);
         b.G_bytes = (size_t)b.dense_verts * 2 * sizeof(float);
         MergedSpace m;
-        if (b.merged) { m = merged_space(b, N, c->d); b.G_bytes = m.G_bytes; }
+        if (b.merged) {
+            m = merged_space(b, N, c->d);
+            const size_t sums = drain_partials(c, b).bytes;
+            b.G_bytes = m.G_bytes > sums ? m.G_bytes : sums;
+        }
         b.ws_bytes = b.G_off + align256(b.G_bytes);
         if (b.split) {
             b.partF_off = b.ws_bytes;
@@ -1161,6 +1185,20 @@ BinParams make_bin_params(const cngp_config *c, const BwdPlan &b, int64_t N) {
 uint32_t most_bins_of(const BinParams &bp) { return bp.slices_f + bp.slices_c > kGridBins ? bp.slices_f + bp.slices_c : kGridBins; }
 uint32_t hist_replicas_of(uint32_t most_bins) { return most_bins <= 64 ? 16u : most_bins <= 512 ? 4u : 1u; }
 
+// What the workgroups of a slice left, added up; nothing where no role has any.
+template <int NP>
+int launch_partial_sums(const Params &p, PartialRoles &roles, const float *sigma, bool zero_first, float *gD_f, float *gDhat_c, hipStream_t s) {
+    roles.first[0] = 0;
+    for (int r = 0; r < 4; ++r) {
+        const SliceParams &sp = roles.sp[r];
+        roles.first[r + 1] = roles.first[r] + (sp.partial ? (uint32_t)sp.nlevels * sp.slices * ((((uint32_t)NP << sp.rows_log2) + kBlock - 1) / kBlock) : 0u);
+    }
+    if (roles.first[4] == 0) return CNGP_OK;
+    LaunchTimer t(s, K_BWD_PARTIAL);
+    bwd_partial_sums_kernel<NP><<<roles.first[4], kBlock, 0, s>>>(p, roles, sigma, zero_first ? 1 : 0, gD_f, gDhat_c);
+    return launch_status("bwd_partial_sums_kernel");
+}
+
 // Binned variant: (the count has run with the preparation launch) merge of the merged levels, offsets, scatter (+ vertex-grid accumulation of the dense levels), drain
 // (+ the two roles of the dense levels, which scan the finished vertex grids).
 template <int D, int NP, typename FeatT, typename IoT>
@@ -1245,16 +1283,23 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
         wgs = (slices && nlevels > 0) ? (uint32_t)kXcds * (((uint32_t)nlevels * sp.slices * sp.chunks + kXcds - 1) / kXcds) : 0u;
         return sp;
     };
+    const DrainPartials left = drain_partials(c, b);
     uint32_t wgs_c = 0, wgs_f = 0, wgs_cv = 0, wgs_fv = 0;
     const uint32_t slices_c = NP > 1 ? b.slices_c : 0;
-    const SliceParams sp_c = role(b.rows_c_log2, slices_c, Geom{b.subs_c, 0}, Ld, Lh, wgs_c);
-    const SliceParams sp_f = role(b.rows_f_log2, b.fused ? 0u : b.slices_f, Geom{b.subs_f, 0}, Ld, Lh, wgs_f);
+    SliceParams sp_c = role(b.rows_c_log2, slices_c, Geom{b.subs_c, 0}, Ld, Lh, wgs_c);
+    SliceParams sp_f = role(b.rows_f_log2, b.fused ? 0u : b.slices_f, Geom{b.subs_f, 0}, Ld, Lh, wgs_f);
     BwdRoles vtx;
     std::memset(&vtx, 0, sizeof(vtx));
     vtx.sp[ROLE_LOGIT_VTX] = role(b.rows_c_log2, slices_c, b.logit_vtx, 0, Ld, wgs_cv);
     vtx.sp[ROLE_FEAT_VTX] = role(b.rows_f_log2, b.merged && b.fused ? 0u : b.slices_f, b.feat_vtx, 0, Ld, wgs_fv);
     vtx.first[ROLE_LOGIT_VTX] = 0;
     vtx.first[ROLE_FEAT_VTX] = wgs_cv;
+    PartialRoles sums;
+    SliceParams *const drained[4] = {&sp_f, &sp_c, &vtx.sp[ROLE_FEAT_VTX], &vtx.sp[ROLE_LOGIT_VTX]};
+    for (int r = 0; r < 4; ++r) {
+        if (left.writers[r] > 1) drained[r]->partial = (double *)((char *)G + left.off[r]);
+        sums.sp[r] = *drained[r];
+    }
     auto kernel = bin_drain_kernel<D, NP, FeatT, IoT>;
     size_t lds = b.lds_f > b.lds_c ? b.lds_f : b.lds_c;                 // slice + the vertex roles' ring buffers
     if (b.fused) {
@@ -1264,10 +1309,13 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     if (int rc = allow_big_lds(kernel, lds)) return rc;
     const uint32_t total = wgs_c + wgs_f + wgs_cv + wgs_fv;
     if (total == 0) return CNGP_OK;
-    LaunchTimer t(s, K_BWD_BIN_DRAIN);
-    kernel<<<total, kSlicedBlock, lds, s>>>(p, sp_c, sp_f, wgs_c, wgs_c + wgs_f, x, dyT, N, (const FeatT *)D_f, sigma, recF, recC,
-                                            baseF, baseC, bp.cap, vtx, b.dense, G, b.merged ? 1 : 0, mb, gD_f, gDhat_c);
-    return launch_status("bin_drain_kernel");
+    {
+        LaunchTimer t(s, K_BWD_BIN_DRAIN);
+        kernel<<<total, kSlicedBlock, lds, s>>>(p, sp_c, sp_f, wgs_c, wgs_c + wgs_f, x, dyT, N, (const FeatT *)D_f, sigma, recF, recC,
+                                                baseF, baseC, bp.cap, vtx, b.dense, G, b.merged ? 1 : 0, mb, gD_f, gDhat_c);
+        if (int rc = launch_status("bin_drain_kernel")) return rc;
+    }
+    return launch_partial_sums<NP>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
 }
 
 template <int D, int NP, typename FeatT, typename IoT>
@@ -1332,7 +1380,8 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
     const size_t lds_grid = (size_t)kDenseSliceVerts * 2 * sizeof(double);
     if (Ld > 0 && lds_grid > lds) lds = lds_grid;
     if (int rc = allow_big_lds(kernel, lds)) return rc;
-    SliceParams sum_f, sum_c;                  // what the chunks of the point roles leave
+    PartialRoles sums;                         // what the chunks of the point roles leave
+    std::memset(&sums, 0, sizeof(sums));
     for (int launch = 0; launch < 2; ++launch) {
         BwdRoles roles;
         std::memset(&roles, 0, sizeof(roles));
@@ -1368,18 +1417,9 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
         LaunchTimer t(s, pts ? K_BWD_SLICED : K_BWD_SLICED_V);
         kernel<<<next, kSlicedBlock, lds, s>>>(p, roles, b.dense, x, (const FeatT *)D_f, sigma, dyT, G, gD_f, gDhat_c, N);
         if (int rc = launch_status("bwd_sliced_kernel")) return rc;
-        if (pts) { sum_c = roles.sp[ROLE_LOGIT_PTS]; sum_f = roles.sp[ROLE_FEAT_PTS]; }
+        if (pts) { sums.sp[0] = roles.sp[ROLE_FEAT_PTS]; sums.sp[1] = roles.sp[ROLE_LOGIT_PTS]; }
     }
-    if (b.split) {
-        const auto blocks_of = [&](const SliceParams &sp) {
-            return sp.partial ? (uint32_t)sp.nlevels * sp.slices * ((((uint32_t)NP << sp.rows_log2) + kBlock - 1) / kBlock) : 0u;
-        };
-        const uint32_t blocks_f = blocks_of(sum_f), blocks_c = blocks_of(sum_c);
-        LaunchTimer t(s, K_BWD_PARTIAL);
-        bwd_partial_sums_kernel<NP><<<blocks_f + blocks_c, kBlock, 0, s>>>(p, sum_f, sum_c, blocks_f, sigma, zero_first ? 1 : 0, gD_f, gDhat_c);
-        return launch_status("bwd_partial_sums_kernel");
-    }
-    return CNGP_OK;
+    return launch_partial_sums<NP>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
 }
 
 // LDS of encode_bwd_small_kernel, 0 where it is not taken.
@@ -1858,11 +1898,12 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
         const int64_t per_f = (int64_t)cfg->N_f * cfg->F, per_c = (int64_t)cfg->N_c * cfg->N_p;
         const bool    sl = N > 0 && b.sliced;
         const int     Ld = sl ? b.dense.count : 0, Lh = cfg->L - Ld;
-        if (!(sl && b.feat_vtx.chunks == 1) && Ld > 0) z.add(grad_D_f, per_f * Ld);
-        const uint32_t wg_f = b.binned ? b.subs_f : b.split ? 1u : b.feat_pts.chunks, wg_c = b.binned ? b.subs_c : b.split ? 1u : b.logit_pts.chunks;
+        const bool    once = b.split || b.summed;       // partial sums: an entry is written once
+        if (!(sl && (b.feat_vtx.chunks == 1 || b.summed)) && Ld > 0) z.add(grad_D_f, per_f * Ld);
+        const uint32_t wg_f = once ? 1u : b.binned ? b.subs_f : b.feat_pts.chunks, wg_c = once ? 1u : b.binned ? b.subs_c : b.logit_pts.chunks;
         if (!(sl && wg_f == 1) && Lh > 0) z.add(grad_D_f + per_f * Ld, per_f * Lh);
         const bool logit = sl && cfg->N_p > 1;
-        if (!(logit && b.logit_vtx.chunks == 1) && Ld > 0) z.add(grad_Dhat_c, per_c * Ld);
+        if (!(logit && (b.logit_vtx.chunks == 1 || b.summed)) && Ld > 0) z.add(grad_Dhat_c, per_c * Ld);
         if (!(logit && wg_c == 1) && Lh > 0) z.add(grad_Dhat_c + per_c * Ld, per_c * Lh);
     }
     if (N == 0) return z.launch(s);

@@ -665,7 +665,7 @@ __device__ __forceinline__ SliceCoord merged_coord(const SliceParams &sp, const 
     return c;
 }
 
-// sp: rows_log2, slices, chunks (= drain workgroups per bin), store_direct, level0, nlevels as in the sliced variant.
+// sp: rows_log2, slices, chunks (= drain workgroups per bin), store_direct, level0, nlevels, partial as in the sliced variant.
 template <int D, int NP, bool MERGED, typename IoT, typename Record>
 __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
                                            const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
@@ -696,6 +696,14 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
     drain_records<D, NP, float, false, 2, true, MERGED>(p, recF + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                                           (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
+    if (sp.partial) {                                                      // as bwd_partial_sums_kernel reads them: all of feature 0, then feature 1
+        double *left = sp.partial + (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
+        for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {
+            const uint32_t f = i >= plane ? 1u : 0u, e = i - f * plane;
+            left[i] = acc[(e / NP) * (2 * NP) + f * NP + (e % NP)];
+        }
+        return;
+    }
     float *out = gD_f + (size_t)co.level * p.N_f * 2 + (size_t)co.slice * plane * 2;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {     // i = (row * NP + k) * 2 + f
         const uint32_t e = i >> 1;
@@ -734,6 +742,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
     drain_records<D, NP, Raw, false, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                               (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
+    if (sp.partial) return store_partial(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)co.level * p.N_c + (size_t)co.slice * rows;
     const float *sig = sigma + row0 * NP;

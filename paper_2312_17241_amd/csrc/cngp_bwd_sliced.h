@@ -587,24 +587,31 @@ __global__ __launch_bounds__(kSlicedBlock) void bwd_sliced_kernel(
 
 // Sums of what the chunks of a slice left, in fp64 and rounded once, for batches that are cut into many chunks to fill the chip: added to
 // the gradients with fp32 atomics, 16 chunks were off from 64 bits by 1.06e-7 (2-norm) where one is by 8.0e-8, and cost as much.  The
-// partial sums (at most 768 slices of 128 KB) are written and read once.  Gradients that are added to are added to with atomics all the
+// partial sums (at most 768 slices of 128 KB) are written and read once.  Of binned batches with tables of few slices the workgroups that
+// drain a bin leave theirs the same way.  Gradients that are added to are added to with atomics all the
 // same: another call may add to them at the same time, from another stream and workspace.  Blocks: 256 entries of a slice of the feature table (two sums
 // each), then 256 logits of a slice of the confidence table; a role whose slices have one chunk each has stored them itself.
+struct PartialRoles {
+    SliceParams sp[4];          // feature, logit; of a binned batch those of its merged levels after them
+    uint32_t    first[5];       // first block of each
+};
 template <int NP>
 __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
-    const Params p, const SliceParams sp_f, const SliceParams sp_c, const uint32_t blocks_f, const float *__restrict__ sigma,
-    const int zero_first, float *__restrict__ gD_f, float *__restrict__ gDhat_c)
+    const Params p, const PartialRoles roles, const float *__restrict__ sigma, const int zero_first, float *__restrict__ gD_f, float *__restrict__ gDhat_c)
 {
-    const bool         logit = blockIdx.x >= blocks_f;
-    const SliceParams &sp = logit ? sp_c : sp_f;
-    const uint32_t plane = NP << sp.rows_log2, per_slice = (plane + kBlock - 1) / kBlock;
-    const uint32_t unit = (blockIdx.x - (logit ? blocks_f : 0u)) / per_slice, i = (blockIdx.x - (logit ? blocks_f : 0u)) % per_slice * kBlock + threadIdx.x;
+    int role = 0;
+    while (role < 3 && blockIdx.x >= roles.first[role + 1]) ++role;
+    const bool         logit = role & 1;
+    const SliceParams &sp = roles.sp[role];
+    const uint32_t block = blockIdx.x - roles.first[role], plane = NP << sp.rows_log2, per_slice = (plane + kBlock - 1) / kBlock;
+    const uint32_t unit = block / per_slice, i = block % per_slice * kBlock + threadIdx.x;
     const uint32_t level = unit / sp.slices, slice = unit % sp.slices;
     const size_t   n = logit ? plane : 2 * (size_t)plane, step = sp.slices * n;
     const double  *in = sp.partial + ((size_t)level * sp.chunks * sp.slices + slice) * n + i;
     if (i >= plane) return;                                   // (plane is a multiple of NP: whole rows)
     if (logit) {
         double Q = 0.0;
+#pragma unroll 4
         for (uint32_t c = 0; c < sp.chunks; ++c) Q += in[c * step];
         const size_t at = ((size_t)(sp.level0 + (int)level) * p.N_c) * NP + (size_t)slice * plane + i;
         const double s = (double)sigma[at];
@@ -616,6 +623,7 @@ __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
         else if (v != 0.0f) atomic_add(gDhat_c + at, v);
     } else {
         double a = 0.0, b = 0.0;
+#pragma unroll 4
         for (uint32_t c = 0; c < sp.chunks; ++c) { a += in[c * step]; b += in[c * step + plane]; }
         float *out = gD_f + 2 * ((size_t)(sp.level0 + (int)level) * p.N_f + (size_t)slice * plane + i);
         const float v0 = (float)a, v1 = (float)b;

@@ -345,6 +345,34 @@ def test_arrays_of_the_merged_levels_do_not_overlap():
     assert merged >= 100 and min(seen.values()) >= 3, (merged, seen)
 
 
+def test_sums_of_drain_workgroups_fit_where_the_entries_were():
+    """Tables of few slices whose levels are merged: what the workgroups of a bin leave, 64-bit sums of a whole slice each, lies inside the
+    region that the merged entries had, which is as large as the larger of the two."""
+    rng = np.random.default_rng(77)
+    seen = {"sums": 0, "larger": 0, "plain": 0}
+    for it in range(600):
+        d, N_p = int(rng.choice([2, 3])), int(2 ** rng.integers(0, 5))
+        N_f, N_c = int(2 ** rng.integers(13, 18)), int(2 ** rng.integers(1, 15)) if N_p > 1 else 1
+        L, N_min, N = int(rng.integers(2, 17)), int(rng.integers(8, 90)), int(2 ** rng.uniform(20.6 - d, 21.5 - d if it % 2 else 21.5))
+        cfg = cngp.Config.from_workload(W.custom(cfg=7, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_min * 64, N=N, feat_dtype="f16", io_dtype="f16"),
+                                        flags=cngp.ZERO_GRADS)
+        p = cngp.bwd_plan_info(cfg, N)
+        if p["merged_levels"] == 0 or p["slices_f"] == 0 or p["slices_f"] + p["slices_c"] >= 24:
+            continue
+        M = p["merged_levels"]
+        tables = [(p["slices_f"], N_f * 16 // p["slices_f"], p["drain_wgs_feat"], p["merged_drain_wgs_feat"])]
+        if N_p > 1:
+            tables.append((p["slices_c"], N_c * N_p * 8 // p["slices_c"], p["drain_wgs_logit"], p["merged_drain_wgs_logit"]))
+        sums = sum(s * b * n * levels for s, b, wgs, merged in tables for n, levels in ((wgs, L - M), (merged, M)) if n > 1)
+        regions = cngp.bwd_plan_layout(cfg, N)
+        entries = (M * (N << d) * 16 + 255) // 256 * 256                          # (the order of the points and the cells behind them)
+        assert regions[2][1] >= max(sums, entries) and regions[2][0] + regions[2][1] <= regions[3][0]
+        seen["sums"] += sums > 0
+        seen["larger"] += sums > entries
+        seen["plain"] += N_p == 1 and sums > 0
+    assert min(seen.values()) >= 3, seen
+
+
 def test_small_binned_batches_pre_reduce_where_the_coarse_bins_are_uneven():
     """Below 2^20 references per level the plan weighs pre-reducing the coarse levels against binning them: many levels with
     few vertices (d = 2) pre-reduce, three-dimensional batches of ray samples bin everything; a caller who bounds the bins,

@@ -10,7 +10,7 @@ import workloads as W
 from parity import check_close
 
 pytestmark = pytest.mark.gpu
-SCAN, DRAIN, MERGE = "encode_bwd_sliced_points_and_grid", "encode_bwd_bin_drain", "encode_bwd_merge"
+SCAN, DRAIN, MERGE, SUMS = "encode_bwd_sliced_points_and_grid", "encode_bwd_bin_drain", "encode_bwd_merge", "encode_bwd_partial_sums"
 
 
 def dev(a):
@@ -20,7 +20,7 @@ def dev(a):
 def run(w, args, room=None, start=None, **kw):
     cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS if start is None else 0, **kw)
     ws = torch.full((cngp.workspace_bytes(cfg, w.N) if room is None else room,), 0xAB, dtype=torch.uint8, device="cuda")
-    gF, gC = (torch.full(s, float("nan") if start is None else start, device="cuda") for s in ((w.L, w.N_f, 2), (w.L, w.N_c, w.N_p)))
+    gF, gC = (torch.full(s, float("nan") if start is None else start, device="cuda") for s in ((w.L, w.N_f, w.F), (w.L, w.N_c, w.N_p)))
     cngp.profile_enable(True)
     cngp.profile_read()
     try:
@@ -62,3 +62,62 @@ def test_tables_of_few_slices_are_binned(d, N, L, N_f, N_c, N_p, N_min, N_max, f
     gF, gC, names = run(w, args, room=room)
     assert SCAN in names and DRAIN not in names
     check(gF, gC)
+
+
+@pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_min,N_max", [
+    (3, 745393, 8, 2**16, 2**11, 8, 40, 2048),                          # one logit slice: 64 workgroups a bin, a scan of nine chunks at most
+    (2, 900001, 6, 2**16, 2**10, 2, 200, 8192),
+    (3, 400003, 8, 2**13, 2**16, 4, 40, 600),                           # one feature slice
+    (3, 600011, 16, 2**16, 1, 1, 16, 2048),                             # plain hashing: levels enough that a scan would not pre-reduce (96 bins)
+])
+def test_binning_few_slices_is_no_less_precise_than_scanning_them(d, N, L, N_f, N_c, N_p, N_min, N_max):
+    """2-norm error against 64 bits, both gradients: the sums of a bin's workgroups meet in 64 bits, a scan's chunks in 32."""
+    w = W.custom(cfg=141, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N, feat_dtype="f16", io_dtype="f16")
+    D_f = W.make_feature_codebook(w)
+    args = W.make_points(w), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w), W.make_upstream_grad(w)
+    refs = oracle.encode_bwd(w, *args)[:2]
+    room = cngp.workspace_bytes(cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, bin_bytes_max=8 << 30), N)
+    binned, scanned = run(w, args), run(w, args, room=room)
+    assert MERGE in binned[2] and SUMS in binned[2] and SCAN in scanned[2]
+    for got, scan, ref in zip(binned, scanned, refs):
+        off, off_scan = (float(np.linalg.norm(g.astype(np.float64) - ref)) for g in (got, scan))
+        assert off <= off_scan
+
+
+def test_sums_of_drain_workgroups_with_the_sparse_softmax_other_widths_and_capture():
+    w = W.custom(cfg=142, d=3, L=8, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=900, N=200003, feat_dtype="f16", io_dtype="f16")
+    D_f = W.make_feature_codebook(w)
+    args = W.make_points(w), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w), W.make_upstream_grad(w)
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args, top_k=3)
+    gF, gC, names = run(w, args, top_k=3)
+    assert SUMS in names
+    check_close("grad D_f", gF, gF_ref, A_f, fp16_out=False)
+    check_close("grad Dhat_c", gC, gC_ref, A_c, fp16_out=False)
+    cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, top_k=3)
+    t, ws = [dev(a) for a in args], cngp.alloc_workspace(cfg, w.N)
+    gF, gC = torch.empty((w.L, w.N_f, 2), device="cuda"), torch.empty((w.L, w.N_c, w.N_p), device="cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        cngp.encode_bwd(cfg, *t, gF, gC, workspace=ws)
+    torch.cuda.current_stream().wait_stream(side)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cngp.encode_bwd(cfg, *t, gF, gC, workspace=ws)
+    for _ in range(3):
+        gF.fill_(float("nan")); gC.fill_(float("nan")); ws.fill_(0xCD)
+        graph.replay()
+        torch.cuda.synchronize()
+        check_close("grad D_f", gF.cpu().numpy(), gF_ref, A_f, fp16_out=False)
+        check_close("grad Dhat_c", gC.cpu().numpy(), gC_ref, A_c, fp16_out=False)
+        cngp.encode_bwd(cfg, *t, gF, gC, workspace=ws)          # eager work between the replays
+        (gF.sum() + gC.sum()).item()
+    w4 = W.custom(cfg=143, d=3, L=8, F=4, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=900, N=200003, feat_dtype="f32", io_dtype="f32")
+    D_f = W.make_feature_codebook(w4)
+    args = W.make_points(w4), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w4), W.make_upstream_grad(w4)
+    gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w4, *args)
+    for start in (None, 0.5):
+        gF, gC, names = run(w4, args, start=start)
+        assert SUMS in names
+        check_close("grad D_f", gF, gF_ref + (start or 0.0), A_f + (start or 0.0), fp16_out=False)
+        check_close("grad Dhat_c", gC, gC_ref + (start or 0.0), A_c + (start or 0.0), fp16_out=False)
