@@ -618,13 +618,18 @@ constexpr uint64_t kMinMergePerVertexPct = 240;
 // much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.
 constexpr uint32_t kMinRunBins = 48;
 // Tables of fewer slices than kMinBinnedSlicesPerLevel are binned all the same where levels are merged (kMinMergeRefs and what stands
-// there): references per level from which (59 drawn batches of 2^20 .. 3 * 2^19 scanned / binned: 0.54 .. 1.76x), slices per level from
-// which, and for N_p <= 2, whose references cost the least, slices times levels that a scan would not pre-reduce.  Backward, scanned / binned with merged levels, us: image2d's tables (8 + 2 slices) 1021 / 778; 62 drawn batches of
-// 3 * 2^19 .. 2^23 references a level from the lines on 1.00 .. 2.5x, 1.33x on average.  Below: 1 + 1 slices 0.91, 2 + 1 0.93 .. 1.34,
-// 4 + 1 0.83 .. 1.37; 8 + 1 with N_p = 2 and five levels to scan 0.91.
+// there) and few_slices_pay says so: references per level from which (59 drawn batches of 2^20 .. 3 * 2^19 scanned / binned: 0.54 .. 1.76x),
+// slices per level from which, slices times levels that a scan would not pre-reduce, and what the scan has to do per reference that is
+// binned.  image2d's tables (8 + 2 slices): backward 958 us scanned, 783 binned.  1742 drawn batches of these tables (d = 2 and 3, 2 .. 16
+// levels, every N_p from 2 on, 3 * 2^19 .. 2^23 references a level, uniform points, rays and a shell), scanned / binned: all of them 1.24x,
+// but the slowest 0.19x (every level pre-reduced: 79.6 us, 411), and 300 below 0.97x; the 912 that these lines take 1.47x, the slowest 0.88x
+// (shell, 407.7 us, 463), 14 below 0.97x.  With six slices 1.1x at most on average, down to 0.81x.
+// They ask for up to 65 times the workspace of the scan, 28 times on the median (image2d's 66 -> 1994 MB; 2^21 points 4238, 3 * 2^20 6354), and
+// from where that passes kMaxAutoBinBytes, at 2^22 points there, the batch is scanned; so is one in a smaller workspace.
 constexpr int64_t  kMinMergedRefs = 3 << 19;
-constexpr uint32_t kMinMergedSlices = 6;
+constexpr uint32_t kMinMergedSlices = 8;
 constexpr int64_t  kMinMergedScans = 48;
+constexpr double   kMinMergedGain = 2.8;
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -873,8 +878,14 @@ int merge_levels(const cngp_config *c, int64_t N) {
     return M;
 }
 
-// Levels that a replicated scan over `per_level` slices pre-reduces: those whose dense vertex grid is small, much smaller than the number
-// of references, and takes clearly fewer slice scans than the level's hashed tables.
+// Whether a level with `verts` vertices is pre-reduced: its dense vertex grid is small, much smaller than the number of references, and takes
+// clearly fewer slice scans than the level's hashed tables.
+bool pre_reduces(uint64_t verts, int64_t refs, uint32_t per_level) {
+    const uint64_t slices = (verts + kDenseSliceVerts - 1) / kDenseSliceVerts;
+    return verts <= kMaxDenseVerts && refs >= kMinRefsPerVertex * (int64_t)verts && (slices * 2 <= per_level || slices <= 1);
+}
+
+// Levels that a replicated scan over `per_level` slices pre-reduces.
 int scan_dense_levels(const cngp_config *c, int64_t N, uint32_t per_level) {
     uint32_t res[kMaxLevels];
     level_table(c, res);
@@ -882,10 +893,19 @@ int scan_dense_levels(const cngp_config *c, int64_t N, uint32_t per_level) {
     for (; l < c->L && l < kMaxDense; ++l) {
         uint64_t verts = 1;
         for (int i = 0; i < c->d; ++i) verts *= (uint64_t)res[l] + 2;
-        const uint64_t slices = (verts + kDenseSliceVerts - 1) / kDenseSliceVerts;
-        if (verts > kMaxDenseVerts || (N << c->d) < kMinRefsPerVertex * (int64_t)verts || (slices * 2 > per_level && slices > 1)) break;
+        if (!pre_reduces(verts, N << c->d, per_level)) break;
     }
     return l;
+}
+
+// Whether binning pays for tables of few slices where levels are merged (kMinMergedRefs).  A scan reads every point once per slice of the
+// levels it does not pre-reduce, with less to do in a slice of logits, and adds up every reference; a merged level leaves less than half
+// of its references to the bins.
+bool few_slices_pay(const cngp_config *c, int64_t N, uint32_t slices_f, uint32_t slices_c) {
+    const int    D = scan_dense_levels(c, N, slices_f + slices_c), U = c->L - D, M = merge_levels(c, N);
+    const double corners = 1 << c->d, refs = 2.0 * corners;
+    const double scan = U * (slices_f + 0.5 * slices_c + 2.0 * refs) + 0.8 * D * corners, binned = (c->L - M + 0.45 * M) * refs;
+    return M >= 1 && slices_f + slices_c >= kMinMergedSlices && U * (int64_t)(slices_f + slices_c) >= kMinMergedScans && scan >= kMinMergedGain * binned;
 }
 
 // Sums that `writers` workgroups per slice of a table leave in the workspace on `levels` levels.
@@ -961,9 +981,9 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
     // tables of a few slices, where enough of the levels are merged
-    b.few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && per_level >= kMinMergedSlices &&
+    b.few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && c->N_p > 1 &&
             !(c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE)) && !c->bin_bytes_max && (N << c->d) >= kMinMergedRefs &&
-            merge_levels(c, N) >= (c->N_p > 1 ? 1 : 4) && (c->N_p > 2 || (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >= kMinMergedScans);
+            few_slices_pay(c, N, b.slices_f, b.slices_c);
     b.binned = b.binned || b.few;
     b.scarce = b.binned && per_level < kMinBinnedSlicesPerLevel && !fused_ok;
     b.fused = b.binned && fused_ok;
@@ -1002,9 +1022,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
             uint64_t verts = 1;
             for (int i = 0; i < c->d; ++i) verts *= (uint64_t)res[l] + 2;
             const uint64_t slices = (verts + kDenseSliceVerts - 1) / kDenseSliceVerts;
-            if (verts > kMaxDenseVerts) break;
-            if ((N << c->d) < kMinRefsPerVertex * (int64_t)verts && !(b.binned && layout == LAYOUT_LEAST)) break;
-            if (slices * 2 > per_level && slices > 1) break;
+            if (!pre_reduces(verts, b.binned && layout == LAYOUT_LEAST ? INT64_MAX : N << c->d, per_level)) break;
             if (b.fused) break;      // both gradients from one pass over the bins: cheaper than the grid sums and vertex scans (measured)
             if (b.binned && l == c->L - 1) break;                        // (at least one level stays hashed)
             b.dense.side[l] = res[l] + 2;

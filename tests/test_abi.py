@@ -218,6 +218,21 @@ def test_backward_plan_is_reported_on_the_host():
     assert cngp.bwd_plan_info(cngp.Config.from_workload(big), big.N)["sliced"] == 0     # too many slices
 
 
+@pytest.mark.parametrize("d,L,N_f,N_c,N_p,N_min,N_max,N,merged", [
+    (2, 16, 2**16, 2**12, 8, 16, 8192, 2**20, 11),             # 8 + 2 slices, seven of sixteen levels that a scan pre-reduces
+    (3, 8, 2**16, 2**11, 8, 40, 2048, 745393, 3),              # 8 + 1, none of eight
+    (2, 12, 2**16, 2**6, 4, 16, 75, 1411859, 0),               # a scan pre-reduces every level: 174 us, binned 619
+    (2, 6, 2**17, 2**6, 4, 16, 65, 394677, 0),                 # the same: 40 us, binned 211
+    (3, 14, 2**14, 2**15, 2, 64, 5041, 637972, 0),             # 2 + 4 slices: 775 us, binned 1199
+    (2, 8, 2**15, 2**14, 4, 16, 273, 1891700, 0),              # two levels to scan of eight: 422 us, binned 593
+    (3, 9, 2**15, 2**14, 2, 64, 1027, 446890, 0),              # 4 + 2: 430 us, binned 562
+])
+def test_tables_of_few_slices_are_binned_only_where_a_scan_has_enough_to_do(d, L, N_f, N_c, N_p, N_min, N_max, N, merged):
+    p = cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(cfg=7, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N,
+                                                              feat_dtype="f16", io_dtype="f16"), flags=cngp.ZERO_GRADS), N)
+    assert p["merged_levels"] == merged and 8 <= p["slices_f"] + p["slices_c"] + 2 < 24
+
+
 def test_merged_levels_are_reported_as_what_they_are():
     """Levels are either merged or pre-reduced on their grids: never both, and each under its own name."""
     plan = lambda flags=0, **kw: cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(**kw), flags=cngp.ZERO_GRADS | flags), kw["N"])

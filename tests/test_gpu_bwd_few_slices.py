@@ -34,8 +34,8 @@ def run(w, args, room=None, start=None, **kw):
 
 @pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_min,N_max,feat,io,merged", [
     (2, 400003, 16, 2**16, 2**12, 8, 16, 8192, "f16", "f16", True),    # 8 + 2 slices
-    (3, 196609, 8, 2**15, 2**12, 8, 16, 600, "f16", "f32", True),      # 4 + 2: the fewest; little more than the fewest points
-    (3, 200003, 8, 2**13, 2**15, 4, 30, 600, "f32", "f16", True),      # 1 + 8
+    (3, 196609, 8, 2**15, 2**13, 8, 36, 400, "f16", "f32", True),      # 4 + 4: the fewest; little more than the fewest points
+    (3, 200003, 8, 2**13, 2**16, 4, 30, 600, "f32", "f16", True),      # 1 + 16
     (2, 500009, 8, 2**16, 2**10, 2, 200, 4000, "f16", "f16", True),    # N_p = 2: 8 + 1, six levels a scan would not pre-reduce
     (3, 196613, 12, 2**16, 1, 1, 100, 8192, "f32", "f32", False),      # plain hashing, 8 slices on 12 levels, none that could be merged
     (3, 110003, 8, 2**17, 1, 1, 60, 2048, "f16", "f16", False),        # 16 slices, fewer points
