@@ -615,7 +615,10 @@ constexpr uint64_t kMinMergePerVertexPct = 240;
 // Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us: sdf3d's tables (32 + 32
 // bins) 30000 points 150 / 140, 100000 345 / 309, 2^18 uniform 723 / 656, 2^20 near a surface 2407 / 2170; 32 + 16 bins 681 / 632,
 // 8 + 64 797 / 746, 64 + 128 1078 / 997, d = 2, 32 + 32 999 / 922.  Below the line the scatter gains as well, but the drain loses as
-// much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.
+// much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.  A table with a single
+// bin has nothing to gain, and its drain lives on the order that a lone wavefront keeps: 72 drawn batches of such tables 0.99x,
+// 27 of them below 0.97x (128 + 1 bins, d = 3, 358780 points: 288 us, in runs 328), while those of two bins and more in both tables, or of plain
+// hashing, gain 1.02 .. 1.19x.
 constexpr uint32_t kMinRunBins = 48;
 // Tables of fewer slices than kMinBinnedSlicesPerLevel are binned all the same where levels are merged (kMinMergeRefs and what stands
 // there) and few_slices_pay says so: references per level from which (59 drawn batches of 2^20 .. 3 * 2^19 scanned / binned: 0.54 .. 1.76x),
@@ -1240,7 +1243,7 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     if (int rc = check_blocks(blocks)) return rc;
     const size_t lds_bins = (size_t)most_bins_of(bp) * sizeof(uint32_t);
     // Direct scatter: one wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
-    // like (measured: drain 7 % faster); with more bins than the scatter in runs takes, four wavefronts share the cursors
+    // like (measured: drain 7 % faster); with kMinRunBins bins and more, where the scatter in runs is not taken, four wavefronts share the cursors
     // (a lone one fills its cache lines too slowly for the memory system to merge the 4-byte writes).
     if constexpr (D <= 3) if (b.merged) {      // the points in the order of their cells (the histogram ran with the preparation), then the entries
         {
@@ -1271,7 +1274,7 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     {
         LaunchTimer t(s, K_BWD_BIN_SCATTER);
         const uint32_t bins = scatter_bins(bp.slices_f, bp.slices_c);
-        if (bp.slices_f + bp.slices_c >= kMinRunBins && bins <= kScatMaxBins) {
+        if (bp.slices_f + bp.slices_c >= kMinRunBins && bins <= kScatMaxBins && bp.slices_f != 1 && bp.slices_c != 1) {
             const int64_t runs = (int64_t)(b.merged ? Lh : Lh + Ld) * bp.chunks + (int64_t)mb.levels * ((mb.chunks + kScatSpan - 1) / kScatSpan);
             if (int rc = allow_big_lds(bin_scatter_runs_kernel<D>, scatter_lds(bins))) return rc;
             bin_scatter_runs_kernel<D><<<(unsigned)runs, kScatBlock, scatter_lds(bins), s>>>(p, bp, b.dense, x, N, cntF, cntC, cntG, recF, recC, recG, mb);

@@ -1,4 +1,4 @@
-// Scatter of the binned backward pass in runs, for levels of 48 bins and more.
+// Scatter of the binned backward pass in runs, for levels of 48 bins and more with more than one of either table.
 //
 // Written straight from the lanes that found them (bin_scatter_kernel), the 64 records of a store go to almost as many bins, and a
 // cache line is requested for each: texture addressers at work 98.7 % of the time (2^20 points near a surface, 64 bins a level: 400 us).

@@ -44,7 +44,7 @@ def check(w, slices, x=None, flags=cngp.ZERO_GRADS | cngp.BWD_BINNED, **want):
     (3, 60001, 2**21, 2**19, 8, (256, 256), 0),                # the most bins
     (3, 30001, 2**21, 2**20, 8, (256, 512), 0),                # more than that
     (3, 200003, 2**18, 2**15, 8, (32, 16), 3),                 # entries of merged levels
-    (2, 400003, 2**19, 2**12, 2, (64, 1), 3),
+    (2, 400003, 2**19, 2**12, 2, (64, 1), 3),                  # a single bin of one table: written directly
     (2, 400003, 2**21, 1, 1, (256, 0), 0),                     # (plain hashing with three levels is not merged)
 ])
 def test_scatter_in_runs_against_the_oracle(d, N, N_f, N_c, N_p, slices, merged):
