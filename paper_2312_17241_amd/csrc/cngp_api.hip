@@ -625,14 +625,15 @@ constexpr uint32_t kMinRunBins = 48;
 // slices per level from which, slices times levels that a scan would not pre-reduce, and what the scan has to do per reference that is
 // binned.  image2d's tables (8 + 2 slices): backward 958 us scanned, 783 binned.  1742 drawn batches of these tables (d = 2 and 3, 2 .. 16
 // levels, every N_p from 2 on, 3 * 2^19 .. 2^23 references a level, uniform points, rays and a shell), scanned / binned: all of them 1.24x,
-// but the slowest 0.19x (every level pre-reduced: 79.6 us, 411), and 300 below 0.97x; the 912 that these lines take 1.47x, the slowest 0.88x
-// (shell, 407.7 us, 463), 14 below 0.97x.  With six slices 1.1x at most on average, down to 0.81x.
+// but the slowest 0.19x (every level pre-reduced: 79.6 us, 411), and 300 below 0.97x; the 912 from a gain of 2.8 on 1.47x, 14 below 0.97x.  Of 208
+// others from 2.8 on 1.42x, nine below 0.97x, the slowest 0.78x (d = 3, L = 6, 4 + 4 slices, 548667 points: 388 us, 496), every one below 0.9x with a gain
+// under 3.0; from there on the slowest 0.95x (d = 2, where the merged levels leave fewer of their references, 2.8 .. 3: 1.14 .. 1.6x).  With six slices 1.1x at most on average, down to 0.81x.
 // They ask for up to 65 times the workspace of the scan, 28 times on the median (image2d's 66 -> 1994 MB; 2^21 points 4238, 3 * 2^20 6354), and
 // from where that passes kMaxAutoBinBytes, at 2^22 points there, the batch is scanned; so is one in a smaller workspace.
 constexpr int64_t  kMinMergedRefs = 3 << 19;
 constexpr uint32_t kMinMergedSlices = 8;
 constexpr int64_t  kMinMergedScans = 48;
-constexpr double   kMinMergedGain = 2.8;
+constexpr double   kMinMergedGain = 3.0, kMinMergedGainFlat = 2.8;      // (d = 3, d = 2)
 constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^d) below which launch overheads win
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
@@ -908,7 +909,7 @@ bool few_slices_pay(const cngp_config *c, int64_t N, uint32_t slices_f, uint32_t
     const int    D = scan_dense_levels(c, N, slices_f + slices_c), U = c->L - D, M = merge_levels(c, N);
     const double corners = 1 << c->d, refs = 2.0 * corners;
     const double scan = U * (slices_f + 0.5 * slices_c + 2.0 * refs) + 0.8 * D * corners, binned = (c->L - M + 0.45 * M) * refs;
-    return M >= 1 && slices_f + slices_c >= kMinMergedSlices && U * (int64_t)(slices_f + slices_c) >= kMinMergedScans && scan >= kMinMergedGain * binned;
+    return M >= 1 && slices_f + slices_c >= kMinMergedSlices && U * (int64_t)(slices_f + slices_c) >= kMinMergedScans && scan >= (c->d == 2 ? kMinMergedGainFlat : kMinMergedGain) * binned;
 }
 
 // Sums that `writers` workgroups per slice of a table leave in the workspace on `levels` levels.

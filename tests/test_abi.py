@@ -226,6 +226,8 @@ def test_backward_plan_is_reported_on_the_host():
     (3, 14, 2**14, 2**15, 2, 64, 5041, 637972, 0),             # 2 + 4 slices: 775 us, binned 1199
     (2, 8, 2**15, 2**14, 4, 16, 273, 1891700, 0),              # two levels to scan of eight: 422 us, binned 593
     (3, 9, 2**15, 2**14, 2, 64, 1027, 446890, 0),              # 4 + 2: 430 us, binned 562
+    (3, 6, 2**15, 2**14, 4, 64, 1024, 548667, 0),              # 4 + 4, two of six levels mergeable: 388 us, binned 496
+    (3, 10, 2**13, 2**16, 2, 32, 1024, 1030647, 0),            # 1 + 8: 1088 us, binned 1324
 ])
 def test_tables_of_few_slices_are_binned_only_where_a_scan_has_enough_to_do(d, L, N_f, N_c, N_p, N_min, N_max, N, merged):
     p = cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(cfg=7, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N,

@@ -34,8 +34,8 @@ def run(w, args, room=None, start=None, **kw):
 
 @pytest.mark.parametrize("d,N,L,N_f,N_c,N_p,N_min,N_max,feat,io,merged", [
     (2, 400003, 16, 2**16, 2**12, 8, 16, 8192, "f16", "f16", True),    # 8 + 2 slices
-    (3, 196609, 8, 2**15, 2**13, 8, 36, 400, "f16", "f32", True),      # 4 + 4: the fewest; little more than the fewest points
-    (3, 200003, 8, 2**13, 2**16, 4, 30, 600, "f32", "f16", True),      # 1 + 16
+    (3, 196609, 8, 2**15, 2**13, 8, 36, 250, "f16", "f32", True),      # 4 + 4: the fewest; little more than the fewest points
+    (3, 200003, 8, 2**13, 2**16, 4, 30, 300, "f32", "f16", True),      # 1 + 16
     (2, 500009, 8, 2**16, 2**10, 2, 200, 4000, "f16", "f16", True),    # N_p = 2: 8 + 1, six levels a scan would not pre-reduce
     (3, 196613, 12, 2**16, 1, 1, 100, 8192, "f32", "f32", False),      # plain hashing, 8 slices on 12 levels, none that could be merged
     (3, 110003, 8, 2**17, 1, 1, 60, 2048, "f16", "f16", False),        # 16 slices, fewer points
@@ -85,7 +85,7 @@ def test_binning_few_slices_is_no_less_precise_than_scanning_them(d, N, L, N_f, 
 
 
 def test_sums_of_drain_workgroups_with_the_sparse_softmax_other_widths_and_capture():
-    w = W.custom(cfg=142, d=3, L=8, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=900, N=200003, feat_dtype="f16", io_dtype="f16")
+    w = W.custom(cfg=142, d=3, L=8, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=300, N=200003, feat_dtype="f16", io_dtype="f16")
     D_f = W.make_feature_codebook(w)
     args = W.make_points(w), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w), W.make_upstream_grad(w)
     gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w, *args, top_k=3)
@@ -112,7 +112,7 @@ def test_sums_of_drain_workgroups_with_the_sparse_softmax_other_widths_and_captu
         check_close("grad Dhat_c", gC.cpu().numpy(), gC_ref, A_c, fp16_out=False)
         cngp.encode_bwd(cfg, *t, gF, gC, workspace=ws)          # eager work between the replays
         (gF.sum() + gC.sum()).item()
-    w4 = W.custom(cfg=143, d=3, L=8, F=4, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=900, N=200003, feat_dtype="f32", io_dtype="f32")
+    w4 = W.custom(cfg=143, d=3, L=8, F=4, N_f=2**16, N_c=2**11, N_p=8, N_min=30, N_max=300, N=200003, feat_dtype="f32", io_dtype="f32")
     D_f = W.make_feature_codebook(w4)
     args = W.make_points(w4), (D_f.astype(np.float64) * 1e4).astype(D_f.dtype), W.make_probe_logits(w4), W.make_upstream_grad(w4)
     gF_ref, gC_ref, A_f, A_c = oracle.encode_bwd(w4, *args)
