@@ -598,9 +598,11 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // Backward, us, without / with merging, at 2^19, 2^20, 3 * 2^19 and 2^21 references per level: nerf3d's tables 244 / 238, 334 / 306,
 // 434 / 403, 541 / 489; sdf3d's 351 / 236, 507 / 407, 669 / 576, 831 / 739; d = 2 (N_f = 2^18, N_c = 2^16, N_p = 8) 343 / 208,
 // 661 / 325, 800 / 463, 926 / 596; N_f = 2^18, N_c = 2^14, N_p = 4 197 / 175, 270 / 231, 343 / 314, 429 / 371; plain hashing
-// (N_f = 2^19) 95 / 98, 296 / 147, 342 / 183, 400 / 226.  81 drawn batches of 2^20 .. 3 * 2^19 references a level of tables that are
-// binned either way: 1.33x faster on average, the slowest 0.94x (307 us, 289); from 2^19 .. 2^20 0.86 .. 1.1x.  The line is an eighth above
-// kMinBinnedPrereduceRefs: up to there callers know the pre-reduced layout by its smaller workspace.
+// (N_f = 2^19) 95 / 98, 296 / 147, 342 / 183, 400 / 226; 2^19 .. 2^20 0.86 .. 1.1x.
+// Up to kMinMergedRefs only with kMinMergeLevels levels, two of them merged, or plain hashing: of 218 drawn batches there of tables that are binned
+// either way these are 130, 1.31x, two of them below 0.97x; the others are 0.99 .. 1.02x on average and 37 of 88 below 0.97x (d = 2, five levels, 64 + 8 slices,
+// 347924 points: 157 us, merged 207).  The line itself is on the safe side, an eighth above kMinBinnedPrereduceRefs: from 2^20 on the tables above gain
+// too, and the plans of the batches in between are as they were.
 // Points anything but evenly spread, without / with: all equal 1719 / 1279 (nerf3d's tables, 2^18 points), in a cube of side 0.02
 // 1233 / 812, on a line 1145 / 951, on a plane 544 / 519; sdf3d's 2^20 points 6127 / 3684, 3693 / 2137, 3548 / 2329, 2780 / 2139.
 // Sum of the kernels of a step, us, lines at 20 / 80 / 150 / 300 / 1500: nerf3d 728 / 611 / 594 / 587 / 601 (649 with grid sums),
@@ -611,6 +613,7 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 // d = 2 1.28x; d = 4, where two or three levels have that many references per vertex, 0.99x (0.78 .. 1.21), and small feature
 // tables with d = 2 and N_p = 2, whose references cost the least, 0.90x: neither is merged.
 constexpr int64_t  kMinMergeRefs = 9 << 17;
+constexpr int      kMinMergeLevels = 8;
 constexpr uint64_t kMinMergePerVertexPct = 240;
 // Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us: sdf3d's tables (32 + 32
 // bins) 30000 points 150 / 140, 100000 345 / 309, 2^18 uniform 723 / 656, 2^20 near a surface 2407 / 2170; 32 + 16 bins 681 / 632,
@@ -934,6 +937,11 @@ DrainPartials drain_partials(const cngp_config *c, const BwdPlan &b) {
     return d;
 }
 
+// Whether merging `levels` levels of a batch from kMinMergeRefs on is worth its launches.
+bool merging_pays(const cngp_config *c, int64_t N, int levels) {
+    return levels > 0 && ((N << c->d) >= kMinMergedRefs || c->N_p == 1 || (c->L >= kMinMergeLevels && levels >= 2));
+}
+
 BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = LAYOUT_MERGED) {
     BwdPlan b;
     std::memset(&b, 0, sizeof(b));
@@ -1008,7 +1016,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         // them more for the levels that are left, and with as few as before their last round is mostly empty -- N_f = 2^8,
         // N_c = 2^16, N_p = 8, 250007 points: 456 us, merged with two workgroups per bin 436 and an error of 1.5e-7 instead of
         // 1.3e-7, with one 468)
-        b.merged = b.dense.count > 0 && !(b.fused && drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L - b.dense.count, per_level_now) !=
+        b.merged = merging_pays(c, N, b.dense.count) && !(b.fused && drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L - b.dense.count, per_level_now) !=
                                                          drain_subs((double)((uint64_t)N << c->d), b.slices_c, c->L, per_level_now));
         // (plain hashing has one table and the cheapest references: three merged levels do not pay for the order of the points.
         // 32 drawn batches, d = 2 and 3, L = 8 .. 16, N_f = 2^18 .. 2^20, without / with merging: three levels 0.965 .. 0.984 (three

@@ -235,6 +235,21 @@ def test_tables_of_few_slices_are_binned_only_where_a_scan_has_enough_to_do(d, L
     assert p["merged_levels"] == merged and 8 <= p["slices_f"] + p["slices_c"] + 2 < 24
 
 
+@pytest.mark.parametrize("d,L,N_f,N_c,N_p,N_min,N_max,N,merged", [
+    (2, 5, 2**19, 2**15, 4, 64, 256, 347924, 0),               # five levels: 157 us, merged 207
+    (3, 7, 2**18, 2**12, 16, 16, 512, 150001, 0),              # seven
+    (3, 8, 2**18, 2**12, 16, 16, 512, 150001, 4),
+    (3, 12, 2**18, 2**11, 4, 64, 1024, 165000, 0),             # one level of twelve: 345 us, merged 381
+    (3, 4, 2**19, 1, 1, 8, 60, 150001, 0), (3, 7, 2**18, 1, 1, 8, 256, 165000, 4),      # plain hashing: four levels are enough
+    (2, 5, 2**19, 2**15, 4, 64, 256, 3 * 2**17, 4),            # 3 * 2^19 references a level: any that can be
+    (3, 12, 2**18, 2**11, 4, 64, 1024, 3 * 2**16, 2),
+])
+def test_shorter_batches_are_merged_where_enough_levels_share_the_launches(d, L, N_f, N_c, N_p, N_min, N_max, N, merged):
+    p = cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(cfg=7, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N,
+                                                              feat_dtype="f16", io_dtype="f16"), flags=cngp.ZERO_GRADS), N)
+    assert p["binned"] == 1 and p["merged_levels"] == merged
+
+
 def test_merged_levels_are_reported_as_what_they_are():
     """Levels are either merged or pre-reduced on their grids: never both, and each under its own name."""
     plan = lambda flags=0, **kw: cngp.bwd_plan_info(cngp.Config.from_workload(W.custom(**kw), flags=cngp.ZERO_GRADS | flags), kw["N"])

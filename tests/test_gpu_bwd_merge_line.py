@@ -17,8 +17,8 @@ def dev(a):
 
 
 @pytest.mark.parametrize("d,L,N_f,N_c,N_p,N_min,N_max,feat,io", [
-    (3, 4, 2**17, 2**14, 8, 16, 300, "f16", "f16"),                    # 16 + 8 slices
-    (2, 4, 2**13, 2**15, 16, 30, 3000, "f32", "f32"),                  # 1 + 32
+    (3, 8, 2**17, 2**14, 8, 16, 300, "f16", "f16"),                    # 16 + 8 slices
+    (2, 8, 2**13, 2**15, 16, 30, 3000, "f32", "f32"),                  # 1 + 32
     (2, 6, 2**18, 1, 1, 16, 2048, "f16", "f16"),                       # plain hashing, 32
 ])
 @pytest.mark.parametrize("past", [0, 1])
