@@ -255,8 +255,7 @@ int cngp_encode_bwd_input(const cngp_config *cfg, const float *x, int64_t N, con
  * cngp_bwd_merge_info; [6] .. [9] then describe no level); [2], [3] slices per level of the feature and
  * of the logit gradient table; [4], [5] point chunks of the feature / logit role on hashed levels;
  * [6], [7] vertex chunks of the two roles on pre-reduced levels; [8] point chunks and [9] total slices
- * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first because of the number of
- * slices (they are as well, whatever stands here, where levels are merged: cngp_bwd_merge_info), and then
+ * of the vertex-grid accumulation; [10] 1 = the hashed levels' references are binned by slice first, and then
  * [11], [12] workgroups that drain one bin of the feature / logit table and [13] point chunks of the binning;
  * with [2] = 0 when a level's feature table is small enough (N_f <= 4096) to be accumulated whole in LDS by the
  * workgroups that drain the confidence-table bins (one pass for both gradients, no pre-reduced levels);

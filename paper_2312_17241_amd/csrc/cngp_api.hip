@@ -553,7 +553,7 @@ struct BwdPlan {
     size_t   sigma_off, dyT_off, G_off, partF_off, partC_off, ws_bytes;
     bool     binned;                    // hashed levels: references binned by slice first (cngp_bwd_binned.h)
     bool     summed;                    // ... and the sums of a bin's drain workgroups meet in the workspace, where the merged entries were
-    bool     few, scarce;               // ... because levels are merged, of tables whose slices alone would be scanned; either these or plain hashing of few slices
+    bool     scarce;                    // ... of tables whose slices alone would be scanned: because levels are merged, or plain hashing of few slices
     bool     fused;                     // ... by slice of the confidence table only: a level's whole feature gradient sits in LDS beside it
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
     uint32_t subs_f, subs_c;            // drain workgroups per bin
@@ -993,10 +993,10 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
     // tables of a few slices, where enough of the levels are merged
-    b.few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && c->N_p > 1 &&
+    const bool few = !b.binned && bin_ok && plenty && bin_bytes <= bin_bytes_max && layout == LAYOUT_MERGED && c->d <= 3 && c->N_p > 1 &&
             !(c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED | CNGP_BWD_NO_PREREDUCE)) && !c->bin_bytes_max && (N << c->d) >= kMinMergedRefs &&
             few_slices_pay(c, N, b.slices_f, b.slices_c);
-    b.binned = b.binned || b.few;
+    b.binned = b.binned || few;
     b.scarce = b.binned && per_level < kMinBinnedSlicesPerLevel && !fused_ok;
     b.fused = b.binned && fused_ok;
     if (b.fused) {
@@ -1762,7 +1762,7 @@ int cngp_bwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
         b.sliced ? 1 : 0, b.merged ? 0 : b.dense.count, (int32_t)(b.fused ? 0 : b.slices_f), (int32_t)b.slices_c,
         (int32_t)b.feat_pts.chunks, (int32_t)b.logit_pts.chunks, b.merged ? 1 : (int32_t)b.feat_vtx.chunks,
         b.merged ? 1 : (int32_t)b.logit_vtx.chunks, b.merged ? 0 : (int32_t)b.grid.chunks, (int32_t)b.dense_slices,
-        b.binned && !b.few ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
+        b.binned ? 1 : 0, (int32_t)b.subs_f, (int32_t)b.subs_c, (int32_t)b.bin_chunks,
         (int32_t)(N > 0 ? (N + per - 1) / per : 1)};
     for (int i = 0; i < CNGP_PLAN_INFO_COUNT; ++i) info[i] = v[i];
     return CNGP_OK;

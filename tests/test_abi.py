@@ -194,7 +194,11 @@ def test_backward_plan_is_reported_on_the_host():
     assert p["binned"] == 1                               # two dozen slices per level: the library bins by itself
     assert cngp.bwd_plan_info(cngp.Config.from_workload(w, flags=cngp.BWD_SLICED), w.N)["binned"] == 0
     im = W.WORKLOADS["image2d"]
-    assert cngp.bwd_plan_info(cngp.Config.from_workload(im), im.N)["binned"] == 0      # ten slices: replicated scan
+    pi = cngp.bwd_plan_info(cngp.Config.from_workload(im), im.N)     # ten slices: binned because eleven levels are merged, else a replicated scan
+    assert pi["binned"] == 1 and pi["merged_levels"] == 11 and pi["bin_chunks"] >= 1 and pi["drain_wgs_feat"] >= 1
+    for scan in (dict(flags=cngp.BWD_SLICED), dict(flags=cngp.BWD_NO_PREREDUCE), dict(bin_bytes_max=8 << 30)):
+        ps = cngp.bwd_plan_info(cngp.Config.from_workload(im, **scan), im.N)
+        assert ps["binned"] == 0 and ps["merged_levels"] == 0 and ps["sliced"] == 1
     huge = cngp.Config.from_workload(w)                   # 2^25 points: the bins would take 32 GiB: 4 passes of 8 GiB
     ph = cngp.bwd_plan_info(huge, 2**25)
     assert ph["binned"] == 1 and ph["passes"] == 4 and cngp.workspace_bytes(huge, 2**25) < 10 << 30
@@ -304,8 +308,8 @@ def test_backward_plan_layout_stays_inside_the_workspace():
     arrays, whose extents the next test checks) are 256-byte aligned, do not
     overlap, and end inside cngp_workspace_bytes; the plan's counts are consistent with each other."""
     rng = np.random.default_rng(2024)
-    seen = {"direct": 0, "sliced": 0, "binned": 0, "passes": 0, "fused": 0, "merged": 0}
-    for it in range(400):
+    seen = {"direct": 0, "sliced": 0, "binned": 0, "passes": 0, "fused": 0, "merged": 0, "few": 0, "plain": 0, "partial sums": 0}
+    for it in range(700):
         d = int(rng.choice([2, 3]))
         N_p = int(2 ** rng.integers(0, 5))
         N_f = int(2 ** rng.integers(max(2, int(np.log2(N_p))), 21))
@@ -316,6 +320,9 @@ def test_backward_plan_layout_stays_inside_the_workspace():
         N = int(rng.choice([1, 63, 4097, 70001, 2**18, 2**20 + 5, 2**22]))
         flags = int(rng.choice([0, 0, cngp.BWD_SLICED, cngp.BWD_BINNED, cngp.BWD_BINNED | cngp.BWD_NO_PREREDUCE, cngp.BWD_SLICED | cngp.BWD_NO_PREREDUCE]))
         bound = int(rng.choice([0, 0, 1 << 20, 1 << 26, 1 << 30]))
+        if it >= 400:                              # tables of a few slices
+            N_f, N_c, L, N_min = int(2 ** rng.integers(13, 18)), int(2 ** rng.integers(8, 16)), int(rng.integers(6, 17)), int(rng.integers(16, 65))
+            N_max, N, flags, bound = N_min * 64, int(2 ** rng.uniform(14, 21)), 0, 0
         w = W.custom(cfg=7, d=d, L=L, N_f=N_f, N_c=N_c, N_p=N_p, N_min=N_min, N_max=N_max, N=N,
                      feat_dtype=str(rng.choice(["f16", "f32"])), io_dtype=str(rng.choice(["f16", "f32"])))
         cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS | flags, bin_bytes_max=bound)
@@ -332,6 +339,12 @@ def test_backward_plan_layout_stays_inside_the_workspace():
         if plan["binned"]:
             assert plan["sliced"] == 1 and plan["bin_chunks"] >= 1 and plan["drain_wgs_feat"] >= 1
             assert len(regions) == 12
+        else:
+            assert plan["merged_levels"] == 0 and len(regions) in (0, 3, 5)          # (5: a scan whose chunks leave partial sums of two tables)
+        few = plan["binned"] == 1 and not flags & cngp.BWD_BINNED and 0 < plan["slices_f"] and plan["slices_f"] + plan["slices_c"] < 24
+        seen["few"] += few and N_p > 1
+        seen["plain"] += few and N_p == 1
+        seen["partial sums"] += len(regions) == 5
         seen["binned" if plan["binned"] else "sliced" if plan["sliced"] else "direct"] += 1
         seen["passes"] += plan["passes"] > 1
         seen["fused"] += plan["binned"] == 1 and plan["slices_f"] == 0
