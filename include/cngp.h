@@ -129,7 +129,8 @@ int cngp_storage_bytes(const cngp_config *cfg, size_t *D_f_bytes, size_t *D_c_le
  * forward calls then need it as well).
  * For a large batch this includes the room to merge references (cngp_bwd_merge_info): 40 bytes for each one of a merged
  * level, while the whole stays within 8 GiB.  cngp_encode_bwd also runs in less where a layout without merging, or one that
- * pre-reduces more of the coarse levels, fits: the workspace of a batch serves every shorter one.
+ * pre-reduces more of the coarse levels, fits, or where passes of half the longest fit in place of its own: the workspace of
+ * a batch serves every shorter one.
  * The workspace must be 256-byte aligned; its contents are undefined before and after each call.
  * Returns 0 for an invalid configuration as well (the encode calls then report the error). */
 size_t cngp_workspace_bytes(const cngp_config *cfg, int64_t N);

@@ -1181,15 +1181,18 @@ const BwdPlan &bwd_plan_for(const cngp_config *c, int64_t N, size_t room) {
 // Points per pass of cngp_encode_bwd.  A batch whose bins would pass the configured limit (or whose references
 // would not fit the 31-bit record positions) is taken in equal passes, each a complete backward over a run
 // of points that accumulates onto the one before, when a pass of that size is binned; otherwise N.
-int64_t bwd_pass_points(const cngp_config *c, int64_t N) {
-    if (N <= 0 || (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED))) return N;
+int64_t most_pass_points(const cngp_config *c) {
     int64_t most = (((int64_t)1 << 31) - 1) >> c->d;
     if (!(c->flags & CNGP_BWD_BINNED) || c->bin_bytes_max) {
         const int64_t per_point = ((int64_t)kRecordBytes << c->d) * c->L * (c->N_p > 1 ? 2 : 1);
         const int64_t by_bytes = (int64_t)((c->bin_bytes_max ? c->bin_bytes_max : kMaxAutoBinBytes) / (uint64_t)per_point);
         if (by_bytes < most) most = by_bytes;
     }
-    most = most >= 65536 ? most / 65536 * 65536 : most / 1024 * 1024;
+    return most >= 65536 ? most / 65536 * 65536 : most / 1024 * 1024;
+}
+int64_t bwd_pass_points(const cngp_config *c, int64_t N) {
+    if (N <= 0 || (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED))) return N;
+    const int64_t most = most_pass_points(c);
     if (N <= most || most <= 0) return N;
     const int64_t passes = (N + most - 1) / most;
     const int64_t per = ((N + passes - 1) / passes + 63) / 64 * 64;
@@ -1197,6 +1200,15 @@ int64_t bwd_pass_points(const cngp_config *c, int64_t N) {
 }
 // Whether passes of `per` points are scanned where the room for their bins is missing.
 bool scanned_in_least_room(const cngp_config *c, int64_t per) { return !make_bwd_plan_uncached(c, per, LAYOUT_LEAST).binned; }
+// Points per pass in a workspace that does not hold passes of bwd_pass_points: at most half the longest, which the workspace of every
+// longer batch in passes holds, as its own passes are no shorter (one more point than fits one pass is taken in two halves); 0 where the
+// batch is no longer than that, or not binned.
+int64_t short_pass_points(const cngp_config *c, int64_t N) {
+    const int64_t half = most_pass_points(c) / 2;
+    if (N <= half || half < 64 || (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED))) return 0;
+    const int64_t passes = (N + half - 1) / half, per = ((N + passes - 1) / passes + 63) / 64 * 64;
+    return scanned_in_least_room(c, per) ? 0 : per;
+}
 
 template <int NP>
 BinParams make_bin_params(const cngp_config *c, const BwdPlan &b, int64_t N) {
@@ -1574,15 +1586,21 @@ size_t least_workspace_pairs(const cngp_config *cfg, int64_t N) {
     return least < bytes ? least : bytes;
 }
 
+// What passes of short_pass_points take at least; 0 where the batch is not taken in those.
+size_t short_passes_workspace_pairs(const cngp_config *cfg, int64_t N) {
+    const int64_t per = short_pass_points(cfg, N);
+    return per > 0 ? workspace_bytes_passes(cfg, N, per, LAYOUT_LEAST) : 0;
+}
+
 // ---------------------------------------------------------------- feature widths other than two
 // F = 1, 4, 8 run as ceil(F / 2) passes over pair planes (cngp_kernels.h, plane_take_kernel): behind the workspace
 // of the two-feature problem sit one plane of D_f, one plane of y or dL/dy, and one plane of grad D_f.
 struct PlaneSpace { size_t pairs, D_off, io_off, g_off, total; };
 cngp_config as_pairs(const cngp_config *c) { cngp_config p = *c; p.F = 2; return p; }
-PlaneSpace plane_space(const cngp_config *c, int64_t N, bool least = false) {
+PlaneSpace plane_space(const cngp_config *c, int64_t N, bool least = false, size_t short_passes = 0) {
     const cngp_config c2 = as_pairs(c);
     PlaneSpace ps;
-    const size_t bwd = least ? least_workspace_pairs(&c2, N) : workspace_bytes_pairs(&c2, N), fwd = fwd_level_plan(&c2, c2.L, N).yT_bytes;
+    const size_t bwd = short_passes ? short_passes : least ? least_workspace_pairs(&c2, N) : workspace_bytes_pairs(&c2, N), fwd = fwd_level_plan(&c2, c2.L, N).yT_bytes;
     ps.pairs = align256(bwd > fwd ? bwd : fwd);
     ps.D_off = ps.pairs;
     ps.io_off = ps.D_off + align256((size_t)c->L * c->N_f * 2 * (c->feat_dtype == CNGP_F16 ? 2 : 4));
@@ -1617,7 +1635,11 @@ int put_plane_dt(int dtype, const void *src, void *dst, int64_t rows, int F, int
 }
 PlaneSpace plane_space_for(const cngp_config *c, int64_t N, size_t room) {
     const PlaneSpace ps = plane_space(c, N);
-    return ps.total <= room ? ps : plane_space(c, N, true);
+    if (ps.total <= room) return ps;
+    const PlaneSpace least = plane_space(c, N, true);
+    const cngp_config c2 = as_pairs(c);
+    const size_t passes = least.total <= room ? 0 : short_passes_workspace_pairs(&c2, N);
+    return passes ? plane_space(c, N, true, passes) : least;
 }
 bool plane_workspace_ok(const void *ws, size_t bytes, const PlaneSpace &ps) {
     return ws && ((uintptr_t)ws & 255u) == 0 && bytes >= ps.total;
@@ -1902,9 +1924,13 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
     int64_t per = bwd_pass_points(cfg, N);
     // (passes whose bins do not fit, of tables that are scanned then: one scan where that fits, which adds fewer fp32 sums to an entry than scans in passes)
     if (per < N && !bwd_plan_for(cfg, per, workspace_bytes).binned && make_bwd_plan(cfg, N, LAYOUT_LEAST).ws_bytes <= workspace_bytes) per = N;
+    size_t least = per < N ? least_workspace_pairs(cfg, N) : 0;
+    if (N > 0 && workspace_bytes < (per < N ? least : bwd_plan_for(cfg, N, workspace_bytes).ws_bytes)) {
+        const size_t passes = short_passes_workspace_pairs(cfg, N);
+        if (passes && passes <= workspace_bytes) { per = short_pass_points(cfg, N); least = passes; }
+    }
     if (per < N) {      // several passes over runs of points; the first one clears if asked, the rest accumulate
-        if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < least_workspace_pairs(cfg, N))
-            return CNGP_ERR_WORKSPACE;
+        if (!workspace || ((uintptr_t)workspace & 255u) || workspace_bytes < least) return CNGP_ERR_WORKSPACE;
         cngp_config   pass = *cfg;
         const size_t  io = cfg->io_dtype == CNGP_F16 ? 2 : 4;
         for (int64_t first = 0; first < N; first += per) {

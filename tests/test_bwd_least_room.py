@@ -63,3 +63,24 @@ def test_a_workspace_of_a_batch_in_passes_serves_every_shorter_one(N):
     have = cngp.workspace_bytes(cfg, N)
     for n in (N - 1, N * 7 // 8, N * 3 // 4, 16_000_000, 14_000_000, 12_000_000, 8_400_000, 300_000, 202209, 1000):
         assert n > N or accepts(cfg, n, have), (n, N)
+
+
+@pytest.mark.parametrize("F", [2, 4])
+@pytest.mark.parametrize("args,bound", [((4, 7, 2**18, 2**8, 16, 2048), 0), ((3, 9, 2**9, 2**17, 16, 2048), 0), ((3, 16, 2**16, 2**14, 16, 2048), 0),
+                                        ((4, 10, 2**16, 2**16, 16, 2048), 1 << 28), ((3, 6, 2**18, 1, 1, 256), 1 << 28), ((2, 12, 2**18, 2**12, 8, 4096), 1 << 26)])
+def test_tables_that_are_always_binned_too(args, bound, F):
+    """One more point than fits a pass is taken in two halves, whose workspace is smaller than that of one pass."""
+    cfg = config(*args, F=F, bin_bytes_max=bound)
+    most = 1                                                  # the longest batch in one pass
+    while cngp.bwd_plan_info(cfg, 2 * most)["passes"] == 1:
+        most *= 2
+    step = most // 2
+    while step:
+        most += step if cngp.bwd_plan_info(cfg, most + step)["passes"] == 1 else 0
+        step //= 2
+    for N in (most + 1, most * 3 // 2, 2 * most + 1, 5 * most + 12345):
+        have = cngp.workspace_bytes(cfg, N)
+        for n in (most // 3, most // 2, most // 2 + 1, most * 3 // 4, most, most + 1, 2 * most, 2 * most + 1, 3 * most, 4 * most, N - 1):
+            assert n > N or accepts(cfg, n, have), (n, N)
+    assert cngp.workspace_bytes(cfg, most + 1) < cngp.workspace_bytes(cfg, most)
+    assert not accepts(cfg, most, cngp.workspace_bytes(cfg, most) // 8) and not accepts(cfg, most, 4096)

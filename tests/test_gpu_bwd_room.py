@@ -71,6 +71,22 @@ def test_a_batch_in_passes_runs_in_the_room_of_its_unmerged_layout(F):
     assert e.value.status == cngp.ERR_WORKSPACE
 
 
+@pytest.mark.parametrize("F,n", [(2, 65536), (2, 130001), (4, 61003)])
+def test_a_workspace_of_passes_serves_the_batch_that_one_pass_would_take(F, n):
+    """65536 points are the longest pass under this bound, one more is taken in two halves, whose room is enough for all of them."""
+    w = W.custom(cfg=94, d=3, L=16, F=F, N_f=2**16, N_c=2**14, N_p=16, N_min=16, N_max=2048, N=n, feat_dtype="f16", io_dtype="f16")
+    cfg = cngp.Config.from_workload(w, flags=cngp.ZERO_GRADS, bin_bytes_max=1 << 26)
+    assert cngp.bwd_plan_info(cfg, 65536)["passes"] == 1 and cngp.bwd_plan_info(cfg, 65537)["passes"] == 2
+    room = cngp.workspace_bytes(cfg, 65537) if n <= 65537 else cngp.workspace_bytes(cfg, 2 * 65536 + 1)
+    assert room < cngp.workspace_bytes(cfg, n)
+    args = args_of(w)
+    run = lambda size: launches(lambda: cngp.encode_bwd(cfg, *args, workspace=torch.empty(size, dtype=torch.uint8, device="cuda")))
+    got, narrow = run(room)
+    ref, wide = run(cngp.workspace_bytes(cfg, n))
+    assert narrow["encode_bwd_bin_drain"] == 2 * wide["encode_bwd_bin_drain"]
+    same(got, ref)
+
+
 def test_plain_hashing_in_passes_is_scanned_in_one_without_room_for_its_bins():
     N = 8_500_003
     cfg = cngp.Config(d=4, L=16, F=2, N_f=2**17, N_c=1, N_p=1, N_min=16, N_max=256, feat_dtype=cngp.F16, io_dtype=cngp.F16, flags=cngp.ZERO_GRADS)
