@@ -552,7 +552,7 @@ struct BwdPlan {
     bool     split;                     // replicated scan in many chunks whose sums meet in the workspace (bwd_partial_sums_kernel)
     size_t   sigma_off, dyT_off, G_off, partF_off, partC_off, ws_bytes;
     bool     binned;                    // hashed levels: references binned by slice first (cngp_bwd_binned.h)
-    bool     summed;                    // ... and the sums of a bin's drain workgroups meet in the workspace, where the merged entries were
+    bool     sum_f, sum_c, sum_wide;    // ... and a table's sums of a bin's drain workgroups meet in the workspace, where the merged entries were; in 64 bits
     bool     scarce;                    // ... of tables whose slices alone would be scanned: because levels are merged, or plain hashing of few slices
     bool     fused;                     // ... by slice of the confidence table only: a level's whole feature gradient sits in LDS beside it
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
@@ -643,10 +643,11 @@ constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pa
 
 // Drain workgroups per bin of a table with `slices` slices per level: about 2^16 records each, and enough workgroups to
 // fill the chip twice, but never less than 8192 records each.  `refs` references per level, `levels` hashed levels.
-// `alone`: of plain hashing with few slices, whose one table has few bins, enough to fill it once (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
-uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool alone = false) {
+// `longer`: of the long bins of a few slices, 1.5 times the records each, whose sums are fewer to add up.  `alone`: of plain hashing with few slices, whose
+// one table has few bins, enough to fill it once (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
+uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool longer = false, bool alone = false) {
     if (!slices) return 1;
-    double want = refs / slices / 65536.0;
+    double want = refs / slices / (longer ? 98304.0 : 65536.0);
     const double fill = (alone ? 256.0 : 512.0) / ((double)levels * slices_per_level), by_size = refs / slices / 8192.0;
     if (want < fill) want = fill;
     if (want > by_size) want = by_size;
@@ -916,12 +917,12 @@ bool few_slices_pay(const cngp_config *c, int64_t N, uint32_t slices_f, uint32_t
 }
 
 // Sums that `writers` workgroups per slice of a table leave in the workspace on `levels` levels.
-size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit, uint32_t writers, int levels) {
-    const size_t slice = ((size_t)c->N_p << (logit ? b.rows_c_log2 : b.rows_f_log2)) * (logit ? 1 : 2) * sizeof(double);
+size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit, uint32_t writers, int levels, size_t sum_bytes) {
+    const size_t slice = ((size_t)c->N_p << (logit ? b.rows_c_log2 : b.rows_f_log2)) * (logit ? 1 : 2) * sum_bytes;
     return writers > 1 ? (size_t)levels * writers * (logit ? b.slices_c : b.slices_f) * slice : 0;
 }
 size_t partial_bytes(const cngp_config *c, const BwdPlan &b, bool logit) {
-    return b.split ? partial_bytes(c, b, logit, (logit ? b.logit_pts : b.feat_pts).chunks, c->L - b.dense.count) : 0;
+    return b.split ? partial_bytes(c, b, logit, (logit ? b.logit_pts : b.feat_pts).chunks, c->L - b.dense.count, sizeof(double)) : 0;
 }
 // Where a binned batch's drain leaves them, from the start of the merged entries on, which nothing reads any more: roles as in PartialRoles.
 struct DrainPartials { uint32_t writers[4]; size_t off[4], bytes; };
@@ -930,9 +931,9 @@ DrainPartials drain_partials(const cngp_config *c, const BwdPlan &b) {
     DrainPartials d;
     d.bytes = 0;
     for (int r = 0; r < 4; ++r) {
-        d.writers[r] = b.summed ? writers[r] : 0;
+        d.writers[r] = (r & 1 ? b.sum_c : b.sum_f) ? writers[r] : 0;
         d.off[r] = d.bytes;
-        d.bytes += align256(partial_bytes(c, b, r & 1, d.writers[r], r < 2 ? c->L - b.dense.count : b.dense.count));
+        d.bytes += align256(partial_bytes(c, b, r & 1, d.writers[r], r < 2 ? c->L - b.dense.count : b.dense.count, b.sum_wide ? sizeof(double) : sizeof(float)));
     }
     return d;
 }
@@ -1064,20 +1065,27 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.bin_chunk_pts = (uint32_t)cp;
         b.bin_chunks = (uint32_t)((N + cp - 1) / cp);
         const double refs = (double)((uint64_t)N << c->d);
-        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce && c->N_p == 1);
-        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce && c->N_p == 1);
+        b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
+        b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
         if (plain_bins) b.subs_f = 1;
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
             b.feat_vtx = Geom{b.fused ? 2u : (b.subs_f + 1) / 2, 0};
             b.logit_vtx = Geom{(b.subs_c + 1) / 2, 0};
-            // Of tables of few slices, which a scan gives up to a dozen chunks per slice, a bin has up to 64 workgroups: their sums meet in
-            // fp64.  Error against 64 bits, 2-norm, logit gradient, scanned / added with fp32 atomics / so: d = 3, L = 12, 8 + 1 slices,
-            // 745393 points, 61 workgroups 1.15e-7 / 1.46e-7 / 0.80e-7; image2d's tables 1.03e-7 / 0.98e-7 / 0.75e-7; none of twelve
-            // tables above 0.83e-7.  568 drawn batches are as fast as with the atomics and 98304 records a workgroup (0.99x on average; image2d's
-            // step 850 us, so 883).
-            b.summed = b.scarce;
+            // Of tables of few slices a bin has up to 64 workgroups, and a scan at most a dozen chunks per slice: a table whose bins have more
+            // of them than that leaves their sums, rounded to 32 bits, in the workspace, where they are added up in 64 (as they are where a
+            // scan rounds only once).  Error against 64 bits, 2-norm, 1e-7, scanned / added with atomics / so: logit gradient d = 3, L = 10, 8 + 1
+            // slices, N_p = 4, 800000 points 1.06 / 1.60 / 0.86, image2d's tables 1.03 / 0.97 / 0.79; 41 drawn tables, either gradient: 0.5 ..
+            // 1.0, none above the scan's.  In 64 bits throughout, of both tables: image2d's step 888 us, so 855, as with atomics alone.
+            if (b.scarce) {
+                const BwdPlan scan = make_bwd_plan_uncached(c, N, LAYOUT_LEAST);
+                const auto least = [&](const Geom &pts, const Geom &vtx) { return scan.dense.count > 0 && vtx.chunks < pts.chunks ? vtx.chunks : pts.chunks; };
+                const uint32_t least_f = least(scan.feat_pts, scan.feat_vtx), least_c = least(scan.logit_pts, scan.logit_vtx);
+                b.sum_f = b.subs_f > scan.feat_pts.chunks || b.feat_vtx.chunks > least_f;
+                b.sum_c = b.slices_c && (b.subs_c > scan.logit_pts.chunks || b.logit_vtx.chunks > least_c);
+                b.sum_wide = (b.sum_f && least_f == 1) || (b.sum_c && least_c == 1);
+            }
             b.merge.levels = (uint32_t)b.dense.count;
             // chunks of at least two rounds, at most 512 of them: sparse parts of space leave several times the entries of
             // dense ones, and the many short workgroups even that out.  With 128 slices of a table or more at most as many as the
@@ -1228,7 +1236,7 @@ uint32_t most_bins_of(const BinParams &bp) { return bp.slices_f + bp.slices_c > 
 uint32_t hist_replicas_of(uint32_t most_bins) { return most_bins <= 64 ? 16u : most_bins <= 512 ? 4u : 1u; }
 
 // What the workgroups of a slice left, added up; nothing where no role has any.
-template <int NP>
+template <int NP, typename Sum>
 int launch_partial_sums(const Params &p, PartialRoles &roles, const float *sigma, bool zero_first, float *gD_f, float *gDhat_c, hipStream_t s) {
     roles.first[0] = 0;
     for (int r = 0; r < 4; ++r) {
@@ -1237,7 +1245,7 @@ int launch_partial_sums(const Params &p, PartialRoles &roles, const float *sigma
     }
     if (roles.first[4] == 0) return CNGP_OK;
     LaunchTimer t(s, K_BWD_PARTIAL);
-    bwd_partial_sums_kernel<NP><<<roles.first[4], kBlock, 0, s>>>(p, roles, sigma, zero_first ? 1 : 0, gD_f, gDhat_c);
+    bwd_partial_sums_kernel<NP, Sum><<<roles.first[4], kBlock, 0, s>>>(p, roles, sigma, zero_first ? 1 : 0, gD_f, gDhat_c);
     return launch_status("bwd_partial_sums_kernel");
 }
 
@@ -1339,7 +1347,8 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     PartialRoles sums;
     SliceParams *const drained[4] = {&sp_f, &sp_c, &vtx.sp[ROLE_FEAT_VTX], &vtx.sp[ROLE_LOGIT_VTX]};
     for (int r = 0; r < 4; ++r) {
-        if (left.writers[r] > 1) drained[r]->partial = (double *)((char *)G + left.off[r]);
+        if (left.writers[r] > 1) drained[r]->partial = (char *)G + left.off[r];
+        drained[r]->wide = b.sum_wide ? 1 : 0;
         sums.sp[r] = *drained[r];
     }
     auto kernel = bin_drain_kernel<D, NP, FeatT, IoT>;
@@ -1357,7 +1366,8 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
                                                 baseF, baseC, bp.cap, vtx, b.dense, G, b.merged ? 1 : 0, mb, gD_f, gDhat_c);
         if (int rc = launch_status("bin_drain_kernel")) return rc;
     }
-    return launch_partial_sums<NP>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
+    return b.sum_wide ? launch_partial_sums<NP, double>(p, sums, sigma, zero_first, gD_f, gDhat_c, s)
+                      : launch_partial_sums<NP, float>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
 }
 
 template <int D, int NP, typename FeatT, typename IoT>
@@ -1438,8 +1448,8 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
             sp.store_direct = (g.chunks == 1 && zero_first) ? 1 : 0;     // matches the clearing in cngp_encode_bwd
             sp.level0 = level0;
             sp.nlevels = present ? nlevels : 0;
-            if (b.split && g.chunks > 1 && role == ROLE_LOGIT_PTS) sp.partial = (double *)((char *)workspace + b.partC_off);
-            if (b.split && g.chunks > 1 && role == ROLE_FEAT_PTS) sp.partial = (double *)((char *)workspace + b.partF_off);
+            if (b.split && g.chunks > 1 && role == ROLE_LOGIT_PTS) sp.partial = (char *)workspace + b.partC_off;
+            if (b.split && g.chunks > 1 && role == ROLE_FEAT_PTS) sp.partial = (char *)workspace + b.partF_off;
             roles.first[role] = next;
             if (present && nlevels > 0)      // 8 equal runs of (level, slice, chunk) units, one per XCD
                 next += (uint32_t)kXcds * (((uint32_t)nlevels * sp.slices * sp.chunks + kXcds - 1) / kXcds);
@@ -1461,7 +1471,7 @@ int launch_bwd_sliced(const cngp_config *c, const Params &p, const BwdPlan &b, c
         if (int rc = launch_status("bwd_sliced_kernel")) return rc;
         if (pts) { sums.sp[0] = roles.sp[ROLE_FEAT_PTS]; sums.sp[1] = roles.sp[ROLE_LOGIT_PTS]; }
     }
-    return launch_partial_sums<NP>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
+    return launch_partial_sums<NP, double>(p, sums, sigma, zero_first, gD_f, gDhat_c, s);
 }
 
 // LDS of encode_bwd_small_kernel, 0 where it is not taken.
@@ -1954,12 +1964,12 @@ int cngp_encode_bwd(const cngp_config *cfg, const float *x, int64_t N, const voi
         const int64_t per_f = (int64_t)cfg->N_f * cfg->F, per_c = (int64_t)cfg->N_c * cfg->N_p;
         const bool    sl = N > 0 && b.sliced;
         const int     Ld = sl ? b.dense.count : 0, Lh = cfg->L - Ld;
-        const bool    once = b.split || b.summed;       // partial sums: an entry is written once
-        if (!(sl && (b.feat_vtx.chunks == 1 || b.summed)) && Ld > 0) z.add(grad_D_f, per_f * Ld);
-        const uint32_t wg_f = once ? 1u : b.binned ? b.subs_f : b.feat_pts.chunks, wg_c = once ? 1u : b.binned ? b.subs_c : b.logit_pts.chunks;
+        const bool    once_f = b.split || b.sum_f, once_c = b.split || b.sum_c;      // partial sums: an entry is written once
+        if (!(sl && (b.feat_vtx.chunks == 1 || b.sum_f)) && Ld > 0) z.add(grad_D_f, per_f * Ld);
+        const uint32_t wg_f = once_f ? 1u : b.binned ? b.subs_f : b.feat_pts.chunks, wg_c = once_c ? 1u : b.binned ? b.subs_c : b.logit_pts.chunks;
         if (!(sl && wg_f == 1) && Lh > 0) z.add(grad_D_f + per_f * Ld, per_f * Lh);
         const bool logit = sl && cfg->N_p > 1;
-        if (!(logit && (b.logit_vtx.chunks == 1 || b.summed)) && Ld > 0) z.add(grad_Dhat_c, per_c * Ld);
+        if (!(logit && (b.logit_vtx.chunks == 1 || b.sum_c)) && Ld > 0) z.add(grad_Dhat_c, per_c * Ld);
         if (!(logit && wg_c == 1) && Lh > 0) z.add(grad_Dhat_c + per_c * Ld, per_c * Lh);
     }
     if (N == 0) return z.launch(s);

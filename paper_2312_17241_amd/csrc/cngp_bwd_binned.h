@@ -697,10 +697,12 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
                                           (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
     if (sp.partial) {                                                      // as bwd_partial_sums_kernel reads them: all of feature 0, then feature 1
-        double *left = sp.partial + (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
+        const size_t at = (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
         for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {
             const uint32_t f = i >= plane ? 1u : 0u, e = i - f * plane;
-            left[i] = acc[(e / NP) * (2 * NP) + f * NP + (e % NP)];
+            const double   v = acc[(e / NP) * (2 * NP) + f * NP + (e % NP)];
+            if (sp.wide) reinterpret_cast<double *>(sp.partial)[at + i] = v;
+            else reinterpret_cast<float *>(sp.partial)[at + i] = (float)v;
         }
         return;
     }
@@ -742,7 +744,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
     drain_records<D, NP, Raw, false, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                               (float)p.N_l[co.level], sp.rows_log2, load, accum);
     __syncthreads();
-    if (sp.partial) return store_partial(sp, co, acc, rows * NP);
+    if (sp.partial) return sp.wide ? store_partial<double>(sp, co, acc, rows * NP) : store_partial<float>(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)co.level * p.N_c + (size_t)co.slice * rows;
     const float *sig = sigma + row0 * NP;

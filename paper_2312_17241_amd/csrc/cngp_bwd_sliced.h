@@ -44,7 +44,8 @@ struct SliceParams {
     int32_t  store_direct;  // 1: every slice is written by exactly one workgroup -> plain stores
     int32_t  level0;        // levels [level0, level0 + nlevels) are covered by this launch
     int32_t  nlevels;
-    double  *partial;       // not NULL: every workgroup leaves its accumulators as they are, [level][chunk][slice], for bwd_partial_sums_kernel
+    char    *partial;       // not NULL: every workgroup leaves its accumulators, [level][chunk][slice], for bwd_partial_sums_kernel
+    int      wide;          // of a drain: in 64 bits, else in 32 (a scan's always are in 64)
 };
 
 // Levels whose dense vertex grid is small enough to pre-reduce the upstream gradient per vertex.
@@ -87,9 +88,10 @@ __device__ __forceinline__ SliceCoord slice_coord(const SliceParams &sp, const u
 }
 
 // A workgroup's accumulators, `n` doubles, where bwd_partial_sums_kernel looks for them.
+template <typename Sum>
 __device__ __forceinline__ void store_partial(const SliceParams &sp, const SliceCoord &co, const double *acc, const uint32_t n) {
-    double *out = sp.partial + (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * n;
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[i] = acc[i];
+    Sum *out = reinterpret_cast<Sum *>(sp.partial) + (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * n;
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) out[i] = (Sum)acc[i];
 }
 
 // A two-feature codebook entry as it sits in memory.
@@ -415,7 +417,7 @@ __device__ __forceinline__ void bwd_feat_sliced(
         scan_chunk<D, NP, true, false, float>(p, sp, co, x, grad + (size_t)l * N * 2, N, 0u, ring_mem, load, accum);
     __syncthreads();
 
-    if (sp.partial) return store_partial(sp, co, acc, plane * 2);
+    if (sp.partial) return store_partial<double>(sp, co, acc, plane * 2);
     float *out = gD_f + (size_t)l * p.N_f * 2 + (size_t)co.slice * plane * 2;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {     // i = (row * NP + k) * 2 + f
         const float v = (float)acc[(i & 1u) * plane + (i >> 1)];
@@ -459,7 +461,7 @@ __device__ __forceinline__ void bwd_logit_sliced(
         scan_chunk<D, NP, false, false, Raw>(p, sp, co, x, grad + (size_t)l * N * 2, N, 0u, ring_mem, load, accum);
     __syncthreads();
 
-    if (sp.partial) return store_partial(sp, co, acc, rows * NP);
+    if (sp.partial) return store_partial<double>(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)l * p.N_c + (size_t)co.slice * rows;
     const float *sig = sigma + row0 * NP;
@@ -588,14 +590,15 @@ __global__ __launch_bounds__(kSlicedBlock) void bwd_sliced_kernel(
 // Sums of what the chunks of a slice left, in fp64 and rounded once, for batches that are cut into many chunks to fill the chip: added to
 // the gradients with fp32 atomics, 16 chunks were off from 64 bits by 1.06e-7 (2-norm) where one is by 8.0e-8, and cost as much.  The
 // partial sums (at most 768 slices of 128 KB) are written and read once.  Of binned batches with tables of few slices the workgroups that
-// drain a bin leave theirs the same way.  Gradients that are added to are added to with atomics all the
+// drain a bin leave theirs the same way, mostly rounded to 32 bits: of image2d's logit gradient 452 slices of 64 KB, 9.6 us (of both tables in
+// 64 bits, 172 MB, 32 us).  Gradients that are added to are added to with atomics all the
 // same: another call may add to them at the same time, from another stream and workspace.  Blocks: 256 entries of a slice of the feature table (two sums
 // each), then 256 logits of a slice of the confidence table; a role whose slices have one chunk each has stored them itself.
 struct PartialRoles {
     SliceParams sp[4];          // feature, logit; of a binned batch those of its merged levels after them
     uint32_t    first[5];       // first block of each
 };
-template <int NP>
+template <int NP, typename Sum>
 __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
     const Params p, const PartialRoles roles, const float *__restrict__ sigma, const int zero_first, float *__restrict__ gD_f, float *__restrict__ gDhat_c)
 {
@@ -607,12 +610,12 @@ __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
     const uint32_t unit = block / per_slice, i = block % per_slice * kBlock + threadIdx.x;
     const uint32_t level = unit / sp.slices, slice = unit % sp.slices;
     const size_t   n = logit ? plane : 2 * (size_t)plane, step = sp.slices * n;
-    const double  *in = sp.partial + ((size_t)level * sp.chunks * sp.slices + slice) * n + i;
+    const Sum     *in = reinterpret_cast<const Sum *>(sp.partial) + ((size_t)level * sp.chunks * sp.slices + slice) * n + i;
     if (i >= plane) return;                                   // (plane is a multiple of NP: whole rows)
     if (logit) {
         double Q = 0.0;
 #pragma unroll 4
-        for (uint32_t c = 0; c < sp.chunks; ++c) Q += in[c * step];
+        for (uint32_t c = 0; c < sp.chunks; ++c) Q += (double)in[c * step];
         const size_t at = ((size_t)(sp.level0 + (int)level) * p.N_c) * NP + (size_t)slice * plane + i;
         const double s = (double)sigma[at];
         double dot = s * Q;
@@ -624,7 +627,7 @@ __global__ __launch_bounds__(kBlock) void bwd_partial_sums_kernel(
     } else {
         double a = 0.0, b = 0.0;
 #pragma unroll 4
-        for (uint32_t c = 0; c < sp.chunks; ++c) { a += in[c * step]; b += in[c * step + plane]; }
+        for (uint32_t c = 0; c < sp.chunks; ++c) { a += (double)in[c * step]; b += (double)in[c * step + plane]; }
         float *out = gD_f + 2 * ((size_t)(sp.level0 + (int)level) * p.N_f + (size_t)slice * plane + i);
         const float v0 = (float)a, v1 = (float)b;
         if (zero_first) { out[0] = v0; out[1] = v1; }

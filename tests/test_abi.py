@@ -3,6 +3,7 @@ validates arguments before touching the GPU, and computes the level table.  No G
 no call here reaches a kernel launch.
 """
 import ctypes
+import dataclasses
 import os
 import re
 
@@ -391,10 +392,10 @@ def test_arrays_of_the_merged_levels_do_not_overlap():
 
 
 def test_sums_of_drain_workgroups_fit_where_the_entries_were():
-    """Tables of few slices whose levels are merged: what the workgroups of a bin leave, 64-bit sums of a whole slice each, lies inside the
+    """Tables of few slices whose levels are merged: what the workgroups of a bin leave, sums of a whole slice each, lies inside the
     region that the merged entries had, which is as large as the larger of the two."""
     rng = np.random.default_rng(77)
-    seen = {"sums": 0, "larger": 0, "plain": 0}
+    seen = {"sums": 0, "larger": 0, "plain": 0, "atomics": 0, "wide": 0}
     for it in range(600):
         d, N_p = int(rng.choice([2, 3])), int(2 ** rng.integers(0, 5))
         N_f, N_c = int(2 ** rng.integers(13, 18)), int(2 ** rng.integers(1, 15)) if N_p > 1 else 1
@@ -405,9 +406,18 @@ def test_sums_of_drain_workgroups_fit_where_the_entries_were():
         if p["merged_levels"] == 0 or p["slices_f"] == 0 or p["slices_f"] + p["slices_c"] >= 24:
             continue
         M = p["merged_levels"]
-        tables = [(p["slices_f"], N_f * 16 // p["slices_f"], p["drain_wgs_feat"], p["merged_drain_wgs_feat"])]
-        if N_p > 1:
-            tables.append((p["slices_c"], N_c * N_p * 8 // p["slices_c"], p["drain_wgs_logit"], p["merged_drain_wgs_logit"]))
+        scan = cngp.bwd_plan_info(dataclasses.replace(cfg, bin_bytes_max=8 << 30), N)          # (a bound: the scan)
+        tables, wide = [], False
+        for role, slices, entries in [("feat", p["slices_f"], N_f * 2)] + ([("logit", p["slices_c"], N_c * N_p)] if N_p > 1 else []):
+            pts, vtx = (scan[f"chunks_{role}_{k}"] for k in ("pts", "vtx"))
+            least, wgs, merged = min(pts, vtx) if scan["dense_levels"] else pts, p[f"drain_wgs_{role}"], p[f"merged_drain_wgs_{role}"]
+            if wgs > pts or merged > least:
+                tables.append((slices, entries // slices, wgs, merged))
+                wide = wide or least == 1
+            else:                           # no more writers than the scan has chunks: the sums are added with atomics, as the scan's are
+                seen["atomics"] += 1
+        tables = [(s, n * (8 if wide else 4), w, m) for s, n, w, m in tables]
+        seen["wide"] += wide
         sums = sum(s * b * n * levels for s, b, wgs, merged in tables for n, levels in ((wgs, L - M), (merged, M)) if n > 1)
         regions = cngp.bwd_plan_layout(cfg, N)
         entries = (M * (N << d) * 16 + 255) // 256 * 256                          # (the order of the points and the cells behind them)
