@@ -1986,10 +1986,10 @@ int cngp_encode_bwd_static(const cngp_config *cfg, const float *x, int64_t N, co
     if (N < 0) return CNGP_ERR_INVALID;
     if (!grad_D_f || !grad_Dhat_c) return CNGP_ERR_NULL;
     if (N > 0 && (!x || !D_f || !Dhat_c || !dy)) return CNGP_ERR_NULL;
-    // The variant is the one cngp_encode_bwd would pick for (cfg, N).  Only the bins of the binned variant grow
-    // with N: they are bounded until everything fits the static array (the batch is then taken in several passes
-    // inside the one call, like any batch beyond cfg->bin_bytes_max) -- as long as a pass is still binned: this
-    // entry point never falls back to a slower variant behind the caller's back.
+    // The variant is the one cngp_encode_bwd would pick for (cfg, N) in a workspace of this size: in one pass where its
+    // smallest layout fits (without merged levels or partial sums, and tables of few slices scanned, where there is no room for those).
+    // Else the bins are bounded until everything fits (the batch is then taken in several passes inside the one call, like any
+    // batch beyond cfg->bin_bytes_max), as long as a pass is still binned: tables that are binned whatever the room are not scanned here.
     cngp_config c = *cfg;
     size_t need = cngp_workspace_bytes(&c, N);
     if (need > kStaticScratchBytes && N > 0) {      // in one pass all the same, if the smallest layout fits
