@@ -1360,9 +1360,11 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     if (int rc = allow_big_lds(kernel, lds)) return rc;
     const uint32_t total = wgs_c + wgs_f + wgs_cv + wgs_fv;
     if (total == 0) return CNGP_OK;
+    // A record costs a feature slice 2.2 ns and a logit slice 1.95 (N_p = 16, both roles in flight), the fixed part of a workgroup is alike.
+    const bool feat_first = wgs_f > 0 && (wgs_c == 0 || 2.2 * b.slices_c * b.subs_c > 1.95 * b.slices_f * b.subs_f);
     {
         LaunchTimer t(s, K_BWD_BIN_DRAIN);
-        kernel<<<total, kSlicedBlock, lds, s>>>(p, sp_c, sp_f, wgs_c, wgs_c + wgs_f, x, dyT, N, (const FeatT *)D_f, sigma, recF, recC,
+        kernel<<<total, kSlicedBlock, lds, s>>>(p, sp_c, sp_f, feat_first ? wgs_f : wgs_c, wgs_c + wgs_f, feat_first ? 1 : 0, x, dyT, N, (const FeatT *)D_f, sigma, recF, recC,
                                                 baseF, baseC, bp.cap, vtx, b.dense, G, b.merged ? 1 : 0, mb, gD_f, gDhat_c);
         if (int rc = launch_status("bin_drain_kernel")) return rc;
     }

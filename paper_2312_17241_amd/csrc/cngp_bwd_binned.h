@@ -398,14 +398,14 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(
 
 // ------------------------------------------------------------------ drain
 // Value of lane `u` of this lane's group of NP lanes.  Groups of 16 (a DPP row), 4 and 2 (inside a quad): one VALU move;
-// groups of 8 (half a row): two, each writing the two banks of four lanes of its half (a cross-lane read through the
+// groups of 8 (half a row): two, the second writing the two banks of four lanes of its half (a cross-lane read through the
 // LDS crossbar instead cost the drain a fifth of its time at N_p = 8).
 template <int NP, int U>
 __device__ __forceinline__ uint32_t group_bcast(const uint32_t v) {
     if constexpr (NP == 16) {                                             // row_newbcast:U
         return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x150 + U, 0xF, 0xF, true);
-    } else if constexpr (NP == 8) {                                       // row_newbcast:U into banks 0-1, row_newbcast:8+U into banks 2-3
-        const int lo = __builtin_amdgcn_update_dpp(0, (int)v, 0x150 + U, 0xF, 0x3, false);
+    } else if constexpr (NP == 8) {                                       // row_newbcast:U, then row_newbcast:8+U into banks 2-3
+        const int lo = __builtin_amdgcn_mov_dpp((int)v, 0x150 + U, 0xF, 0xF, true);
         return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)v, 0x150 + 8 + U, 0xF, 0xC, false);
     } else if constexpr (NP == 4) {                                       // quad_perm:[U,U,U,U]
         return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, U * 0x55, 0xF, 0xF, true);
@@ -457,18 +457,18 @@ __device__ __forceinline__ void accum_steps(const uint4 &r, const T (&g)[NP], Ac
 // BOTH (records of a confidence-table bin, both gradients accumulated): the gather reads the row INSIDE the
 // slice (the softmax row of the record's own confidence row), the accumulator row is the other table's.
 // ACC: doubles per candidate of an accumulator row (2 where both features of a row sit side by side).
+// `clear` prepares what the workgroup accumulates in; a barrier follows it.
 // BY_FEAT: the bin belongs to a slice of the feature table (rows by hash), else of the confidence table (hash2).
 // MERGED: the records are entries, which hold their rows and g.
-template <int D, int NP, typename T, bool BOTH, int ACC, bool BY_FEAT, bool MERGED, typename Record, typename IoT, typename Load, typename Accum>
+template <int D, int NP, typename T, bool BOTH, int ACC, bool BY_FEAT, bool MERGED, typename Record, typename IoT, typename Clear, typename Load, typename Accum>
 __device__ __forceinline__ void drain_records(const Params &p, const Record *__restrict__ rec, const uint32_t beg, const uint32_t end,
                                               const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
-                                              const uint32_t rows_log2, Load load, Accum accum)
+                                              const uint32_t rows_log2, Clear clear, Load load, Accum accum)
 {
     const uint32_t row_lo_mask = (1u << rows_log2) - 1u;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint32_t stride = kSlicedWaves * 64u;
     uint32_t b = beg + wave * 64u;
-    if (b >= end) return;
     const uint32_t last = end - 1u;
     using Pair = typename std::conditional<sizeof(IoT) == 2, uint32_t, float2>::type;   // dL/dy of a level as stored
     // Four stages, a batch apart, over four register buffers (unrolled four times, so no buffer is copied):
@@ -534,12 +534,20 @@ __device__ __forceinline__ void drain_records(const Params &p, const Record *__r
                        __float_as_uint(wt * gy.y), (BOTH ? other : inside) * (uint32_t)(ACC * NP * sizeof(double)));
         gather_steps<NP, 0>(r, g, load);
     };
-    // prologue: batches b, b + stride, b + 2 stride enter the pipeline
-    stage_a(b, Q[0]);
-    stage_a(b + stride, Q[1]);
-    stage_a(b + 2 * stride, Q[2]);
-    stage_b(Q[0], S[0]);
-    stage_b(Q[1], S[1]);
+    // prologue: batches b, b + stride, b + 2 stride enter the pipeline, and the accumulators are cleared while their loads are under way
+    const bool some = b < end;                               // (the same for all lanes of a wavefront)
+    if (some) {
+        stage_a(b, Q[0]);
+        stage_a(b + stride, Q[1]);
+        stage_a(b + 2 * stride, Q[2]);
+    }
+    clear();
+    if (some) {
+        stage_b(Q[0], S[0]);
+        stage_b(Q[1], S[1]);
+    }
+    __syncthreads();
+    if (!some) return;
     stage_c(b, Q[0], S[0], R[0], G[0]);
 #define CNGP_DRAIN_STEP(P0, P1, P2, P3)                                                  \
         stage_a(b + 3 * stride, Q[P3]);                                                  \
@@ -653,31 +661,26 @@ __global__ __launch_bounds__(kSlicedBlock) void bin_grid_drain_kernel(
 }
 
 // Merged levels are of unequal work: every level over all XCDs, the last one, which has the most entries, first (a level to an
-// XCD, as the others: 470 us for nerf3d's drain where this took 415).
-__device__ __forceinline__ SliceCoord merged_coord(const SliceParams &sp, const uint32_t i) {
-    const uint32_t per_level = sp.slices * sp.chunks, total = per_level * (uint32_t)sp.nlevels;
-    const uint32_t unit = total - 1u - i, rem = unit % per_level;
+// XCD, as the others: 470 us for nerf3d's drain where this took 415).  `i`: the workgroup among those of its level and role.
+__device__ __forceinline__ SliceCoord merged_coord(const SliceParams &sp, const int level, const uint32_t i) {
     SliceCoord c;
-    c.index = i < total ? (int)(unit / per_level) : -1;
-    c.level = sp.level0 + c.index;
-    c.chunk = rem / sp.slices;
-    c.slice = rem % sp.slices;
+    c.index = level;
+    c.level = sp.level0 + level;
+    c.chunk = i / sp.slices;
+    c.slice = i % sp.slices;
     return c;
 }
 
 // sp: rows_log2, slices, chunks (= drain workgroups per bin), store_direct, level0, nlevels, partial as in the sliced variant.
 template <int D, int NP, bool MERGED, typename IoT, typename Record>
-__device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
+__device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &sp, const SliceCoord co, unsigned char *smem,
                                            const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
                                            const float *__restrict__ sigma, const Record *__restrict__ recF,
                                            const uint32_t *__restrict__ baseF, const uint32_t cap, float *__restrict__ gD_f)
 {
     const uint32_t rows = 1u << sp.rows_log2, plane = rows * NP;
     double *acc = reinterpret_cast<double *>(smem);
-    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
-    for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) acc[i] = 0.0;
-    __syncthreads();
     // accumulators [row][f][k]: the NP lanes of a record add to NP consecutive doubles, and feature 1 sits a constant
     // NP doubles behind feature 0 (an immediate offset of the LDS instruction)
     const char    *sig_l = reinterpret_cast<const char *>(sigma + (size_t)co.level * p.N_c * NP);   // uniform: scalar base of the gathers
@@ -691,10 +694,11 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
         atomicAdd(a, (double)(s * g.x));
         atomicAdd(a + NP, (double)(s * g.y));
     };
+    auto clear = [&]() { for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) acc[i] = 0.0; };
     uint32_t beg, end;
     bin_range(baseF, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
     drain_records<D, NP, float, false, 2, true, MERGED>(p, recF + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                                          (float)p.N_l[co.level], sp.rows_log2, load, accum);
+                                          (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
     __syncthreads();
     if (sp.partial) {                                                      // as bwd_partial_sums_kernel reads them: all of feature 0, then feature 1
         const size_t at = (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
@@ -716,7 +720,7 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
 }
 
 template <int D, int NP, bool MERGED, typename FeatT, typename IoT, typename Record>
-__device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
+__device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &sp, const SliceCoord co, unsigned char *smem,
                                             const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
                                             const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
                                             const Record *__restrict__ recC, const uint32_t *__restrict__ baseC,
@@ -724,10 +728,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
 {
     const uint32_t rows = 1u << sp.rows_log2;
     double *acc = reinterpret_cast<double *>(smem);
-    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
-    for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) acc[i] = 0.0;
-    __syncthreads();
     const FeatT   *F_l = D_f + (size_t)co.level * p.N_f * 2;
     const uint32_t k = (threadIdx.x & 63) % NP;
     using Raw = typename RawPair<FeatT>::type;
@@ -739,26 +740,16 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
         const float2 feat = RawPair<FeatT>::to_float2(raw);
         atomicAdd(reinterpret_cast<double *>(acc_k + off), (double)fmaf(feat.x, g.x, feat.y * g.y));
     };
+    auto clear = [&]() { for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) acc[i] = 0.0; };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
     drain_records<D, NP, Raw, false, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                              (float)p.N_l[co.level], sp.rows_log2, load, accum);
+                              (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
     __syncthreads();
     if (sp.partial) return sp.wide ? store_partial<double>(sp, co, acc, rows * NP) : store_partial<float>(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)co.level * p.N_c + (size_t)co.slice * rows;
-    const float *sig = sigma + row0 * NP;
-    float       *out = gDhat_c + row0 * NP;
-    for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) {
-        const double Q = acc[i];
-        const double s = (double)sig[i];
-        double dot = s * Q;
-#pragma unroll
-        for (int o = NP / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, NP);
-        const float v = (float)(s * (Q - dot));
-        if (sp.store_direct) out[i] = v;
-        else if (v != 0.0f) atomic_add(out + i, v);
-    }
+    flush_logits<NP>(acc, rows * NP, sigma + row0 * NP, gDhat_c + row0 * NP, sp.store_direct);
 }
 
 // Small feature table: both gradients from the confidence-table bins in one pass.  LDS holds the slice of
@@ -767,7 +758,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
 // rows of this slice instead of the whole table.  The feature gradient goes out with atomics (every
 // workgroup of the level holds a share of it): the caller has cleared it.
 template <int D, int NP, bool MERGED, typename FeatT, typename IoT, typename Record>
-__device__ __forceinline__ void drain_both(const Params &p, const SliceParams &sp, const uint32_t wg, unsigned char *smem,
+__device__ __forceinline__ void drain_both(const Params &p, const SliceParams &sp, const SliceCoord co, unsigned char *smem,
                                            const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
                                            const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
                                            const Record *__restrict__ recC, const uint32_t *__restrict__ baseC,
@@ -778,12 +769,12 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     double *accQ = reinterpret_cast<double *>(smem);                    // [rows][NP]
     double *accF = accQ + (size_t)rows * NP;                            // [2][N_f]: feature 0 of every entry, then feature 1
     Raw    *feat = reinterpret_cast<Raw *>(accF + 2 * (size_t)plane);   // [N_f]
-    const SliceCoord co = MERGED ? merged_coord(sp, wg) : slice_coord(sp, wg);
     if (co.index < 0) return;
     const Raw *F_l = reinterpret_cast<const Raw *>(D_f + (size_t)co.level * p.N_f * 2);
-    for (uint32_t i = threadIdx.x; i < rows * NP + 2 * plane; i += kSlicedBlock) accQ[i] = 0.0;
-    for (uint32_t i = threadIdx.x; i < plane; i += kSlicedBlock) feat[i] = F_l[i];
-    __syncthreads();
+    auto clear = [&]() {
+        for (uint32_t i = threadIdx.x; i < rows * NP + 2 * plane; i += kSlicedBlock) accQ[i] = 0.0;
+        for (uint32_t i = threadIdx.x; i < plane; i += kSlicedBlock) feat[i] = F_l[i];
+    };
     const size_t   row0 = (size_t)co.level * p.N_c + (size_t)co.slice * rows;
     const uint32_t k = (threadIdx.x & 63) % NP;
     const char *sig_k = reinterpret_cast<const char *>(sigma + row0 * NP + k);          // this lane's candidate, this slice's rows
@@ -802,34 +793,25 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
     drain_records<D, NP, float, true, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                                      (float)p.N_l[co.level], sp.rows_log2, load, accum);
+                                      (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
     __syncthreads();
     float *outF = gD_f + (size_t)co.level * p.N_f * 2;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {     // i = entry * 2 + f
         const float v = (float)accF[(i & 1u) * plane + (i >> 1)];
         if (v != 0.0f) atomic_add(outF + i, v);
     }
-    const float *sig = sigma + row0 * NP;
-    float       *out = gDhat_c + row0 * NP;
-    for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) {
-        const double Q = accQ[i];
-        const double s = (double)sig[i];
-        double dot = s * Q;
-#pragma unroll
-        for (int o = NP / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, NP);
-        const float v = (float)(s * (Q - dot));
-        if (sp.store_direct) out[i] = v;
-        else if (v != 0.0f) atomic_add(out + i, v);
-    }
+    flush_logits<NP>(accQ, rows * NP, sigma + row0 * NP, gDhat_c + row0 * NP, sp.store_direct);
 }
 
-// Workgroups [0, first_feat) drain the confidence-table bins, [first_feat, first_vtx) the feature-table
-// bins; the rest are the two roles of the first levels: of the merged ones the same drains of their entries, of the
+// The first workgroups drain the bins of one table, those up to first_vtx the bins of the other, the longer ones first (feat_first);
+// the rest are the two roles of the first levels: of the merged ones the same drains of their entries, of the
 // pre-reduced ones those of cngp_bwd_sliced.h (they scan the vertex grids that the launch before this one has
-// completed), sharing the launch so that the CUs stay busy.
+// completed), sharing the launch so that the CUs stay busy.  Long ones first because a CU holds one workgroup and the last round is
+// never full: 20011 ray samples, 256 workgroups of 25 us and 128 of 37, took 66 us with the short ones first.  Merged levels descend, both
+// tables' workgroups of a level side by side: table after table the second one's longest began last.
 template <int D, int NP, typename FeatT, typename IoT>
 __global__ __launch_bounds__(kSlicedBlock) void bin_drain_kernel(
-    const Params p, const SliceParams sp_c, const SliceParams sp_f, const uint32_t first_feat, const uint32_t first_vtx,
+    const Params p, const SliceParams sp_c, const SliceParams sp_f, const uint32_t first_second, const uint32_t first_vtx, const int feat_first,
     const float *__restrict__ x, const IoT *__restrict__ dyT, const int64_t N,
     const FeatT *__restrict__ D_f, const float *__restrict__ sigma,
     const BinRecord *__restrict__ recF, const BinRecord *__restrict__ recC,
@@ -838,24 +820,35 @@ __global__ __launch_bounds__(kSlicedBlock) void bin_drain_kernel(
     float *__restrict__ gD_f, float *__restrict__ gDhat_c)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    if (blockIdx.x < first_feat) {
-        if constexpr (NP > 1) {
-            if (sp_f.nlevels == 0) drain_both<D, NP, false, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gD_f, gDhat_c);
-            else drain_logit<D, NP, false, FeatT, IoT>(p, sp_c, blockIdx.x, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gDhat_c);
+    if (blockIdx.x < first_vtx) {
+        const bool     second = blockIdx.x >= first_second;
+        const uint32_t wg = second ? blockIdx.x - first_second : blockIdx.x;
+        if (second == (feat_first != 0)) {
+            if constexpr (NP > 1) {
+                const SliceCoord co = slice_coord(sp_c, wg);
+                if (co.index < 0) return;
+                if (sp_f.nlevels == 0) drain_both<D, NP, false, FeatT, IoT>(p, sp_c, co, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gD_f, gDhat_c);
+                else drain_logit<D, NP, false, FeatT, IoT>(p, sp_c, co, smem, x, dyT, N, D_f, sigma, recC, baseC, cap, gDhat_c);
+            }
+        } else {
+            const SliceCoord co = slice_coord(sp_f, wg);
+            if (co.index < 0) return;
+            drain_feat<D, NP, false, IoT>(p, sp_f, co, smem, x, dyT, N, sigma, recF, baseF, cap, gD_f);
         }
-    } else if (blockIdx.x < first_vtx) {
-        drain_feat<D, NP, false, IoT>(p, sp_f, blockIdx.x - first_feat, smem, x, dyT, N, sigma, recF, baseF, cap, gD_f);
     } else {
         const uint32_t wg = blockIdx.x - first_vtx;
         const SliceParams &vc = vtx.sp[ROLE_LOGIT_VTX], &vf = vtx.sp[ROLE_FEAT_VTX];
         if (merged) {
-            if (wg < vtx.first[ROLE_FEAT_VTX]) {
-                if constexpr (NP > 1) {
-                    if (vf.nlevels == 0) drain_both<D, NP, true, FeatT, IoT>(p, vc, wg, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gD_f, gDhat_c);
-                    else drain_logit<D, NP, true, FeatT, IoT>(p, vc, wg, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gDhat_c);
-                }
-            } else {
-                drain_feat<D, NP, true, IoT>(p, vf, wg - vtx.first[ROLE_FEAT_VTX], smem, x, dyT, N, sigma, mb.recF, mb.baseF, cap, gD_f);
+            const uint32_t of_c = vc.nlevels ? vc.slices * vc.chunks : 0u, of_f = vf.nlevels ? vf.slices * vf.chunks : 0u;     // of a level
+            const int      level = (int)mb.levels - 1 - (int)(wg / (of_c + of_f));
+            const uint32_t i = wg % (of_c + of_f);
+            if (level < 0) return;
+            if (i < of_f) {
+                drain_feat<D, NP, true, IoT>(p, vf, merged_coord(vf, level, i), smem, x, dyT, N, sigma, mb.recF, mb.baseF, cap, gD_f);
+            } else if constexpr (NP > 1) {
+                const SliceCoord co = merged_coord(vc, level, i - of_f);
+                if (of_f == 0u) drain_both<D, NP, true, FeatT, IoT>(p, vc, co, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gD_f, gDhat_c);
+                else drain_logit<D, NP, true, FeatT, IoT>(p, vc, co, smem, x, dyT, N, D_f, sigma, mb.recC, mb.baseC, cap, gDhat_c);
             }
         } else if (wg < vtx.first[ROLE_FEAT_VTX]) {
             if (NP > 1)

@@ -427,6 +427,49 @@ __device__ __forceinline__ void bwd_feat_sliced(
 }
 
 // ------------------------------------------------------------------ logit gradient
+// Sum over the NP lanes of a row, by moves inside a row of 16 lanes (the order of the terms is that of the exchanges
+// with lane ^ 1, ^ 2, ^ 4, ^ 8, whose two cross-lane LDS reads each kept the flush of a slice from its loads).
+template <int NP>
+__device__ __forceinline__ double row_total(double v) {
+    static_assert(NP <= 16, "a row of 16 lanes");
+    auto moved = [](const double t, auto ctrl) {
+        constexpr int C = decltype(ctrl)::value;
+        const uint64_t b = __builtin_bit_cast(uint64_t, t);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)b, C, 0xF, 0xF, true);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_mov_dpp((int)(uint32_t)(b >> 32), C, 0xF, 0xF, true);
+        return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+    };
+    if (NP >= 2)  v += moved(v, std::integral_constant<int, 0xB1>());     // quad_perm:[1,0,3,2]
+    if (NP >= 4)  v += moved(v, std::integral_constant<int, 0x4E>());     // quad_perm:[2,3,0,1]
+    if (NP >= 8)  v += moved(v, std::integral_constant<int, 0x141>());    // row_half_mirror
+    if (NP >= 16) v += moved(v, std::integral_constant<int, 0x140>());    // row_mirror
+    return v;
+}
+
+// Softmax Jacobian of a slice's `n` accumulators, whole rows of NP, then out to HBM; NP consecutive lanes hold one row.  The
+// softmax rows are loaded eight at a time: one by one a slice's sixteen loads per lane were a chain of memory latencies (10 us).
+template <int NP>
+__device__ __forceinline__ void flush_logits(const double *acc, const uint32_t n, const float *__restrict__ sig, float *__restrict__ out, const bool direct) {
+    constexpr uint32_t kAhead = 8;
+    for (uint32_t i0 = threadIdx.x; i0 < n; i0 += kAhead * kSlicedBlock) {
+        float s[kAhead];
+#pragma unroll
+        for (uint32_t t = 0; t < kAhead; ++t) {
+            const uint32_t i = i0 + t * kSlicedBlock;
+            s[t] = sig[i < n ? i : i0];
+        }
+#pragma unroll
+        for (uint32_t t = 0; t < kAhead; ++t) {
+            const uint32_t i = i0 + t * kSlicedBlock;
+            if (i >= n) break;                                        // (n is a multiple of NP: whole rows leave together)
+            const double Q = acc[i], sd = (double)s[t];
+            const float  v = (float)(sd * (Q - row_total<NP>(sd * Q)));
+            if (direct) out[i] = v;
+            else if (v != 0.0f) atomic_add(out + i, v);
+        }
+    }
+}
+
 template <int D, int NP, bool VERTEX, typename FeatT, typename GradT>
 __device__ __forceinline__ void bwd_logit_sliced(
     const Params &p, const SliceParams &sp, const DenseLevels &dl, const uint32_t wg, unsigned char *smem,
@@ -464,18 +507,7 @@ __device__ __forceinline__ void bwd_logit_sliced(
     if (sp.partial) return store_partial<double>(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
     const size_t row0 = (size_t)l * p.N_c + (size_t)co.slice * rows;
-    const float *sig = sigma + row0 * NP;
-    float       *out = gDhat_c + row0 * NP;
-    for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) {
-        const double Q = acc[i];
-        const double s = (double)sig[i];
-        double dot = s * Q;
-#pragma unroll
-        for (int o = NP / 2; o > 0; o >>= 1) dot += __shfl_xor(dot, o, NP);
-        const float v = (float)(s * (Q - dot));
-        if (sp.store_direct) out[i] = v;
-        else if (v != 0.0f) atomic_add(out + i, v);
-    }
+    flush_logits<NP>(acc, rows * NP, sigma + row0 * NP, gDhat_c + row0 * NP, sp.store_direct);
 }
 
 // ------------------------------------------------------------------ per-vertex pre-reduction
