@@ -7,7 +7,8 @@
 //               table (by hash) and of the confidence table (by hash2); histogram in LDS
 //   2. offsets  exclusive prefix sums: where every (chunk, slice) writes inside the level's record array
 //   3. scatter  the same walk again, every reference written as a 4-byte record  point index * 2^d + corner
-//               to its slice's bin, positions handed out by LDS counters that start at the offsets
+//               to its slice's bin, positions handed out by LDS counters that start at the offsets; of the feature table one
+//               record for the two corners of an edge along dimension 0 (below)
 //   4. drain    a workgroup owns a slice as fp64 accumulators in LDS, as in the sliced variant, but reads
 //               only its own bin, coalesced, one record per lane: the lane re-derives the two hashed rows and
 //               weight * dL/dy of its record from the point (some thirty instructions per record, against 12
@@ -29,6 +30,14 @@ namespace cngp {
 constexpr int kBinBlock = 64;
 
 // A binned corner reference: point index * 2^d + corner (the host keeps N * 2^d below 2^31 per pass).
+//
+// In a bin of the feature table the corner is an even one, and the record stands for it and the next, the two ends of an edge
+// along dimension 0.  The first factor of `hash` is 1, so their rows are v ^ t and (v + 1) ^ t: in the same slice unless v ends in as
+// many ones as a slice's rows have bits.  Then, and only then, both slices have the record.  Whoever drains it takes the corners whose
+// row is in its slice and whose weight is not zero.  That is half the records to write and read, and half the points and upstream
+// gradients to gather.  Scatter and drain, us, a record per corner / per edge: 2^20 points near a surface (N_p = 8, 32 + 32 bins) 236 + 1485 /
+// 198 + 1407, image2d (8 + 2 bins) 95 + 372 / 93 + 363, nerf3d (N_p = 16, 8 + 16 bins) 61 + 336 / 52 + 335: there LDS and vector ALU bound
+// the drain, which has as many corners to add as before.
 using BinRecord = uint32_t;
 constexpr size_t kRecordBytes = sizeof(BinRecord);
 
@@ -121,6 +130,16 @@ __device__ __forceinline__ void corner_rows(const Cell<D> &cell, const Params &p
     h2 = cell.hash2(c) & p.c_mask;
 }
 
+// The slices whose bins hold the edge (c, c + 1) of a cell: how many of them (0 where neither corner has a weight), and which.
+template <int D>
+__device__ __forceinline__ uint32_t edge_slices(const uint32_t h1a, const uint32_t h1b, const bool live_a, const bool live_b,
+                                                const uint32_t rows_f_log2, uint32_t &first, uint32_t &second) {
+    const uint32_t a = h1a >> rows_f_log2, b = h1b >> rows_f_log2;
+    first = live_a ? a : b;
+    second = b;
+    return (live_a || live_b ? 1u : 0u) + (live_a && live_b && a != b ? 1u : 0u);
+}
+
 // Workgroups [0, nlevels * chunks) count the hashed levels; the next level0 * chunks ones count the pre-reduced levels
 // 0 .. level0 - 1 by slice of their vertex grid, unless those are merged (which counts them itself).
 template <int D>
@@ -172,12 +191,18 @@ __device__ __forceinline__ void bin_count_block(
         Cell<D> cell;
         cell.locate(xp, p.N_l[l]);
 #pragma unroll
-        for (int c = 0; c < (1 << D); ++c) {
-            if (cell.weight(c) == 0.0f) continue;
-            uint32_t h1, h2;
-            corner_rows<D>(cell, p, c, h1, h2);
-            if (bp.slices_f) atomicAdd(&mine[h1 >> bp.rows_f_log2], 1u);
-            if (bp.slices_c) atomicAdd(&mine[bp.slices_f + (h2 >> bp.rows_c_log2)], 1u);
+        for (int c = 0; c < (1 << D); c += 2) {
+            uint32_t h1[2], h2[2], first, second;
+            bool live[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                corner_rows<D>(cell, p, c + e, h1[e], h2[e]);
+                live[e] = cell.weight(c + e) != 0.0f;
+                if (bp.slices_c && live[e]) atomicAdd(&mine[bp.slices_f + (h2[e] >> bp.rows_c_log2)], 1u);
+            }
+            const uint32_t n_f = edge_slices<D>(h1[0], h1[1], live[0], live[1], bp.rows_f_log2, first, second);
+            if (bp.slices_f && n_f) atomicAdd(&mine[first], 1u);
+            if (bp.slices_f && n_f > 1) atomicAdd(&mine[second], 1u);
         }
     }
     __syncthreads();
@@ -379,19 +404,19 @@ __global__ __launch_bounds__(256) void bin_scatter_kernel(
         Cell<D> cell;
         cell.locate(xp, p.N_l[l]);
 #pragma unroll
-        for (int c = 0; c < (1 << D); ++c) {
-            if (cell.weight(c) == 0.0f) continue;
-            uint32_t h1, h2;
-            corner_rows<D>(cell, p, c, h1, h2);
+        for (int c = 0; c < (1 << D); c += 2) {
             const uint32_t ref = ((uint32_t)n << D) | (uint32_t)c;
-            if (bp.slices_f) {
-                const uint32_t posF = atomicAdd(&cursor[h1 >> bp.rows_f_log2], 1u);
-                outF[posF] = ref;
+            uint32_t h1[2], h2[2], first, second;
+            bool live[2];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                corner_rows<D>(cell, p, c + e, h1[e], h2[e]);
+                live[e] = cell.weight(c + e) != 0.0f;
+                if (bp.slices_c && live[e]) outC[atomicAdd(&cursor[bp.slices_f + (h2[e] >> bp.rows_c_log2)], 1u)] = ref + (uint32_t)e;
             }
-            if (bp.slices_c) {
-                const uint32_t posC = atomicAdd(&cursor[bp.slices_f + (h2 >> bp.rows_c_log2)], 1u);
-                outC[posC] = ref;
-            }
+            const uint32_t n_f = edge_slices<D>(h1[0], h1[1], live[0], live[1], bp.rows_f_log2, first, second);
+            if (bp.slices_f && n_f) outF[atomicAdd(&cursor[first], 1u)] = ref;
+            if (bp.slices_f && n_f > 1) outF[atomicAdd(&cursor[second], 1u)] = ref;
         }
     }
 }
@@ -458,9 +483,8 @@ __device__ __forceinline__ void accum_steps(const uint4 &r, const T (&g)[NP], Ac
 // slice (the softmax row of the record's own confidence row), the accumulator row is the other table's.
 // ACC: doubles per candidate of an accumulator row (2 where both features of a row sit side by side).
 // `clear` prepares what the workgroup accumulates in; a barrier follows it.
-// BY_FEAT: the bin belongs to a slice of the feature table (rows by hash), else of the confidence table (hash2).
-// MERGED: the records are entries, which hold their rows and g.
-template <int D, int NP, typename T, bool BOTH, int ACC, bool BY_FEAT, bool MERGED, typename Record, typename IoT, typename Clear, typename Load, typename Accum>
+// MERGED: the records are entries, which hold their rows and g; else the bin belongs to a slice of the confidence table.
+template <int D, int NP, typename T, bool BOTH, int ACC, bool MERGED, typename Record, typename IoT, typename Clear, typename Load, typename Accum>
 __device__ __forceinline__ void drain_records(const Params &p, const Record *__restrict__ rec, const uint32_t beg, const uint32_t end,
                                               const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
                                               const uint32_t rows_log2, Clear clear, Load load, Accum accum)
@@ -525,8 +549,8 @@ __device__ __forceinline__ void drain_records(const Params &p, const Record *__r
             h1 &= p.row_mask;
             h2 &= p.c_mask;
             gy = pair_to_float2(src.y);
-            inside = (BY_FEAT ? h1 : h2) & row_lo_mask;
-            other = BY_FEAT ? h2 : h1;
+            inside = h2 & row_lo_mask;
+            other = h1;
         }
         // once per record: byte offset of the row the gather reads (candidate 0), and byte offset of the
         // accumulator row in LDS; the lanes of the group add their candidate's share
@@ -563,6 +587,111 @@ __device__ __forceinline__ void drain_records(const Params &p, const Record *__r
         CNGP_DRAIN_STEP(3, 0, 1, 2)
     }
 #undef CNGP_DRAIN_STEP
+}
+
+// The same for the bins of the feature table, whose records are edges: a record's two corners follow each other through stages C and D,
+// so that the gathers of one are under way while the other is accumulated.  A corner that is not this slice's, or has no weight, adds
+// zero to the row of the one that is and has (whose softmax row it reads too: a NaN goes where it would have gone anyway).
+template <int D, int NP, typename IoT, typename Clear, typename Load, typename Accum>
+__device__ __forceinline__ void drain_edges(const Params &p, const BinRecord *__restrict__ rec, const uint32_t beg, const uint32_t end,
+                                            const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
+                                            const uint32_t rows_log2, const uint32_t slice, Clear clear, Load load, Accum accum)
+{
+    const uint32_t row_lo_mask = (1u << rows_log2) - 1u;
+    const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const uint32_t stride = kSlicedWaves * 64u;
+    uint32_t b = beg + wave * 64u;
+    const uint32_t last = end - 1u;
+    using Pair = typename std::conditional<sizeof(IoT) == 2, uint32_t, float2>::type;
+    BinRecord Q[4];
+    struct Point { float xp[D]; Pair y; };
+    Point S[4];
+    uint4 R[2][2];                                           // of a batch's two corners: gather offset, weight * dL/dy, LDS offset
+    float G[2][NP];                                          // what the gathers bring, by corner
+    auto stage_a = [&](const uint32_t base, BinRecord &q) {
+        const uint32_t i = base + lane;
+        q = __builtin_nontemporal_load(rec + (i < last ? i : last));
+    };
+    auto stage_b = [&](const BinRecord q, Point &src) {
+        const uint32_t n = q >> D;
+#pragma unroll
+        for (int j = 0; j < D; ++j) src.xp[j] = x[(size_t)n * D + j];
+        src.y = reinterpret_cast<const Pair *>(dy_l)[n];
+    };
+    auto stage_c = [&](const uint32_t base, const BinRecord q, const Point &src, uint4 (&r)[2]) {
+        float    wt[2];
+        uint32_t h1[2], h2[2];
+        {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int j = 0; j < D; ++j) {
+                const float pos = src.xp[j] * res;           // one rounded fp32 multiply
+                const float fl = floorf(pos);
+                const float w = pos - fl;
+                if (j == 0) {
+                    const uint32_t v = (uint32_t)fl;
+                    wt[0] = 1.0f - w;                        // (the factors in the order of corner_weight)
+                    wt[1] = w;
+                    h1[0] = v * kPi[0];
+                    h1[1] = h1[0] + kPi[0];
+                    h2[0] = v * kPi2[0];
+                    h2[1] = h2[0] + kPi2[0];
+                } else {
+                    const uint32_t up = (q >> j) & 1u, v = (uint32_t)fl + up, t1 = v * kPi[j], t2 = v * kPi2[j];
+                    const float    f = up ? w : 1.0f - w;
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) { wt[e] *= f; h1[e] ^= t1; h2[e] ^= t2; }
+                }
+            }
+        }
+        const float2 gy = pair_to_float2(src.y);
+        bool         mine[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            h1[e] &= p.row_mask;
+            mine[e] = wt[e] != 0.0f && (h1[e] >> rows_log2) == slice;
+        }
+        const bool live = base + lane < end;                 // beyond the bin: contributes nothing
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            const uint32_t row = mine[e] ? h1[e] : h1[1 - e], other = (mine[e] ? h2[e] : h2[1 - e]) & p.c_mask;
+            const bool     adds = live && mine[e];
+            r[e] = make_uint4(other * (uint32_t)(NP * sizeof(float)), __float_as_uint(adds ? wt[e] * gy.x : 0.0f), __float_as_uint(adds ? wt[e] * gy.y : 0.0f),
+                              (row & row_lo_mask) * (uint32_t)(2 * NP * sizeof(double)));
+        }
+    };
+    const bool some = b < end;
+    if (some) {
+        stage_a(b, Q[0]);
+        stage_a(b + stride, Q[1]);
+        stage_a(b + 2 * stride, Q[2]);
+    }
+    clear();
+    if (some) {
+        stage_b(Q[0], S[0]);
+        stage_b(Q[1], S[1]);
+    }
+    __syncthreads();
+    if (!some) return;
+    stage_c(b, Q[0], S[0], R[0]);
+    gather_steps<NP, 0>(R[0][0], G[0], load);
+#define CNGP_EDGE_STEP(P0, P1, P2, P3)                                                   \
+        stage_a(b + 3 * stride, Q[P3]);                                                  \
+        stage_b(Q[P2], S[P2]);                                                           \
+        gather_steps<NP, 0>(R[P0 & 1][1], G[1], load);                                   \
+        accum_steps<NP, 0, false>(R[P0 & 1][0], G[0], accum);                            \
+        stage_c(b + stride, Q[P1], S[P1], R[P1 & 1]);                                    \
+        gather_steps<NP, 0>(R[P1 & 1][0], G[0], load);                                   \
+        accum_steps<NP, 0, false>(R[P0 & 1][1], G[1], accum);                            \
+        b += stride;                                                                     \
+        if (b >= end) break;
+    for (;;) {
+        CNGP_EDGE_STEP(0, 1, 2, 3)
+        CNGP_EDGE_STEP(1, 2, 3, 0)
+        CNGP_EDGE_STEP(2, 3, 0, 1)
+        CNGP_EDGE_STEP(3, 0, 1, 2)
+    }
+#undef CNGP_EDGE_STEP
 }
 
 // The records of (level index li, slice, sub) of one role: sub-range `sub` of `subs` equal parts of the bin.
@@ -697,8 +826,10 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
     auto clear = [&]() { for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) acc[i] = 0.0; };
     uint32_t beg, end;
     bin_range(baseF, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, float, false, 2, true, MERGED>(p, recF + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                                          (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
+    const IoT *dy_l = dyT + (size_t)co.level * N * 2;
+    const float res = (float)p.N_l[co.level];
+    if constexpr (MERGED) drain_records<D, NP, float, false, 2, true>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, clear, load, accum);
+    else drain_edges<D, NP>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, co.slice, clear, load, accum);
     __syncthreads();
     if (sp.partial) {                                                      // as bwd_partial_sums_kernel reads them: all of feature 0, then feature 1
         const size_t at = (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
@@ -743,7 +874,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
     auto clear = [&]() { for (uint32_t i = threadIdx.x; i < rows * NP; i += kSlicedBlock) acc[i] = 0.0; };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, Raw, false, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+    drain_records<D, NP, Raw, false, 1, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                               (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
     __syncthreads();
     if (sp.partial) return sp.wide ? store_partial<double>(sp, co, acc, rows * NP) : store_partial<float>(sp, co, acc, rows * NP);
@@ -792,7 +923,7 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, float, true, 1, false, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+    drain_records<D, NP, float, true, 1, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
                                       (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
     __syncthreads();
     float *outF = gD_f + (size_t)co.level * p.N_f * 2;

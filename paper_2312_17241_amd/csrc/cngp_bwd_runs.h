@@ -96,29 +96,34 @@ __device__ __forceinline__ void scatter_refs_in_runs(
                 float    wt;
                 if (half) { corner_rows<D>(cell, p, (int)(c | 8u) & kLast, h1, h2); wt = cell.weight((int)(c | 8u) & kLast); }
                 else      { corner_rows<D>(cell, p, (int)c, h1, h2); wt = cell.weight((int)c); }
-                bf[k] = h1 >> bp.rows_f_log2;
+                bf[k] = h1;
                 bc[k] = c_at + (h2 >> bp.rows_c_log2);
                 live |= there && wt != 0.0f ? 1u << k : 0u;         // weight zero: adds nothing, and was not counted
             }
         }
+        uint32_t edges = 0;                                         // records of the feature table: of an edge in its even corner's place, a second one in the odd one's
+#pragma unroll
+        for (uint32_t k = 0; k < kScatRefsPer; k += 2) {
+            uint32_t first_bin, second_bin;
+            const uint32_t n_f = edge_slices<D>(bf[k], bf[k + 1], live >> k & 1u, live >> k & 2u, bp.rows_f_log2, first_bin, second_bin);
+            bf[k] = first_bin;
+            bf[k + 1] = second_bin;
+            edges |= (n_f > 1u ? 3u : n_f) << k;
+        }
         if (r0 + kScatRefs < items) fetch(r0 + kScatRefs);
 #pragma unroll
         for (uint32_t k = 0; k < kScatRefsPer; ++k) {
-            if (live >> k & 1u) {
-                if (sf) bf[k] |= atomicAdd(&mine[bf[k]], 1u) << 16;
-                if (sc) bc[k] |= atomicAdd(&mine[bc[k]], 1u) << 16;
-            }
+            if (sf && (edges >> k & 1u)) bf[k] |= atomicAdd(&mine[bf[k]], 1u) << 16;
+            if (sc && (live >> k & 1u)) bc[k] |= atomicAdd(&mine[bc[k]], 1u) << 16;
         }
         __syncthreads();
         scatter_places(hist, delta, made, bins, c_at, cursor);
         __syncthreads();
 #pragma unroll
         for (uint32_t k = 0; k < kScatRefsPer; ++k) {
-            if (live >> k & 1u) {
-                const uint32_t ref = t * kScatRefsPer + k;
-                if (sf) first[mine[bf[k] & 0xFFFFu] + (bf[k] >> 16)] = ref | bf[k] << 16;
-                if (sc) second[mine[bc[k] & 0xFFFFu] + (bc[k] >> 16)] = ref | bc[k] << 16;
-            }
+            const uint32_t ref = t * kScatRefsPer + k;
+            if (sf && (edges >> k & 1u)) first[mine[bf[k] & 0xFFFFu] + (bf[k] >> 16)] = (ref & ~1u) | bf[k] << 16;
+            if (sc && (live >> k & 1u)) second[mine[bc[k] & 0xFFFFu] + (bc[k] >> 16)] = ref | bc[k] << 16;
         }
         __syncthreads();
         const uint32_t ref_at = ((uint32_t)n0 << D) + r0;
