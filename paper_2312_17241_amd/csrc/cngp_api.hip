@@ -196,6 +196,7 @@ struct FwdLevelPlan {
     size_t   lds = 0;            // dynamic LDS of the kernel
     LevelSplit split = {};       // levels that interpolate from a resolved grid; points per workgroup of either kind
     size_t   yT_bytes = 0;       // the level-major copy of the encodings: the workspace this variant needs
+    GroupSplit group = {};       // levels whose tables all fit in LDS, several to a workgroup: rows of y are written directly
 };
 constexpr int64_t kCus = 256;
 // Corner lookups (N * L * 2^d) up to which encode_fwd_kernel, one launch with every lookup in flight at once, is the
@@ -212,6 +213,7 @@ constexpr int     kFewLevels = 8;
 constexpr size_t  kLevelLdsBudget = 156 * 1024;
 constexpr int64_t kLevelPartPoints = 65536;              // points per workgroup when the batch is large
 constexpr uint64_t kFwdL2Bytes = 3u << 20;               // of an XCD's 4 MB, what tables can count on
+constexpr int64_t kGroupPartPoints = 65536;              // points per workgroup of several levels
 
 FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, int64_t N) {
     FwdLevelPlan f;
@@ -324,6 +326,29 @@ FwdLevelPlan fwd_level_plan_uncached(const cngp_config *c, int levels_loaded, in
         if (verts[l] * entry > f.lds) f.lds = verts[l] * entry;
     }
     f.yT_bytes = (size_t)N * c->L * 2 * io;
+    // Several levels to a workgroup (encode_fwd_group_kernel), where all their tables fit: as many fours as do and as make whole groups of
+    // the levels, but no more than leave a workgroup of one round a whole step of points.  Level kernel and rows / groups, us: the compressed model
+    // (four levels to a workgroup) 2^13 points 11 / 10, 2^16 16 / 13, 2^18 36 / 29, 2^20 114 / 91, 2^22 417 / 340; with fp32 encodings 523 / 356;
+    // N_f = 2^12, N_c = 2^14 2^13 11 / 8, 2^18 31 / 23, 2^22 345 / 256; d = 2, L = 12, N_f = 2^10 2^22 191 / 106.  N_f = 2^8, N_c = 2^12, of
+    // which sixteen levels fit: 2^22 points 341 / 263, but 2^16 14 / 22, where four take 10.
+    const size_t bits = c->index_format == CNGP_IDX_BITS ? (index_level_bytes(c) + 4 + 15) & ~(size_t)15 : probes, of_level = bits + (size_t)c->N_f * entry;
+    int group = (int)(kLevelLdsBudget / of_level) / (int)kQuad * (int)kQuad;
+    if (group > c->L) group = c->L / (int)kQuad * (int)kQuad;
+    auto at_once = [&](int levels) {                         // parts of the batch that run side by side, a whole number of them on every XCD
+        const int64_t per_xcd = kCus / kFwdXcds / (c->L / levels);
+        return (per_xcd > 1 ? per_xcd : 1) * (int64_t)kFwdXcds;
+    };
+    while (group > 0 && (c->L % group || (group > (int)kQuad && N < at_once(group) * step))) group -= (int)kQuad;
+    if (resident >= c->N_f && group > 0 && levels_loaded == c->L) {
+        GroupSplit &gs = f.group;
+        gs.levels = (uint32_t)group;
+        gs.groups = (uint32_t)(c->L / group);
+        gs.probes = (uint32_t)bits;
+        gs.stride = (uint32_t)of_level;
+        const int64_t parts = at_once(group), rounds = (N + parts * kGroupPartPoints - 1) / (parts * kGroupPartPoints);
+        gs.per = ((N + parts * rounds - 1) / (parts * rounds) + 63) / 64 * 64;
+        gs.parts = (uint32_t)((N + gs.per - 1) / gs.per);
+    }
     return f;
 }
 
@@ -345,9 +370,27 @@ template <int D, typename FeatT, typename IoT>
 int launch_fwd_level(const cngp_config *c, const FwdLevelPlan &f, const Params &p, const float *x, int64_t N, const void *D_f,
                      const void *D_c, void *y, void *yT, hipStream_t s, const int32_t *perm, bool rows = true) {
     const size_t  c_stride = index_level_bytes(c);
+    const int vec = (c_stride % 16 == 0 && ((uintptr_t)D_c & 15u) == 0) ? 1 : 0;
+    if (f.group.levels && rows && !perm && ((uintptr_t)y & 15u) == 0) {          // (rows of a multiple of four levels: whole pieces of 16 bytes)
+        const int64_t blocks = ((int64_t)f.group.parts + kFwdXcds - 1) / kFwdXcds * kFwdXcds * f.group.groups;
+        if (int rc = check_blocks(blocks)) return rc;
+        const size_t lds = (size_t)f.group.levels * f.group.stride;
+#define CNGP_FWD_GROUP_LAUNCH(FMT)                                                                          \
+    do {                                                                                                    \
+        auto kernel = encode_fwd_group_kernel<D, FeatT, IoT, FMT>;                                          \
+        if (int rc = allow_big_lds(kernel, lds)) return rc;                                                 \
+        LaunchTimer t(s, K_FWD);                                                                            \
+        kernel<<<(unsigned)blocks, kLevelBlock, lds, s>>>(p, x, (const FeatT *)D_f, (const uint8_t *)D_c,   \
+                                                          (IoT *)y, N, (uint32_t)c_stride, vec, f.group);   \
+    } while (0)
+        if (c->index_format == CNGP_IDX_PACKED4) CNGP_FWD_GROUP_LAUNCH(kFmtPacked4);
+        else if (c->index_format == CNGP_IDX_BITS) CNGP_FWD_GROUP_LAUNCH(kFmtBits);
+        else CNGP_FWD_GROUP_LAUNCH(kFmtU8);
+#undef CNGP_FWD_GROUP_LAUNCH
+        return launch_status("encode_fwd_group_kernel");
+    }
     const int64_t blocks = (int64_t)f.split.hash_units + f.split.grid_first[f.split.dense];
     if (int rc = check_blocks(blocks)) return rc;
-    const int vec = (c_stride % 16 == 0 && ((uintptr_t)D_c & 15u) == 0) ? 1 : 0;
 #define CNGP_FWD_LEVEL_LAUNCH(FMT)                                                                          \
     do {                                                                                                    \
         auto kernel = encode_fwd_level_kernel<D, FeatT, IoT, FMT>;                                          \

@@ -269,6 +269,114 @@ __global__ __launch_bounds__(kLevelBlock) void encode_fwd_level_kernel(
     else look_up(std::false_type{});
 }
 
+// Levels whose tables fit in LDS side by side, four or a multiple of four of them (compressed models: the paper's Table 3 row takes 25 KB a
+// level).  A workgroup then has a point's encodings of that many neighbouring levels together and writes them to the rows of y itself, 16 or
+// 32 bytes at a time: no level-major copy, no second pass.  The compressed model, 2^22 points: 312 us
+// for the level kernel and 113 for the rows, so 338.
+// The workgroups of a part's groups of levels run on one XCD at the same time, so that its L2 puts the pieces of a row together before
+// they leave for memory.  What bounds it is what bounds the level kernel with all lookups in LDS: LDS and vector ALU, both at work 90 % of the time.
+struct GroupSplit {
+    uint32_t levels = 0, groups = 0, parts = 0;              // levels per workgroup (0: not taken); groups of them; parts of the batch
+    int64_t  per = 0;                                        // points per part
+    uint32_t probes = 0, stride = 0;                         // LDS bytes of a level's index codebook, and of a level
+};
+constexpr uint32_t kQuad = 4;            // levels that leave together
+
+template <int D, typename FeatT, typename IoT, int FMT>
+__global__ __launch_bounds__(kLevelBlock) void encode_fwd_group_kernel(
+    const Params p, const float *__restrict__ x, const FeatT *__restrict__ D_f, const uint8_t *__restrict__ D_c,
+    IoT *__restrict__ y, const int64_t N, const uint32_t c_stride, const int vec, const GroupSplit gs)
+{
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int      t = threadIdx.x;
+    const uint32_t j = blockIdx.x / kFwdXcds, part = j / gs.groups * kFwdXcds + blockIdx.x % kFwdXcds, l0 = j % gs.groups * gs.levels;
+    if (part >= gs.parts) return;
+    const int64_t n_begin = (int64_t)part * gs.per, n_end = n_begin + gs.per < N ? n_begin + gs.per : N;
+    if (n_begin >= n_end) return;
+    const uint32_t lds_c = (p.N_c + 1u) / 2u, feat_bytes = p.N_f * (uint32_t)(2 * sizeof(FeatT));      // (a multiple of 16: host)
+    for (uint32_t g = 0; g < gs.levels; ++g) {
+        unsigned char *tables = smem + g * gs.stride;
+        const unsigned char *F_l = reinterpret_cast<const unsigned char *>(D_f + (size_t)(l0 + g) * p.N_f * 2);
+        stage_probes<FMT, kLevelBlock>(tables, D_c + (size_t)(l0 + g) * c_stride, c_stride, lds_c, vec, t);
+        for (uint32_t i = (uint32_t)t * 16u; i < feat_bytes; i += kLevelBlock * 16u)
+            *reinterpret_cast<uint4 *>(tables + gs.probes + i) = *reinterpret_cast<const uint4 *>(F_l + i);
+    }
+    __syncthreads();
+    // (a wavefront takes runs of 128 points; a lane beyond the part repeats its last point, as in the level kernel)
+    constexpr int64_t kStep = (int64_t)kLevelUnroll * kLevelBlock;
+    auto point = [&](const int64_t first, const int u) {
+        const int64_t n = first + u * 64 + (t & 63);
+        return n < n_end ? n : n_end - 1;
+    };
+    auto fetch = [&](const int64_t first, float (&xp)[kLevelUnroll][D]) {
+#pragma unroll
+        for (int u = 0; u < kLevelUnroll; ++u) {
+            const int64_t n = point(first, u);
+#pragma unroll
+            for (int i = 0; i < D; ++i) xp[u][i] = x[n * D + i];
+        }
+    };
+    struct alignas(2 * sizeof(IoT)) Piece { IoT v[2]; };     // a level's two features
+    const size_t row = (size_t)p.L * 2;
+    float xp[kLevelUnroll][D], next[kLevelUnroll][D];
+    const int64_t first = n_begin + (int64_t)(t >> 6) * (64 * kLevelUnroll);
+    fetch(first, xp);
+    for (int64_t n0 = first; n0 < n_end; n0 += kStep) {
+        fetch(n0 + kStep, next);
+        Piece out[kLevelUnroll][kQuad];
+#pragma unroll 1                                             // (four levels at once, mixed by the compiler, take 128 registers and spill)
+        for (uint32_t g = 0; g < gs.levels; ++g) {
+            const uint8_t *probes = smem + g * gs.stride;
+            const FeatT   *feats = reinterpret_cast<const FeatT *>(probes + gs.probes);
+            uint32_t idx[kLevelUnroll][1 << D];
+            float    wt[kLevelUnroll][1 << D];
+#pragma unroll
+            for (int u = 0; u < kLevelUnroll; ++u) {
+                Cell<D> cell;
+                cell.locate(xp[u], p.N_l[l0 + g]);
+#pragma unroll
+                for (int c = 0; c < (1 << D); ++c) {
+                    idx[u][c] = probe_base(cell.hash1(c), p) +
+                                (FMT == kFmtBits ? read_probe_bits_lds(probes, cell.hash2(c) & p.c_mask, p.log2_Np)
+                                                 : read_probe<kFmtPacked4>(probes, cell.hash2(c) & p.c_mask, p.log2_Np));
+                    wt[u][c] = cell.weight(c);
+                }
+            }
+            float2 feat[kLevelUnroll][1 << D];
+#pragma unroll
+            for (int u = 0; u < kLevelUnroll; ++u)
+#pragma unroll
+                for (int c = 0; c < (1 << D); ++c) feat[u][c] = load_pair(feats, idx[u][c]);
+#pragma unroll
+            for (int u = 0; u < kLevelUnroll; ++u) {
+                float y0 = 0.0f, y1 = 0.0f;
+#pragma unroll
+                for (int c = 0; c < (1 << D); ++c) {
+                    y0 = fmaf(wt[u][c], feat[u][c].x, y0);
+                    y1 = fmaf(wt[u][c], feat[u][c].y, y1);
+                }
+#pragma unroll
+                for (uint32_t i = 0; i + 1 < kQuad; ++i) out[u][i] = out[u][i + 1];
+                store_pair(out[u][kQuad - 1].v, 0, y0, y1);
+            }
+            if (g % kQuad == kQuad - 1u) {
+#pragma unroll
+                for (int u = 0; u < kLevelUnroll; ++u) {
+                    uint4 piece[sizeof(out[0]) / 16];
+                    __builtin_memcpy(piece, out[u], sizeof(piece));
+                    uint4 *dst = reinterpret_cast<uint4 *>(y + (size_t)point(n0, u) * row + (size_t)(l0 + g - (kQuad - 1u)) * 2);
+#pragma unroll
+                    for (int i = 0; i < (int)(sizeof(out[0]) / 16); ++i) dst[i] = piece[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kLevelUnroll; ++u)
+#pragma unroll
+            for (int i = 0; i < D; ++i) xp[u][i] = next[u][i];
+    }
+}
+
 // yT[l][n] (pairs) -> y[row(n)][l], row(n) = perm ? perm[n] : n; levels from L_loaded on are written as zeros.
 // One workgroup per 256 points: coalesced reads per level into a padded LDS tile, then the tile's rows leave as one
 // contiguous block (whole rows, piece by piece, under a permutation).
