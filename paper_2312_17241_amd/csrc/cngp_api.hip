@@ -2220,8 +2220,8 @@ int mlp_dims(const cngp_mlp_config *cfg, MlpDims *d) {
 // A persistent grid: every wavefront walks over tiles of 32 points.  At most `per_cu` workgroups per CU
 // (what fits at once), and no more than gives each wavefront `min_tiles` tiles, so that the staging of the
 // weights, which every workgroup repeats, stays a small part of its work.
-unsigned mlp_blocks(int64_t tiles, int per_cu, int min_tiles) {
-    const int64_t per_block = (int64_t)(kMlpBlock / 64) * min_tiles;
+unsigned mlp_blocks(int64_t tiles, int per_cu, int min_tiles, int block = kMlpBlock) {
+    const int64_t per_block = (int64_t)(block / 64) * min_tiles;
     const int64_t want = (tiles + per_block - 1) / per_block;
     const int64_t cap = 256 * (int64_t)per_cu;
     return (unsigned)(want < cap ? want : cap);
@@ -2243,6 +2243,7 @@ int cngp_mlp_fwd(const cngp_mlp_config *cfg, const void *y, int64_t N, const voi
     const int64_t tiles = (N + 31) / 32;
     hipStream_t s = (hipStream_t)stream;
     d.vec_in = (cfg->n_in % 4 == 0 && aligned(y, 16)) ? 1 : 0;
+    d.vec_out = (cfg->n_out % 4 == 0 && aligned(out, 16)) ? 1 : 0;
     LaunchTimer t(s, K_MLP_FWD);
     if (cfg->io_dtype == CNGP_F16)
         mlp_fwd_kernel<__half><<<mlp_blocks(tiles, 3, 4), kMlpBlock, kMlpFwdLds, s>>>(d, (const __half *)y, N, (const __half *)W, out, tiles);
@@ -2282,6 +2283,7 @@ int cngp_encode_mlp_fwd(const cngp_config *cfg, const cngp_mlp_config *mlp, cons
                           : launch_fwd_level<4, float, __half>(&c16, f, p, x, N, D_f, D_c, nullptr, workspace, s, nullptr, false);
             if (rc) return rc;
             const int64_t tiles = (N + 31) / 32;
+            d.vec_out = (d.n_out % 4 == 0 && aligned(out, 16)) ? 1 : 0;
             LaunchTimer t(s, K_MLP_FWD);
             mlp_fwd_kernel<__half, true><<<mlp_blocks(tiles, 3, 4), kMlpBlock, kMlpFwdLds, s>>>(d, (const __half *)workspace, N, (const __half *)W, out, tiles);
             return launch_status("mlp_fwd_kernel");
@@ -2311,12 +2313,12 @@ int cngp_mlp_bwd(const cngp_mlp_config *cfg, const void *y, int64_t N, const voi
         auto kernel = mlp_bwd_kernel<__half>;
         if (int rc = allow_big_lds(kernel, kMlpBwdLds)) return rc;
         LaunchTimer t(s, K_MLP_BWD);
-        kernel<<<mlp_blocks(tiles, 1, 4), kMlpBlock, kMlpBwdLds, s>>>(d, (const __half *)y, N, (const __half *)W, dout, (__half *)dy, grad_W, tiles);
+        kernel<<<mlp_blocks(tiles, 1, 2, kMlpBwdBlock), kMlpBwdBlock, kMlpBwdLds, s>>>(d, (const __half *)y, N, (const __half *)W, dout, (__half *)dy, grad_W, tiles);
     } else {
         auto kernel = mlp_bwd_kernel<float>;
         if (int rc = allow_big_lds(kernel, kMlpBwdLds)) return rc;
         LaunchTimer t(s, K_MLP_BWD);
-        kernel<<<mlp_blocks(tiles, 1, 4), kMlpBlock, kMlpBwdLds, s>>>(d, (const float *)y, N, (const __half *)W, dout, (float *)dy, grad_W, tiles);
+        kernel<<<mlp_blocks(tiles, 1, 2, kMlpBwdBlock), kMlpBwdBlock, kMlpBwdLds, s>>>(d, (const float *)y, N, (const __half *)W, dout, (float *)dy, grad_W, tiles);
     }
     return launch_status("mlp_bwd_kernel");
 }
