@@ -90,11 +90,20 @@ int validate(const cngp_config *c) {
 
 // Table 1 (N_min, N_max, L): geometric growth, floor with a 1e-6 guard so that exact powers
 // (in particular N_{L-1} = N_max) survive the rounding of exp / pow.
+// (The last table is kept, per thread: sixteen powers are half a microsecond of a call.)
 void level_table(const cngp_config *c, uint32_t *out) {
     if (c->L == 1) { out[0] = c->N_min; return; }
-    const double b = std::exp(std::log((double)c->N_max / (double)c->N_min) / (double)(c->L - 1));
-    for (int l = 0; l < c->L; ++l)
-        out[l] = (uint32_t)std::floor((double)c->N_min * std::pow(b, (double)l) + 1e-6);
+    thread_local uint32_t kept[kMaxLevels], kept_min = 0, kept_max = 0;
+    thread_local int32_t  kept_L = 0;
+    if (c->L != kept_L || c->N_min != kept_min || c->N_max != kept_max) {
+        const double b = std::exp(std::log((double)c->N_max / (double)c->N_min) / (double)(c->L - 1));
+        for (int l = 0; l < c->L; ++l)
+            kept[l] = (uint32_t)std::floor((double)c->N_min * std::pow(b, (double)l) + 1e-6);
+        kept_L = c->L;
+        kept_min = c->N_min;
+        kept_max = c->N_max;
+    }
+    std::memcpy(out, kept, sizeof(uint32_t) * (size_t)c->L);
 }
 
 Params make_params(const cngp_config *c) {
