@@ -468,6 +468,12 @@ __device__ __forceinline__ void accum_steps(const uint4 &r, const T (&g)[NP], Ac
     }
 }
 
+// Which of a row's two features a lane adds first.  An LDS atomic on doubles serves 16 lanes, 128 bytes, at a time, and with N_p below 16 those are
+// several rows': all at feature 0, which takes the same banks of every row, they wait for each other.  So every other group of N_p
+// lanes begins with feature 1 (N_p = 8, random rows of a slice: 3.9 additions per clock and CU in one order, 7.2 in both; N_p = 16 7.1 either way).
+template <int NP>
+__device__ __forceinline__ uint32_t first_feature() { return NP < 16 ? ((threadIdx.x & 63u) / NP) & 1u : 0u; }
+
 // Records [beg, end) of one bin.  A wavefront takes batches of 64 records round-robin with the other
 // wavefronts of the workgroup; EVERY LANE LOADS ONE RECORD of a batch (a 16-byte load each: loading a
 // record with all NP lanes that work on it costs NP times the return bandwidth of the memory pipeline,
@@ -482,12 +488,12 @@ __device__ __forceinline__ void accum_steps(const uint4 &r, const T (&g)[NP], Ac
 // BOTH (records of a confidence-table bin, both gradients accumulated): the gather reads the row INSIDE the
 // slice (the softmax row of the record's own confidence row), the accumulator row is the other table's.
 // ACC: doubles per candidate of an accumulator row (2 where both features of a row sit side by side).
-// `clear` prepares what the workgroup accumulates in; a barrier follows it.
+// `clear` prepares what the workgroup accumulates in; a barrier follows it.  `swap`: the lane's records pass their g in the other order.
 // MERGED: the records are entries, which hold their rows and g; else the bin belongs to a slice of the confidence table.
 template <int D, int NP, typename T, bool BOTH, int ACC, bool MERGED, typename Record, typename IoT, typename Clear, typename Load, typename Accum>
 __device__ __forceinline__ void drain_records(const Params &p, const Record *__restrict__ rec, const uint32_t beg, const uint32_t end,
                                               const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
-                                              const uint32_t rows_log2, Clear clear, Load load, Accum accum)
+                                              const uint32_t rows_log2, const bool swap, Clear clear, Load load, Accum accum)
 {
     const uint32_t row_lo_mask = (1u << rows_log2) - 1u;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -552,6 +558,7 @@ __device__ __forceinline__ void drain_records(const Params &p, const Record *__r
             inside = h2 & row_lo_mask;
             other = h1;
         }
+        if (swap) gy = make_float2(gy.y, gy.x);
         // once per record: byte offset of the row the gather reads (candidate 0), and byte offset of the
         // accumulator row in LDS; the lanes of the group add their candidate's share
         r = make_uint4((BOTH ? inside : other) * (uint32_t)(NP * sizeof(T)), __float_as_uint(wt * gy.x),
@@ -595,7 +602,7 @@ __device__ __forceinline__ void drain_records(const Params &p, const Record *__r
 template <int D, int NP, typename IoT, typename Clear, typename Load, typename Accum>
 __device__ __forceinline__ void drain_edges(const Params &p, const BinRecord *__restrict__ rec, const uint32_t beg, const uint32_t end,
                                             const float *__restrict__ x, const IoT *__restrict__ dy_l, const float res,
-                                            const uint32_t rows_log2, const uint32_t slice, Clear clear, Load load, Accum accum)
+                                            const uint32_t rows_log2, const uint32_t slice, const bool swap, Clear clear, Load load, Accum accum)
 {
     const uint32_t row_lo_mask = (1u << rows_log2) - 1u;
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -644,8 +651,9 @@ __device__ __forceinline__ void drain_edges(const Params &p, const BinRecord *__
                 }
             }
         }
-        const float2 gy = pair_to_float2(src.y);
-        bool         mine[2];
+        float2 gy = pair_to_float2(src.y);
+        if (swap) gy = make_float2(gy.y, gy.x);
+        bool   mine[2];
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             h1[e] &= p.row_mask;
@@ -810,26 +818,25 @@ __device__ __forceinline__ void drain_feat(const Params &p, const SliceParams &s
     const uint32_t rows = 1u << sp.rows_log2, plane = rows * NP;
     double *acc = reinterpret_cast<double *>(smem);
     if (co.index < 0) return;
-    // accumulators [row][f][k]: the NP lanes of a record add to NP consecutive doubles, and feature 1 sits a constant
-    // NP doubles behind feature 0 (an immediate offset of the LDS instruction)
+    // accumulators [row][f][k]: the NP lanes of a record add to NP consecutive doubles, then to those of the other feature
     const char    *sig_l = reinterpret_cast<const char *>(sigma + (size_t)co.level * p.N_c * NP);   // uniform: scalar base of the gathers
     const uint32_t k = (threadIdx.x & 63) % NP, k4 = k * (uint32_t)sizeof(float);
-    char          *acc_k = reinterpret_cast<char *>(acc + k);
+    const uint32_t f = first_feature<NP>();
+    char          *acc_k = reinterpret_cast<char *>(acc + k + f * NP), *then_k = reinterpret_cast<char *>(acc + k + (1u - f) * NP);
     auto load = [&](const uint32_t off) -> float {           // off: byte offset of the softmax row
         return NP == 1 ? 1.0f : *reinterpret_cast<const float *>(sig_l + (off + k4));
     };
-    auto accum = [&](const uint32_t off, const float2 g, const float s) {      // off: byte offset of the accumulator row
-        double *a = reinterpret_cast<double *>(acc_k + off);
-        atomicAdd(a, (double)(s * g.x));
-        atomicAdd(a + NP, (double)(s * g.y));
+    auto accum = [&](const uint32_t off, const float2 g, const float s) {      // off: byte offset of the accumulator row; g: in the lane's order
+        atomicAdd(reinterpret_cast<double *>(acc_k + off), (double)(s * g.x));
+        atomicAdd(reinterpret_cast<double *>(then_k + off), (double)(s * g.y));
     };
     auto clear = [&]() { for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) acc[i] = 0.0; };
     uint32_t beg, end;
     bin_range(baseF, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
     const IoT *dy_l = dyT + (size_t)co.level * N * 2;
     const float res = (float)p.N_l[co.level];
-    if constexpr (MERGED) drain_records<D, NP, float, false, 2, true>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, clear, load, accum);
-    else drain_edges<D, NP>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, co.slice, clear, load, accum);
+    if constexpr (MERGED) drain_records<D, NP, float, false, 2, true>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, f != 0u, clear, load, accum);
+    else drain_edges<D, NP>(p, recF + (size_t)co.index * cap, beg, end, x, dy_l, res, sp.rows_log2, co.slice, f != 0u, clear, load, accum);
     __syncthreads();
     if (sp.partial) {                                                      // as bwd_partial_sums_kernel reads them: all of feature 0, then feature 1
         const size_t at = (((size_t)co.index * sp.chunks + co.chunk) * sp.slices + co.slice) * plane * 2;
@@ -875,7 +882,7 @@ __device__ __forceinline__ void drain_logit(const Params &p, const SliceParams &
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
     drain_records<D, NP, Raw, false, 1, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                              (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
+                              (float)p.N_l[co.level], sp.rows_log2, false, clear, load, accum);
     __syncthreads();
     if (sp.partial) return sp.wide ? store_partial<double>(sp, co, acc, rows * NP) : store_partial<float>(sp, co, acc, rows * NP);
     // softmax Jacobian per row, then out to HBM; NP consecutive lanes hold one row
@@ -898,7 +905,7 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     using Raw = typename RawPair<FeatT>::type;
     const uint32_t rows = 1u << sp.rows_log2, plane = p.N_f;            // plane: feature entries of a level
     double *accQ = reinterpret_cast<double *>(smem);                    // [rows][NP]
-    double *accF = accQ + (size_t)rows * NP;                            // [2][N_f]: feature 0 of every entry, then feature 1
+    double *accF = accQ + (size_t)rows * NP;                            // [row][f][k], as drain_feat
     Raw    *feat = reinterpret_cast<Raw *>(accF + 2 * (size_t)plane);   // [N_f]
     if (co.index < 0) return;
     const Raw *F_l = reinterpret_cast<const Raw *>(D_f + (size_t)co.level * p.N_f * 2);
@@ -909,26 +916,28 @@ __device__ __forceinline__ void drain_both(const Params &p, const SliceParams &s
     const size_t   row0 = (size_t)co.level * p.N_c + (size_t)co.slice * rows;
     const uint32_t k = (threadIdx.x & 63) % NP;
     const char *sig_k = reinterpret_cast<const char *>(sigma + row0 * NP + k);          // this lane's candidate, this slice's rows
-    char       *accF_k = reinterpret_cast<char *>(accF + k), *accQ_k = reinterpret_cast<char *>(accQ + k);
+    const bool  swap = first_feature<NP>() != 0u;
+    char       *accF_k = reinterpret_cast<char *>(accF + k + (swap ? NP : 0)), *then_k = reinterpret_cast<char *>(accF + k + (swap ? 0 : NP));
+    char       *accQ_k = reinterpret_cast<char *>(accQ + k);
     const char *feat_k = reinterpret_cast<const char *>(feat + k);
     auto load = [&](const uint32_t off) -> float { return *reinterpret_cast<const float *>(sig_k + off); };
-    // offF: byte offset of the feature row among fp64 accumulators (row * NP * 8); offS: of the confidence row
+    // offF: byte offset of the feature row among fp64 accumulators (row * 2 * NP * 8); offS: of the confidence row
     // among floats (row * NP * 4)
     auto accum = [&](const uint32_t offF, const float2 g, const float s, const uint32_t offS) {
-        const float2 f = RawPair<FeatT>::to_float2(*reinterpret_cast<const Raw *>(feat_k + offF / 8u * sizeof(Raw)));
-        double *a = reinterpret_cast<double *>(accF_k + offF);
-        atomicAdd(a, (double)(s * g.x));
-        atomicAdd(a + plane, (double)(s * g.y));
+        const float2 f = RawPair<FeatT>::to_float2(*reinterpret_cast<const Raw *>(feat_k + offF / 16u * sizeof(Raw)));
+        atomicAdd(reinterpret_cast<double *>(accF_k + offF), (double)(s * (swap ? g.y : g.x)));
+        atomicAdd(reinterpret_cast<double *>(then_k + offF), (double)(s * (swap ? g.x : g.y)));
         atomicAdd(reinterpret_cast<double *>(accQ_k + 2u * offS), (double)fmaf(f.x, g.x, f.y * g.y));
     };
     uint32_t beg, end;
     bin_range(baseC, sp.slices, (uint32_t)co.index, co.slice, co.chunk, sp.chunks, beg, end);
-    drain_records<D, NP, float, true, 1, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
-                                      (float)p.N_l[co.level], sp.rows_log2, clear, load, accum);
+    drain_records<D, NP, float, true, 2, MERGED>(p, recC + (size_t)co.index * cap, beg, end, x, dyT + (size_t)co.level * N * 2,
+                                      (float)p.N_l[co.level], sp.rows_log2, false, clear, load, accum);
     __syncthreads();
     float *outF = gD_f + (size_t)co.level * p.N_f * 2;
     for (uint32_t i = threadIdx.x; i < plane * 2; i += kSlicedBlock) {     // i = entry * 2 + f
-        const float v = (float)accF[(i & 1u) * plane + (i >> 1)];
+        const uint32_t e = i >> 1;
+        const float v = (float)accF[(e / NP) * (2 * NP) + (i & 1u) * NP + (e % NP)];
         if (v != 0.0f) atomic_add(outF + i, v);
     }
     flush_logits<NP>(accQ, rows * NP, sigma + row0 * NP, gDhat_c + row0 * NP, sp.store_direct);
