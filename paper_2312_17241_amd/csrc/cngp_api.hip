@@ -640,6 +640,19 @@ constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated sca
 // where a coarse level's few vertices collide; the slowest 0.95x (12.2 us against 11.5).
 constexpr size_t   kSmallBwdLds = 128 * 1024;
 constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
+// Tables with several slices of both kinds are binned sooner: from kMinBinnedSoonRefs, and with many candidates, whose scans and atomics
+// cost the most, from kMinBinnedCandidateRefs.  us, before (scan, below 2^19 references atomics) / binned: 8 + 16 slices, N_p = 16 2^18.5 126 / 73,
+// 2^19.5 96 / 76, 2^20.3 133 / 88, 2^21 185 / 118; 32 + 32, N_p = 8 2^20.3 148 / 107, 2^21 197 / 124, but 2^18.6 75 / 92, 2^19.1 97 / 91; 16 + 8,
+// N_p = 4 2^19.1 56 / 63; d = 2 16 + 16, N_p = 16 2^19.9 78 / 80.  With one slice of either table the drain has few, long workgroups: 1 + 32, N_p = 8
+// 2^20.7 118 / 170, 32 + 2, N_p = 16 2^20.8 170 / 198.
+constexpr int64_t  kMinBinnedSoonRefs = 1 << 20, kMinBinnedCandidateRefs = 1 << 18;
+// 56 drawn batches that this and the next rule bin: 1.05 .. 5.1x, 1.9x on average; left out: d = 4 (16 + 8, N_p = 16 2^19.1 48 / 53), 96 slices (2^18.2 104 / 106), a small feature table with 256
+// slices of the other (2^18.3 101 / 163), or with 64 and fewer candidates (N_p = 8 2^18.1 60 / 69).
+constexpr uint32_t kMinBinnedSoonSlices = 8, kManyCandidates = 16, kMostCandidateSlices = 64;
+// A small feature table is binned from here on (kMinSlicedRefs: above it the scan's sums meet in 64 bits); us, atomics / binned: N_f = 2^8, N_c = 2^14, N_p = 16
+// 3608 points 250 / 47; N_f = 2^12, N_c = 2^15, N_p = 8 3504 points 76 / 55, 4756 points, L = 8 57 / 40.
+constexpr int64_t  kMinBinnedFusedRefs = 1 << 18;
+constexpr int64_t  kFewBinChunks = 1024;        // workgroups of the scatter, one per level and chunk, up to which each has four wavefronts
 // References per level (N * 2^d) from which the binned variant, where it does not merge, always pre-reduces coarse levels; below,
 // binned_bwd_us decides.
 // Backward, us, with / without, beyond it: nerf3d's tables 163840 points 384 / 403, 2^18 539 / 569; sdf3d's 2^20 2786 / 3294;
@@ -1042,7 +1055,12 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
                        per_level >= kMinBinnedPlainSlices && (N << c->d) * (int64_t)per_level >= kMinBinnedPlainScans &&
                        (c->L - scan_dense_levels(c, N, per_level)) * (int64_t)per_level >=
                            (c->d <= 3 && layout == LAYOUT_MERGED && (N << c->d) >= kMinMergeRefs && merge_levels(c, N) >= 4 ? kMinMergedScans : kMinBinnedPlainGroups);
-    b.binned = bin_ok && plenty && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
+    const bool both = b.slices_f >= kMinBinnedSoonSlices && b.slices_c >= kMinBinnedSoonSlices && per_level >= kMinBinnedSlicesPerLevel;
+    const int64_t refs = (N << c->d) * c->L;
+    const bool soon = layout != LAYOUT_LEAST && !c->bin_bytes_max && !plenty && !(c->flags & CNGP_BWD_NO_PREREDUCE) &&
+                      ((both && refs >= kMinBinnedSoonRefs) || (both && c->d == 3 && c->N_p >= kManyCandidates && per_level <= kMostCandidateSlices && refs >= kMinBinnedCandidateRefs) ||
+                       (fused_ok && per_level >= 4 && (c->N_c >> fused_rows_c_log2) <= (c->N_p >= kManyCandidates ? kMostCandidateSlices : kMostCandidateSlices / 2) && refs >= kMinBinnedFusedRefs && !enough));
+    b.binned = bin_ok && (plenty || soon) && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
     // tables of a few slices, where enough of the levels are merged
@@ -1340,7 +1358,9 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
         kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, ma.order, mb);
         if (int rc = launch_status("bwd_merge_kernel")) return rc;
     }
-    const unsigned bin_block = bp.slices_f + bp.slices_c >= kMinRunBins ? 256u : (unsigned)kBinBlock;
+    // So do the chunks of a short batch, which leave most SIMDs without a wavefront: the walk of 1024 points by one is a chain of memory latencies
+    // (scatter, us, one wavefront / four: 320 workgroups 25 / 13, 640 27 / 17, 1264 29 / 23; but the drain of 1570 loses 3 % of 270, more than that gains).
+    const unsigned bin_block = bp.slices_f + bp.slices_c >= kMinRunBins || blocks <= kFewBinChunks ? 256u : (unsigned)kBinBlock;
     {
         LaunchTimer t(s, K_BWD_BIN_OFFSETS);
         uint32_t big = bp.slices_f > bp.slices_c ? bp.slices_f : bp.slices_c;
