@@ -608,6 +608,7 @@ struct BwdPlan {
     bool     scarce;                    // ... of tables whose slices alone would be scanned: because levels are merged, or plain hashing of few slices
     bool     fused;                     // ... by slice of the confidence table only: a level's whole feature gradient sits in LDS beside it
     uint32_t bin_chunks, bin_chunk_pts; // point chunks of the count / scatter kernels
+    bool     lone;                      // one drain workgroup per bin (kMostSoonRefsPerBin)
     uint32_t subs_f, subs_c;            // drain workgroups per bin
     size_t   cntF_off, cntC_off, baseF_off, baseC_off, recF_off, recC_off;
     size_t   cntG_off, baseG_off, recG_off;          // pre-reduced levels binned by slice of their vertex grid; merged ones by slice of the tables
@@ -646,12 +647,22 @@ constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which 
 // N_p = 4 2^19.1 56 / 63; d = 2 16 + 16, N_p = 16 2^19.9 78 / 80.  With one slice of either table the drain has few, long workgroups: 1 + 32, N_p = 8
 // 2^20.7 118 / 170, 32 + 2, N_p = 16 2^20.8 170 / 198.
 constexpr int64_t  kMinBinnedSoonRefs = 1 << 20, kMinBinnedCandidateRefs = 1 << 18;
-// 56 drawn batches that this and the next rule bin: 1.05 .. 5.1x, 1.9x on average; left out: d = 4 (16 + 8, N_p = 16 2^19.1 48 / 53), 96 slices (2^18.2 104 / 106), a small feature table with 256
+// 90 drawn batches that this and the next rules bin (d = 2 .. 4, 1 .. 16 levels): 68 with atomics before 1.08 .. 17.9x, 3.4x on average, 22 scanned before
+// 1.08 .. 2.8x, 1.8x; left out: d = 4 (16 + 8, N_p = 16 2^19.1 48 / 53), 96 slices (2^18.2 104 / 106), a small feature table with 256
 // slices of the other (2^18.3 101 / 163), or with 64 and fewer candidates (N_p = 8 2^18.1 60 / 69).
 constexpr uint32_t kMinBinnedSoonSlices = 8, kManyCandidates = 16, kMostCandidateSlices = 64;
 // A small feature table is binned from here on (kMinSlicedRefs: above it the scan's sums meet in 64 bits); us, atomics / binned: N_f = 2^8, N_c = 2^14, N_p = 16
 // 3608 points 250 / 47; N_f = 2^12, N_c = 2^15, N_p = 8 3504 points 76 / 55, 4756 points, L = 8 57 / 40.
 constexpr int64_t  kMinBinnedFusedRefs = 1 << 18;
+// Where such a batch was scanned (kMinSlicedRefs), its bins have one drain workgroup each: a scan rounds the fp64 sum of an entry once, while two
+// workgroups and more round theirs to fp32 before they meet.  Few levels then leave few, long bins: with more than kMostSoonRefsPerBin references times levels
+// in a bin of the table with fewer slices the batch is scanned (never from eight levels on).  us, scanned / binned (in brackets with the
+// workgroups that fill the chip), and the errors of both gradients against 64 bits, 2-norm, 1e-8: 8 + 16 slices, N_p = 16, L = 8, 17559 points 85 / 69 (57),
+// 8.00 8.22 / 7.76 7.97 (8.19 7.97), 30573 115 / 95 (80), 8.08 8.30 / 7.76 7.99 (8.50 8.44); L = 6, 23413 91 / 78 (56), 40765 96 / 113 (84); L = 4, 18821 67 / 65
+// (48), 35119 80 / 99 (54), 8.11 8.32 / 7.77 7.96 (8.72 8.42); L = 1, 140479 49 / 305 (62).  32 + 32, N_p = 8, L = 4, 61147 122 / 69 (80); L = 2, 70239 69 / 65
+// (53), 122295 92 / 95 (72).  Points anything but evenly spread, 8 + 16, L = 8, 30573: all equal 239 / 189, on a plane 112 / 95, in a cube of side
+// 0.02 237 / 333; L = 16, 15287: 357 / 192, 207 / 73, 357 / 192; 32 + 32, L = 8, 30573: 273 / 205, 153 / 72, 292 / 127.
+constexpr int64_t  kMostSoonRefsPerBin = 4096;
 constexpr int64_t  kFewBinChunks = 1024;        // workgroups of the scatter, one per level and chunk, up to which each has four wavefronts
 // References per level (N * 2^d) from which the binned variant, where it does not merge, always pre-reduces coarse levels; below,
 // binned_bwd_us decides.
@@ -881,7 +892,7 @@ double binned_bwd_us(const cngp_config *c, int64_t N, const BwdPlan &b, int Ld) 
         const double seen = verts < refs ? verts : refs;
         for (const uint32_t s : tables) {
             if (!s) continue;
-            const uint32_t subs = drain_subs(refs, s, c->L - Ld, slices);
+            const uint32_t subs = b.lone ? 1u : drain_subs(refs, s, c->L - Ld, slices);
             const double   mean = seen / s;
             double fullest = mean + std::sqrt(2.0 * mean * std::log(s > 2 ? (double)s : 2.0)) + (mean < 3.0 ? 1.0 : 0.0);    // vertices of the fullest bin
             if (fullest > seen) fullest = seen;
@@ -1057,9 +1068,13 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
                            (c->d <= 3 && layout == LAYOUT_MERGED && (N << c->d) >= kMinMergeRefs && merge_levels(c, N) >= 4 ? kMinMergedScans : kMinBinnedPlainGroups);
     const bool both = b.slices_f >= kMinBinnedSoonSlices && b.slices_c >= kMinBinnedSoonSlices && per_level >= kMinBinnedSlicesPerLevel;
     const int64_t refs = (N << c->d) * c->L;
+    const int64_t per_bin = (N << c->d) / (b.slices_f < b.slices_c ? b.slices_f : b.slices_c ? b.slices_c : 1u);      // references of the longer bins
+    const bool few_bins = enough && per_bin > kMostSoonRefsPerBin * c->L;
     const bool soon = layout != LAYOUT_LEAST && !c->bin_bytes_max && !plenty && !(c->flags & CNGP_BWD_NO_PREREDUCE) &&
-                      ((both && refs >= kMinBinnedSoonRefs) || (both && c->d == 3 && c->N_p >= kManyCandidates && per_level <= kMostCandidateSlices && refs >= kMinBinnedCandidateRefs) ||
+                      ((both && !few_bins && refs >= kMinBinnedSoonRefs) ||
+                       (both && !few_bins && c->d == 3 && c->N_p >= kManyCandidates && per_level <= kMostCandidateSlices && refs >= kMinBinnedCandidateRefs) ||
                        (fused_ok && per_level >= 4 && (c->N_c >> fused_rows_c_log2) <= (c->N_p >= kManyCandidates ? kMostCandidateSlices : kMostCandidateSlices / 2) && refs >= kMinBinnedFusedRefs && !enough));
+    b.lone = soon && enough && !(c->flags & CNGP_BWD_BINNED);
     b.binned = bin_ok && (plenty || soon) && (per_level >= kMinBinnedSlicesPerLevel || (fused_ok && per_level >= 4) || plain) && bin_bytes <= bin_bytes_max;
     if (c->flags & CNGP_BWD_BINNED) b.binned = bin_ok;
     if (c->flags & (CNGP_BWD_DIRECT | CNGP_BWD_SLICED)) b.binned = false;
@@ -1138,6 +1153,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
         b.subs_f = drain_subs(refs, b.slices_f, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
         b.subs_c = drain_subs(refs, b.slices_c, b.merged ? c->L : Lh, b.slices_f + b.slices_c, b.scarce, b.scarce && c->N_p == 1);
         if (plain_bins) b.subs_f = 1;
+        if (b.lone) b.subs_f = b.subs_c = 1;
         if (b.fused) b.subs_f = 2;              // never one writer per entry: the feature gradient is cleared first and added to
         if (b.merged) {
             // half as many drain workgroups per bin: at most about half of a merged level's references are left
