@@ -1070,7 +1070,7 @@ BwdPlan make_bwd_plan_uncached(const cngp_config *c, int64_t N, Layout layout = 
     const int64_t refs = (N << c->d) * c->L;
     const int64_t per_bin = (N << c->d) / (b.slices_f < b.slices_c ? b.slices_f : b.slices_c ? b.slices_c : 1u);      // references of the longer bins
     const bool few_bins = enough && per_bin > kMostSoonRefsPerBin * c->L;
-    const bool soon = layout != LAYOUT_LEAST && !c->bin_bytes_max && !plenty && !(c->flags & CNGP_BWD_NO_PREREDUCE) &&
+    const bool soon = layout != LAYOUT_LEAST && !c->bin_bytes_max && !plenty &&
                       ((both && !few_bins && refs >= kMinBinnedSoonRefs) ||
                        (both && !few_bins && c->d == 3 && c->N_p >= kManyCandidates && per_level <= kMostCandidateSlices && refs >= kMinBinnedCandidateRefs) ||
                        (fused_ok && per_level >= 4 && (c->N_c >> fused_rows_c_log2) <= (c->N_p >= kManyCandidates ? kMostCandidateSlices : kMostCandidateSlices / 2) && refs >= kMinBinnedFusedRefs && !enough));

@@ -35,3 +35,15 @@ def test_drawn_batches():
             assert (plan["drain_wgs_feat"], plan["drain_wgs_logit"]) == (1, 1), (cfg, N, plan)
             assert plan["merged_levels"] == 0
     assert seen > 100
+
+
+def test_a_flag_about_coarse_levels_does_not_change_the_variant():
+    rng, seen = random.Random(6), 0
+    for _ in range(2000):
+        d, L = rng.choice((2, 3, 3, 4)), rng.randint(1, 20)
+        sizes = d, L, 2**rng.randint(6, 18), 2**rng.randint(11, 17), 2**rng.randint(1, 4), 2048
+        N = int(2 ** rng.uniform(17, 21) / (L << d))
+        plain, flagged = (cngp.bwd_plan_info(config(*sizes, flags=f), N) for f in (cngp.ZERO_GRADS, cngp.ZERO_GRADS | cngp.BWD_NO_PREREDUCE))
+        seen += plain["binned"]
+        assert flagged["binned"] == plain["binned"] and flagged["dense_levels"] == 0, (sizes, N)
+    assert seen > 200
