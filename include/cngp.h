@@ -148,16 +148,24 @@ size_t cngp_fwd_workspace_bytes(const cngp_config *cfg, int64_t N);
 enum {
     CNGP_FWD_ROUTE_LANES = 0,   /* one launch, one lane per (point, level), both tables read from memory */
     CNGP_FWD_ROUTE_TILE = 1,    /* one launch, tiles of points, a level's index codebook staged in LDS    */
-    CNGP_FWD_ROUTE_LEVEL = 2    /* level-resident, then a kernel that turns level-major encodings into rows */
+    CNGP_FWD_ROUTE_LEVEL = 2    /* level-resident: a workgroup keeps one level's codebooks in LDS, then a kernel turns level-major
+                                   encodings into rows; or several levels' and writes the rows itself (cngp_fwd_group_levels) */
 };
 int cngp_fwd_route(const cngp_config *cfg, int32_t levels_loaded, int64_t N, size_t workspace_bytes, int32_t *grids);
 
 /* The level-resident variant for this configuration and N: info[0] = 1 if it can be taken (cngp_fwd_workspace_bytes is
  * not 0; cngp_fwd_route says whether a call does take it), info[1] = entries of a level's feature codebook it keeps in LDS
  * (of N_f), info[2] = runs of points a looked-up level is cut into (a level on a resolved grid is cut by its own
- * cost), info[3] = bytes of LDS per workgroup.  Host only. */
+ * cost), info[3] = bytes of LDS per workgroup.  Where cngp_fwd_group_levels is not 0, info[2] and info[3] are that kernel's.
+ * Host only. */
 enum { CNGP_FWD_PLAN_INFO_COUNT = 4 };
 int cngp_fwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info);
+
+/* Levels to a workgroup (a multiple of four that divides L) where CNGP_FWD_ROUTE_LEVEL is one launch that keeps the codebooks of
+ * several levels in LDS and writes the rows of y itself: where they fit, for a call of all levels in the order of the points whose y is
+ * 16-byte aligned.  0: a workgroup has one level, and a second launch makes the rows, which is what the other calls get in any case.
+ * Such a launch does not touch the workspace, but is taken only with the room all the same.  Or CNGP_ERR_*.  Host only. */
+int cngp_fwd_group_levels(const cngp_config *cfg, int64_t N);
 
 /* Forward encoding (Eq. 6; Fig. 3: enclosing vertices, two hashes, probe lookup, feature
  * gather, d-linear interpolation, concatenation over levels; the forward pass uses the baked

@@ -103,6 +103,8 @@ def _load():
     lib.cngp_bwd_merge_info.argtypes = [cfgp, i64, vp]
     lib.cngp_fwd_plan_info.restype = ctypes.c_int
     lib.cngp_fwd_plan_info.argtypes = [cfgp, i64, vp]
+    lib.cngp_fwd_group_levels.restype = ctypes.c_int
+    lib.cngp_fwd_group_levels.argtypes = [cfgp, i64]
     lib.cngp_fwd_route.restype = ctypes.c_int
     lib.cngp_fwd_route.argtypes = [cfgp, ctypes.c_int32, i64, sz, vp]
     lib.cngp_bwd_plan_layout.restype = ctypes.c_int
@@ -274,6 +276,14 @@ def fwd_plan_info(cfg: Config, N: int) -> dict:
     c = cfg.c()
     _check(_lib.cngp_fwd_plan_info(ctypes.byref(c), N, info))
     return dict(zip(("level_resident", "resident_entries", "parts", "lds_bytes"), list(info)))
+
+
+def fwd_group_levels(cfg: Config, N: int) -> int:
+    """Levels to a workgroup where the level-resident forward writes the rows of y itself; 0 where it does not (see cngp_fwd_group_levels)."""
+    levels = _lib.cngp_fwd_group_levels(cfg._ref(), N)
+    if levels < 0:
+        _check(levels)
+    return levels
 
 
 def bwd_plan_info(cfg: Config, N: int) -> dict:

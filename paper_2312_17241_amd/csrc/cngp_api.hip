@@ -1846,9 +1846,16 @@ int cngp_fwd_plan_info(const cngp_config *cfg, int64_t N, int32_t *info) {
     const FwdLevelPlan f = fwd_level_plan(&pairs, cfg->L, N);
     info[0] = f.use ? 1 : 0;
     info[1] = (int32_t)f.resident;
-    info[2] = (int32_t)f.split.hash_parts;
-    info[3] = (int32_t)(f.lds);
+    info[2] = (int32_t)(f.group.levels ? f.group.parts : f.split.hash_parts);
+    info[3] = (int32_t)(f.group.levels ? (size_t)f.group.levels * f.group.stride : f.lds);
     return CNGP_OK;
+}
+
+int cngp_fwd_group_levels(const cngp_config *cfg, int64_t N) {
+    if (int rc = validate(cfg)) return rc;
+    if (N < 0) return CNGP_ERR_INVALID;
+    const cngp_config pairs = as_pairs(cfg);
+    return (int)fwd_level_plan(&pairs, cfg->L, N).group.levels;
 }
 
 int cngp_fwd_route(const cngp_config *cfg, int32_t levels_loaded, int64_t N, size_t workspace_bytes, int32_t *grids) {
