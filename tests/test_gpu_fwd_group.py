@@ -43,10 +43,10 @@ def passes(call):
     (3, 16, 2**8, 2**16, 8, "f16", "f16", "bits"),              # 25 KB a level: four of them
     (3, 16, 2**8, 2**16, 8, "f16", "f32", "u8"),
     (3, 16, 2**12, 2**13, 16, "f32", "f32", "packed4"),
-    (2, 12, 2**10, 2**12, 4, "f16", "f16", "u8"),               # all twelve in large batches
+    (2, 12, 2**10, 2**12, 4, "f16", "f16", "u8"),
     (4, 8, 2**9, 2**10, 2, "f32", "f16", "bits"),
     (3, 4, 2**10, 1, 1, "f16", "f32", "bits"),                  # no index codebook at all
-    (2, 20, 2**8, 2**12, 8, "f16", "f16", "packed4"),       # 20 levels in fours
+    (2, 20, 2**8, 2**12, 8, "f16", "f16", "packed4"),
 ])
 @pytest.mark.parametrize("N", [1, 2049, 70001, 300007])
 def test_groups_of_levels_equal_the_tile_variant(d, L, N_f, N_c, N_p, feat, io, fmt, N):
@@ -58,6 +58,41 @@ def test_groups_of_levels_equal_the_tile_variant(d, L, N_f, N_c, N_p, feat, io, 
     assert not rows and bool((y[N] == 7.0).all())
     want = cngp.encode_fwd(cngp.Config.from_workload(w, flags=cngp.FWD_TILE, index_format=FMT[fmt]), *args)
     assert torch.equal(y[:N], want)
+
+
+@pytest.mark.parametrize("d,L,N_f,N_c,N_p,feat,io,fmt,N,levels", [      # more than four: from enough points on for a step of each workgroup of one round
+    (3, 16, 2**8, 2**12, 8, "f16", "f16", "packed4", 300007, 8),
+    (3, 16, 2**8, 2**12, 8, "f16", "f32", "u8", 2**19 + 77, 16),
+    (2, 12, 2**10, 2**12, 4, "f16", "f16", "u8", 2**19 + 77, 12),
+    (4, 8, 2**9, 2**10, 2, "f32", "f16", "bits", 2**19 + 77, 8),
+    (2, 20, 2**8, 2**12, 8, "f16", "f16", "bits", 2**19 + 77, 20),
+])
+@pytest.mark.parametrize("shift", [0, 4])                       # bytes past a 16-byte boundary where the index codebook begins: 0 is copied in pieces of 16
+def test_larger_groups_equal_the_tile_variant(d, L, N_f, N_c, N_p, feat, io, fmt, N, levels, shift):
+    w, (x, D_f, D_c) = case(d, L, N_f, N_c, N_p, feat, io, fmt, N)
+    moved = torch.empty(D_c.numel() + shift, dtype=torch.uint8, device="cuda")[shift:].view(D_c.shape)
+    moved.copy_(D_c)
+    assert moved.data_ptr() % 16 == shift
+    cfg = cngp.Config.from_workload(w, flags=cngp.FWD_LEVEL, index_format=FMT[fmt])
+    assert cngp.fwd_group_levels(cfg, N) == levels
+    ws = torch.empty(cngp.fwd_workspace_bytes(cfg, N), dtype=torch.uint8, device="cuda").fill_(0xAB)
+    y = torch.full((N + 1, 2 * L), 7.0, dtype=torch.float16 if io == "f16" else torch.float32, device="cuda")
+    _, rows = passes(lambda: cngp.encode_fwd(cfg, x, D_f, moved, y[:N], workspace=ws))
+    assert not rows and bool((y[N] == 7.0).all()) and bool((ws == 0xAB).all())
+    assert torch.equal(y[:N], cngp.encode_fwd(cngp.Config.from_workload(w, flags=cngp.FWD_TILE, index_format=FMT[fmt]), x, D_f, D_c))
+
+
+@pytest.mark.parametrize("fmt,shift", [("u8", 1), ("packed4", 3), ("bits", 8)])
+def test_groups_of_four_with_an_index_codebook_off_a_boundary(fmt, shift):
+    N = 5003
+    w, (x, D_f, D_c) = case(3, 16, 2**8, 2**12, 8, "f16", "f16", fmt, N)
+    moved = torch.empty(D_c.numel() + shift, dtype=torch.uint8, device="cuda")[shift:].view(D_c.shape)
+    moved.copy_(D_c)
+    level, tile = (cngp.Config.from_workload(w, flags=f, index_format=FMT[fmt]) for f in (cngp.FWD_LEVEL, cngp.FWD_TILE))
+    assert cngp.fwd_group_levels(level, N) == 4
+    ws = torch.empty(cngp.fwd_workspace_bytes(level, N), dtype=torch.uint8, device="cuda")
+    got, rows = passes(lambda: cngp.encode_fwd(level, x, D_f, moved, workspace=ws))
+    assert not rows and torch.equal(got, cngp.encode_fwd(tile, x, D_f, D_c))
 
 
 @pytest.mark.parametrize("L,shift,levels,perm", [(10, 0, None, False), (16, 1, None, False), (16, 0, 9, False), (16, 0, None, True)])
