@@ -640,7 +640,7 @@ constexpr uint32_t kMaxSlicesPerLevel = 128;   // beyond this the replicated sca
 // 2^19 references, kernel alone against the direct one: 2.4x faster on average (up to 48 KB 2.6x, 96 .. 128 KB 1.6x), up to 145x
 // where a coarse level's few vertices collide; the slowest 0.95x (12.2 us against 11.5).
 constexpr size_t   kSmallBwdLds = 128 * 1024;
-constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which the library bins by itself (measured: 2^14 points of the headline shape)
+constexpr int64_t  kMinBinnedRefs = 1 << 21;    // corner references from which any table that can be binned with a gain is (measured: 2^14 points of the headline shape)
 // Tables with several slices of both kinds are binned sooner: from kMinBinnedSoonRefs, and with many candidates, whose scans and atomics
 // cost the most, from kMinBinnedCandidateRefs.  us, before (scan, below 2^19 references atomics) / binned: 8 + 16 slices, N_p = 16 2^18.5 126 / 73,
 // 2^19.5 96 / 76, 2^20.3 133 / 88, 2^21 185 / 118; 32 + 32, N_p = 8 2^20.3 148 / 107, 2^21 197 / 124, but 2^18.6 75 / 92, 2^19.1 97 / 91; 16 + 8,
@@ -663,7 +663,11 @@ constexpr int64_t  kMinBinnedFusedRefs = 1 << 18;
 // (53), 122295 92 / 95 (72).  Points anything but evenly spread, 8 + 16, L = 8, 30573: all equal 239 / 189, on a plane 112 / 95, in a cube of side
 // 0.02 237 / 333; L = 16, 15287: 357 / 192, 207 / 73, 357 / 192; 32 + 32, L = 8, 30573: 273 / 205, 153 / 72, 292 / 127.
 constexpr int64_t  kMostSoonRefsPerBin = 4096;
-constexpr int64_t  kFewBinChunks = 1024;        // workgroups of the scatter, one per level and chunk, up to which each has four wavefronts
+// Workgroups of the scatter, one per level and chunk, up to which each has four wavefronts: so few leave most SIMDs without one, and the walk of 1024 points by a
+// single wavefront is a chain of memory latencies (scatter, us, one wavefront / four: 320 workgroups 25 / 13, 640 27 / 17, 1264 29 / 23; but the
+// drain of 1570 loses 3 % of 270, more than that gains).  Whole backward, one / four, 25 batches up to the line, a table with a single bin or several: 1.00 .. 1.28x; 1 + 32
+// slices, N_p = 8, 16411 points 149 / 137, 63001 173 / 171; 32 + 1, N_p = 4, 63001 117 / 112; 8 + 16, N_p = 16, 2048 60 / 47, 63001 169 / 162.
+constexpr int64_t  kFewBinChunks = 1024;
 // References per level (N * 2^d) from which the binned variant, where it does not merge, always pre-reduces coarse levels; below,
 // binned_bwd_us decides.
 // Backward, us, with / without, beyond it: nerf3d's tables 163840 points 384 / 403, 2^18 539 / 569; sdf3d's 2^20 2786 / 3294;
@@ -691,7 +695,7 @@ constexpr int64_t  kMinBinnedPrereduceRefs = 1 << 20;
 constexpr int64_t  kMinMergeRefs = 9 << 17;
 constexpr int      kMinMergeLevels = 8;
 constexpr uint64_t kMinMergePerVertexPct = 240;
-// Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us: sdf3d's tables (32 + 32
+// Bins of a level from which the scatter writes in runs (cngp_bwd_runs.h).  Backward, direct / in runs, us, with a record per corner in both tables' bins: sdf3d's tables (32 + 32
 // bins) 30000 points 150 / 140, 100000 345 / 309, 2^18 uniform 723 / 656, 2^20 near a surface 2407 / 2170; 32 + 16 bins 681 / 632,
 // 8 + 64 797 / 746, 64 + 128 1078 / 997, d = 2, 32 + 32 999 / 922.  Below the line the scatter gains as well, but the drain loses as
 // much: 32 + 8 bins 579 / 579, 16 + 16 624 / 621, 16 + 8 566 / 576, nerf3d's 8 + 16 533 / 542, 32 + 2 564 / 594.  A table with a single
@@ -717,8 +721,8 @@ constexpr int64_t  kMinSlicedRefs = 1 << 19;    // corner references (N * L * 2^
 constexpr uint64_t kMaxDenseVerts = 32ull * kDenseSliceVerts;   // largest vertex grid that is pre-reduced
 constexpr int64_t  kMinRefsPerVertex = 4;      // below this reuse the vertex pass saves nothing
 
-// Drain workgroups per bin of a table with `slices` slices per level: about 2^16 records each, and enough workgroups to
-// fill the chip twice, but never less than 8192 records each.  `refs` references per level, `levels` hashed levels.
+// Drain workgroups per bin of a table with `slices` slices per level: about 2^16 corners each (a record, or half of one in the feature table's
+// bins), and enough workgroups to fill the chip twice, but never less than 8192 each.  `refs` references per level, `levels` hashed levels.
 // `longer`: of the long bins of a few slices, 1.5 times the records each, whose sums are fewer to add up.  `alone`: of plain hashing with few slices, whose
 // one table has few bins, enough to fill it once (N_f = 2^17, L = 16, 100000 points: 131 us, so 83).
 uint32_t drain_subs(double refs, uint32_t slices, int levels, uint32_t slices_per_level, bool longer = false, bool alone = false) {
@@ -872,6 +876,7 @@ void choose_geometry(const cngp_config *c, int64_t N, BwdPlan &b, const bool spl
 // CUs and its longest workgroup: a coarse level has few vertices, all of a vertex's references fall into one bin, and the
 // bins of such a level are far from equal (d = 2, N_min = 16: 324 vertices for all the references of the coarsest level).
 // Pre-reducing takes that away and makes its workgroups scan the whole vertex grid per slice, besides one launch more.
+// (Fitted with a record per corner in either table's bins; the feature table's hold half as many now, so that what is binned costs less than this says.)
 // Fitted to 560 drawn configurations (d = 2 .. 4, 2 .. 24 levels, N_f 2^12 .. 2^19, N_c to 2^17, uniform points, rays and a
 // shell), each timed both ways: 12 % off on average, and 13 % on the ratio of the two ways.  Always pre-reducing was 1.19x slower than
 // the better of the two on average, never pre-reducing 1.08x (up to 4.6x); this choice 1.009x.  With / without, us: nerf3d's
@@ -984,7 +989,8 @@ int scan_dense_levels(const cngp_config *c, int64_t N, uint32_t per_level) {
 
 // Whether binning pays for tables of few slices where levels are merged (kMinMergedRefs).  A scan reads every point once per slice of the
 // levels it does not pre-reduce, with less to do in a slice of logits, and adds up every reference; a merged level leaves less than half
-// of its references to the bins.
+// of its references to the bins.  (`refs`: a record per corner and table, as measured then; the feature table's bins hold half as many now, so the
+// line is on the safe side.)
 bool few_slices_pay(const cngp_config *c, int64_t N, uint32_t slices_f, uint32_t slices_c) {
     const int    D = scan_dense_levels(c, N, slices_f + slices_c), U = c->L - D, M = merge_levels(c, N);
     const double corners = 1 << c->d, refs = 2.0 * corners;
@@ -1357,9 +1363,6 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     const int64_t blocks = (int64_t)(b.merged ? Lh : Lh + Ld) * bp.chunks + (int64_t)mb.levels * mb.chunks;
     if (int rc = check_blocks(blocks)) return rc;
     const size_t lds_bins = (size_t)most_bins_of(bp) * sizeof(uint32_t);
-    // Direct scatter: one wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
-    // like (measured: drain 7 % faster); with kMinRunBins bins and more, where the scatter in runs is not taken, four wavefronts share the cursors
-    // (a lone one fills its cache lines too slowly for the memory system to merge the 4-byte writes).
     if constexpr (D <= 3) if (b.merged) {      // the points in the order of their cells (the histogram ran with the preparation), then the entries
         {
             LaunchTimer t(s, K_BWD_CELLS);
@@ -1374,8 +1377,9 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
         kernel<<<(b.merge.chunks + kXcds - 1) / kXcds * kXcds * b.merge.levels, kMergeBlock, kMergeLdsBytes, s>>>(p, bp, b.merge, x, dy, N, ma.order, mb);
         if (int rc = launch_status("bwd_merge_kernel")) return rc;
     }
-    // So do the chunks of a short batch, which leave most SIMDs without a wavefront: the walk of 1024 points by one is a chain of memory latencies
-    // (scatter, us, one wavefront / four: 320 workgroups 25 / 13, 640 27 / 17, 1264 29 / 23; but the drain of 1570 loses 3 % of 270, more than that gains).
+    // Direct scatter: one wavefront per chunk keeps a bin's records in the order of the points, which the drain's gathers
+    // like (measured: drain 7 % faster).  Four wavefronts share the cursors with kMinRunBins bins and more, where the scatter in runs is not taken
+    // (a lone one fills its cache lines too slowly for the memory system to merge the 4-byte writes), and where the chunks are few (kFewBinChunks).
     const unsigned bin_block = bp.slices_f + bp.slices_c >= kMinRunBins || blocks <= kFewBinChunks ? 256u : (unsigned)kBinBlock;
     {
         LaunchTimer t(s, K_BWD_BIN_OFFSETS);
@@ -1448,7 +1452,10 @@ int launch_bwd_binned(const cngp_config *c, const Params &p, const BwdPlan &b, c
     if (int rc = allow_big_lds(kernel, lds)) return rc;
     const uint32_t total = wgs_c + wgs_f + wgs_cv + wgs_fv;
     if (total == 0) return CNGP_OK;
-    // A record costs a feature slice 2.2 ns and a logit slice 1.95 (N_p = 16, both roles in flight), the fixed part of a workgroup is alike.
+    // A corner costs a feature slice 2.2 ns and a logit slice 1.95 (N_p = 16, both roles in flight), the fixed part of a workgroup is alike.  Backward, us,
+    // logits / features first: workgroups of features twice as long, 8 + 16 slices, N_p = 16, 20011 points 92 / 76, 60007 198 / 169, 131101 (two per bin) 328 / 315; four or eight times,
+    // 4 + 32, N_p = 8, 20011 127 / 107, 60007 202 / 179; half as long or less, 32 + 4, N_p = 4, 90 / 103, 32 + 2, N_p = 8, 60007 131 / 166.  Alike, where it matters
+    // little, features first take 0.98 .. 1.05 of the time (4 + 32 with eight per bin and one, 262144 points 468 / 488; 16 + 16, L = 8 272 / 279; 32 + 32, N_p = 8, 500009 903 / 890).
     const bool feat_first = wgs_f > 0 && (wgs_c == 0 || 2.2 * b.slices_c * b.subs_c > 1.95 * b.slices_f * b.subs_f);
     {
         LaunchTimer t(s, K_BWD_BIN_DRAIN);

@@ -26,7 +26,8 @@ namespace cngp {
 // Count and scatter run one workgroup per chunk of points.  With a single wavefront (the default block size)
 // the records a chunk adds to a bin follow the order of the points, so the drain's gathers of a batch of
 // records (the points and their upstream gradients) fall into a few cache lines instead of one line per
-// record; the host launches 256 lanes instead where there are as many bins as for the scatter in runs (cngp_bwd_runs.h), which is not taken.
+// record; the host launches 256 lanes for the scatter instead where there are as many bins as for the one in runs (cngp_bwd_runs.h), which is
+// not taken, and in short batches, whose few chunks a lone wavefront each walks too slowly.
 constexpr int kBinBlock = 64;
 
 // A binned corner reference: point index * 2^d + corner (the host keeps N * 2^d below 2^31 per pass).

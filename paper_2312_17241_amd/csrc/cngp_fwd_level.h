@@ -271,10 +271,10 @@ __global__ __launch_bounds__(kLevelBlock) void encode_fwd_level_kernel(
 
 // Levels whose tables fit in LDS side by side, four or a multiple of four of them (compressed models: the paper's Table 3 row takes 25 KB a
 // level).  A workgroup then has a point's encodings of that many neighbouring levels together and writes them to the rows of y itself, 16 or
-// 32 bytes at a time: no level-major copy, no second pass.  The compressed model, 2^22 points: 312 us
-// for the level kernel and 113 for the rows, so 338.
+// 32 bytes at a time: no level-major copy, no second pass.  The compressed model, 2^22 points: level kernel
+// and rows 417 us, so 340.
 // The workgroups of a part's groups of levels run on one XCD at the same time, so that its L2 puts the pieces of a row together before
-// they leave for memory.  What bounds it is what bounds the level kernel with all lookups in LDS: LDS and vector ALU, both at work 90 % of the time.
+// they leave for memory.  What bounds it is what bounds the level kernel with all lookups in LDS: LDS, at work 86 % of the time, and vector ALU, 81 %.
 struct GroupSplit {
     uint32_t levels = 0, groups = 0, parts = 0;              // levels per workgroup (0: not taken); groups of them; parts of the batch
     int64_t  per = 0;                                        // points per part
